@@ -117,8 +117,10 @@ int mp_loss_scale_update(mp_scale_state* st, mp_stream stream);
  * attention products Q K^T (trans_w = 0) and P V (trans_w = 1) and their gradients use the same
  * entry points.  Batched use: batch_outer x batch_inner independent problems; operand t of batch
  * (o, i) starts at t + o*s?_outer + i*s?_inner (elements).  Strides of 0 broadcast.
- * Fast (MFMA) path needs 16-byte aligned base pointers and ld / batch strides that are multiples
- * of 8 elements; anything else runs a slow scalar kernel with the same results contract.
+ * Any pointer (element-aligned), leading dimension and stride runs on the matrix cores as long as a row of each operand,
+ * as stored, has at least 8 elements (and N is a multiple of 4 where an fp32 addend or output is given); anything else
+ * runs a slow scalar kernel with the same results contract.  16-byte aligned pointers with extents, leading dimensions
+ * and strides in multiples of 8 (better: of the tile shapes, 128 or 256) are the fastest case.
  * ------------------------------------------------------------------------------------------ */
 enum { MP_EPI_NONE = 0, MP_EPI_BIAS = 1, MP_EPI_BIAS_RELU = 2 };
 

@@ -36,8 +36,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
             s.x += h2f(bias[n]); s.y += h2f(bias[n + 1]); s.z += h2f(bias[n + 2]); s.w += h2f(bias[n + 3]);
         }
         const uint16_t h0 = f2h(s.x), h1 = f2h(s.y), h2 = f2h(s.z), h3 = f2h(s.w);
-        *reinterpret_cast<uint2*>(C + m * ldc + n) =
-            make_uint2((unsigned)h0 | ((unsigned)h1 << 16), (unsigned)h2 | ((unsigned)h3 << 16));
+        *reinterpret_cast<u32x2_u*>(C + m * ldc + n) = u32x2g{(unsigned)h0 | ((unsigned)h1 << 16), (unsigned)h2 | ((unsigned)h3 << 16)};
         bad |= half_nonfinite(h0) | half_nonfinite(h1) | half_nonfinite(h2) | half_nonfinite(h3);
     }
     if (found_inf && __any(bad)) {
@@ -45,7 +44,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
     }
 }
 
-// Scalar kernel with the same contract, for shapes/alignments the matrix-core path does not take.
+// Scalar kernel with the same contract, for the few shapes the matrix-core path does not take (see matrix_path_ok).
 __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g, int a_kc, int b_kc) {
     const long long mn  = (long long)g.M * g.N;
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -161,11 +160,21 @@ static bool fast_path_ok(const GemmArgs& g) {
     return true;
 }
 
+// What the matrix-core kernels take: a straddling piece of 8 elements is loaded so that it ends at the border, so the
+// stored direction of an operand must hold at least 8 elements; fp32 outputs and addends move 4 columns at a time; and
+// an offset inside a tile must fit the buffer size.  Alignment and multiples of 8 do not matter.
+static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
+    if (g.K == 0 || (a_kc ? g.K : g.M) < 8 || (b_kc ? g.K : g.N) < 8) return false;
+    if ((g.acc_in || g.C32) && (g.N & 3) != 0) return false;
+    return g.lda < (1 << 21) && g.ldb < (1 << 21);
+}
+
 // ws: split-K partial buffer (may be NULL when !allow_split).
 static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool allow_split, float* ws, size_t ws_floats,
                     hipStream_t hs) {
     if (g.M == 0 || g.N == 0 || batches == 0) return MP_OK;
-    if (!fast_path_ok(g) || batches > 65535 || g.K == 0) {
+    g.aligned = fast_path_ok(g);
+    if (!matrix_path_ok(g, a_kc, b_kc) || batches > 65535) {
         if (batches > 65535) {
             set_error("gemm: more than 65535 batches");
             return MP_E_UNSUPPORTED;
@@ -196,7 +205,7 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     // weight gradients.  A contraction-contiguous operand arrives there in 64-byte row pieces, which costs what the
     // saved LDS stores gain, so forward and input-gradient products stay on the register-staged kernel)
     const int bm = kTiles[p.tile].bm, bn = kTiles[p.tile].bn;
-    if (dtl_mode() != 0 && others == 1 && bm >= 128 && bn >= 128 && g.M % bm == 0 && g.N % bn == 0 && g.K % DK == 0 && g.K >= DK &&
+    if (dtl_mode() != 0 && g.aligned && others == 1 && bm >= 128 && bn >= 128 && g.M % bm == 0 && g.N % bn == 0 && g.K % DK == 0 && g.K >= DK &&
         (a_kc || !b_kc) && (dtl_mode() == 2 || (!a_kc && !b_kc))) {
         const int gxd = ntiles > kCUs ? kCUs : ntiles;   // one workgroup per compute unit (its ring of stages fills the LDS)
         if (a_kc && b_kc) return launch_dtl_tile<true, true>(p.tile, g, gxd, hs);

@@ -254,7 +254,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             c_stage = c_stage + 1 == DNS ? 0 : c_stage + 1;
         }
         asm volatile("s_nop 15\n\ts_nop 15");
-        gemm_epilogue<TM, TN, false>(g, acc, m0 + wm * WM + er, ncol, 0, 0, 0, false, fold_bias, bad);
+        gemm_epilogue<TM, TN, INTERIOR>(g, acc, m0 + wm * WM + er, ncol, 0, 0, 0, false, fold_bias, bad);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the ring's last (unused) loads have landed before the LDS is reused
     __syncthreads();

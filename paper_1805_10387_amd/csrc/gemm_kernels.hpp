@@ -48,6 +48,7 @@ struct GemmArgs {
     float           alpha;
     int             k_per_split;  // multiple of BK; == K rounded up when not split
     int             tiles_m, tiles_n;
+    int             aligned;      // pointers 16-byte aligned, leading dimensions and batch strides multiples of 8
 };
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
@@ -75,9 +76,16 @@ __device__ __forceinline__ float acc_put(float v) {
 
 __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
 
+// The same vectors at any element alignment: the hardware takes global accesses at byte granularity, so rows that start
+// at odd addresses (a leading dimension that is no multiple of 8) move in 16-byte pieces like any other.
+typedef u32x4 u32x4_u __attribute__((aligned(2)));
+typedef unsigned u32x2g __attribute__((ext_vector_type(2)));
+typedef u32x2g u32x2_u __attribute__((aligned(2)));
+typedef f32x4 f32x4_u __attribute__((aligned(4)));
+
 // 16-byte global load of 8 halves starting at p[0], of which only the first `valid` (0..8) exist.
 __device__ __forceinline__ u32x4 load8_guard(const uint16_t* p, int valid) {
-    if (valid >= 8) return *reinterpret_cast<const u32x4*>(p);
+    if (valid >= 8) return *reinterpret_cast<const u32x4_u*>(p);
     // ragged tail: element loads, assembled with compile-time indices only (no addressable local)
     unsigned w0 = 0, w1 = 0, w2 = 0, w3 = 0;
     if (valid > 0) w0 |= (unsigned)p[0];
@@ -87,15 +95,52 @@ __device__ __forceinline__ u32x4 load8_guard(const uint16_t* p, int valid) {
     if (valid > 4) w2 |= (unsigned)p[4];
     if (valid > 5) w2 |= (unsigned)p[5] << 16;
     if (valid > 6) w3 |= (unsigned)p[6];
-    if (valid > 7) w3 |= (unsigned)p[7] << 16;
     return u32x4{w0, w1, w2, w3};
 }
+// Store the first `valid` (1..7) of 8 packed halves.
+__device__ __forceinline__ void store8_tail(uint16_t* p, const u32x4& v, int valid) {
+    p[0] = (uint16_t)v[0];
+    if (valid > 1) p[1] = (uint16_t)(v[0] >> 16);
+    if (valid > 2) p[2] = (uint16_t)v[1];
+    if (valid > 3) p[3] = (uint16_t)(v[1] >> 16);
+    if (valid > 4) p[4] = (uint16_t)v[2];
+    if (valid > 5) p[5] = (uint16_t)(v[2] >> 16);
+    if (valid > 6) p[6] = (uint16_t)v[3];
+}
+
+// How a kernel variant treats the borders of the matrices (chosen per launch, see launch_one):
+//   INTERIOR  every tile lies inside the matrices: plain loads and stores, no tests.
+//   EDGE      tiles may stick out, but every 8-element piece an operand is moved in lies wholly inside or wholly outside.
+//   TAIL      pieces may straddle the border (an extent that is no multiple of 8).
+// EDGE and TAIL stay branch-free in the k-loop: operands come through buffer loads, and a lane whose piece lies outside
+// presents an offset beyond the buffer's size, for which the hardware returns zero.  A straddling piece is loaded so
+// that it ENDS at the border (no byte outside the row is read) and shifted down in registers, which also fills its
+// missing elements with zeros.
+// (An iteration of a 1021 x 512 -> 12001 projection: 43.6 ms with its three products on the scalar kernel, whose every
+// multiply costs a 2-byte load, 0.27 ms here; of a 1500 x 161 -> 1024 -> 29 network: 1.96 ms -> 0.10 ms.  Against the
+// guarded loads that EDGE used before, a branch around every piece: 520 x 256 -> 3000, 93 -> 64 us.)
+enum : int { INTERIOR = 0, EDGE = 1, TAIL = 2 };
+constexpr unsigned BUF_SIZE = 0x80000000u;   // operand offsets inside a tile stay below this (checked by the host) ...
+constexpr unsigned BUF_OUT  = 0x80000000u;   // ... and this one is outside
+__device__ __forceinline__ u32x4 buffer_piece(const uint16_t* tile, unsigned byte_off) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(tile), 0, BUF_SIZE, 0x00020000);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);
+}
+// v >> (16 s) over the whole vector, s = 0..7
+__device__ __forceinline__ u32x4 shift_down(u32x4 v, int s) {
+    const bool s4 = s & 4, s2 = s & 2;
+    v = u32x4{s4 ? v[2] : v[0], s4 ? v[3] : v[1], s4 ? 0u : v[2], s4 ? 0u : v[3]};
+    v = u32x4{s2 ? v[1] : v[0], s2 ? v[2] : v[1], s2 ? v[3] : v[2], s2 ? 0u : v[3]};
+    const unsigned b = (s & 1) << 4;
+    return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], b), __builtin_amdgcn_alignbit(v[2], v[1], b),
+                 __builtin_amdgcn_alignbit(v[3], v[2], b), v[3] >> b};
+}
+// elements by which a piece with c valid elements has to be loaded early
+__device__ __forceinline__ int tail_shift(int c) { return (c > 0 && c < 8) ? 8 - c : 0; }
 
 // ---- global -> registers -> LDS.  R = tile rows (BM or BN).  Up to 8 x 16 bytes per lane.
 // Addresses are split into a wave-uniform part (tile origin, advanced per k-step; lives in scalar
 // registers) and a per-lane part computed once, so the k-loop carries almost no address arithmetic.
-// load<false> is straight-line code (no bounds tests) for tiles that lie fully inside the matrix
-// and the k-range; load<true> tests every access and zero-fills, and is only taken at the edges.
 template <int R>
 struct KCLoader {  // operand stored [row][k]; `tile` points at element (row0, k0)
     static constexpr int NV = R / 32;  // vectors per lane (lane -> row tid/8 + 32 i, k-slot tid%8)
@@ -103,32 +148,40 @@ struct KCLoader {  // operand stored [row][k]; `tile` points at element (row0, k
     u32x4                v[NV];
     unsigned             lane_off;     // elements from the tile origin
     int                  lds_off[2];   // byte offset inside the LDS tile for even / odd i (before + i*4096)
+    int                  sh;           // TAIL: how far the pieces now in v were loaded early
     __device__ __forceinline__ void init(int ld) {
         const int r0 = threadIdx.x >> 3, kv = threadIdx.x & 7;
         lane_off   = (unsigned)r0 * (unsigned)ld + kv * 8;
         lds_off[0] = r0 * 128 + ((kv ^ swz(r0)) << 4);
         lds_off[1] = r0 * 128 + ((kv ^ swz(r0) ^ 4) << 4);
+        sh         = 0;
     }
-    template <bool GUARD, int I>
+    template <int MODE, int I>
     __device__ __forceinline__ void load_one(const uint16_t* tile, int ld, int rows_left, int k_left) {
-        const uint16_t* p = tile + (long long)(32 * I) * ld + lane_off;
-        if (GUARD) {
-            const int r = (threadIdx.x >> 3) + 32 * I;
-            v[I] = (r < rows_left) ? load8_guard(p, k_left - (int)(threadIdx.x & 7) * 8) : u32x4{0u, 0u, 0u, 0u};
+        if constexpr (MODE != INTERIOR) {
+            const int c   = k_left - (int)(threadIdx.x & 7) * 8;
+            unsigned  off = 2u * lane_off + (unsigned)(64 * I) * (unsigned)ld;
+            if constexpr (MODE == TAIL) {
+                sh = tail_shift(c);
+                off += 16 - 2 * sh;  // (relative to 8 elements ahead of the tile: the first piece may start that much early)
+            }
+            const bool in = (int)(threadIdx.x >> 3) < rows_left - 32 * I && c > 0;
+            v[I]          = buffer_piece(MODE == TAIL ? tile - 8 : tile, in ? off : BUF_OUT);
         } else {
-            v[I] = *reinterpret_cast<const u32x4*>(p);
+            v[I] = *reinterpret_cast<const u32x4*>(tile + (long long)(32 * I) * ld + lane_off);
         }
     }
-    template <int I>
-    __device__ __forceinline__ void store_one(char* lds) const {
-        *reinterpret_cast<u32x4*>(lds + lds_off[I & 1] + I * 4096) = v[I];
+    template <int MODE, int I>
+    __device__ __forceinline__ void store_one(char* lds) {
+        *reinterpret_cast<u32x4*>(lds + lds_off[I & 1] + I * 4096) = MODE == TAIL ? shift_down(v[I], sh) : v[I];
     }
-    template <bool GUARD>
+    template <int MODE>
     __device__ __forceinline__ void load(const uint16_t* tile, int ld, int rows_left, int k_left) {
-        static_for<NV>([&](auto ic) { load_one<GUARD, decltype(ic)::value>(tile, ld, rows_left, k_left); });
+        static_for<NV>([&](auto ic) { load_one<MODE, decltype(ic)::value>(tile, ld, rows_left, k_left); });
     }
-    __device__ __forceinline__ void store(char* lds) const {
-        static_for<NV>([&](auto ic) { store_one<decltype(ic)::value>(lds); });
+    template <int MODE>
+    __device__ __forceinline__ void store(char* lds) {
+        static_for<NV>([&](auto ic) { store_one<MODE, decltype(ic)::value>(lds); });
     }
 };
 
@@ -143,6 +196,7 @@ struct OCLoader {  // operand stored [k][row]; `tile` points at element (k0, row
     unsigned lane_off;
     int      lds_row0;  // byte offset of (row rg*8, k kg*KB) before the slot swizzle: row*128 + within-slot bytes
     int      lds_slot;  // (slot of k = kg*KB) ^ (rg & 7); slot(i) = lds_slot ^ i   [swz(rg*8 + i) = (i ^ rg) & 7]
+    int      sh;        // TAIL: how far the pieces now in v were loaded early
     // Which block a lane owns.  R = 128 stores 8 bytes per lane, and the LDS takes such a store 16 lanes (128 bytes, one
     // pass over its banks) at a time: with rg = tid % 16 the 16 lanes of a pass would share one k group, i.e. the same
     // 8-byte half of their 16-byte slots, and only 8 slots exist per pass: a two-way conflict on every store.  So a
@@ -155,15 +209,21 @@ struct OCLoader {  // operand stored [k][row]; `tile` points at element (k0, row
         lane_off = (unsigned)k * (unsigned)ld + rg * 8;
         lds_row0 = rg * 8 * 128 + (k & 7) * 2;
         lds_slot = ((k >> 3) ^ rg) & 7;
+        sh       = 0;
     }
-    template <bool GUARD, int J>
+    template <int MODE, int J>
     __device__ __forceinline__ void load_one(const uint16_t* tile, int ld, int rows_left, int k_left) {
-        const uint16_t* p = tile + (long long)J * ld + lane_off;
-        if (GUARD) {
-            const int rg = row_group(threadIdx.x), kg = k_group(threadIdx.x);
-            v[J] = (kg * KB + J < k_left) ? load8_guard(p, rows_left - rg * 8) : u32x4{0u, 0u, 0u, 0u};
+        if constexpr (MODE != INTERIOR) {
+            const int c   = rows_left - row_group(threadIdx.x) * 8;
+            unsigned  off = 2u * (lane_off + (unsigned)J * (unsigned)ld);
+            if constexpr (MODE == TAIL) {
+                sh = tail_shift(c);
+                off += 16 - 2 * sh;  // (relative to 8 elements ahead of the tile, as above)
+            }
+            const bool in = k_group(threadIdx.x) * KB < k_left - J && c > 0;
+            v[J]          = buffer_piece(MODE == TAIL ? tile - 8 : tile, in ? off : BUF_OUT);
         } else {
-            v[J] = *reinterpret_cast<const u32x4*>(p);
+            v[J] = *reinterpret_cast<const u32x4*>(tile + (long long)J * ld + lane_off);
         }
     }
     // half (k = j, row I) of the block is the low or high half of word I/2 of v[j]
@@ -188,16 +248,21 @@ struct OCLoader {  // operand stored [k][row]; `tile` points at element (k0, row
         }
     }
     // store item J of KB covers 8/KB of the block's 8 LDS rows, so that items and loads pair up 1:1
-    template <int J>
-    __device__ __forceinline__ void store_one(char* lds) const {
+    template <int MODE, int J>
+    __device__ __forceinline__ void store_one(char* lds) {
+        if constexpr (MODE == TAIL && J == 0) {  // (a row piece mixes all of the block's vectors)
+#pragma unroll
+            for (int j = 0; j < KB; ++j) v[j] = shift_down(v[j], sh);
+        }
         static_for<8 / KB>([&](auto rc) { store_row<J*(8 / KB) + decltype(rc)::value>(lds); });
     }
-    template <bool GUARD>
+    template <int MODE>
     __device__ __forceinline__ void load(const uint16_t* tile, int ld, int rows_left, int k_left) {
-        static_for<KB>([&](auto jc) { load_one<GUARD, decltype(jc)::value>(tile, ld, rows_left, k_left); });
+        static_for<KB>([&](auto jc) { load_one<MODE, decltype(jc)::value>(tile, ld, rows_left, k_left); });
     }
-    __device__ __forceinline__ void store(char* lds) const {
-        static_for<KB>([&](auto jc) { store_one<decltype(jc)::value>(lds); });
+    template <int MODE>
+    __device__ __forceinline__ void store(char* lds) {
+        static_for<KB>([&](auto jc) { store_one<MODE, decltype(jc)::value>(lds); });
     }
 };
 
@@ -233,7 +298,7 @@ struct OperandStream {
 
 // ---- epilogue of one wave tile (TM x TN matrix-core tiles of 32 x 32), in the layout the matrix cores leave the result
 // in.  mrow = first output row of this lane (row of the wave tile + lane % 32), ncol = first column of the wave tile.
-template <int TM, int TN, bool EDGE>
+template <int TM, int TN, int MODE>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[TM][TN], const int mrow, const int ncol,
                                               const int bo, const int bi, const int bz, const bool split,
                                               const bool fold_bias, bool& bad) {
@@ -250,19 +315,21 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
     if (aux) aux += bo * g.sc_o + bi * g.sc_i;
     float*     C32   = g.C32 ? g.C32 + (long long)bz * g.M * g.N : nullptr;
 
-    // (N is a multiple of 8 on this path, so a 16-byte piece of a row is either fully inside or fully outside)
+    // (N is a multiple of 8 here unless MODE is TAIL, so a 16-byte piece of a row is either fully inside or fully outside;
+    // fp32 outputs and addends have N a multiple of 4 in every mode)
+    constexpr bool GUARD = MODE != INTERIOR;
     if (C32) {  // raw accumulator out: split-K partial, or fp32 result with alpha and addend
         static_for<TM * TN * 4>([&](auto tc) {
             constexpr int t = decltype(tc)::value, i = t / (TN * 4), j = (t / 4) % TN, q = t % 4;
             const int m = mrow + 32 * i, n = ncol + 32 * j + 8 * q + 4 * eh;
-            if (EDGE && (m >= g.M || n >= g.N)) return;
+            if (GUARD && (m >= g.M || n >= g.N)) return;
             f32x4 v = {acc_get(acc[i][j][4 * q]), acc_get(acc[i][j][4 * q + 1]), acc_get(acc[i][j][4 * q + 2]), acc_get(acc[i][j][4 * q + 3])};
             const long long mn = (long long)m * g.N + n;
             if (!split) {
                 v *= g.alpha;
-                if (g.acc_in) v += *reinterpret_cast<const f32x4*>(g.acc_in + mn);
+                if (g.acc_in) v += *reinterpret_cast<const f32x4_u*>(g.acc_in + mn);
             }
-            *reinterpret_cast<f32x4*>(C32 + mn) = v;
+            *reinterpret_cast<f32x4_u*>(C32 + mn) = v;
         });
     } else {
         typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -273,9 +340,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
             static_for<TM * TN * 4>([&](auto tc) {
                 constexpr int t = decltype(tc)::value, i = t / (TN * 4), j = (t / 4) % TN, q = t % 4;
                 const int m = mrow + 32 * i, n = ncol + 32 * j + 8 * q + 4 * eh;
-                const bool in = !EDGE || (m < g.M && n < g.N);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
+                    const bool in = !GUARD || (m < g.M && n + (MODE == TAIL ? e : 0) < g.N);
                     float x = acc_get(acc[i][j][4 * q + e]) * g.alpha;
                     if (g.acc_in && in) x += g.acc_in[(long long)m * g.N + n + e];
                     if (g.bias && !fold_bias && in) x += h2f(g.bias[n + e]);
@@ -293,7 +360,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
                 constexpr int ch = decltype(cc)::value;
                 const int     m = mrow + 32 * i, n = ncol + 16 * ch + 8 * eh;
                 av[i & 1][ch]   = u32x4{0u, 0u, 0u, 0u};
-                if (!EDGE || (m < g.M && n < g.N)) av[i & 1][ch] = *reinterpret_cast<const u32x4*>(aux + (long long)m * g.ld_aux + n);
+                const uint16_t* p = aux + (long long)m * g.ld_aux + n;
+                if (!GUARD) av[i & 1][ch] = *reinterpret_cast<const u32x4*>(p);
+                else if (m < g.M && n < g.N) av[i & 1][ch] = MODE == TAIL ? load8_guard(p, g.N - n) : *reinterpret_cast<const u32x4_u*>(p);
             });
         };
         if (aux) aux_load(std::integral_constant<int, 0>{});
@@ -333,7 +402,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
                 static_for<2>([&](auto cc) {
                     constexpr int c = decltype(cc)::value;
                     const int     n = ncol + 32 * j + 16 * c + 8 * eh;
-                    if (EDGE && (m >= g.M || n >= g.N)) return;
+                    if (GUARD && (m >= g.M || n >= g.N)) return;
+                    const bool whole = MODE != TAIL || n + 8 <= g.N;
                     u32x4 out = {d[4 * c], d[4 * c + 1], d[4 * c + 2], d[4 * c + 3]};
                     if (aux) {
                         const u32x4 a = av[i & 1][2 * j + c];
@@ -354,11 +424,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
                     if (g.found_inf) {
 #pragma unroll
                         for (int w = 0; w < 4; ++w) {
-                            const unsigned mw = out[w] & 0x7FFF7FFFu;
+                            unsigned mw = out[w] & 0x7FFF7FFFu;
+                            if (MODE == TAIL) {  // columns beyond N do not count (they may hold inf * 0)
+                                if (n + 2 * w >= g.N) mw = 0u;
+                                else if (n + 2 * w + 1 >= g.N) mw &= 0xFFFFu;
+                            }
                             mag               = __builtin_elementwise_max(mag, __builtin_bit_cast(u16x2, mw));
                         }
                     }
-                    *reinterpret_cast<u32x4*>(C + (long long)m * g.ldc + n) = out;
+                    uint16_t* const o = C + (long long)m * g.ldc + n;
+                    if (!GUARD) *reinterpret_cast<u32x4*>(o) = out;
+                    else if (whole) *reinterpret_cast<u32x4_u*>(o) = out;
+                    else store8_tail(o, out, g.N - n);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -369,9 +446,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[T
 
 // One output tile: tile number `pid` of problem g (tiles are numbered in bands of GROUP tile-rows), batch `by`, k-split
 // `bz` of `nz`; `pid_next` is the tile this workgroup takes afterwards (same problem, batch and split), or -1.
-// EDGE = false: every tile lies fully inside the matrices and K is a multiple of BK, so neither the
-// loads nor the stores carry bounds tests.  EDGE = true: every access is tested (ragged shapes).
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, bool EDGE>
+// MODE: see above (INTERIOR: every tile lies fully inside the matrices and K is a multiple of BK).
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, int MODE>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, const int pid_next, const int by, const int bz,
                                           const int nz, char* smem, OperandStream<BM, BN, A_KC, B_KC>& S, bool& bad) {
     static_assert(WAVES_M * WAVES_N == 4, "four waves per workgroup");
@@ -420,7 +496,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
             constexpr int t = decltype(tc)::value, j = t / 4, q = t % 4;
             const int     n = col0 + 32 * j + 8 * q + 4 * eh;  // 4 consecutive columns: one 8-byte load
             S.bias[t]       = {0u, 0u};
-            if (!EDGE || n < g.N) S.bias[t] = *reinterpret_cast<const u32x2b*>(g.bias + n);
+            if (MODE == INTERIOR) S.bias[t] = *reinterpret_cast<const u32x2b*>(g.bias + n);
+            else if (n + 4 <= g.N) S.bias[t] = *reinterpret_cast<const u32x2_u*>(g.bias + n);
+            else if (MODE == TAIL && n < g.N) {
+                unsigned b0 = g.bias[n], b1 = 0u;
+                if (n + 1 < g.N) b0 |= (unsigned)g.bias[n + 1] << 16;
+                if (n + 2 < g.N) b1 = g.bias[n + 2];
+                S.bias[t] = {b0, b1};
+            }
         });
     };
     if (fold_bias) {
@@ -454,7 +537,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
     // Where the stream goes behind this tile's last k-tile: on to the next tile (interior tiles with an even number of
     // at least 4 k-tiles: the register sets and LDS stages then end the tile in the roles they start one in), or
     // nowhere (see load_next).
-    const bool      chain = !EDGE && pid_next >= 0 && nkt >= 4 && (nkt & 1) == 0;
+    const bool      chain = MODE == INTERIOR && pid_next >= 0 && nkt >= 4 && (nkt & 1) == 0;
     const uint16_t *nta = nullptr, *ntb = nullptr;
     int             ncol1 = 0;
     if (chain) {
@@ -485,8 +568,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
         S.k_next = in ? S.k_next + BK : (chain ? kbeg : S.k_next);
     };
     auto load_next = [&](auto& la, auto& lb) {
-        la.template load<EDGE>(S.ta, g.lda, g.M - m0, kend - S.k_next);
-        lb.template load<EDGE>(S.tb, g.ldb, g.N - n0, kend - S.k_next);
+        la.template load<MODE>(S.ta, g.lda, g.M - m0, kend - S.k_next);
+        lb.template load<MODE>(S.tb, g.ldb, g.N - n0, kend - S.k_next);
         advance();
     };
     // One pipeline step: issue the global loads of a later tile into (ln_a, ln_b), multiply the tile in
@@ -512,7 +595,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
             bf[kk & 1][f - TM] =
                 *reinterpret_cast<const f16x8*>(stage + A_BYTES + offb[kk ^ (((f - TM) & 1) << 1)] + (f - TM) * 4096);
     };
-    auto step = [&](auto& ln_a, auto& ln_b, const auto& st_a, const auto& st_b, const char* sa, char* da) {
+    auto step = [&](auto& ln_a, auto& ln_b, auto& st_a, auto& st_b, const char* sa, char* da) {
         constexpr int MS = TM * TN;                                // matrix-core instructions per slice
         constexpr int NM = MS * KS;                                // ... per step
         constexpr int NB = MS * (KS - 1);                          // ... in front of the barrier
@@ -522,13 +605,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
         const int rows_a = g.M - m0, rows_b = g.N - n0, k_left = kend - S.k_next;
         auto gload = [&](auto gc) {
             constexpr int i = decltype(gc)::value;
-            if constexpr (i < NA) ln_a.template load_one<EDGE, i>(S.ta, g.lda, rows_a, k_left);
-            else ln_b.template load_one<EDGE, i - NA>(S.tb, g.ldb, rows_b, k_left);
+            if constexpr (i < NA) ln_a.template load_one<MODE, i>(S.ta, g.lda, rows_a, k_left);
+            else ln_b.template load_one<MODE, i - NA>(S.tb, g.ldb, rows_b, k_left);
         };
         auto lstore = [&](auto gc) {
             constexpr int i = decltype(gc)::value;
-            if constexpr (i < NA) st_a.template store_one<i>(da);
-            else st_b.template store_one<i - NA>(da + A_BYTES);
+            if constexpr (i < NA) st_a.template store_one<MODE, i>(da);
+            else st_b.template store_one<MODE, i - NA>(da + A_BYTES);
         };
         __builtin_amdgcn_sched_barrier(0);
         // Hand-placed order, pinned by scheduling barriers: behind matrix-core instruction m go the next
@@ -563,8 +646,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
     if (!S.primed) {
         load_next(S.la0, S.lb0);
         load_next(S.la1, S.lb1);
-        S.la0.store(smem);
-        S.lb0.store(smem + A_BYTES);
+        S.la0.template store<MODE>(smem);
+        S.lb0.template store<MODE>(smem + A_BYTES);
         __syncthreads();
     }
     // step kt multiplies tile kt out of stage kt&1, stores tile kt+1 (loaded one step earlier) into the
@@ -582,10 +665,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int pid, cons
     S.primed = chain;
     if (chain && fold_bias) load_bias(ncol1);
 
-    gemm_epilogue<TM, TN, EDGE>(g, acc, m0 + wm * WM + er, ncol, bo, bi, bz, nz > 1, fold_bias, bad);
+    gemm_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM + er, ncol, bo, bi, bz, nz > 1, fold_bias, bad);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, bool EDGE>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, int MODE>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs g) {
     extern __shared__ __align__(16) char smem[];
     bool bad = false;
@@ -603,7 +686,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs g) {
     S.init(g.lda, g.ldb);
     for (int vb = blockIdx.x; vb < ntiles; vb += gridDim.x) {
         const int nvb = vb + gridDim.x;
-        gemm_tile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, EDGE>(g, tile_of(vb), nvb < ntiles ? tile_of(nvb) : -1, blockIdx.y,
+        gemm_tile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, MODE>(g, tile_of(vb), nvb < ntiles ? tile_of(nvb) : -1, blockIdx.y,
                                                              blockIdx.z, gridDim.z, smem, S, bad);
     }
     if (g.found_inf && __any(bad)) {
@@ -721,7 +804,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_grouped_kernel(GroupArgs ga
         bool bad = false;
         OperandStream<BM, BN, A_KC, B_KC> S;
         S.init(g.lda, g.ldb);
-        gemm_tile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, false>(g, vb - first, -1, 0, 0, 1, smem, S, bad);
+        gemm_tile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, INTERIOR>(g, vb - first, -1, 0, 0, 1, smem, S, bad);
         bad_any |= bad;
         __syncthreads();  // (tiles of different problems: keep the LDS stages of one tile apart from the next)
     }
@@ -734,26 +817,29 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_grouped_kernel(GroupArgs ga
 // The kernel templates are instantiated in one translation unit per operand layout (gemm_kk.hip, gemm_ko.hip,
 // gemm_oo.hip: explicit instantiations of launch_tile / launch_grouped), which compile in parallel; gemm.hip holds
 // the planner and the C entry points and only declares them.
-template <int BM, int BN, int WM_, int WN_, bool AKC, bool BKC, bool EDGE>
+template <int BM, int BN, int WM_, int WN_, bool AKC, bool BKC, int MODE>
 static int launch_variant(const GemmArgs& g, dim3 grid, hipStream_t hs) {
     constexpr size_t  lds = 2 * (size_t)(BM + BN) * 128;
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WM_, WN_, AKC, BKC, EDGE>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<BM, BN, WM_, WN_, AKC, BKC, MODE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM_, WN_, AKC, BKC, EDGE>), grid, dim3(GEMM_THREADS), lds, hs, g);
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM_, WN_, AKC, BKC, MODE>), grid, dim3(GEMM_THREADS), lds, hs, g);
     MP_LAUNCH_CHECK("gemm launch");
     return MP_OK;
 }
 
 template <int BM, int BN, int WM_, int WN_, bool AKC, bool BKC>
 static int launch_one(const GemmArgs& g, dim3 grid, hipStream_t hs) {
-    const bool edge = (g.M % BM) != 0 || (g.N % BN) != 0 || (g.K % BK) != 0;
-    return edge ? launch_variant<BM, BN, WM_, WN_, AKC, BKC, true>(g, grid, hs)
-                : launch_variant<BM, BN, WM_, WN_, AKC, BKC, false>(g, grid, hs);
+    // an operand moves in pieces of 8 along its stored direction, outputs along N
+    const bool tail = (AKC ? g.K : g.M) % 8 != 0 || (BKC ? g.K : g.N) % 8 != 0 || g.N % 8 != 0;
+    const bool edge = (g.M % BM) != 0 || (g.N % BN) != 0 || (g.K % BK) != 0 || !g.aligned;
+    if (tail) return launch_variant<BM, BN, WM_, WN_, AKC, BKC, TAIL>(g, grid, hs);
+    return edge ? launch_variant<BM, BN, WM_, WN_, AKC, BKC, EDGE>(g, grid, hs)
+                : launch_variant<BM, BN, WM_, WN_, AKC, BKC, INTERIOR>(g, grid, hs);
 }
 
 template <bool AKC, bool BKC>

@@ -194,6 +194,67 @@ def test_gemm_dx_relu_mask_and_residual_add():
     assert_close16(out, L.add_store(MIXED, base, other), 1e-3, what="dx add")
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 9), (65, 31, 63), (129, 257, 65), (260, 100, 71), (200, 523, 129)])
+def test_gemm_extents_and_strides_of_any_parity(tile, M, N, K):
+    """Extents that are no multiple of 8 (pieces that straddle the border, one to seven valid elements), odd leading
+    dimensions and odd pointers, every tile shape: all three products with every epilogue, nothing written outside the
+    output columns.  The bound is that of the aligned shapes: the sums differ from the oracle's in fp32 order only."""
+    r = RNG(M + 3 * N + 7 * K)
+    x, w, b = S16(r.standard_normal((M, K))), S16(r.standard_normal((N, K)) * 0.1), S16(r.standard_normal(N))
+    dy, other = S16(r.standard_normal((M, N))), S16(r.standard_normal((M, K)))
+    src = S16(np.maximum(other, 0))
+
+    def odd(a):     # a matrix inside a wider one with an odd row length, starting at an odd element
+        rows, cols = a.shape
+        ld = cols + (3 if cols % 2 == 0 else 2)
+        buf = torch.full((rows * ld + 9,), 7.0, dtype=torch.float16, device="cuda")
+        v = buf[1:1 + rows * ld].view(rows, ld)
+        v[:, :cols] = h16(a)
+        return v, ld
+
+    (xd, ldx), (wd, ldw), (dyd, ldy), (od, lda), (sd, _) = odd(x), odd(w), odd(dy), odd(other), odd(src)
+    bd = torch.zeros(N + 1, dtype=torch.float16, device="cuda")
+    bd[1:] = h16(b)
+    outs = lambda rows, cols: odd(np.zeros((rows, cols)))[0]  # noqa: E731
+    st = make_state()
+    mp.mp_gemm_tuning_override(tile, 2)
+    try:
+        for epi in (0, 1, 2):
+            y = outs(M, N)
+            mp.mp_gemm_fwd(mp.gemm_desc(M, N, K, ldx=ldx, ldw=ldw, ldy=y.shape[1], epilogue=epi), xd, wd, bd[1:] if epi else None, None, y)
+            assert_close16(y[:, :N], L.linear_fwd(MIXED, x, w, b if epi else None, relu=epi == 2), 1e-3, max_ulp=1, what=f"fwd {epi}")
+            assert torch.all(y[:, N:] == 7.0)
+        d = mp.gemm_desc(M, N, K, ldx=ldx, ldw=ldw, ldy=ldy)
+        dx_ref, dw_ref, db_ref = L.linear_bwd(MIXED, dy, x, w)
+        dx = outs(M, K)
+        mp.mp_gemm_bwd_dx(d, dyd, wd, dx)
+        assert_close16(dx[:, :K], dx_ref, 1e-3, max_ulp=1, what="dx")
+        mp.mp_gemm_bwd_dx(d, dyd, wd, dx, relu_src=sd, ld_aux=lda)
+        assert_close16(dx[:, :K], L.relu_mask(MIXED, dx_ref, src), 1e-3, max_ulp=1, what="dx relu")
+        mp.mp_gemm_bwd_dx(d, dyd, wd, dx, add=od, ld_aux=lda)
+        assert_close16(dx[:, :K], L.add_store(MIXED, dx_ref, other), 1e-3, what="dx add")
+        assert torch.all(dx[:, K:] == 7.0)
+        dw, db = outs(N, K), empty16(N)
+        ws = ws_bytes(mp.mp_gemm_bwd_dw_workspace_bytes(d, True))
+        mp.mp_gemm_bwd_dw(d, dyd, xd, dw, db, st, ws)
+        assert_close16(dw[:, :K], dw_ref, 1e-3, max_ulp=1, what="dw")
+        assert_close16(db, db_ref, 1e-3, max_ulp=1, what="db")
+        assert torch.all(dw[:, K:] == 7.0)
+        # W stored [K, N] (the other orientation of the second operand), and an fp32 addend where N allows it
+        wt, ldwt = odd(np.ascontiguousarray(w.T))
+        y = outs(M, N)
+        mp.mp_gemm_fwd(mp.gemm_desc(M, N, K, ldx=ldx, ldw=ldwt, ldy=y.shape[1], trans_w=1, alpha=0.5), xd, wt, None, None, y)
+        assert_close16(y[:, :N], MIXED.store(np.float32(0.5) * (x @ w.T)), 1e-3, max_ulp=1, what="fwd, W[K,N], alpha")
+        if N % 4 == 0:
+            part = f32(dy)
+            mp.mp_gemm_fwd(mp.gemm_desc(M, N, K, ldx=ldx, ldw=ldw, ldy=y.shape[1], epilogue=1), xd, wd, bd[1:], part, y)
+            assert_close16(y[:, :N], MIXED.store((x @ w.T + dy) + b), 1e-3, max_ulp=1, what="fwd with addend")
+    finally:
+        mp.mp_gemm_tuning_override(-1, 1)
+    assert mp.scale_state_read(st).found_inf == 0
+
+
 def test_gemm_leading_dimensions_and_unaligned_fallback():
     r = RNG(8)
     M, N, K = 70, 90, 50                      # K, N not multiples of 8: slow path
