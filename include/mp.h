@@ -340,8 +340,8 @@ int mp_lstm_cell_bwd(int B, int H, const mp_half* gates, int ldg, const float* c
 /* A whole LSTM layer over all time steps in ONE launch per direction (the recurrent encoder of the Section 2 listing
  * and Section 5.1; arithmetic of Sections 3.1 / 3.2 as in the per-step calls: fp16 operands, fp32 sums, each gate sum
  * and each h_t rounded once to fp16, cell state fp32).  Unrolled step by step a layer is a chain of small dependent
- * launches; here every workgroup keeps its rows of the recurrent weights on chip for all T steps and the steps are
- * separated by a grid-wide barrier inside the kernel.
+ * launches; here every workgroup keeps its rows of the recurrent weights on chip for all T steps and the
+ * workgroups exchange their slices of a step's result inside the kernel.
  *
  *   forward : gates_t = RNE16( gx_t + h_{t-1} W_h^T + b ),   W_h = columns [I, I+H) of w[4H, ldw], gate blocks (i, f, g, o)
  *             c_t = sigma(f) c_{t-1} + sigma(i) tanh(g)  (fp32),   h_t = RNE16( sigma(o) tanh(c_t) )
@@ -358,23 +358,27 @@ int mp_lstm_cell_bwd(int B, int H, const mp_half* gates, int ldg, const float* c
  *     dh_above device fp16 [T*B, ld_up]: gradient reaching h_t from above (leading dimension d->ld_up).
  *     dgates   device fp16 [T*B, 4H] out.  The input gradient dgates W_x and the weight / bias gradients are ordinary
  *              large products over all T*B rows afterwards (mp_gemm_bwd_dx, mp_gemm_bwd_dw).
- *   status   device int32, must be 0 on entry (the caller clears it; it is never cleared here).  The kernel's step
- *            barrier waits at most wait_limit_us (0: 2 s) for the other workgroups; a wait that runs out sets
- *            *status nonzero, every workgroup then leaves its loop, and the outputs are undefined.  A nonzero status
- *            on entry makes the kernel stop at its first barrier.  Check it wherever the host next synchronises.
- *   ws       device, mp_lstm_layer_workspace_bytes() bytes, 4-byte aligned (step flags; cleared by the call).
- * All H / 16 workgroups must be resident at once: the call returns MP_E_UNSUPPORTED if the device has fewer compute
- * units, and launches of this kind that may run at the same time (other streams) must together fit the device.
+ *   status   device int32, must be 0 on entry (the caller clears it; it is never cleared here).  In every time step the
+ *            kernel waits at most wait_limit_us (0: 2 s) for the other workgroups' results; a wait that runs out sets
+ *            *status nonzero, all workgroups then run to their end without waiting, and the outputs are undefined.  A
+ *            nonzero status on entry makes the kernel stop waiting at its first wait.  Check it wherever the host next
+ *            synchronises.
+ *   ws       device, mp_lstm_layer_workspace_bytes() bytes, 16-byte aligned (through which the workgroups exchange
+ *            their slices of a step; cleared by the call).
+ * All H / 16 x ceil(B / 8) workgroups must be resident at once, two to a compute unit: the call returns
+ * MP_E_UNSUPPORTED if the device has too few compute units, and launches of this kind that may run at the same time
+ * (other streams) must together fit the device.
  * Supported: B <= 32, H a multiple of 128 up to 1024, I, ldw, ldxh multiples of 8, ld_up even, 16-byte aligned
  * pointers; otherwise MP_E_UNSUPPORTED (run the layer with mp_gemm_fwd_ws / mp_lstm_cell_fwd step by step).
- * debug_extra_participants (0 in production) makes the barrier wait for that many flags nobody raises: with a small
+ * debug_extra_participants (0 in production) makes every wait last as if something never arrived: with a small
  * wait_limit_us it lets a test drive the time-out path while every wave still exits normally. */
 typedef struct mp_lstm_layer_desc {
     int32_t T, B, I, H;       /* time steps, batch rows, input width, hidden units                         */
     int32_t ldw, ldxh, ld_up; /* leading dimensions of w, xh, and of h_up (forward) / dh_above (backward)   */
-    int32_t wait_limit_us;    /* bound of one barrier wait; 0 = 2 000 000                                   */
+    int32_t wait_limit_us;    /* bound of one wait; 0 = 2 000 000                                   */
     int32_t debug_extra_participants;
-    int32_t reserved;
+    int32_t step_rows;        /* rows from one time step to the next in gx, gates, c, xh, h_up / dh_above and dgates;
+                                 0: B.  Larger than B, the call works on B rows of a larger batch                */
 } mp_lstm_layer_desc;
 size_t mp_lstm_layer_workspace_bytes(void);
 int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d /* host */, const float* gx, const mp_half* w, const mp_half* bias,

@@ -39,7 +39,7 @@ class GemmGroupItem(C.Structure):
 class LstmLayerDesc(C.Structure):
     _fields_ = [("T", C.c_int32), ("B", C.c_int32), ("I", C.c_int32), ("H", C.c_int32),
                 ("ldw", C.c_int32), ("ldxh", C.c_int32), ("ld_up", C.c_int32), ("wait_limit_us", C.c_int32),
-                ("debug_extra_participants", C.c_int32), ("reserved", C.c_int32)]
+                ("debug_extra_participants", C.c_int32), ("step_rows", C.c_int32)]
 
 
 class TensorDesc(C.Structure):

@@ -213,8 +213,8 @@ def mp_lstm_cell_bwd(B, H, gates, ldg, c_prev, c, dh_a, ld_a, dh_b, ld_b, dc, dg
                                      _p(dgates), _stream()))
 
 
-def lstm_layer_desc(T, B, I, H, ldw, ldxh, ld_up, wait_limit_us=0, debug_extra_participants=0) -> L.LstmLayerDesc:
-    return L.LstmLayerDesc(T, B, I, H, ldw, ldxh, ld_up, wait_limit_us, debug_extra_participants, 0)
+def lstm_layer_desc(T, B, I, H, ldw, ldxh, ld_up, wait_limit_us=0, debug_extra_participants=0, step_rows=0) -> L.LstmLayerDesc:
+    return L.LstmLayerDesc(T, B, I, H, ldw, ldxh, ld_up, wait_limit_us, debug_extra_participants, step_rows)
 
 
 def mp_lstm_layer_workspace_bytes() -> int:

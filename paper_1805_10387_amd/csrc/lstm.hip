@@ -4,285 +4,403 @@
 //
 // A layer unrolled over time is a chain of small dependent products (batch rows x [4H, H]): launched one by one a time
 // step costs its launches and first-load latencies, not its bytes.  Here each workgroup owns RL_UNITS hidden units of
-// RL_ROWS batch rows for the whole sequence (batch rows never mix in the recurrence, so each block of rows is a grid
-// of its own with its own step barrier):
+// RL_ROWS batch rows for the whole sequence (batch rows never mix in the recurrence, so each block of rows is a group
+// of workgroups of its own that never waits for another):
 //   forward : its 4 x RL_UNITS rows of the recurrent weight block W_h live in registers as matrix-core fragments for
-//             all T steps; per step it reads h_{t-1} (all units, B x H fp16) from memory, forms its gate sums, adds
-//             the input half x_t W_x^T (computed for all steps at once by one large product beforehand, kept fp32, so
-//             the gate sum is still rounded once), updates its cells (c in registers, fp32) and publishes its slice
-//             of h_t.
+//             all T steps; per step it takes h_{t-1} (all units) from the exchange ring, forms its gate sums, adds the
+//             input half x_t W_x^T (computed for all steps at once by one large product beforehand, kept fp32, so the
+//             gate sum is still rounded once), updates its cells (c in registers, fp32) and publishes its slice of h_t.
 //   backward: its RL_UNITS columns of W_h (as W_h^T fragments) live in registers; per step it runs the cell backward
 //             for its units (the recurrent gradient of its own units and the cell-state gradient never leave the
-//             workgroup), publishes its slice of dgates_t, and after the step barrier contracts the whole dgates_t
-//             (B x 4H) with its columns to get the recurrent gradient of its units for step t - 1.
-// One grid-wide barrier per time step: every workgroup stores a step number into its own flag word and polls all flag
-// words (no shared counter to serialise on).  All workgroups must be co-resident, so the grid never exceeds the number
-// of compute units; the wait is bounded in wall-clock time and a workgroup that gives up raises *status, which makes
-// every other workgroup give up too: the grid always drains.
+//             workgroup), publishes its slice of dgates_t, and contracts the whole dgates_t (rows x 4H) with its columns
+//             to get the recurrent gradient of its units for step t - 1.
+//
+// What bounds a time step is the trip of a small tensor from every workgroup to every other through the memory system.
+// There is no barrier and no flag: the data announce themselves.  The exchanged slice of a step goes to a slot of a
+// ring of RL_RING slots that is filled with a bit pattern no published value has (RL_EMPTY), with device-scope stores,
+// and a reader loads the whole slice with device-scope loads until none of it is empty.  One trip per step instead of
+// three (data acknowledged - flag raised - flag seen - data fetched), no cache write-back or invalidation, and a wave
+// waits for exactly the values it multiplies.  Slots lie in the order the matrix cores take them (one coalesced 1 KB
+// load per fragment pair), and a publisher writes whole 128-byte lines.
+//   Reuse: P_n (the slice of step n) is published by a workgroup after a workgroup barrier behind which all its waves
+//   have read P_(n-1).  So once a workgroup has seen P_(n-1) from everybody, everybody has read P_(n-2), and after
+//   publishing P_n it empties its part of P_(n-2); that is acknowledged ahead of its P_(n+1), and only
+//   who has seen P_(n+1) from everybody looks for P_(n+2), which takes the slot over.
+//   8 batch rows per workgroup, not the matrix core's 16: a group then reads half as much (64 KB per workgroup and
+//   backward step, 0.4 us at the vector cache's 64 bytes a clock) and 32 rows x 1024 units occupy 256 workgroups.  The 16
+//   columns of an operand hold 8 rows of two successive k-steps; each is multiplied with both k-steps' weights into
+//   separate sums, and the half of each result that pairs the right ones is kept.
+// (4 layers x 50 steps, 1024 units, batch 32, us per time step: one flag per workgroup behind a device-scope release and
+// acquire, 16 rows per workgroup: 6.7 forward, 10.0 backward; now 2.2 and 2.8.)
+// All workgroups must be co-resident: the register use allows two per compute unit and the host refuses larger grids.
+// Every wait is bounded in wall-clock time; a wave that gives up raises *status and stops waiting, which makes every other
+// wave give up too, and all of them walk the remaining steps without waiting: the grid always drains.
 #include "cell_math.hpp"
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace mp {
 
 constexpr int RL_THREADS = 256;  // 4 waves: each takes a quarter of the contraction
 constexpr int RL_UNITS   = 16;   // hidden units per workgroup = one 16-row matrix-core block per gate
-constexpr int RL_ROWS    = 16;   // batch rows per workgroup = one matrix-core block; more rows: more workgroups (grid y)
+constexpr int RL_ROWS    = 8;    // batch rows per workgroup; more rows: more workgroups (grid y)
 constexpr int RL_MAX_H   = 1024; // register budget of the fragment arrays below
-constexpr int RL_FLAG_WORDS = 128;  // flag words per barrier group (one group per block of batch rows)
+constexpr int RL_MAX_B   = 32;
+constexpr int RL_RING    = 4;    // slots of the exchange ring
+constexpr int RL_VMCNT0 = 0x0F70;  // operand of s_waitcnt: all vector memory operations done, nothing else waited for
+constexpr uint16_t RL_EMPTY = 0xFFFF;  // a NaN; published NaNs of this pattern lose one payload bit on the way
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef short    s16x4 __attribute__((ext_vector_type(4)));
 
 struct RlSync {
-    int*      flags;        // nwait words, zero at launch; workgroup g stores the number of the step it has finished
-    int*      status;       // 0 on entry; set nonzero by a workgroup whose wait ran out
-    int       nwait;        // flags to wait for (= gridDim.x; tests may ask for more, which never arrive)
+    char*     ring;         // [groups][RL_RING][slot bytes], all RL_EMPTY at launch
+    int*      status;       // 0 on entry; set nonzero by a wave whose wait ran out
+    int       never;        // tests: behave as if part of every slice never arrived
     long long limit_ticks;  // bound of one wait, in ticks of the constant 100 MHz clock
 };
 
-// This workgroup has finished `step`: its flag is raised once all its global stores of the step are visible
-// device-wide.  The workgroup barrier waits until every wave's stores have left the compute unit and orders them
-// before thread 0, whose device-scope release store then publishes them (one write-back of the cache level that
-// other compute-unit clusters cannot see, per workgroup and step, instead of one per wave).
-__device__ __forceinline__ void grid_arrive(const RlSync& s, int step) {
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(s.flags + blockIdx.x, step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+constexpr int RL_DEVICE_SCOPE = 16;  // cache-policy bit (sc1) of the buffer intrinsics: coherent across the device
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rl_ring(char* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
 }
 
-// Wait until every flag has reached `step`.  Returns false (for the whole workgroup alike) when the wait was
-// abandoned: its time ran out, or another workgroup had already given up.  Wave 0 polls (lane i watches flags i,
-// i + 64, ...), takes the device-scope acquire, and hands the verdict to the other waves through `verdict` (LDS)
-// and a workgroup barrier, which orders everything they read afterwards behind that acquire.
-__device__ __forceinline__ bool grid_wait(const RlSync& s, int step, int* verdict) {
-    if (threadIdx.x < 64) {
-        const long long t0 = wall_clock64();
-        int             ok = 1;
-        for (;;) {
-            int mine = 1;
-            for (int i = threadIdx.x; i < s.nwait; i += 64)
-                mine &= __hip_atomic_load(s.flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= step;
-            if (__all(mine)) break;
-            const int give_up = (wall_clock64() - t0 > s.limit_ticks) ||
-                                __hip_atomic_load(s.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-            if (__any(give_up)) {  // (lanes read the clock a few ticks apart: the wave decides as one)
-                ok = 0;
-                break;
+// The NP fragment pairs (1 KB apart) of a published slice, loaded until nothing in them is empty.  HALF_LAST: only lanes
+// with (lane & 8) == 0 of the last pair are ever published.  Waves decide alone; `dead` (wave-uniform) is set when this
+// or another wave gave up, and ends all waiting.
+template <int NP, bool HALF_LAST>
+__device__ __forceinline__ void rl_take(__amdgpu_buffer_rsrc_t ring, unsigned off, u32x4 (&f)[NP], const RlSync& s, bool& dead) {
+    const bool upper = (threadIdx.x & 8) != 0;
+    long long  t0    = 0;
+    for (int it = 0;; ++it) {
+        asm volatile("" ::: "memory");  // (every round loads anew)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) f[p] = __builtin_amdgcn_raw_buffer_load_b128(ring, off + p * 1024, 0, RL_DEVICE_SCOPE);
+        if (HALF_LAST && upper) f[NP - 1] = u32x4{0u, 0u, 0u, 0u};
+        u16x2 m = {0, 0};  // the largest half seen: RL_EMPTY is the largest pattern there is
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const unsigned x = f[p][w];
+                m                = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, x));
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (threadIdx.x == 0) {
-            if (!ok) atomicOr(s.status, 1);
-            *verdict = ok;
+        const bool missing = m[0] == RL_EMPTY || m[1] == RL_EMPTY || s.never != 0;
+        if (dead || !__any(missing)) return;
+        if ((it & 15) == 0) {
+            const long long now = wall_clock64();
+            if (it == 0) t0 = now;
+            const int give_up = (now - t0 > s.limit_ticks) ||
+                                __hip_atomic_load(s.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+            if (__any(give_up)) {  // (lanes read the clock a few ticks apart: the wave decides as one)
+                dead = true;
+                if ((threadIdx.x & 63) == 0) atomicOr(s.status, 1);
+            }
         }
     }
-    __syncthreads();
-    return *verdict != 0;
 }
 
+// x of this lane (lanes 0-7 of each 16) plus y of the lane 8 further on
+__device__ __forceinline__ float rl_add_upper(float x, float y) {
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), 0x108, 0xF, 0xF, true));
+}
+
+// The 8 values of lanes 8 j .. 8 j + 7, packed, in lane 8 j (row shifts within 16 lanes), none of them RL_EMPTY.
+__device__ __forceinline__ u32x4 rl_gather8(uint16_t h) {
+    const int      v  = h == RL_EMPTY ? RL_EMPTY - 1 : h;
+    const unsigned w  = (unsigned)v | ((unsigned)__builtin_amdgcn_update_dpp(0, v, 0x101, 0xF, 0xF, true) << 16);
+    return u32x4{w, (unsigned)__builtin_amdgcn_update_dpp(0, (int)w, 0x102, 0xF, 0xF, true),
+                 (unsigned)__builtin_amdgcn_update_dpp(0, (int)w, 0x104, 0xF, 0xF, true),
+                 (unsigned)__builtin_amdgcn_update_dpp(0, (int)w, 0x106, 0xF, 0xF, true)};
+}
 __device__ __forceinline__ f16x8 as_frag(const u32x4& v) { return __builtin_bit_cast(f16x8, v); }
 
 // ------------------------------------------------------------------------------------------------ forward
 struct LstmFwdArgs {
     int             T, B, I, H;
-    const float*    gx;     // [T*B, 4H] fp32: x_t W_x^T
+    long long       step_rows;  // rows from one time step to the next in all tensors (>= B)
+    const float*    gx;     // [T*step_rows, 4H] fp32: x_t W_x^T
     const uint16_t* w;      // [4H, ldw]; recurrent block = columns I .. I+H
     int             ldw;
     const uint16_t* bias;   // [4H]
-    uint16_t*       gates;  // [T*B, 4H] out
-    float*          c;      // [(T+1)*B, H]: rows of step 0 given, steps 1..T out
-    uint16_t*       xh;     // [T*B, ldxh]: h_{t-1} is read from columns I.. of step t, h_t written to step t+1
+    uint16_t*       gates;  // [T*step_rows, 4H] out
+    float*          c;      // [(T+1)*step_rows, H]: rows of step 0 given, steps 1..T out
+    uint16_t*       xh;     // [T*step_rows, ldxh]: h_0 is read from columns I.. of step 0, h_t written to step t+1
     int             ldxh;
-    uint16_t*       h_up;   // [T*B, ld_up] or NULL: h_t also goes here
+    uint16_t*       h_up;   // [T*step_rows, ld_up] or NULL: h_t also goes here
     int             ld_up;
     RlSync          sync;
 };
+// fragment pairs per wave (a wave contracts over H / 4 hidden units) and bytes of one slot
+__host__ __device__ constexpr int      rl_fwd_pairs(int H) { return (H / 128 + 1) / 2; }
+__host__ __device__ constexpr unsigned rl_fwd_slot(int H) { return 4u * 1024u * rl_fwd_pairs(H); }
 
-__global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void lstm_layer_fwd_kernel(LstmFwdArgs a) {
-    __shared__ float red[4][16][65];  // per wave: partial gate sums [batch row][16 g + unit]
-    __shared__ int   verdict;
+template <int HB>  // H = 128 HB
+__global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_layer_fwd_kernel(LstmFwdArgs a) {
+    __shared__ __align__(16) float red[2][4][RL_ROWS][80];  // per step parity and wave: partial gate sums [row][16 g + unit] (row stride: 64 banks + 16)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
-    const int H = a.H, I = a.I, B = a.B, T = a.T;
+    constexpr int H = 128 * HB;
+    const int I = a.I, T = a.T;
     const int j0  = blockIdx.x * RL_UNITS;   // this workgroup's hidden units
-    const int b0  = blockIdx.y * RL_ROWS;    // ... and batch rows (the recurrence never mixes batch rows)
-    const int nb  = min(RL_ROWS, B - b0);
-    const int Kw  = H >> 2;             // this wave's share of the contraction over h
-    const int nks = Kw >> 5;            // matrix-core steps of 32
+    const int b0  = blockIdx.y * RL_ROWS;    // ... and batch rows
+    const int nb  = min(RL_ROWS, a.B - b0);
+    constexpr int Kw  = H / 4;          // this wave's share of the contraction over h
+    constexpr int nks = HB;             // matrix-core steps of 32
+    constexpr int np  = rl_fwd_pairs(H);
     const int k0  = wave * Kw + 8 * lq; // first k of this lane's 8 consecutive values, + 32 ks
-    RlSync    sync = a.sync;
-    sync.flags += blockIdx.y * RL_FLAG_WORDS;  // one barrier group per block of batch rows
+    constexpr unsigned slot = rl_fwd_slot(H);
+    const __amdgpu_buffer_rsrc_t ring = rl_ring(a.sync.ring + (size_t)blockIdx.y * RL_RING * slot, RL_RING * slot);
+    bool dead = false;
 
     // W_h fragments, resident for the whole sequence: gate g, unit lr, 8 consecutive k
-    u32x4 wf[4][8];
+    u32x4 wf[4][nks];
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            wf[g][ks] = u32x4{0u, 0u, 0u, 0u};
-            if (ks < nks) wf[g][ks] = *reinterpret_cast<const u32x4*>(a.w + (long long)(g * H + j0 + lr) * a.ldw + I + k0 + 32 * ks);
-        }
+        for (int ks = 0; ks < nks; ++ks)
+            wf[g][ks] = *reinterpret_cast<const u32x4*>(a.w + (long long)(g * H + j0 + lr) * a.ldw + I + k0 + 32 * ks);
 
-    // cell ownership: thread -> batch row b0 + cr, unit j0 + cu
+    // cell ownership (waves 0 and 1): thread -> batch row b0 + cr, unit j0 + cu.  Rows beyond the batch repeat the last one
+    // (their values are published but never stored), so that no load hangs on a condition.
     const int  cr = tid >> 4, cu = tid & 15;
-    const bool cell = cr < nb;
-    float      cst = 0.f, bia[4];
+    const bool owner = cr < RL_ROWS, cell = cr < nb;
+    const long long brow = b0 + min(cr, nb - 1);
+    float    cst = 0.f, bia[4] = {0.f, 0.f, 0.f, 0.f}, gx0[4], gx1[4];
+    uint16_t g16[4] = {0, 0, 0, 0}, h16 = 0;
+    auto     load_gx = [&](int t, float (&gx)[4]) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) bia[g] = h2f(a.bias[g * H + j0 + cu]);
-    if (cell) cst = a.c[(long long)(b0 + cr) * H + j0 + cu];
+        for (int g = 0; g < 4; ++g) gx[g] = a.gx[(t * a.step_rows + brow) * 4 * H + g * H + j0 + cu];
+    };
+    if (owner) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) bia[g] = h2f(a.bias[g * H + j0 + cu]);
+        cst = a.c[brow * H + j0 + cu];
+        load_gx(0, gx0);
+    }
+    auto store_step = [&](int t) {  // what step t leaves in memory
+        const long long row = t * a.step_rows + brow;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) a.gates[row * 4 * H + g * H + j0 + cu] = g16[g];
+        a.c[(row + a.step_rows) * H + j0 + cu] = cst;
+        if (t + 1 < T) a.xh[(row + a.step_rows) * a.ldxh + I + j0 + cu] = h16;
+        if (a.h_up != nullptr) a.h_up[row * a.ld_up + j0 + cu] = h16;
+    };
+    // where this workgroup's units lie in a slot: fragment pair, k-step of the pair, and the lane rows of its two 8-unit pieces
+    const int      pks = (j0 % Kw) >> 5, plq = ((j0 & 31) >> 3) + (cu >> 3);
+    const unsigned pub = ((j0 / Kw) * np + (pks >> 1)) * 1024 + (plq * 16 + (pks & 1) * 8 + cr) * 16;
 
-    for (int t = 0; t < T; ++t) {
-        const long long row0 = (long long)t * B + b0;
-        // the input half of this thread's gate sums does not depend on the recurrence: request it ahead of the wait
-        float gxv[4] = {0.f, 0.f, 0.f, 0.f};
-        if (cell) {
+    // gx: the input half of this step's gate sums, gxn: of the next step's.
+    // Order of the memory instructions: a slice is published ahead of everything else of its step, and the workgroup looks
+    // for the others' only when its own is acknowledged: polling loads queue ahead of stores on their way out and keep
+    // invalidated lines moving between the caches (both kernels 25-30 % slower with waves that poll from the start).
+    // Results and the next inputs follow, and their latency runs under the flight of the slices.
+    auto step = [&](const int t, const float (&gx)[4], float (&gxn)[4]) {
+        // lane lr < 8: row lr, k-step 2 p of pair p; lr >= 8: row lr - 8, k-step 2 p + 1
+        u32x4 f[np];
+        if (t == 0) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) gxv[g] = a.gx[(row0 + cr) * 4 * H + g * H + j0 + cu];
-        }
-        if (t > 0 && !grid_wait(sync, t, &verdict)) return;  // every workgroup's slice of h_{t-1} (these rows) is in memory
-        const uint16_t* hprev = a.xh + row0 * a.ldxh + I;
-        u32x4           af[8];
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            af[ks] = u32x4{0u, 0u, 0u, 0u};
-            if (ks < nks && lr < nb) af[ks] = *reinterpret_cast<const u32x4*>(hprev + (long long)lr * a.ldxh + k0 + 32 * ks);
-        }
-        f32x4 acc[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            if (ks < nks) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_frag(wf[g][ks]), as_frag(af[ks]), acc[g], 0, 0, 0);
+            for (int p = 0; p < np; ++p) {
+                f[p] = u32x4{0u, 0u, 0u, 0u};
+                if (2 * p + (lr >> 3) < nks && (lr & 7) < nb)
+                    f[p] = *reinterpret_cast<const u32x4*>(a.xh + (long long)(b0 + (lr & 7)) * a.ldxh + I + k0 + 32 * (2 * p + (lr >> 3)));
             }
+        } else {
+            rl_take<np, (nks & 1) != 0>(ring, ((t - 1) % RL_RING) * slot + wave * np * 1024 + lane * 16, f, a.sync, dead);
         }
-        // acc[g][r] = partial sum of gate g, unit 4 lq + r, batch row lr
+        f32x4 acc[2][4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < 4; ++g) acc[0][g] = acc[1][g] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave][lr][16 * g + 4 * lq + r] = acc[g][r];
-        __syncthreads();
-        if (cell) {
-            uint16_t g16[4], h16;
-            float    gs[4];
+        for (int ks = 0; ks < nks; ++ks) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                acc[ks & 1][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_frag(wf[g][ks]), as_frag(f[ks >> 1]), acc[ks & 1][g], 0, 0, 0);
+        }
+        // acc[.][g][r] = partial sum of gate g, unit 4 lq + r, column lr; columns 0-7 are right for even k-steps, 8-15 for odd
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f32x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = rl_add_upper(acc[0][g][r], acc[1][g][r]);
+            if (lr < 8) *reinterpret_cast<f32x4*>(&red[t & 1][wave][lr][16 * g + 4 * lq]) = v;
+        }
+        lds_barrier();
+        if (owner) {
+            float gs[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int   n = 16 * g + cu;
-                const float s = ((red[0][cr][n] + red[1][cr][n]) + red[2][cr][n]) + red[3][cr][n];
-                g16[g]        = f2h((s + gxv[g]) + bia[g]);  // the gate sum's one rounding to storage
-                gs[g]         = h2f(g16[g]);
+                const int n = 16 * g + cu;
+                float     s = red[t & 1][0][cr][n];
+#pragma unroll
+                for (int q = 1; q < 4; ++q) s += red[t & 1][q][cr][n];
+                g16[g] = f2h((s + gx[g]) + bia[g]);  // the gate sum's one rounding to storage
+                gs[g]  = h2f(g16[g]);
             }
             cst = lstm_cell_forward(gs[0], gs[1], gs[2], gs[3], cst, &h16);
-            const long long row = row0 + cr;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) a.gates[row * 4 * H + g * H + j0 + cu] = g16[g];
-            a.c[(row + B) * H + j0 + cu] = cst;
-            if (t + 1 < T) a.xh[(row + B) * a.ldxh + I + j0 + cu] = h16;
-            if (a.h_up != nullptr) a.h_up[row * a.ld_up + j0 + cu] = h16;
+            if (t + 1 < T) {
+                const u32x4 piece = rl_gather8(h16);
+                if ((cu & 7) == 0) {
+                    __builtin_amdgcn_raw_buffer_store_b128(piece, ring, (t % RL_RING) * slot + pub, 0, RL_DEVICE_SCOPE);
+                    if (t >= 2)
+                        __builtin_amdgcn_raw_buffer_store_b128(u32x4{~0u, ~0u, ~0u, ~0u}, ring, ((t - 2) % RL_RING) * slot + pub, 0,
+                                                               RL_DEVICE_SCOPE);
+                }
+            }
+            // acknowledged: also what was emptied is empty for everybody, ahead of this workgroup's next slice
+            __builtin_amdgcn_s_waitcnt(RL_VMCNT0);
         }
-        if (t + 1 < T) grid_arrive(sync, t + 1);  // (its workgroup barrier also keeps `red` of this step apart from the next)
+        // (`red` of this parity is written again two steps on, behind this barrier)
+        lds_barrier();
+        if (cell) store_step(t);
+        if (owner && t + 1 < T) load_gx(t + 1, gxn);
+    };
+    for (int t = 0; t < T; t += 2) {
+        step(t, gx0, gx1);
+        if (t + 1 < T) step(t + 1, gx1, gx0);
     }
 }
 
 // ------------------------------------------------------------------------------------------------ backward
 struct LstmBwdArgs {
     int             T, B, I, H;
+    long long       step_rows;
     const uint16_t* w;         // [4H, ldw]
     int             ldw;
-    const uint16_t* gates;     // [T*B, 4H]
-    const float*    c;         // [(T+1)*B, H]
-    const uint16_t* dh_above;  // [T*B, ld_above]: gradient reaching h_t from the layer above (or the loss)
+    const uint16_t* gates;     // [T*step_rows, 4H]
+    const float*    c;         // [(T+1)*step_rows, H]
+    const uint16_t* dh_above;  // [T*step_rows, ld_above]: gradient reaching h_t from the layer above (or the loss)
     int             ld_above;
-    uint16_t*       dgates;    // [T*B, 4H] out
+    uint16_t*       dgates;    // [T*step_rows, 4H] out
     RlSync          sync;
 };
+__host__ __device__ constexpr unsigned rl_bwd_slot(int H) { return 4u * 1024u * (H / 64); }
 
-__global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1))) void lstm_layer_bwd_kernel(LstmBwdArgs a) {
-    __shared__ float red[4][16][17];  // per wave: partial recurrent gradient [batch row][unit]
-    __shared__ int   verdict;
+template <int HB>
+__global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_layer_bwd_kernel(LstmBwdArgs a) {
+    __shared__ __align__(16) float red[2][4][RL_ROWS][16];  // per step parity and wave: partial recurrent gradients [row][unit]
+    __shared__ __align__(16) char stage[4][1024];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
-    const int H = a.H, I = a.I, B = a.B, T = a.T;
+    constexpr int H = 128 * HB;
+    const int I = a.I, T = a.T;
     const int j0  = blockIdx.x * RL_UNITS;
     const int b0  = blockIdx.y * RL_ROWS;
-    const int nb  = min(RL_ROWS, B - b0);
-    const int nks = H >> 5;                // this wave contracts over the H rows of gate block `wave`, 32 at a time
-    const int n0  = wave * H + 8 * lq;     // first gate row of this lane's 8 consecutive values, + 32 ks
-    RlSync    sync = a.sync;
-    sync.flags += blockIdx.y * RL_FLAG_WORDS;
+    const int nb  = min(RL_ROWS, a.B - b0);
+    constexpr int nks = H / 32;            // this wave contracts over the H rows of gate block `wave`, 32 at a time
+    constexpr int np  = nks / 2;
+    constexpr unsigned slot = rl_bwd_slot(H);
+    const __amdgpu_buffer_rsrc_t ring = rl_ring(a.sync.ring + (size_t)blockIdx.y * RL_RING * slot, RL_RING * slot);
+    bool dead = false;
 
-    // W_h^T fragments: unit lr, 8 consecutive gate rows n: W[n][I + j0 + lr] (a strided gather, once per launch)
-    u32x4 wt[32];
+    // W_h^T fragments: unit lr, 8 consecutive gate rows n = wave H + 32 ks + 8 lq ...: W[n][I + j0 + lr].  Read as row
+    // pieces of 8 units, turned by the transposing LDS read (see gemm_dtl.hpp for its lane mapping): 32 rows at a time
+    // through 1 KB of this wave's own LDS.
+    u32x4 wt[nks];
 #pragma unroll
-    for (int ks = 0; ks < 32; ++ks) {
-        wt[ks] = u32x4{0u, 0u, 0u, 0u};
-        if (ks < nks) {
-            const uint16_t* p = a.w + (long long)(n0 + 32 * ks) * a.ldw + I + j0 + lr;
-            unsigned        q[4];
+    for (int ks = 0; ks < nks; ++ks)
+        wt[ks] = *reinterpret_cast<const u32x4*>(a.w + (long long)(wave * H + 32 * ks + (lane >> 1)) * a.ldw + I + j0 + 8 * (lane & 1));
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                q[e] = (unsigned)p[(long long)(2 * e) * a.ldw] | ((unsigned)p[(long long)(2 * e + 1) * a.ldw] << 16);
-            wt[ks] = u32x4{q[0], q[1], q[2], q[3]};
-        }
+    for (int ks = 0; ks < nks; ++ks) {
+        char* st = stage[wave];
+        *reinterpret_cast<u32x4*>(st + (lane >> 1) * 32 + (lane & 1) * 16) = wt[ks];
+        const char* rd = st + (8 * lq + (lr >> 2)) * 32 + (lr & 3) * 8;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)rd);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(rd + 4 * 32));
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        wt[ks]        = __builtin_bit_cast(u32x4, v);
     }
 
-    const int  cr = tid >> 4, cu = tid & 15;
-    const bool cell = cr < nb;
+    const int  cr = tid >> 4, cu = tid & 15;  // (as in the forward kernel)
+    const bool owner = cr < RL_ROWS, cell = cr < nb;
+    const long long brow = b0 + min(cr, nb - 1);
     float      dc = 0.f, dhrec = 0.f;
+    const int      pks = j0 >> 5, plq = ((j0 & 31) >> 3) + (cu >> 3);
+    const unsigned pub = (pks >> 1) * 1024 + (plq * 16 + (pks & 1) * 8 + cr) * 16;  // + gate * np * 1024
 
-    // inputs of one cell-backward step for this thread's cell (they do not depend on the recurrence, so the next
-    // step's are requested while the workgroup waits at the step barrier)
+    // inputs of one cell-backward step for this thread's cell (they do not depend on the recurrence: requested two steps
+    // ahead)
     struct CellIn {
         uint16_t gp[4], da;
         float    cp, cn;
     };
-    auto load_cell = [&](int t) {
-        CellIn q{};
-        if (cell) {
-            const long long row = (long long)t * B + b0 + cr;
+    auto load_cell = [&](int t, CellIn& q) {
+        const long long row = t * a.step_rows + brow;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) q.gp[g] = a.gates[row * 4 * H + g * H + j0 + cu];
-            q.cp = a.c[row * H + j0 + cu];
-            q.cn = a.c[(row + B) * H + j0 + cu];
-            q.da = a.dh_above[row * a.ld_above + j0 + cu];
-        }
-        return q;
+        for (int g = 0; g < 4; ++g) q.gp[g] = a.gates[row * 4 * H + g * H + j0 + cu];
+        q.cp = a.c[row * H + j0 + cu];
+        q.cn = a.c[(row + a.step_rows) * H + j0 + cu];
+        q.da = a.dh_above[row * a.ld_above + j0 + cu];
     };
-    CellIn in = load_cell(T - 1);
+    CellIn in0, in1;
+    if (owner) {
+        load_cell(T - 1, in0);
+        if (T > 1) load_cell(T - 2, in1);
+    }
 
-    for (int t = T - 1; t >= 0; --t) {
-        const long long row0 = (long long)t * B + b0;
-        if (cell) {
-            uint16_t d4[4];
+    auto step = [&](const int t, CellIn& in) {
+        const int n = T - 1 - t;  // number of the slice
+        uint16_t  d4[4] = {0, 0, 0, 0};
+        auto      store_step = [&] {
+            uint16_t* o = a.dgates + (t * a.step_rows + brow) * 4 * H + j0 + cu;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) o[g * H] = d4[g];
+        };
+        if (owner) {
             dc = lstm_cell_backward(h2f(in.gp[0]), h2f(in.gp[1]), h2f(in.gp[2]), h2f(in.gp[3]), in.cp, in.cn, h2f(in.da) + dhrec, dc, d4);
+            if (t > 0) {
+                u32x4 piece[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) a.dgates[(row0 + cr) * 4 * H + g * H + j0 + cu] = d4[g];
+                for (int g = 0; g < 4; ++g) piece[g] = rl_gather8(d4[g]);
+                if ((cu & 7) == 0) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        __builtin_amdgcn_raw_buffer_store_b128(piece[g], ring, (n % RL_RING) * slot + g * np * 1024 + pub, 0, RL_DEVICE_SCOPE);
+                    if (n >= 2) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            __builtin_amdgcn_raw_buffer_store_b128(u32x4{~0u, ~0u, ~0u, ~0u}, ring,
+                                                                   ((n - 2) % RL_RING) * slot + g * np * 1024 + pub, 0, RL_DEVICE_SCOPE);
+                    }
+                }
+            }
         }
-        if (t == 0) break;
-        const int step = T - t;                       // 1 .. T-1
-        grid_arrive(sync, step);
-        in = load_cell(t - 1);
-        if (!grid_wait(sync, step, &verdict)) return;           // these rows of dgates_t are complete in memory
-        // recurrent gradient of this workgroup's units: dgates_t[rows, 4H] W_h[:, j0 .. j0+16).  All of this lane's
-        // pieces of dgates_t are requested at once (one memory latency), then multiplied.
-        const uint16_t* dg = a.dgates + row0 * 4 * H;
-        u32x4           af[32];
-#pragma unroll
-        for (int ks = 0; ks < 32; ++ks) {
-            af[ks] = u32x4{0u, 0u, 0u, 0u};
-            if (ks < nks && lr < nb) af[ks] = *reinterpret_cast<const u32x4*>(dg + (long long)lr * 4 * H + n0 + 32 * ks);
+        if (t == 0) {
+            if (cell) store_step();
+            return;
         }
-        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};  // two chains: even and odd steps
+        if (owner) __builtin_amdgcn_s_waitcnt(RL_VMCNT0);  // (as in the forward kernel)
+        lds_barrier();  // (nobody looks before the own slice is on its way, as in the forward kernel)
+        if (cell) store_step();
+        if (owner && t >= 2) load_cell(t - 2, in);
+        // recurrent gradient of this workgroup's units: dgates_t[rows, 4H] W_h[:, j0 .. j0+16)
+        u32x4 f[np];
+        rl_take<np, false>(ring, (n % RL_RING) * slot + wave * np * 1024 + lane * 16, f, a.sync, dead);
+        f32x4 acc[4];  // k-step ks into chain ks % 4
 #pragma unroll
-        for (int ks = 0; ks < 32; ++ks)
-            if (ks < nks) acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_frag(wt[ks]), as_frag(af[ks]), acc[ks & 1], 0, 0, 0);
-        // acc[.][r] = partial sum for unit 4 lq + r, batch row lr
+        for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][lr][4 * lq + r] = acc[0][r] + acc[1][r];
-        __syncthreads();
-        if (cell) {
-            const float s = ((red[0][cr][cu] + red[1][cr][cu]) + red[2][cr][cu]) + red[3][cr][cu];
-            dhrec         = round16(s);              // the recurrent gradient is a stored (fp16) tensor
+        for (int ks = 0; ks < nks; ++ks)
+            acc[ks & 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_frag(wt[ks]), as_frag(f[ks >> 1]), acc[ks & 3], 0, 0, 0);
+        // acc[.][r] = partial sum for unit 4 lq + r, column lr; columns 0-7 are right for even k-steps, 8-15 for odd
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = rl_add_upper(acc[0][r] + acc[2][r], acc[1][r] + acc[3][r]);
+        if (lr < 8) *reinterpret_cast<f32x4*>(&red[t & 1][wave][lr][4 * lq]) = v;
+        lds_barrier();
+        if (owner) {
+            float s = red[t & 1][0][cr][cu];
+#pragma unroll
+            for (int q = 1; q < 4; ++q) s += red[t & 1][q][cr][cu];
+            dhrec = round16(s);              // the recurrent gradient is a stored (fp16) tensor
         }
-        // (`red` is next written behind the next step's barrier)
+        // (`red` of this parity is written again two steps on, behind the next barriers)
+    };
+    for (int t = T - 1; t >= 0; t -= 2) {
+        step(t, in0);
+        if (t >= 1) step(t - 1, in1);
     }
 }
 
@@ -290,46 +408,63 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
 
 using namespace mp;
 
+// f(std::integral_constant<int, H / 128>)
+template <typename F>
+static void rl_with_width(int H, F f) {
+    switch (H / 128) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        default: f(std::integral_constant<int, 8>{}); break;
+    }
+}
+
 static int rl_check(const mp_lstm_layer_desc* d, const char* who, int* nwg) {
     MP_REQUIRE(d != nullptr, "%s: desc is NULL", who);
     MP_REQUIRE(d->T >= 1 && d->B >= 1 && d->I >= 0 && d->H >= 1, "%s: bad sizes T=%d B=%d I=%d H=%d", who, d->T, d->B, d->I, d->H);
     MP_REQUIRE(d->ldw >= d->I + d->H && d->ldxh >= d->I + d->H, "%s: leading dimension smaller than I + H", who);
     MP_REQUIRE(d->wait_limit_us >= 0 && d->debug_extra_participants >= 0 && d->debug_extra_participants <= 64,
                "%s: bad wait limit / debug participants", who);
-    if (d->B > 32 || d->H % 128 != 0 || d->H > RL_MAX_H || d->I % 8 != 0 || d->ldw % 8 != 0 || d->ldxh % 8 != 0) {
+    if (d->B > RL_MAX_B || d->H % 128 != 0 || d->H > RL_MAX_H || d->I % 8 != 0 || d->ldw % 8 != 0 || d->ldxh % 8 != 0) {
         set_error("%s: the persistent kernel needs B <= 32, H a multiple of 128 up to %d, and I / ldw / ldxh multiples of 8 "
                   "(got B=%d H=%d I=%d ldw=%d ldxh=%d); run the layer step by step instead", who, RL_MAX_H, d->B, d->H, d->I,
                   d->ldw, d->ldxh);
         return MP_E_UNSUPPORTED;
     }
+    MP_REQUIRE(d->step_rows == 0 || d->step_rows >= d->B, "%s: step_rows=%d smaller than B=%d", who, d->step_rows, d->B);
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return hip_fail(e, who);
     *nwg = d->H / RL_UNITS;
     const int groups = (d->B + RL_ROWS - 1) / RL_ROWS;
-    if (*nwg * groups > cus) {  // every workgroup must be resident at once, or the step barrier cannot complete
-        set_error("%s: %d workgroups needed, the device has %d compute units", who, *nwg * groups, cus);
+    if (*nwg * groups > 2 * cus) {  // every workgroup must be resident at once (two fit a compute unit), or no wait can end
+        set_error("%s: %d workgroups needed, the device has %d compute units for two each", who, *nwg * groups, cus);
         return MP_E_UNSUPPORTED;
     }
     return MP_OK;
 }
 
-// step flags: two barrier groups (B <= 32 rows in blocks of 16) of up to 64 workgroups + 64 debug words each
-extern "C" size_t mp_lstm_layer_workspace_bytes(void) { return 2 * RL_FLAG_WORDS * sizeof(int); }
+// the exchange rings of the largest shape: one per block of batch rows, backward slices being the larger ones
+extern "C" size_t mp_lstm_layer_workspace_bytes(void) { return (size_t)(RL_MAX_B / RL_ROWS) * RL_RING * rl_bwd_slot(RL_MAX_H); }
 
-static int rl_sync(const mp_lstm_layer_desc* d, int nwg, int32_t* status, void* ws, size_t ws_bytes, mp_stream stream,
+static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, mp_stream stream,
                    const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
-    if (!ws || ws_bytes < mp_lstm_layer_workspace_bytes() || (reinterpret_cast<uintptr_t>(ws) & 3u)) {
-        set_error("%s: workspace of %zu bytes needed, %zu given", who, mp_lstm_layer_workspace_bytes(), ws_bytes);
+    if (!ws || ws_bytes < mp_lstm_layer_workspace_bytes() || !aligned16(ws)) {
+        set_error("%s: 16-byte aligned workspace of %zu bytes needed, %zu given", who, mp_lstm_layer_workspace_bytes(), ws_bytes);
         return MP_E_WORKSPACE;
     }
-    const int rc = mp_fill_u32(mp_lstm_layer_workspace_bytes() / 4, 0u, ws, stream);  // flags start at zero (a kernel: capturable)
+    const size_t used = (size_t)((d->B + RL_ROWS - 1) / RL_ROWS) * RL_RING * slot;
+    const int    rc   = mp_fill_u32(used / 4, ~0u, ws, stream);  // everything starts empty (a kernel: capturable)
     if (rc != MP_OK) return rc;
-    out->flags       = static_cast<int*>(ws);
+    out->ring        = static_cast<char*>(ws);
     out->status      = status;
-    out->nwait       = nwg + d->debug_extra_participants;
+    out->never       = d->debug_extra_participants > 0;
     out->limit_ticks = (d->wait_limit_us > 0 ? (long long)d->wait_limit_us : 2000000ll) * 100;  // 100 MHz clock
     return MP_OK;
 }
@@ -345,12 +480,14 @@ extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, c
     MP_REQUIRE(aligned16(w) && aligned16(xh) && aligned16(gx) && aligned16(gates) && aligned16(c) && (h_up == nullptr || aligned16(h_up)),
                "mp_lstm_layer_fwd: pointers must be 16-byte aligned");
     LstmFwdArgs a{};
-    rc = rl_sync(d, nwg, status, ws, ws_bytes, stream, "mp_lstm_layer_fwd", &a.sync);
+    rc = rl_sync(d, rl_fwd_slot(d->H), status, ws, ws_bytes, stream, "mp_lstm_layer_fwd", &a.sync);
     if (rc) return rc;
-    a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H;
+    a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.gx = gx; a.w = w; a.ldw = d->ldw; a.bias = bias; a.gates = gates; a.c = c; a.xh = xh; a.ldxh = d->ldxh;
     a.h_up = h_up; a.ld_up = d->ld_up;
-    hipLaunchKernelGGL(lstm_layer_fwd_kernel, dim3(nwg, (d->B + RL_ROWS - 1) / RL_ROWS), dim3(RL_THREADS), 0, as_stream(stream), a);
+    rl_with_width(d->H, [&](auto hb) {
+        hipLaunchKernelGGL(lstm_layer_fwd_kernel<decltype(hb)::value>, dim3(nwg, (d->B + RL_ROWS - 1) / RL_ROWS), dim3(RL_THREADS), 0, as_stream(stream), a);
+    });
     MP_LAUNCH_CHECK("mp_lstm_layer_fwd");
     return MP_OK;
 }
@@ -366,11 +503,13 @@ extern "C" int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d, const mp_half* w, 
     MP_REQUIRE(aligned16(w) && aligned16(gates) && aligned16(c) && aligned16(dh_above) && aligned16(dgates),
                "mp_lstm_layer_bwd: pointers must be 16-byte aligned");
     LstmBwdArgs a{};
-    rc = rl_sync(d, nwg, status, ws, ws_bytes, stream, "mp_lstm_layer_bwd", &a.sync);
+    rc = rl_sync(d, rl_bwd_slot(d->H), status, ws, ws_bytes, stream, "mp_lstm_layer_bwd", &a.sync);
     if (rc) return rc;
-    a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H;
+    a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.w = w; a.ldw = d->ldw; a.gates = gates; a.c = c; a.dh_above = dh_above; a.ld_above = d->ld_up; a.dgates = dgates;
-    hipLaunchKernelGGL(lstm_layer_bwd_kernel, dim3(nwg, (d->B + RL_ROWS - 1) / RL_ROWS), dim3(RL_THREADS), 0, as_stream(stream), a);
+    rl_with_width(d->H, [&](auto hb) {
+        hipLaunchKernelGGL(lstm_layer_bwd_kernel<decltype(hb)::value>, dim3(nwg, (d->B + RL_ROWS - 1) / RL_ROWS), dim3(RL_THREADS), 0, as_stream(stream), a);
+    });
     MP_LAUNCH_CHECK("mp_lstm_layer_bwd");
     return MP_OK;
 }
