@@ -368,8 +368,9 @@ int mp_lstm_cell_bwd(int B, int H, const mp_half* gates, int ldg, const float* c
  * All H / 16 x ceil(B / 8) workgroups must be resident at once, two to a compute unit: the call returns
  * MP_E_UNSUPPORTED if the device has too few compute units, and launches of this kind that may run at the same time
  * (other streams) must together fit the device.
- * Supported: B <= 32, H a multiple of 128 up to 1024, I, ldw, ldxh multiples of 8, ld_up even, 16-byte aligned
- * pointers; otherwise MP_E_UNSUPPORTED (run the layer with mp_gemm_fwd_ws / mp_lstm_cell_fwd step by step).
+ * Supported: H a multiple of 128 up to 1024 and B <= 32, or with step_rows given H a multiple of 64 up to 1024 and any
+ * B whose workgroups fit the device (at most 2 per compute unit); I, ldw, ldxh multiples of 8, ld_up even, 16-byte
+ * aligned pointers; otherwise MP_E_UNSUPPORTED (run the layer with mp_gemm_fwd_ws / mp_lstm_cell_fwd step by step).
  * debug_extra_participants (0 in production) makes every wait last as if something never arrived: with a small
  * wait_limit_us it lets a test drive the time-out path while every wave still exits normally. */
 typedef struct mp_lstm_layer_desc {
@@ -378,9 +379,11 @@ typedef struct mp_lstm_layer_desc {
     int32_t wait_limit_us;    /* bound of one wait; 0 = 2 000 000                                   */
     int32_t debug_extra_participants;
     int32_t step_rows;        /* rows from one time step to the next in gx, gates, c, xh, h_up / dh_above and dgates;
-                                 0: B.  Larger than B, the call works on B rows of a larger batch                */
+                                 0: B.  Larger than B, the call works on B rows of a larger batch.  A caller that gives
+                                 it (>= B) sizes ws with mp_lstm_layer_desc_workspace_bytes and has the wider range  */
 } mp_lstm_layer_desc;
 size_t mp_lstm_layer_workspace_bytes(void);
+size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d /* host */); /* for calls that give step_rows */
 int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d /* host */, const float* gx, const mp_half* w, const mp_half* bias,
                       mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws, size_t ws_bytes,
                       mp_stream stream);

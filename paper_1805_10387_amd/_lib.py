@@ -89,6 +89,7 @@ SIGNATURES = {
     "mp_lstm_cell_fwd": (_I, [_I, _I, _P, _I, _P, _P, _P, _I, _P, _I, _P]),
     "mp_lstm_cell_bwd": (_I, [_I, _I, _P, _I, _P, _P, _P, _I, _P, _I, _P, _P, _P]),
     "mp_lstm_layer_workspace_bytes": (_SZ, []),
+    "mp_lstm_layer_desc_workspace_bytes": (_SZ, [C.POINTER(LstmLayerDesc)]),
     "mp_lstm_layer_fwd": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_lstm_layer_bwd": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_cast_f32_to_f16": (_I, [_SZ, _P, _P, _P]),

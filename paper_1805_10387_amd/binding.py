@@ -221,6 +221,10 @@ def mp_lstm_layer_workspace_bytes() -> int:
     return L.load().mp_lstm_layer_workspace_bytes()
 
 
+def mp_lstm_layer_desc_workspace_bytes(desc) -> int:
+    return L.load().mp_lstm_layer_desc_workspace_bytes(C.byref(desc))
+
+
 def mp_lstm_layer_fwd(desc, gx, w, bias, gates, c, xh, h_up, status, ws):
     _check(L.load().mp_lstm_layer_fwd(C.byref(desc), _p(gx), _p(w), _p(bias), _p(gates), _p(c), _p(xh), _p(h_up), _p(status),
                                       _p(ws), ws.numel() * ws.element_size(), _stream()))

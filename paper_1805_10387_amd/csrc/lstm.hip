@@ -67,18 +67,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rl_ring(char* base, unsigned b
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
 }
 
-// The NP fragment pairs (1 KB apart) of a published slice, loaded until nothing in them is empty.  HALF_LAST: only lanes
-// with (lane & 8) == 0 of the last pair are ever published.  Waves decide alone; `dead` (wave-uniform) is set when this
+// The NP fragment pairs (1 KB apart) of a published slice, loaded until nothing in them is empty.  GUARD_LAST: lanes
+// without last_ok never get anything in the last pair (it reads as zero there).  Waves decide alone; `dead` (wave-uniform) is set when this
 // or another wave gave up, and ends all waiting.
-template <int NP, bool HALF_LAST>
-__device__ __forceinline__ void rl_take(__amdgpu_buffer_rsrc_t ring, unsigned off, u32x4 (&f)[NP], const RlSync& s, bool& dead) {
-    const bool upper = (threadIdx.x & 8) != 0;
+template <int NP, bool GUARD_LAST>
+__device__ __forceinline__ void rl_take(__amdgpu_buffer_rsrc_t ring, unsigned off, bool last_ok, u32x4 (&f)[NP],
+                                        const RlSync& s, bool& dead) {
     long long  t0    = 0;
     for (int it = 0;; ++it) {
         asm volatile("" ::: "memory");  // (every round loads anew)
 #pragma unroll
         for (int p = 0; p < NP; ++p) f[p] = __builtin_amdgcn_raw_buffer_load_b128(ring, off + p * 1024, 0, RL_DEVICE_SCOPE);
-        if (HALF_LAST && upper) f[NP - 1] = u32x4{0u, 0u, 0u, 0u};
+        if (GUARD_LAST && !last_ok) f[NP - 1] = u32x4{0u, 0u, 0u, 0u};
         u16x2 m = {0, 0};  // the largest half seen: RL_EMPTY is the largest pattern there is
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -134,23 +134,26 @@ struct LstmFwdArgs {
     int             ld_up;
     RlSync          sync;
 };
-// fragment pairs per wave (a wave contracts over H / 4 hidden units) and bytes of one slot
-__host__ __device__ constexpr int      rl_fwd_pairs(int H) { return (H / 128 + 1) / 2; }
+// The contraction over h is cut into k-steps of 32, dealt to the 4 waves in runs that differ by at most one.  Most
+// k-steps of a wave, fragment pairs per wave, and bytes of one slot:
+__host__ __device__ constexpr int      rl_fwd_steps(int H) { return (H / 32 + 3) / 4; }
+__host__ __device__ constexpr int      rl_fwd_pairs(int H) { return (rl_fwd_steps(H) + 1) / 2; }
 __host__ __device__ constexpr unsigned rl_fwd_slot(int H) { return 4u * 1024u * rl_fwd_pairs(H); }
 
-template <int HB>  // H = 128 HB
+template <int HQ>  // H = 64 HQ
 __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_layer_fwd_kernel(LstmFwdArgs a) {
     __shared__ __align__(16) float red[2][4][RL_ROWS][80];  // per step parity and wave: partial gate sums [row][16 g + unit] (row stride: 64 banks + 16)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
-    constexpr int H = 128 * HB;
+    constexpr int H = 64 * HQ;
     const int I = a.I, T = a.T;
     const int j0  = blockIdx.x * RL_UNITS;   // this workgroup's hidden units
     const int b0  = blockIdx.y * RL_ROWS;    // ... and batch rows
     const int nb  = min(RL_ROWS, a.B - b0);
-    constexpr int Kw  = H / 4;          // this wave's share of the contraction over h
-    constexpr int nks = HB;             // matrix-core steps of 32
-    constexpr int np  = rl_fwd_pairs(H);
-    const int k0  = wave * Kw + 8 * lq; // first k of this lane's 8 consecutive values, + 32 ks
+    constexpr int nks = rl_fwd_steps(H), np = rl_fwd_pairs(H);
+    constexpr int each = H / 32 / 4, more = H / 32 % 4;    // k-steps of every wave; that many waves have one more
+    const int mine = each + (wave < more ? 1 : 0);
+    const int k0   = 32 * (wave * each + min(wave, more)) + 8 * lq;  // first k of this lane's 8 consecutive values, + 32 ks
+    const bool last_ok = 2 * (np - 1) + (lr >> 3) < mine;            // this lane's k-step of the last pair exists
     constexpr unsigned slot = rl_fwd_slot(H);
     const __amdgpu_buffer_rsrc_t ring = rl_ring(a.sync.ring + (size_t)blockIdx.y * RL_RING * slot, RL_RING * slot);
     bool dead = false;
@@ -160,8 +163,10 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int ks = 0; ks < nks; ++ks)
-            wf[g][ks] = *reinterpret_cast<const u32x4*>(a.w + (long long)(g * H + j0 + lr) * a.ldw + I + k0 + 32 * ks);
+        for (int ks = 0; ks < nks; ++ks) {
+            wf[g][ks] = u32x4{0u, 0u, 0u, 0u};
+            if (more == 0 || ks < mine) wf[g][ks] = *reinterpret_cast<const u32x4*>(a.w + (long long)(g * H + j0 + lr) * a.ldw + I + k0 + 32 * ks);
+        }
 
     // cell ownership (waves 0 and 1): thread -> batch row b0 + cr, unit j0 + cu.  Rows beyond the batch repeat the last one
     // (their values are published but never stored), so that no load hangs on a condition.
@@ -189,8 +194,9 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (a.h_up != nullptr) a.h_up[row * a.ld_up + j0 + cu] = h16;
     };
     // where this workgroup's units lie in a slot: fragment pair, k-step of the pair, and the lane rows of its two 8-unit pieces
-    const int      pks = (j0 % Kw) >> 5, plq = ((j0 & 31) >> 3) + (cu >> 3);
-    const unsigned pub = ((j0 / Kw) * np + (pks >> 1)) * 1024 + (plq * 16 + (pks & 1) * 8 + cr) * 16;
+    const int      jks = j0 >> 5, jw = jks < more * (each + 1) ? jks / (each + 1) : (each > 0 ? (jks - more) / (each > 0 ? each : 1) : 0);
+    const int      pks = jks - (jw * each + min(jw, more)), plq = ((j0 & 31) >> 3) + (cu >> 3);
+    const unsigned pub = (jw * np + (pks >> 1)) * 1024 + (plq * 16 + (pks & 1) * 8 + cr) * 16;
 
     // gx: the input half of this step's gate sums, gxn: of the next step's.
     // Order of the memory instructions: a slice is published ahead of everything else of its step, and the workgroup looks
@@ -204,11 +210,11 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int p = 0; p < np; ++p) {
                 f[p] = u32x4{0u, 0u, 0u, 0u};
-                if (2 * p + (lr >> 3) < nks && (lr & 7) < nb)
+                if (2 * p + (lr >> 3) < mine && (lr & 7) < nb)
                     f[p] = *reinterpret_cast<const u32x4*>(a.xh + (long long)(b0 + (lr & 7)) * a.ldxh + I + k0 + 32 * (2 * p + (lr >> 3)));
             }
         } else {
-            rl_take<np, (nks & 1) != 0>(ring, ((t - 1) % RL_RING) * slot + wave * np * 1024 + lane * 16, f, a.sync, dead);
+            rl_take<np, (more != 0 || (nks & 1) != 0)>(ring, ((t - 1) % RL_RING) * slot + wave * np * 1024 + lane * 16, last_ok, f, a.sync, dead);
         }
         f32x4 acc[2][4];
 #pragma unroll
@@ -278,12 +284,12 @@ struct LstmBwdArgs {
 };
 __host__ __device__ constexpr unsigned rl_bwd_slot(int H) { return 4u * 1024u * (H / 64); }
 
-template <int HB>
+template <int HQ>
 __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_layer_bwd_kernel(LstmBwdArgs a) {
     __shared__ __align__(16) float red[2][4][RL_ROWS][16];  // per step parity and wave: partial recurrent gradients [row][unit]
     __shared__ __align__(16) char stage[4][1024];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lq = lane >> 4;
-    constexpr int H = 128 * HB;
+    constexpr int H = 64 * HQ;
     const int I = a.I, T = a.T;
     const int j0  = blockIdx.x * RL_UNITS;
     const int b0  = blockIdx.y * RL_ROWS;
@@ -377,7 +383,7 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (owner && t >= 2) load_cell(t - 2, in);
         // recurrent gradient of this workgroup's units: dgates_t[rows, 4H] W_h[:, j0 .. j0+16)
         u32x4 f[np];
-        rl_take<np, false>(ring, (n % RL_RING) * slot + wave * np * 1024 + lane * 16, f, a.sync, dead);
+        rl_take<np, false>(ring, (n % RL_RING) * slot + wave * np * 1024 + lane * 16, true, f, a.sync, dead);
         f32x4 acc[4];  // k-step ks into chain ks % 4
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -408,19 +414,13 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 
 using namespace mp;
 
-// f(std::integral_constant<int, H / 128>)
-template <typename F>
+// f(std::integral_constant<int, H / 64>)
+template <int HQ = 1, typename F>
 static void rl_with_width(int H, F f) {
-    switch (H / 128) {
-        case 1: f(std::integral_constant<int, 1>{}); break;
-        case 2: f(std::integral_constant<int, 2>{}); break;
-        case 3: f(std::integral_constant<int, 3>{}); break;
-        case 4: f(std::integral_constant<int, 4>{}); break;
-        case 5: f(std::integral_constant<int, 5>{}); break;
-        case 6: f(std::integral_constant<int, 6>{}); break;
-        case 7: f(std::integral_constant<int, 7>{}); break;
-        default: f(std::integral_constant<int, 8>{}); break;
+    if constexpr (HQ < RL_MAX_H / 64) {
+        if (H > 64 * HQ) return rl_with_width<HQ + 1>(H, f);
     }
+    f(std::integral_constant<int, HQ>{});
 }
 
 static int rl_check(const mp_lstm_layer_desc* d, const char* who, int* nwg) {
@@ -429,10 +429,12 @@ static int rl_check(const mp_lstm_layer_desc* d, const char* who, int* nwg) {
     MP_REQUIRE(d->ldw >= d->I + d->H && d->ldxh >= d->I + d->H, "%s: leading dimension smaller than I + H", who);
     MP_REQUIRE(d->wait_limit_us >= 0 && d->debug_extra_participants >= 0 && d->debug_extra_participants <= 64,
                "%s: bad wait limit / debug participants", who);
-    if (d->B > RL_MAX_B || d->H % 128 != 0 || d->H > RL_MAX_H || d->I % 8 != 0 || d->ldw % 8 != 0 || d->ldxh % 8 != 0) {
-        set_error("%s: the persistent kernel needs B <= 32, H a multiple of 128 up to %d, and I / ldw / ldxh multiples of 8 "
-                  "(got B=%d H=%d I=%d ldw=%d ldxh=%d); run the layer step by step instead", who, RL_MAX_H, d->B, d->H, d->I,
-                  d->ldw, d->ldxh);
+    // (a caller that gives step_rows has asked mp_lstm_layer_desc_workspace_bytes for its workspace)
+    const int rows = d->step_rows > 0 ? 0x7FFFFFFF : RL_MAX_B, unit = d->step_rows > 0 ? 64 : 128;
+    if (d->B > rows || d->H % unit != 0 || d->H > RL_MAX_H || d->I % 8 != 0 || d->ldw % 8 != 0 || d->ldxh % 8 != 0) {
+        set_error("%s: the persistent kernel needs H a multiple of %d up to %d, and I / ldw / ldxh multiples of 8, and without "
+                  "step_rows B <= %d (got B=%d H=%d I=%d ldw=%d ldxh=%d); run the layer step by step instead", who, unit, RL_MAX_H,
+                  RL_MAX_B, d->B, d->H, d->I, d->ldw, d->ldxh);
         return MP_E_UNSUPPORTED;
     }
     MP_REQUIRE(d->step_rows == 0 || d->step_rows >= d->B, "%s: step_rows=%d smaller than B=%d", who, d->step_rows, d->B);
@@ -449,14 +451,19 @@ static int rl_check(const mp_lstm_layer_desc* d, const char* who, int* nwg) {
     return MP_OK;
 }
 
-// the exchange rings of the largest shape: one per block of batch rows, backward slices being the larger ones
-extern "C" size_t mp_lstm_layer_workspace_bytes(void) { return (size_t)(RL_MAX_B / RL_ROWS) * RL_RING * rl_bwd_slot(RL_MAX_H); }
+// the exchange rings: one per block of batch rows, backward slices being the larger ones
+static size_t rl_rings(int B, int H) { return (size_t)((B + RL_ROWS - 1) / RL_ROWS) * RL_RING * rl_bwd_slot(H); }
+extern "C" size_t mp_lstm_layer_workspace_bytes(void) { return rl_rings(RL_MAX_B, RL_MAX_H); }
+extern "C" size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d) {
+    return d && d->B > 0 && d->H > 0 && d->H % 64 == 0 && d->H <= RL_MAX_H ? rl_rings(d->B, d->H) : 0;
+}
 
 static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, mp_stream stream,
                    const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
-    if (!ws || ws_bytes < mp_lstm_layer_workspace_bytes() || !aligned16(ws)) {
-        set_error("%s: 16-byte aligned workspace of %zu bytes needed, %zu given", who, mp_lstm_layer_workspace_bytes(), ws_bytes);
+    const size_t need = d->step_rows > 0 ? rl_rings(d->B, d->H) : mp_lstm_layer_workspace_bytes();
+    if (!ws || ws_bytes < need || !aligned16(ws)) {
+        set_error("%s: 16-byte aligned workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
         return MP_E_WORKSPACE;
     }
     const size_t used = (size_t)((d->B + RL_ROWS - 1) / RL_ROWS) * RL_RING * slot;

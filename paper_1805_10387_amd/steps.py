@@ -371,8 +371,11 @@ class LSTMStep(_StepBase):
         z16 = lambda *s: torch.zeros(s, dtype=torch.float16, device="cuda")
         z32 = lambda *s: torch.zeros(s, dtype=torch.float32, device="cuda")
         self.in_dims = [wl.d_in if l == 0 else H for l in range(NL)]
-        self.persistent = (persistent and Bt <= 32 and H % 128 == 0 and H <= 1024 and all(i % 8 == 0 for i in self.in_dims)
-                           and H // 16 <= torch.cuda.get_device_properties(0).multi_processor_count)
+        # batch rows one launch of the recurrent kernels takes: all its workgroups (16 units x 8 rows each) run at once,
+        # two to a compute unit; a larger batch takes several launches
+        block = 8 * (2 * torch.cuda.get_device_properties(0).multi_processor_count // max(H // 16, 1))
+        self.persistent = persistent and H % 64 == 0 and H <= 1024 and all(i % 8 == 0 for i in self.in_dims) and block > 0
+        self.row_blocks = [(r, min(block, Bt - r)) for r in range(0, Bt, block)] if self.persistent else []
         self.xh = [z16(T, Bt, self.in_dims[l] + H) for l in range(NL)]      # h_0 = 0 stays in xh[l][0][:, I:]
         self.gates = [z16(T, Bt, 4 * H) for _ in range(NL)]
         self.c = [z32(T + 1, Bt, H) for _ in range(NL)]                      # c_0 = 0
@@ -392,12 +395,25 @@ class LSTMStep(_StepBase):
             self.gx = z32(T * Bt, 4 * H)                                     # input half of the gate sums, all steps
             self.dx = [z16(T * Bt, max(self.in_dims)) for _ in range(2)]     # input gradient of a layer, all steps
             self.rl_status = torch.zeros(1, dtype=torch.int32, device="cuda")
-            self.rl_ws = torch.zeros(B.mp_lstm_layer_workspace_bytes() // 4, dtype=torch.int32, device="cuda")
+            rows = self.row_blocks[0][1]
+            self.rl_ws = torch.zeros(B.mp_lstm_layer_desc_workspace_bytes(B.lstm_layer_desc(T, rows, 0, H, H, H, H, step_rows=Bt)) // 4,
+                                     dtype=torch.int32, device="cuda")
             # x W_x^T and dgates W_x: the input columns [0, I) of W[4H, I+H], all T*B rows at once
             self.d_in_all = [B.gemm_desc(T * Bt, 4 * H, self.in_dims[l], ldx=self.in_dims[l] + H, ldw=self.in_dims[l] + H)
                              for l in range(NL)]
             self.d_dx_all = [B.gemm_desc(T * Bt, 4 * H, self.in_dims[l], ldx=self.in_dims[l], ldw=self.in_dims[l] + H)
                              for l in range(NL)]
+
+            # arguments of the recurrent calls: per layer and block of batch rows
+            self.rl_fwd, self.rl_bwd = [], []
+            for l in range(NL):
+                I = self.in_dims[l]
+                up, ldup = (self.xh[l + 1], self.in_dims[l + 1] + H) if l + 1 < NL else (self.y, H)
+                above, ld_above = (self.dx[(l + 1) % 2].view(-1)[:T * Bt * H].view(T, Bt, H) if l + 1 < NL else self.dy), H
+                self.rl_fwd.append([(B.lstm_layer_desc(T, n, I, H, I + H, I + H, ldup, step_rows=Bt), self.gx[r:], self.gates[l][0, r:],
+                                     self.c[l][0, r:], self.xh[l][0, r:], up[0, r:]) for r, n in self.row_blocks])
+                self.rl_bwd.append([(B.lstm_layer_desc(T, n, I, H, I + H, I + H, ld_above, step_rows=Bt), self.gates[l][0, r:],
+                                     self.c[l][0, r:], above[0, r:], self.dgates[0, r:]) for r, n in self.row_blocks])
 
     def set_batch(self, batch):
         x = _h16(batch["x"])
@@ -418,23 +434,16 @@ class LSTMStep(_StepBase):
         wl, w, g = self.wl, self.P.w16, self.P.g16
         T, Bt, H, NL = wl.seq_len, wl.batch_size, wl.hidden, wl.n_layers
         for l in range(NL):
-            I = self.in_dims[l]
             B.mp_gemm_fwd(self.d_in_all[l], self.xh[l], w[f"l{l}.w"], None, None, None, self.gx)
-            up, ldup = (self.xh[l + 1], self.in_dims[l + 1] + H) if l + 1 < NL else (self.y, H)
-            d = B.lstm_layer_desc(T, Bt, I, H, I + H, I + H, ldup)
-            B.mp_lstm_layer_fwd(d, self.gx, w[f"l{l}.w"], w[f"l{l}.b"], self.gates[l], self.c[l], self.xh[l], up,
-                                self.rl_status, self.rl_ws)
+            for d, gx, gates, c, xh, up in self.rl_fwd[l]:
+                B.mp_lstm_layer_fwd(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, self.rl_ws)
         B.mp_mse_scaled(T * Bt, H, self.y, self.target, H, self.st, self.loss, self.dy, self.ws)
-        above, ld_above = self.dy, H
         for l in range(NL - 1, -1, -1):
-            I = self.in_dims[l]
-            d = B.lstm_layer_desc(T, Bt, I, H, I + H, I + H, ld_above)
-            B.mp_lstm_layer_bwd(d, w[f"l{l}.w"], self.gates[l], self.c[l], above, self.dgates, self.rl_status, self.rl_ws)
-            dx = self.dx[l % 2].view(-1)[:T * Bt * I].view(T * Bt, I)
-            B.mp_gemm_bwd_dx(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], dx)
+            for d, gates, c, above, dgates in self.rl_bwd[l]:
+                B.mp_lstm_layer_bwd(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, self.rl_ws)
+            B.mp_gemm_bwd_dx(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2])
             B.mp_gemm_bwd_dw(self.d_gate_all[l], self.dgates, self.xh[l], g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)
-            above, ld_above = dx, I
-        self.dx_input = above
+        self.dx_input = self.dx[0].view(-1)[:T * Bt * self.in_dims[0]].view(T * Bt, self.in_dims[0])
 
     def _forward_backward_stepwise(self):
         wl, w, g = self.wl, self.P.w16, self.P.g16

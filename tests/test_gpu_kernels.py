@@ -794,6 +794,46 @@ def test_lstm_persistent_layer_kernels(T, Bn, I, H):
     assert_close16(o["db"], db_ref, 1e-3, what="db")
 
 
+@pytest.mark.parametrize("T,Bn,I,H", [(9, 9, 8, 640), (6, 31, 16, 896), (8, 3, 8, 512), (5, 24, 0, 768), (12, 32, 32, 1024)])
+def test_lstm_persistent_layer_exchange_ring(T, Bn, I, H):
+    """More time steps than the exchange ring has slots, every kind of k-step count per wave, batches that fill their
+    8-row blocks and batches that do not, against the oracle layer."""
+    test_lstm_persistent_layer_kernels(T, Bn, I, H)
+
+
+@pytest.mark.parametrize("T,Bn,I,H,block", [(6, 40, 24, 64, 40), (7, 65, 8, 192, 33), (5, 20, 16, 320, 8), (6, 64, 40, 1024, 64)])
+def test_lstm_persistent_layer_step_rows(T, Bn, I, H, block):
+    """Calls that give step_rows: widths that are multiples of 64 only (waves with unequal or no shares of the
+    contraction), batches of more than 32 rows, and a batch in blocks of rows, against the oracle layer."""
+    r = RNG(T * 1000 + Bn + I + H)
+    x_seq, dh_seq = S16(r.standard_normal((T, Bn, I))), S16(r.standard_normal((T, Bn, H)))
+    w, b = S16(r.uniform(-0.1, 0.1, (4 * H, I + H))), S16(r.standard_normal(4 * H) * 0.1)
+    h_ref, (xh_ref, gates_ref, c_ref, _) = L.lstm_layer_fwd(MIXED, x_seq, w, b)
+    ld = I + H
+    xh = torch.zeros(T, Bn, ld, dtype=torch.float16, device="cuda")
+    xh[:, :, :I].copy_(h16(x_seq))
+    wd, bd, gx, up = h16(w), h16(b), empty32(T * Bn, 4 * H), empty16(T, Bn, H)
+    mp.mp_gemm_fwd(mp.gemm_desc(T * Bn, 4 * H, I, ldx=ld, ldw=ld), xh, wd, None, None, None, gx)
+    gates, c, dgates = empty16(T, Bn, 4 * H), torch.zeros(T + 1, Bn, H, dtype=torch.float32, device="cuda"), empty16(T, Bn, 4 * H)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dh = h16(dh_seq)
+    for r0 in range(0, Bn, block):
+        d = mp.lstm_layer_desc(T, min(block, Bn - r0), I, H, ld, ld, H, step_rows=Bn)
+        ws = torch.zeros(mp.mp_lstm_layer_desc_workspace_bytes(d) // 4, dtype=torch.int32, device="cuda")
+        mp.mp_lstm_layer_fwd(d, gx[r0:], wd, bd, gates[0, r0:], c[0, r0:], xh[0, r0:], up[0, r0:], status, ws)
+        mp.mp_lstm_layer_bwd(d, wd, gates[0, r0:], c[0, r0:], dh[0, r0:], dgates[0, r0:], status, ws)
+    assert int(status.item()) == 0
+    assert_close16(gates[0], gates_ref[0], 1e-3, max_ulp=1, what="gate sums of step 0")
+    for name, got, ref in (("gates", gates, gates_ref), ("h", up, h_ref), ("xh", xh, xh_ref)):
+        assert_close16(got, ref, 1e-3, what=name)
+    assert rel_fro(np32(c), np.stack(c_ref)) <= 1e-3
+    _, dw_ref, db_ref = L.lstm_layer_bwd(MIXED, dh_seq, (np32(xh), np32(gates), list(np32(c)), I), w)
+    dw, db, dall = empty16(4 * H, ld), empty16(4 * H), mp.gemm_desc(T * Bn, 4 * H, ld)
+    mp.mp_gemm_bwd_dw(dall, dgates, xh, dw, db, None, ws_bytes(mp.mp_gemm_bwd_dw_workspace_bytes(dall, True)))
+    assert_close16(dw, dw_ref, 1e-3, what="dW")
+    assert_close16(db, db_ref, 1e-3, what="db")
+
+
 def test_lstm_persistent_layer_timeout_path_and_rejections():
     """The step barrier's wait is bounded: asked to wait for a flag nobody raises (debug_extra_participants) with a
     2 ms limit, every workgroup gives up, the kernels end normally and *status reports it; a poisoned status makes the
