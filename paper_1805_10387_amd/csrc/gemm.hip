@@ -16,6 +16,7 @@ extern template int launch_dtl_tile<false, false>(int, const GemmArgs&, int, hip
 extern template int launch_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
 extern template int launch_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
 extern template int launch_dtl_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
+extern template int launch_dtl_grouped<256, 128>(const GroupArgs&, int, hipStream_t);
 extern template int launch_dtl_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
 
 // Sum split-K partials in split order, scale, round once, optional non-finite flag.
@@ -406,7 +407,7 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_state* st, mp_stream stream) {
     MP_REQUIRE(items != nullptr && count >= 1 && count <= GROUP_MAX, "mp_gemm_bwd_dw_grouped: 1..%d items", GROUP_MAX);
     GemmArgs args[GROUP_MAX];
-    bool     all256 = true, all128 = true;
+    bool     m256 = true, n256 = true, k32 = true;
     for (int i = 0; i < count; ++i) {
         const mp_gemm_desc* d = &items[i].desc;
         int rc = check_desc(d, "mp_gemm_bwd_dw_grouped");
@@ -431,10 +432,30 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
                       "(weights) / 64 (rows); use mp_gemm_bwd_dw", i);
             return MP_E_UNSUPPORTED;
         }
-        all256 = all256 && g.M % 256 == 0 && g.N % 256 == 0;
+        m256 = m256 && g.M % 256 == 0;
+        n256 = n256 && g.N % 256 == 0;
+        k32  = k32 && g.K % DK == 0;
     }
-    (void)all128;
-    const int bm = all256 ? 256 : 128;
+    // Tile shape: the one with the least estimated time, rounds of one work item per compute unit times the tile's time
+    // (relative efficiencies as in kTiles).  Large tiles win once they fill the chip (a layer with d_model 1024: 192 tiles
+    // of 256 x 256 and 56 strips in one round); with fewer, most compute units would idle through a long contraction
+    // (d_model 512, 4096 tokens: 48 such tiles, 92 us, against 192 of 128 x 128, 49 us).
+    const bool dtl = dtl_mode() != 0 && k32;
+    int        bm = 128, bn = 128;
+    double     best_cost = 1e300;
+    for (int t : {0, 1, 3}) {
+        const int tm = kTiles[t].bm, tn = kTiles[t].bn;
+        if ((tm == 256 && !m256) || (tn == 256 && !n256) || (t == 1 && !dtl)) continue;
+        long long n_items = 0;
+        for (int i = 0; i < count; ++i)
+            n_items += (long long)(args[i].M / tm) * (args[i].N / tn) + (items[i].db ? items[i].desc.N / BIAS_COLS : 0);
+        const double cost = (double)((n_items + kCUs - 1) / kCUs) * tm * tn / kTiles[t].eff;
+        if (cost < best_cost) {
+            best_cost = cost;
+            bm        = tm;
+            bn        = tn;
+        }
+    }
     // longest contraction first, so that the tiles that take longest start first
     int order[GROUP_MAX];
     for (int i = 0; i < count; ++i) order[i] = i;
@@ -446,7 +467,7 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
     for (int i = 0; i < count; ++i) {
         GemmArgs g = args[order[i]];
         g.tiles_m  = g.M / bm;
-        g.tiles_n  = g.N / bm;
+        g.tiles_n  = g.N / bn;
         ga.p[i]          = g;
         ga.tile_start[i] = (int)total;
         total += (long long)g.tiles_m * g.tiles_n;
@@ -466,9 +487,9 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
         strips += it.desc.N / BIAS_COLS;      // N is a multiple of 128 here (checked above for either orientation)
     }
     for (int i = ga.nbias; i <= GROUP_MAX; ++i) ga.strip_start[i] = strips;
-    bool k32 = true;
-    for (int i = 0; i < count; ++i) k32 = k32 && ga.p[i].K % DK == 0;
-    if (dtl_mode() != 0 && k32)
-        return all256 ? launch_dtl_grouped<256, 256>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, kCUs, as_stream(stream));
-    return all256 ? launch_grouped<256, 256>(ga, kCUs, as_stream(stream)) : launch_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
+    if (dtl) {
+        if (bn == 256) return launch_dtl_grouped<256, 256>(ga, kCUs, as_stream(stream));
+        return bm == 256 ? launch_dtl_grouped<256, 128>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, kCUs, as_stream(stream));
+    }
+    return bm == 256 ? launch_grouped<256, 256>(ga, kCUs, as_stream(stream)) : launch_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
 }

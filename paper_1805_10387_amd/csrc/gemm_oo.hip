@@ -7,5 +7,6 @@ template int launch_dtl_tile<false, false>(int, const GemmArgs&, int, hipStream_
 template int launch_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
 template int launch_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
 template int launch_dtl_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
+template int launch_dtl_grouped<256, 128>(const GroupArgs&, int, hipStream_t);
 template int launch_dtl_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
 }  // namespace mp
