@@ -186,6 +186,17 @@ int mp_gemm_bwd_dw(const mp_gemm_desc* desc /* host */, const mp_half* dY, const
                    mp_half* dW, mp_half* db, mp_scale_state* st, void* ws, size_t ws_bytes,
                    mp_stream stream);
 
+/* Both gradients of a linear layer from one gradient dY: exactly mp_gemm_bwd_dw(d_dw, dY, X, dW, db, st, ws) and
+ * mp_gemm_bwd_dx_ws(d_dx, dY, W, relu_src, add, ld_aux, dX, ws), whose arguments these are (same results contract; the
+ * fp32 summation order may differ).  d_dx and d_dw agree in M, N and ldy; K, ldx and ldw may differ (an LSTM's input
+ * gradient takes some of the columns of W that its weight gradient has).  For small unbatched products (trans_w 0) the
+ * two and the bias gradient are one launch; mp_gemm_bwd_both_joint tells (1) for a pair of descriptors.  A workspace too
+ * small for mp_gemm_bwd_dw is an error only where the call is not one launch. */
+int mp_gemm_bwd_both(const mp_gemm_desc* d_dx /* host */, const mp_half* dY, const mp_half* W, const mp_half* relu_src,
+                     const mp_half* add, int32_t ld_aux, mp_half* dX, const mp_gemm_desc* d_dw /* host */, const mp_half* X,
+                     mp_half* dW, mp_half* db, mp_scale_state* st, void* ws, size_t ws_bytes, mp_stream stream);
+int mp_gemm_bwd_both_joint(const mp_gemm_desc* d_dx /* host */, const mp_gemm_desc* d_dw /* host */);
+
 /* Several weight-gradient products (Section 3.1: fp16 operands, fp32 accumulation, one rounding) in one launch.
  * Each of a layer's dW = dY^T X alone has too few output tiles to occupy the chip without splitting its
  * contraction; together they do.  items: host array of `count` (1..8) problems, each a descriptor as for
@@ -210,7 +221,7 @@ int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_
  * a training step never calls it): force every following contraction onto tile shape `tile`
  * (index into the library's tile table: 0 = 256x256, 1 = 256x128, 2 = 128x256, 3 = 128x128, 4 = 128x64,
  * 5 = 64x128, 6 = 64x64, 7 = 32x128, 8 = 256x192 for products whose operands are both stored
- * contraction-contiguous, else 256x256) and, where splitting the contraction is allowed, onto `splits`
+ * contraction-contiguous, else 256x256, 9 / 10 = 32x32 with the contraction dealt to 4 / 8 waves, unbatched) and, where splitting the contraction is allowed, onto `splits`
  * (0..16; 0 = 1) splits, reduced until every split owns at least one k-tile.  tile >= the table size or splits
  * outside 0..16: MP_E_INVAL.  tile < 0 restores the built-in choice.  Results do not depend on it beyond fp32
  * summation order.

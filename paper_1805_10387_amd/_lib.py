@@ -67,6 +67,8 @@ SIGNATURES = {
     "mp_gemm_split_workspace_bytes": (_SZ, [C.POINTER(GemmDesc)]),
     "mp_gemm_fwd_ws": (_I, [C.POINTER(GemmDesc), _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_gemm_bwd_dx_ws": (_I, [C.POINTER(GemmDesc), _P, _P, _P, _P, C.c_int32, _P, _P, _SZ, _P]),
+    "mp_gemm_bwd_both": (_I, [C.POINTER(GemmDesc), _P, _P, _P, _P, C.c_int32, _P, C.POINTER(GemmDesc), _P, _P, _P, _P, _P, _SZ, _P]),
+    "mp_gemm_bwd_both_joint": (_I, [C.POINTER(GemmDesc), C.POINTER(GemmDesc)]),
     "mp_gemm_bwd_dw_grouped": (_I, [C.POINTER(GemmGroupItem), _I, _P, _P]),
     "mp_gemm_tuning_override": (_I, [_I, _I]),
     "mp_gemm_tuning_dtl": (_I, [_I]),

@@ -108,6 +108,15 @@ def mp_gemm_bwd_dw(desc: GemmDesc, dY, X, dW, db=None, st=None, ws=None):
                                    0 if ws is None else ws.numel() * ws.element_size(), _stream()))
 
 
+def mp_gemm_bwd_both(d_dx: GemmDesc, dY, W, dX, d_dw: GemmDesc, X, dW, db=None, st=None, ws=None, relu_src=None, add=None, ld_aux=0):
+    _check(L.load().mp_gemm_bwd_both(C.byref(d_dx), _p(dY), _p(W), _p(relu_src), _p(add), ld_aux, _p(dX), C.byref(d_dw), _p(X), _p(dW),
+                                     _p(db), _p(st), _p(ws), _nbytes(ws), _stream()))
+
+
+def mp_gemm_bwd_both_joint(d_dx: GemmDesc, d_dw: GemmDesc) -> bool:
+    return bool(L.load().mp_gemm_bwd_both_joint(C.byref(d_dx), C.byref(d_dw)))
+
+
 def gemm_group(items):
     """Host array for mp_gemm_bwd_dw_grouped from (desc, dY, X, dW[, db]) tuples; keeps the tensors alive."""
     arr = (L.GemmGroupItem * len(items))()

@@ -1,7 +1,9 @@
 // Contractions: planner, split-K finish, generic fallback and the C entry points.  The matrix-core kernel templates are
 // in gemm_kernels.hpp and are instantiated in gemm_kk.hip / gemm_ko.hip / gemm_oo.hip.
 #include "gemm_dtl.hpp"
+#include "gemm_small.hpp"
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
@@ -96,7 +98,22 @@ static const TileCfg kTiles[] = {{256, 256, 1.00f}, {256, 128, 0.85f}, {128, 256
                                  {256, 192, 0.88f}};
 constexpr int   kTileKcOnly = 8;  // first index of the shapes restricted to that operand layout
 constexpr int   kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+// then 32 x 32 with the contraction dealt to 4 or to 8 waves (gemm_small.hpp), unbatched only
+constexpr int   kTileSmall4 = kNumTiles, kTileSmall8 = kNumTiles + 1;
 constexpr int   kCUs      = 256;
+
+// Products for the small kernel: up to two workgroups per compute unit, and not so long a contraction that reading the
+// operand panels anew for every 32 x 32 tile outweighs the short chain.  us alone, larger tiles against this kernel:
+// 64 x 1024 over 256 4.1 / 3.0, 64 x 256 over 1024 6.7 / 4.4, 520 x 256 over 3000 16.3 / 8.3, 1024 x 161 over 1500 15.2 / 7.9;
+// beyond the line 512 x 512 over 4096 13.0 / 16.8, 1024 x 1024 over 1024 7.3 / 10.0.
+static long long small_tiles(int M, int N) { return ((M + 31) / 32) * (long long)((N + 31) / 32); }
+static bool      small_wins(int M, int N, int K) {
+    const long long t = small_tiles(M, N);
+    return t <= 2 * kCUs && K <= 4096 && t * K <= 3072ll * kCUs;
+}
+// 8 waves (64 KB of LDS) when a workgroup has its compute unit to itself and each wave several k-tiles: 512 x 512 over
+// 4096 20.7 -> 16.8 us, 1500 x 29 over 1024 6.6 -> 5.7; shorter contractions lose 0.2 us in the longer final sum.
+static int small_waves(long long tiles, int K) { return tiles <= kCUs && K > 512 ? 8 : 4; }
 
 struct Plan {
     int tile, splits, k_per_split;
@@ -113,7 +130,7 @@ static int dtl_mode() { return g_dtl_mode; }
 static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool kc_kc = false) {
     // tuning aid (mp_gemm_tuning_override): force a tile shape / split count
     if (g_force_tile >= 0) {
-        int t = g_force_tile < (kc_kc ? kNumTiles : kTileKcOnly) ? g_force_tile : 0, sp = allow_split ? g_force_splits : 1;
+        int t = g_force_tile < (kc_kc ? kNumTiles : kTileKcOnly) || g_force_tile >= kTileSmall4 ? g_force_tile : 0, sp = allow_split ? g_force_splits : 1;
         if (sp < 1) sp = 1;
         if (sp > 16) sp = 16;
         // every split must own at least one k-tile: (sp - 1) * k_per_split < K, as in the planner's own search
@@ -124,6 +141,8 @@ static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
         }
         return Plan{t, sp, kps > 0 ? kps : BK};
     }
+    if (batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
+        return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK};
     Plan   best{0, 1, 0};
     double best_cost = 1e300;
     for (int t = 0; t < (kc_kc ? kNumTiles : kTileKcOnly); ++t) {
@@ -190,12 +209,16 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc && b_kc);
     if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc && b_kc);
     g.k_per_split = p.k_per_split;
-    g.tiles_m     = (g.M + kTiles[p.tile].bm - 1) / kTiles[p.tile].bm;
-    g.tiles_n     = (g.N + kTiles[p.tile].bn - 1) / kTiles[p.tile].bn;
+    if (p.tile >= kTileSmall4 && (batches != 1 || (!a_kc && b_kc))) p.tile = 6;
+    const bool    small = p.tile >= kTileSmall4;
+    const int     waves = p.tile == kTileSmall4 ? 4 : 8;
+    const TileCfg tile  = small ? TileCfg{32, 32, 0.f} : kTiles[p.tile];
+    g.tiles_m     = (g.M + tile.bm - 1) / tile.bm;
+    g.tiles_n     = (g.N + tile.bn - 1) / tile.bn;
     // persistent along x: at most as many workgroups as fit on the chip at once (a multiple of 8, see the tile
     // mapping); batches and splits keep their own grid dimensions
     const int  ntiles   = g.tiles_m * g.tiles_n;
-    const int  lds_kib  = 2 * (kTiles[p.tile].bm + kTiles[p.tile].bn) * 128 / 1024;
+    const int  lds_kib  = 2 * (tile.bm + tile.bn) * 128 / 1024;
     const int  resident = kCUs * (lds_kib > 80 ? 1 : 2);
     const long long others = batches * p.splits;
     const int  gx = (others == 1 && ntiles > resident) ? resident : ntiles;
@@ -205,7 +228,7 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     // (built for all three operand layouts, used where it is the faster one: both operands output-contiguous, i.e. the
     // weight gradients.  A contraction-contiguous operand arrives there in 64-byte row pieces, which costs what the
     // saved LDS stores gain, so forward and input-gradient products stay on the register-staged kernel)
-    const int bm = kTiles[p.tile].bm, bn = kTiles[p.tile].bn;
+    const int bm = tile.bm, bn = tile.bn;
     if (dtl_mode() != 0 && g.aligned && others == 1 && bm >= 128 && bn >= 128 && g.M % bm == 0 && g.N % bn == 0 && g.K % DK == 0 && g.K >= DK &&
         (a_kc || !b_kc) && (dtl_mode() == 2 || (!a_kc && !b_kc))) {
         const int gxd = ntiles > kCUs ? kCUs : ntiles;   // one workgroup per compute unit (its ring of stages fills the LDS)
@@ -221,7 +244,8 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
         k.bias      = nullptr;
     }
     int rc;
-    if (a_kc && b_kc) rc = launch_tile<true, true>(p.tile, k, grid, hs);
+    if (small) rc = launch_small_tile(waves, a_kc, b_kc, k, p.splits, hs);
+    else if (a_kc && b_kc) rc = launch_tile<true, true>(p.tile, k, grid, hs);
     else if (a_kc && !b_kc) rc = launch_tile<true, false>(p.tile, k, grid, hs);
     else if (!a_kc && !b_kc) rc = launch_tile<false, false>(p.tile, k, grid, hs);
     else {
@@ -274,7 +298,7 @@ static size_t splitk_floats_any(int M, int N, int K, bool allow, bool kc_kc) {
 }
 
 extern "C" int mp_gemm_tuning_override(int tile, int splits) {
-    MP_REQUIRE(tile < kNumTiles, "mp_gemm_tuning_override: tile index %d out of range (%d shapes)", tile, kNumTiles);
+    MP_REQUIRE(tile <= kTileSmall8, "mp_gemm_tuning_override: tile index %d out of range (%d shapes)", tile, kTileSmall8 + 1);
     MP_REQUIRE(tile < 0 || (splits >= 0 && splits <= 16), "mp_gemm_tuning_override: splits %d outside 0..16", splits);
     g_force_tile   = tile;
     g_force_splits = splits > 0 ? splits : 1;
@@ -402,6 +426,54 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
         return mp_colsum(d->M, d->N, dY, d->ldy, db, st, cs_ws, cs_b, stream);
     }
     return MP_OK;
+}
+
+// One launch for both gradients: each product for the small kernel by itself, and together no more than three workgroups
+// per compute unit.  (An iteration of a 64 x 256 -> 1024 -> 256 network: JOINT_FIGURES)
+static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
+    const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
+    if (g_force_tile >= 0 || !plain(dx) || !plain(dw)) return false;
+    return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M) &&
+           small_tiles(dx->M, dx->K) + small_tiles(dw->N, dw->K) + (dw->N + SM_STRIP - 1) / SM_STRIP <= 3 * kCUs;
+}
+
+extern "C" int mp_gemm_bwd_both_joint(const mp_gemm_desc* d_dx, const mp_gemm_desc* d_dw) {
+    return d_dx && d_dw && both_joint(d_dx, d_dw) ? 1 : 0;
+}
+
+extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, const mp_half* W, const mp_half* relu_src,
+                                const mp_half* add, int32_t ld_aux, mp_half* dX, const mp_gemm_desc* d_dw, const mp_half* X,
+                                mp_half* dW, mp_half* db, mp_scale_state* st, void* ws, size_t ws_bytes, mp_stream stream) {
+    int rc = check_desc(d_dx, "mp_gemm_bwd_both");
+    if (rc == MP_OK) rc = check_desc(d_dw, "mp_gemm_bwd_both");
+    if (rc) return rc;
+    MP_REQUIRE(d_dx->M == d_dw->M && d_dx->N == d_dw->N && d_dx->ldy == d_dw->ldy, "mp_gemm_bwd_both: the products do not share dY");
+    MP_REQUIRE(dY && W && dX && X && dW, "mp_gemm_bwd_both: NULL operand");
+    MP_REQUIRE(!(relu_src && add), "mp_gemm_bwd_both: relu_src and add may not both be given");
+    MP_REQUIRE(!(relu_src || add) || ld_aux >= d_dx->K, "mp_gemm_bwd_both: ld_aux=%d smaller than K", ld_aux);
+    if (both_joint(d_dx, d_dw)) {
+        BothArgs b{};
+        GemmArgs& x = b.dx;
+        x.A = dY; x.B = W; x.C = dX; x.relu_src = relu_src; x.add = add; x.ld_aux = ld_aux;
+        x.M = d_dx->M; x.N = d_dx->K; x.K = d_dx->N;
+        x.lda = d_dx->ldy; x.ldb = d_dx->ldw; x.ldc = d_dx->ldx; x.alpha = d_dx->alpha; x.batch_inner = 1;
+        GemmArgs& w = b.dw;
+        w.A = dY; w.B = X; w.C = dW; w.found_inf = st ? &st->found_inf : nullptr;
+        w.M = d_dw->N; w.N = d_dw->K; w.K = d_dw->M;
+        w.lda = d_dw->ldy; w.ldb = d_dw->ldx; w.ldc = d_dw->ldw; w.alpha = d_dw->alpha; w.batch_inner = 1;
+        if (matrix_path_ok(x, true, false) && matrix_path_ok(w, false, false)) {
+            for (GemmArgs* g : {&x, &w}) {
+                g->tiles_m = (g->M + 31) / 32;
+                g->tiles_n = (g->N + 31) / 32;
+            }
+            b.dY = dY; b.db = db; b.rows = d_dw->M; b.cols = d_dw->N; b.ld = d_dw->ldy;
+            return launch_small_both(small_waves((long long)x.tiles_m * x.tiles_n + (long long)w.tiles_m * w.tiles_n, std::max(x.K, w.K)), b,
+                                     as_stream(stream));
+        }
+    }
+    rc = mp_gemm_bwd_dw(d_dw, dY, X, dW, db, st, ws, ws_bytes, stream);
+    if (rc) return rc;
+    return mp_gemm_bwd_dx_ws(d_dx, dY, W, relu_src, add, ld_aux, dX, ws, ws_bytes, stream);
 }
 
 extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_state* st, mp_stream stream) {

@@ -1,0 +1,316 @@
+// Contraction kernel for small problems: 64 x 64 output tiles whose CONTRACTION is dealt to the four waves of a workgroup
+// (wave w takes the 64-deep k-tiles w, w + 4, ...), each with the whole tile in its accumulators and its own LDS; the four
+// partial sums are added once at the end, in wave order.  Same arithmetic and results contract as gemm_kernels.hpp
+// (paper Section 3.1: fp16 operands, fp32 sums, one rounding); the fp32 summation order differs.
+//
+// What bounds a small product is the chain launch - first operands - k-tile after k-tile - results, not bandwidth.  In
+// the kernels of gemm_kernels.hpp the waves share each k-tile behind a workgroup barrier, 0.2 us a k-tile; here no wave
+// waits for another inside the loop and the chain is a quarter as long.  (SMALL_FIGURES)
+// Operands come through buffer loads, so ragged borders cost no branches (see EDGE and TAIL there); an operand stored
+// along the output direction is turned by byte permutes on its way to LDS.
+#pragma once
+#include "gemm_kernels.hpp"
+
+namespace mp {
+
+constexpr int E        = 32;            // tile edge
+constexpr int SM_DEPTH = 4;             // k-tiles a wave has on their way
+constexpr int SM_WAVE  = 2 * E * 128;   // LDS bytes of one wave: a k-tile of both operands, later its partial sums
+constexpr int sm_lds(int waves) { return waves * SM_WAVE; }
+
+// One k-tile (E rows x 64 k) of an operand, loaded and staged by one wave.
+template <bool KC, int MODE>
+struct WaveOperand {
+    static constexpr int NV = E / 8;          // 16-byte pieces per lane
+    static constexpr int RG = E / 8;          // output-contiguous: groups of 8 rows; a lane owns NV k x 8 rows
+    u32x4    v[NV];
+    unsigned lane_off;  // elements from the k-tile's origin
+    int      sh;        // TAIL: how far the pieces now in v were loaded early
+    // KC: row hi + 8 i, k-piece lo; else: k = NV hi + i, row piece lo
+    static __device__ __forceinline__ int lo() { return KC ? threadIdx.x & 7 : threadIdx.x & (RG - 1); }
+    static __device__ __forceinline__ int hi() { return KC ? (threadIdx.x & 63) >> 3 : (threadIdx.x & 63) / RG; }
+    __device__ __forceinline__ void init(int ld) {
+        lane_off = (unsigned)(KC ? hi() : NV * hi()) * (unsigned)ld + lo() * 8;
+        sh       = 0;
+    }
+    __device__ __forceinline__ void load(const uint16_t* tile, int ld, int rows_left, int k_left) {
+        const int c = (KC ? k_left : rows_left) - lo() * 8;       // elements of this lane's pieces that exist
+        if (MODE == TAIL) sh = tail_shift(c);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            unsigned off = 2u * (lane_off + (unsigned)(KC ? 8 * i : i) * (unsigned)ld);
+            if (MODE == TAIL) off += 16 - 2 * sh;
+            const bool in = c > 0 && (KC ? hi() < rows_left - 8 * i : NV * hi() < k_left - i);
+            v[i]          = buffer_piece(MODE == TAIL ? tile - 8 : tile, in ? off : BUF_OUT);
+        }
+    }
+    // into LDS rows of 64 k (128 bytes), 16-byte slot ^ swz(row)
+    __device__ __forceinline__ void store(char* lds) {
+        if (MODE == TAIL) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[i] = shift_down(v[i], sh);
+        }
+        if constexpr (KC) {
+            static_for<NV>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                *reinterpret_cast<u32x4*>(lds + i * 1024 + hi() * 128 + ((lo() ^ hi() ^ i) << 4)) = v[i];
+            });
+        } else {
+            static_for<8>([&](auto ic) {  // row 8 lo + i: its halves at k = NV hi ... NV hi + NV - 1
+                constexpr int i = decltype(ic)::value;
+                unsigned      t[NV / 2];
+#pragma unroll
+                for (int p = 0; p < NV / 2; ++p)
+                    t[p] = __builtin_amdgcn_perm(v[2 * p + 1][i >> 1], v[2 * p][i >> 1], (i & 1) ? 0x07060302u : 0x05040100u);
+                char* const row = lds + lo() * 1024 + i * 128;
+                if constexpr (NV == 8) *reinterpret_cast<u32x4*>(row + ((hi() ^ i ^ lo()) << 4)) = u32x4{t[0], t[1], t[2], t[3]};
+                else *reinterpret_cast<u32x2g*>(row + (((hi() >> 1) ^ i ^ lo()) << 4) + (hi() & 1) * 8) = u32x2g{t[0], t[1]};
+            });
+        }
+    }
+};
+
+// Output tile (tm, tn) of problem g, k-tiles [kt0, kt1).  split: leave the raw sums in C32 (partials of a split
+// contraction, or the fp32 result with scale and addend when !split).
+template <int NW, bool A_KC, bool B_KC, int MODE>
+__device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, const int tn, const int kt0, const int kt1, float* C32,
+                                           const bool split, char* smem, bool& bad) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    constexpr int T = E / 32;
+    const int m0 = tm * E, n0 = tn * E;
+    char* const own = smem + wave * SM_WAVE;
+
+    f32x16 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j) acc[i][j] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+    WaveOperand<A_KC, MODE> a[SM_DEPTH];  // k-tiles on their way
+    WaveOperand<B_KC, MODE> b[SM_DEPTH];
+#pragma unroll
+    for (int d = 0; d < SM_DEPTH; ++d) {
+        a[d].init(g.lda);
+        b[d].init(g.ldb);
+    }
+    auto load = [&](auto& a, auto& b, const int kt) {
+        const long long k = (long long)kt * BK;
+        a.load(A_KC ? g.A + (long long)m0 * g.lda + k : g.A + k * g.lda + m0, g.lda, g.M - m0, g.K - (int)k);
+        b.load(B_KC ? g.B + (long long)n0 * g.ldb + k : g.B + k * g.ldb + n0, g.ldb, g.N - n0, g.K - (int)k);
+    };
+    // fragment of slice kk: row r (+ 32), k-slot 2 kk + h; swz(row + 32) = swz(row) ^ 4
+    int off[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) off[c] = r * 128 + ((((2 * c) | h) ^ swz(r)) << 4);
+    auto step = [&](auto& a, auto& b, const int kt) {
+        a.store(own);
+        b.store(own + E * 128);
+        if (kt + NW * SM_DEPTH < kt1) load(a, b, kt + NW * SM_DEPTH);
+        static_for<4>([&](auto kc) {
+            constexpr int kk = decltype(kc)::value;
+            f16x8         af[T], bf[T];
+#pragma unroll
+            for (int f = 0; f < T; ++f) {
+                af[f] = *reinterpret_cast<const f16x8*>(own + off[kk ^ (f << 1)] + f * 4096);
+                bf[f] = *reinterpret_cast<const f16x8*>(own + E * 128 + off[kk ^ (f << 1)] + f * 4096);
+            }
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[j], af[i], acc[i][j], 0, 0, 0);
+        });
+    };
+    int kt = kt0 + wave;
+#pragma unroll
+    for (int d = 0; d < SM_DEPTH; ++d)
+        if (kt + NW * d < kt1) load(a[d], b[d], kt + NW * d);
+    for (; kt < kt1; kt += NW * SM_DEPTH) {
+#pragma unroll
+        for (int d = 0; d < SM_DEPTH; ++d)
+            if (kt + NW * d < kt1) step(a[d], b[d], kt + NW * d);
+    }
+
+    // partial sums, row-major fp32 in 16-byte slots ^ (row % (E / 4)): lane (r, h) holds row 32 i + r, columns 32 j + 8 q + 4 h ...
+    constexpr int SX = E / 4 - 1;
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(own + (32 * i + r) * (4 * E) + (((8 * j + 2 * q + h) ^ (r & SX)) << 4)) =
+                    f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    __syncthreads();
+    // wave w finishes rows E / NW w ..., a lane (of the first E E / 8 / NW) 8 consecutive columns of one
+    const uint16_t* const aux = g.relu_src ? g.relu_src : g.add;
+    constexpr int         CG = E / 8;  // column groups
+    const int             cg = lane % CG, n = n0 + 8 * cg;
+    {
+        const int row = E / NW * wave + lane / CG, m = m0 + row;
+        if (m >= g.M || n >= g.N || lane / CG >= E / NW) return;
+        float x[8];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const char* s = smem + row * (4 * E) + (((2 * cg + q) ^ (row & SX)) << 4);
+            f32x4       t = *reinterpret_cast<const f32x4*>(s);
+#pragma unroll
+            for (int w = 1; w < NW; ++w) t += *reinterpret_cast<const f32x4*>(s + w * SM_WAVE);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * q + e] = t[e];
+        }
+        const long long mn = (long long)m * g.N + n;
+        const int       left = g.N - n;
+        if (!split && (g.alpha != 1.f || g.acc_in)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[e] *= g.alpha;
+                if (g.acc_in && e < left) x[e] += g.acc_in[mn + e];
+            }
+        }
+        if (C32) {  // (N is a multiple of 4)
+            *reinterpret_cast<f32x4_u*>(C32 + mn) = f32x4{x[0], x[1], x[2], x[3]};
+            if (left > 4) *reinterpret_cast<f32x4_u*>(C32 + mn + 4) = f32x4{x[4], x[5], x[6], x[7]};
+            return;
+        }
+        if (g.bias) {
+            const u32x4 b = MODE == TAIL ? load8_guard(g.bias + n, left) : *reinterpret_cast<const u32x4_u*>(g.bias + n);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] += h2f((uint16_t)((e & 1) ? (b[e >> 1] >> 16) : (b[e >> 1] & 0xFFFFu)));
+        }
+        if (g.relu) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = (x[e] < 0.f) ? 0.f : x[e];  // (keeps a NaN)
+        }
+        uint16_t o[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = f2h(x[e]);
+        if (aux) {
+            const uint16_t* ap = aux + (long long)m * g.ld_aux + n;
+            const u32x4     av = MODE == TAIL ? load8_guard(ap, left) : *reinterpret_cast<const u32x4_u*>(ap);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint16_t t = (uint16_t)((e & 1) ? (av[e >> 1] >> 16) : (av[e >> 1] & 0xFFFFu));
+                if (g.relu_src) o[e] = h2f(t) > 0.f ? o[e] : (uint16_t)0;
+                else o[e] = f2h(h2f(o[e]) + h2f(t));
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bad |= half_nonfinite(o[e]) && (MODE != TAIL || e < left);
+        const u32x4 out = {(unsigned)o[0] | ((unsigned)o[1] << 16), (unsigned)o[2] | ((unsigned)o[3] << 16),
+                           (unsigned)o[4] | ((unsigned)o[5] << 16), (unsigned)o[6] | ((unsigned)o[7] << 16)};
+        uint16_t* const dst = g.C + (long long)m * g.ldc + n;
+        if (MODE != TAIL || left >= 8) *reinterpret_cast<u32x4_u*>(dst) = out;
+        else store8_tail(dst, out, left);
+    }
+}
+
+// tile number -> tile of the problem: an XCD (consecutive workgroup ids go round the 8 of them) gets a contiguous run
+__device__ __forceinline__ int small_tile_of(const int id, const int n) {
+    const int x = id & 7;
+    return x * (n >> 3) + min(x, n & 7) + (id >> 3);
+}
+
+// grid: (tiles, 1, splits of the contraction); g.k_per_split is a multiple of BK
+template <int NW, bool A_KC, bool B_KC, int MODE>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
+    extern __shared__ __align__(16) char smem[];
+    bool      bad = false;
+    const int t = small_tile_of(blockIdx.x, g.tiles_m * g.tiles_n), per = g.k_per_split / BK, nkt = (g.K + BK - 1) / BK;
+    const bool split = gridDim.z > 1;
+    small_tile<NW, A_KC, B_KC, MODE>(g, t / g.tiles_n, t % g.tiles_n, blockIdx.z * per, min(nkt, (int)(blockIdx.z + 1) * per),
+                                 g.C32 ? g.C32 + (long long)blockIdx.z * g.M * g.N : nullptr, split, smem, bad);
+    if (g.found_inf && __any(bad)) {
+        if ((threadIdx.x & 63) == 0) atomicOr(g.found_inf, 1);
+    }
+}
+
+// Both gradients of a linear layer in one launch: tiles of dX, tiles of dW, and strips of column sums of dY (the bias
+// gradient), numbered one after the other.  They share dY and depend on nothing else, and each alone leaves most of a
+// small layer's time to launches.
+struct BothArgs {
+    GemmArgs        dx, dw;
+    const uint16_t* dY;       // [rows, cols] of the bias gradient
+    uint16_t*       db;       // or NULL
+    int             rows, cols, ld;
+};
+
+// db[SM_STRIP strip ...] = RNE16(fp32 column sums): pairs of columns, 16 rows in flight per thread (the chain of rounds is
+// what a strip costs: 1500 rows in 6 rounds, or 3 with 8 waves), rows added in a fixed order.
+constexpr int SM_STRIP = 32;
+typedef unsigned u32_u __attribute__((aligned(2)));
+template <int NW>
+__device__ __forceinline__ void small_colsum(const BothArgs& b, const int strip, char* smem, bool& bad) {
+    constexpr int LANES = 4 * NW, U = 16;
+    const int     cp = threadIdx.x & 15, rl = threadIdx.x >> 4, c = SM_STRIP * strip + 2 * cp;
+    const bool    two = c + 1 < b.cols, one = c < b.cols;
+    float         s0 = 0.f, s1 = 0.f;
+    for (int r0 = rl; r0 < b.rows; r0 += LANES * U) {
+        unsigned v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int       rr = r0 + LANES * u;
+            const uint16_t* p  = b.dY + (long long)rr * b.ld + c;
+            v[u] = 0u;
+            if (rr < b.rows) {
+                if (two) v[u] = *reinterpret_cast<const u32_u*>(p);
+                else if (one) v[u] = *p;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            s0 += h2f((uint16_t)(v[u] & 0xFFFFu));
+            s1 += h2f((uint16_t)(v[u] >> 16));
+        }
+    }
+    float* red = reinterpret_cast<float*>(smem);
+    red[rl * SM_STRIP + 2 * cp] = s0;
+    red[rl * SM_STRIP + 2 * cp + 1] = s1;
+    __syncthreads();
+    if (threadIdx.x < SM_STRIP && SM_STRIP * strip + (int)threadIdx.x < b.cols) {
+        float t = 0.f;
+#pragma unroll
+        for (int q = 0; q < LANES; ++q) t += red[q * SM_STRIP + threadIdx.x];
+        const uint16_t hv = f2h(t);
+        b.db[SM_STRIP * strip + threadIdx.x] = hv;
+        bad |= half_nonfinite(hv);
+    }
+}
+
+template <int NW, int MODE>
+__global__ __launch_bounds__(64 * NW) void gemm_small_both_kernel(BothArgs b) {
+    extern __shared__ __align__(16) char smem[];
+    bool      bad = false;
+    const int ndx = b.dx.tiles_m * b.dx.tiles_n, ndw = b.dw.tiles_m * b.dw.tiles_n;
+    const int id = blockIdx.x;
+    if (id < ndx) {
+        const int t = small_tile_of(id, ndx);
+        small_tile<NW, true, false, MODE>(b.dx, t / b.dx.tiles_n, t % b.dx.tiles_n, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
+        return;  // (dX has no overflow flag)
+    }
+    if (id < ndx + ndw) {
+        const int t = id - ndx;
+        small_tile<NW, false, false, MODE>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
+    } else {
+        small_colsum<NW>(b, id - ndx - ndw, smem, bad);
+    }
+    if (b.dw.found_inf && __any(bad)) {
+        if ((threadIdx.x & 63) == 0) atomicOr(b.dw.found_inf, 1);
+    }
+}
+
+// ------------------------------------------------------------------------------------ launches
+template <int NW, bool AKC, bool BKC>
+int launch_small(const GemmArgs& g, int splits, hipStream_t hs) {
+    const bool tail = (AKC ? g.K : g.M) % 8 != 0 || (BKC ? g.K : g.N) % 8 != 0 || g.N % 8 != 0;
+    const dim3 grid(g.tiles_m * g.tiles_n, 1, splits);
+    if (tail) hipLaunchKernelGGL((gemm_small_kernel<NW, AKC, BKC, TAIL>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
+    else hipLaunchKernelGGL((gemm_small_kernel<NW, AKC, BKC, EDGE>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
+    MP_LAUNCH_CHECK("gemm launch (small)");
+    return MP_OK;
+}
+int launch_small_tile(int waves, bool a_kc, bool b_kc, const GemmArgs& g, int splits, hipStream_t hs);
+int launch_small_both(int waves, const BothArgs& b, hipStream_t hs);
+
+}  // namespace mp

@@ -143,10 +143,9 @@ class MLPStep(_StepBase):
         B.mp_gemm_fwd(self.d1, self.x, w["w1"], w["b1"], None, self.h)
         B.mp_gemm_fwd(self.d2, self.h, w["w2"], w["b2"], None, self.y)
         B.mp_mse_scaled(R, do, self.y, self.target, do, self.st, self.loss, self.dy, self.ws)
-        B.mp_gemm_bwd_dw(self.d2, self.dy, self.h, g["w2"], g["b2"], st, self.ws)
-        B.mp_gemm_bwd_dx(self.d2, self.dy, w["w2"], self.dpre, relu_src=self.h, ld_aux=self.wl.d_hidden)
-        B.mp_gemm_bwd_dw(self.d1, self.dpre, self.x, g["w1"], g["b1"], st, self.ws)
-        B.mp_gemm_bwd_dx(self.d1, self.dpre, w["w1"], self.dx)
+        B.mp_gemm_bwd_both(self.d2, self.dy, w["w2"], self.dpre, self.d2, self.h, g["w2"], g["b2"], st, self.ws,
+                           relu_src=self.h, ld_aux=self.wl.d_hidden)
+        B.mp_gemm_bwd_both(self.d1, self.dpre, w["w1"], self.dx, self.d1, self.x, g["w1"], g["b1"], st, self.ws)
 
 
 # ====================================================================================== configs 2, 3
@@ -195,6 +194,10 @@ class TransformerStep(_StepBase):
                      sx=(S * 3 * d, dk), sw=(S * 3 * d, dk), sy=(h * S * S, S * S))
         self.d_c = G(S, dk, S, ldx=S, ldw=3 * d, ldy=d, trans_w=1, batch_outer=NB, batch_inner=h,
                      sx=(h * S * S, S * S), sw=(S * 3 * d, dk), sy=(S * d, dk))
+        # a layer small enough for it: both gradients of each linear layer in one launch (then there is no grouped launch
+        # and nothing for a second stream)
+        self.joint_bwd = grouped_dw and all(B.mp_gemm_bwd_both_joint(x, x) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2))
+        self.grouped_dw = self.grouped_dw and not self.joint_bwd
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)]
         need += [B.mp_gemm_bwd_dw_workspace_bytes(self.d_s, False), B.mp_gemm_bwd_dw_workspace_bytes(self.d_c, False),
                  B.mp_layernorm_bwd_workspace_bytes(T, d), B.mp_loss_workspace_bytes(T, d)]
@@ -236,8 +239,19 @@ class TransformerStep(_StepBase):
         wl, w, g, st, ws = self.wl, self.P.w16, self.P.g16, self.st_grad, self.ws
         T, d, f, h, S, NB = wl.tokens, wl.d_model, wl.d_ff, wl.n_heads, wl.seq_len, wl.n_seq
         main = torch.cuda.current_stream()
-        side = self.side_stream if self.two_streams else None
+        side = self.side_stream if self.two_streams and not self.joint_bwd else None
         done = {}
+
+        def linear_bwd(desc, dy, wname, bname, x, dx, forked, **epi):
+            """Gradients of one linear layer.  Jointly in one launch where the model is small enough; else the input
+            gradient here, and the weight gradient on the side stream unless the grouped launch takes it (the bias
+            gradients `bname` that a LayerNorm backward produces have forked=False)."""
+            if self.joint_bwd:
+                B.mp_gemm_bwd_both(desc, dy, w[wname], dx, desc, x, g[wname], g[bname], st, ws, **epi)
+                return
+            if not self.grouped_dw:
+                fork(lambda wsx: B.mp_gemm_bwd_dw(desc, dy, x, g[wname], g[bname] if forked else None, st, wsx))
+            B.mp_gemm_bwd_dx(desc, dy, w[wname], dx, **epi)
 
         def fork(fn):
             """Run fn (weight-gradient calls) on the side stream after everything enqueued so far on main."""
@@ -261,23 +275,17 @@ class TransformerStep(_StepBase):
             x = self.x0 if l == 0 else self.act[l - 1]["y2"]
             # dz2 is the gradient of g = W2 f + b2 too, so its column sums are b2's gradient
             B.mp_layernorm_bwd(T, d, dy2, a["y1"], a["g"], w[p + "ln2_g"], a["mean2"], a["rstd2"], dz2,
-                               g[p + "ln2_g"], g[p + "ln2_b"], st, ws, dz_colsum=g[p + "b2"])
+                               g[p + "ln2_g"], g[p + "ln2_b"], st, ws, dz_colsum=None if self.joint_bwd else g[p + "b2"])
             self._t("dy2", l, dy2)
             self._t("dz2", l, dz2)
-            if not self.grouped_dw:
-                fork(lambda wsx: B.mp_gemm_bwd_dw(self.d_f2, dz2, a["f"], g[p + "w2"], None, st, wsx))
-            B.mp_gemm_bwd_dx(self.d_f2, dz2, w[p + "w2"], df, relu_src=a["f"], ld_aux=f)
+            linear_bwd(self.d_f2, dz2, p + "w2", p + "b2", a["f"], df, False, relu_src=a["f"], ld_aux=f)
             self._t("df", l, df)
-            if not self.grouped_dw:
-                fork(lambda wsx: B.mp_gemm_bwd_dw(self.d_f1, df, a["y1"], g[p + "w1"], g[p + "b1"], st, wsx))
-            B.mp_gemm_bwd_dx(self.d_f1, df, w[p + "w1"], self.dy1, add=dz2, ld_aux=d)
+            linear_bwd(self.d_f1, df, p + "w1", p + "b1", a["y1"], self.dy1, True, add=dz2, ld_aux=d)
             self._t("dy1", l, self.dy1)
             B.mp_layernorm_bwd(T, d, self.dy1, x, a["a"], w[p + "ln1_g"], a["mean1"], a["rstd1"], dz1,
-                               g[p + "ln1_g"], g[p + "ln1_b"], st, ws, dz_colsum=g[p + "bo"])
+                               g[p + "ln1_g"], g[p + "ln1_b"], st, ws, dz_colsum=None if self.joint_bwd else g[p + "bo"])
             self._t("dz1", l, dz1)
-            if not self.grouped_dw:
-                fork(lambda wsx: B.mp_gemm_bwd_dw(self.d_o, dz1, a["ctx"], g[p + "wo"], None, st, wsx))
-            B.mp_gemm_bwd_dx(self.d_o, dz1, w[p + "wo"], self.dctx)
+            linear_bwd(self.d_o, dz1, p + "wo", p + "bo", a["ctx"], self.dctx, False)
             self._t("dctx", l, self.dctx)
             # attention: dP = dctx V^T, dV = P^T dctx, dS = softmax', dQ = alpha dS K, dK = alpha dS^T Q
             if self.fused_attention:
@@ -291,9 +299,7 @@ class TransformerStep(_StepBase):
                 B.mp_gemm_bwd_dx(self.d_s, self.dp, a["qkv"][:, d:], dqkv)
                 B.mp_gemm_bwd_dw(self.d_s, self.dp, a["qkv"], dqkv[:, d:], None, None, ws)
             self._t("dqkv", l, dqkv)
-            if not self.grouped_dw:
-                fork(lambda wsx: B.mp_gemm_bwd_dw(self.d_qkv, dqkv, x, g[p + "wqkv"], g[p + "bqkv"], st, wsx))
-            B.mp_gemm_bwd_dx(self.d_qkv, dqkv, w[p + "wqkv"], dx, add=dz1, ld_aux=d)
+            linear_bwd(self.d_qkv, dqkv, p + "wqkv", p + "bqkv", x, dx, True, add=dz1, ld_aux=d)
             self._t("dx", l, dx)
             if self.grouped_dw:
                 # all four operand pairs of this layer are still in place (the temporaries alternate by layer); the
@@ -333,7 +339,8 @@ class XentStep(_StepBase):
         self.logits = torch.empty(T, V, dtype=torch.float16, device="cuda")   # overwritten by dlogits
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.desc = B.gemm_desc(T, V, d, epilogue=ML.MP_EPI_BIAS)
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, False), B.mp_softmax_xent_db_workspace_bytes(T, V)))
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, False), B.mp_gemm_split_workspace_bytes(self.desc),
+                           B.mp_softmax_xent_db_workspace_bytes(T, V)))
 
     def set_batch(self, batch):
         self.h.copy_(_h16(batch["h"]))
@@ -345,8 +352,7 @@ class XentStep(_StepBase):
         B.mp_gemm_fwd(self.desc, self.h, w["w"], w["b"], None, self.logits)
         # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits
         B.mp_softmax_xent_scaled_db(T, V, self.logits, V, self.targets, self.st, self.loss, self.logits, g["b"], self.ws)
-        B.mp_gemm_bwd_dw(self.desc, self.logits, self.h, g["w"], None, self.st_grad, self.ws)
-        B.mp_gemm_bwd_dx(self.desc, self.logits, w["w"], self.dh)
+        B.mp_gemm_bwd_both(self.desc, self.logits, w["w"], self.dh, self.desc, self.h, g["w"], None, self.st_grad, self.ws)
 
 
 # ====================================================================================== config 5
@@ -441,8 +447,8 @@ class LSTMStep(_StepBase):
         for l in range(NL - 1, -1, -1):
             for d, gates, c, above, dgates in self.rl_bwd[l]:
                 B.mp_lstm_layer_bwd(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, self.rl_ws)
-            B.mp_gemm_bwd_dx(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2])
-            B.mp_gemm_bwd_dw(self.d_gate_all[l], self.dgates, self.xh[l], g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)
+            B.mp_gemm_bwd_both(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2], self.d_gate_all[l], self.xh[l],
+                               g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)
         self.dx_input = self.dx[0].view(-1)[:T * Bt * self.in_dims[0]].view(T * Bt, self.in_dims[0])
 
     def _forward_backward_stepwise(self):

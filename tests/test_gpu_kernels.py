@@ -194,7 +194,7 @@ def test_gemm_dx_relu_mask_and_residual_add():
     assert_close16(out, L.add_store(MIXED, base, other), 1e-3, what="dx add")
 
 
-@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 9), (65, 31, 63), (129, 257, 65), (260, 100, 71), (200, 523, 129)])
 def test_gemm_extents_and_strides_of_any_parity(tile, M, N, K):
     """Extents that are no multiple of 8 (pieces that straddle the border, one to seven valid elements), odd leading
