@@ -29,7 +29,9 @@ def _p(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # torch's current stream of the current device as a raw hipStream_t, without a Stream object around it (which costs
+    # as much as a launch: 2.8 us against 0.3 us a call)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def mp_version() -> int:
