@@ -987,6 +987,23 @@ def test_update_matches_oracle(kind, t_prev, wd):
         assert np.array_equal(bits(d["w16"]), half_bits(MIXED.store(np32(d["w32"]))))
 
 
+@pytest.mark.parametrize("poison", [False, True])
+@pytest.mark.parametrize("n", [2048 * 1024 - 2, 2048 * 1024 + 5, 2 * 2048 * 1024 + 1023, 4 * 2048 * 1024 + 4])
+def test_update_workgroup_shares(n, poison):
+    """Parameter counts around the lines where a workgroup takes 1, 2, 4 or 8 pieces, in two tensors: every element is
+    updated once, and a value that is not finite is found in the last element of the list."""
+    sizes = [n - 1500, 1500]
+    ts = _tensors(RNG(24), sizes)
+    host, dev, ost, dst, found = _run_update(ts, "adam", 2.0 ** 7, 3, poison=(1, 1499, np.inf) if poison else None)
+    assert found == int(poison) and dst.opt_step == ost.opt_step == 3 + (not poison)
+    for h, d in zip(host, dev):
+        if poison:
+            assert np.array_equal(np32(d["w32"]), h["w32"]) and np.array_equal(np32(d["v"]), h["v"])
+        else:  # tolerances as in test_update_matches_oracle
+            assert rel_fro(np32(d["w32"]), h["w32"]) <= 1e-5 and np.abs(np32(d["w32"]) - h["w32"]).max() <= 1e-5 * np.abs(h["w32"]).max()
+            assert rel_fro(np32(d["m"]), h["m"]) <= 1e-6 and rel_fro(np32(d["v"]), h["v"]) <= 1e-6
+
+
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 @pytest.mark.parametrize("where", [(0, 0), (2, 4095), (5, 32), (45, 63)])
 def test_update_skips_on_nonfinite_and_halves_scale(bad, where):
