@@ -374,7 +374,7 @@ int mp_lstm_cell_bwd(int B, int H, const mp_half* gates, int ldg, const float* c
  *            *status nonzero, all workgroups then run to their end without waiting, and the outputs are undefined.  A
  *            nonzero status on entry makes the kernel stop waiting at its first wait.  Check it wherever the host next
  *            synchronises.
- *   ws       device, mp_lstm_layer_workspace_bytes() bytes, 16-byte aligned (through which the workgroups exchange
+ *   ws       device, mp_lstm_layer_workspace_bytes() bytes, 4-byte aligned (through which the workgroups exchange
  *            their slices of a step; cleared by the call).
  * All H / 16 x ceil(B / 8) workgroups must be resident at once, two to a compute unit: the call returns
  * MP_E_UNSUPPORTED if the device has too few compute units, and launches of this kind that may run at the same time

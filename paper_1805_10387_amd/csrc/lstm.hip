@@ -452,7 +452,8 @@ static int rl_check(const mp_lstm_layer_desc* d, const char* who, int* nwg) {
 }
 
 // the exchange rings: one per block of batch rows, backward slices being the larger ones
-static size_t rl_rings(int B, int H) { return (size_t)((B + RL_ROWS - 1) / RL_ROWS) * RL_RING * rl_bwd_slot(H); }
+// (16 bytes more than they hold, so that a workspace at any 4-byte boundary has room for them at a 16-byte one)
+static size_t rl_rings(int B, int H) { return (size_t)((B + RL_ROWS - 1) / RL_ROWS) * RL_RING * rl_bwd_slot(H) + 16; }
 extern "C" size_t mp_lstm_layer_workspace_bytes(void) { return rl_rings(RL_MAX_B, RL_MAX_H); }
 extern "C" size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d) {
     return d && d->B > 0 && d->H > 0 && d->H % 64 == 0 && d->H <= RL_MAX_H ? rl_rings(d->B, d->H) : 0;
@@ -462,14 +463,15 @@ static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, 
                    const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
     const size_t need = d->step_rows > 0 ? rl_rings(d->B, d->H) : mp_lstm_layer_workspace_bytes();
-    if (!ws || ws_bytes < need || !aligned16(ws)) {
-        set_error("%s: 16-byte aligned workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
+    if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 3u)) {
+        set_error("%s: 4-byte aligned workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
         return MP_E_WORKSPACE;
     }
+    char* const  ring = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 15) & ~(uintptr_t)15);
     const size_t used = (size_t)((d->B + RL_ROWS - 1) / RL_ROWS) * RL_RING * slot;
-    const int    rc   = mp_fill_u32(used / 4, ~0u, ws, stream);  // everything starts empty (a kernel: capturable)
+    const int    rc   = mp_fill_u32(used / 4, ~0u, ring, stream);  // everything starts empty (a kernel: capturable)
     if (rc != MP_OK) return rc;
-    out->ring        = static_cast<char*>(ws);
+    out->ring        = ring;
     out->status      = status;
     out->never       = d->debug_extra_participants > 0;
     out->limit_ticks = (d->wait_limit_us > 0 ? (long long)d->wait_limit_us : 2000000ll) * 100;  // 100 MHz clock

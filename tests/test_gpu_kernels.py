@@ -834,6 +834,25 @@ def test_lstm_persistent_layer_step_rows(T, Bn, I, H, block):
     assert_close16(db, db_ref, 1e-3, what="db")
 
 
+def test_lstm_persistent_layer_workspace_at_any_word():
+    """A workspace of the stated size at a 4-byte boundary that is no 16-byte boundary is enough."""
+    T, Bn, I, H = 6, 32, 8, 1024
+    r = RNG(78)
+    w = h16(r.uniform(-0.05, 0.05, (4 * H, I + H)))
+    gx, bias = f32(r.standard_normal((T * Bn, 4 * H))), h16(np.zeros(4 * H))
+    got = []
+    for lead in (0, 1):
+        words = mp.mp_lstm_layer_workspace_bytes() // 4
+        buf = torch.zeros(words + lead + 64, dtype=torch.int32, device="cuda")
+        gates, c, status = empty16(T, Bn, 4 * H), torch.zeros(T + 1, Bn, H, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        xh, up = torch.zeros(T, Bn, I + H, dtype=torch.float16, device="cuda"), empty16(T, Bn, H)
+        d = mp.lstm_layer_desc(T, Bn, I, H, I + H, I + H, H)
+        mp.mp_lstm_layer_fwd(d, gx, w, bias, gates, c, xh, up, status, buf[lead:lead + words])
+        assert int(status.item()) == 0 and torch.all(buf[lead + words:] == 0)
+        got.append(up)
+    assert torch.equal(got[0], got[1])
+
+
 def test_lstm_persistent_layer_timeout_path_and_rejections():
     """The step barrier's wait is bounded: asked to wait for a flag nobody raises (debug_extra_participants) with a
     2 ms limit, every workgroup gives up, the kernels end normally and *status reports it; a poisoned status makes the
