@@ -180,13 +180,17 @@ static bool fast_path_ok(const GemmArgs& g) {
     return true;
 }
 
+// Leading dimensions up to which an offset inside a tile of 256 (of 64) rows stays inside the buffer size.
+constexpr int LD_BUFFER_256 = 1 << 21, LD_BUFFER_64 = 1 << 24;
+
 // What the matrix-core kernels take: a straddling piece of 8 elements is loaded so that it ends at the border, so the
 // stored direction of an operand must hold at least 8 elements; fp32 outputs and addends move 4 columns at a time; and
 // an offset inside a tile must fit the buffer size.  Alignment and multiples of 8 do not matter.
 static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
     if (g.K == 0 || (a_kc ? g.K : g.M) < 8 || (b_kc ? g.K : g.N) < 8) return false;
     if ((g.acc_in || g.C32) && (g.N & 3) != 0) return false;
-    return g.lda < (1 << 21) && g.ldb < (1 << 21);
+    const bool interior = g.aligned && g.M % 64 == 0 && g.N % 64 == 0 && g.K % BK == 0;  // (no buffer offsets in 64 x 64 tiles)
+    return interior || std::max(g.lda, g.ldb) < LD_BUFFER_64;
 }
 
 // ws: split-K partial buffer (may be NULL when !allow_split).
@@ -208,6 +212,9 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     }
     Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc && b_kc);
     if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc && b_kc);
+    // very long rows: 64 x 64 tiles, unless all loads are plain ones
+    if (std::max(g.lda, g.ldb) >= LD_BUFFER_256 && !(g.aligned && g.M % 256 == 0 && g.N % 256 == 0 && g.K % BK == 0 && p.tile < kTileKcOnly))
+        p = Plan{6, 1, (g.K + BK - 1) / BK * BK};
     g.k_per_split = p.k_per_split;
     if (p.tile >= kTileSmall4 && (batches != 1 || (!a_kc && b_kc))) p.tile = 6;
     const bool    small = p.tile >= kTileSmall4;
@@ -429,7 +436,8 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 }
 
 // One launch for both gradients: each product for the small kernel by itself, and together no more than three workgroups
-// per compute unit.  (An iteration of a 64 x 256 -> 1024 -> 256 network: JOINT_FIGURES)
+// per compute unit.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and the small tiles,
+// of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
     if (g_force_tile >= 0 || !plain(dx) || !plain(dw)) return false;
@@ -461,7 +469,7 @@ extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, con
         w.A = dY; w.B = X; w.C = dW; w.found_inf = st ? &st->found_inf : nullptr;
         w.M = d_dw->N; w.N = d_dw->K; w.K = d_dw->M;
         w.lda = d_dw->ldy; w.ldb = d_dw->ldx; w.ldc = d_dw->ldw; w.alpha = d_dw->alpha; w.batch_inner = 1;
-        if (matrix_path_ok(x, true, false) && matrix_path_ok(w, false, false)) {
+        if (std::max(std::max(x.lda, x.ldb), w.ldb) < LD_BUFFER_64 && matrix_path_ok(x, true, false) && matrix_path_ok(w, false, false)) {
             for (GemmArgs* g : {&x, &w}) {
                 g->tiles_m = (g->M + 31) / 32;
                 g->tiles_n = (g->N + 31) / 32;

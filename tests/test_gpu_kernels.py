@@ -794,6 +794,28 @@ def test_lstm_persistent_layer_kernels(T, Bn, I, H):
     assert_close16(o["db"], db_ref, 1e-3, what="db")
 
 
+@pytest.mark.parametrize("ld", [(1 << 21) - 1, 1 << 21, (1 << 21) + 3])
+def test_gemm_leading_dimension_beyond_the_large_tiles(ld):
+    """Leading dimensions around 2^21, where an offset inside a 256-row tile comes near the end of the buffer range and the
+    rule changes to 64 x 64 tiles: a product over rows and one over columns of the same wide matrix."""
+    M, N, K = 300, 40, 72
+    r = RNG(ld % 1000)
+    x, w, dy = S16(r.standard_normal((M, K))), S16(r.standard_normal((N, K)) * 0.1), S16(r.standard_normal((M, N)))
+    buf = torch.zeros(M * ld, dtype=torch.float16, device="cuda")
+    xd = buf.view(M, ld)
+    xd[:, :K] = h16(x)
+    y, dw = empty16(M, N), empty16(N, K)
+    for tile in (-1, 0):
+        mp.mp_gemm_tuning_override(tile, 1)
+        try:
+            mp.mp_gemm_fwd(mp.gemm_desc(M, N, K, ldx=ld), xd, h16(w), None, None, y)
+            mp.mp_gemm_bwd_dw(mp.gemm_desc(M, N, K, ldx=ld), h16(dy), xd, dw, None, None, ws_bytes(1 << 20))
+        finally:
+            mp.mp_gemm_tuning_override(-1, 1)
+        assert_close16(y, L.linear_fwd(MIXED, x, w, None), 1e-3, max_ulp=1, what="fwd")
+        assert_close16(dw, L.linear_bwd(MIXED, dy, x, w)[1], 1e-3, max_ulp=1, what="dw")
+
+
 @pytest.mark.parametrize("T,Bn,I,H", [(9, 9, 8, 640), (6, 31, 16, 896), (8, 3, 8, 512), (5, 24, 0, 768), (12, 32, 32, 1024)])
 def test_lstm_persistent_layer_exchange_ring(T, Bn, I, H):
     """More time steps than the exchange ring has slots, every kind of k-step count per wave, batches that fill their
