@@ -74,11 +74,15 @@ __global__ __launch_bounds__(GL_THREADS) void finish_colsum_kernel(const float* 
 }
 
 // --------------------------------------------------------------------------- column sums
-// Workgroup = 8 column-groups x 32 row-lanes; VEC columns per column-group (a row piece of 8 x 16 B =
-// one 128-byte line per row when VEC = 8).
-template <int VEC>
+// Workgroup = 8 column-groups x 32 row-lanes, 8 columns per column-group (a row piece of 8 x 16 B = one 128-byte line per
+// row).  Rows may start at any element and have any length: the pieces are loaded as they lie (the hardware takes any
+// address), and only a last, partial piece goes element by element.  (1021 x 12001 with 2-byte loads, one column per
+// column-group: 27 us; for the iteration's gain see xent_cached_kernel.)
+typedef unsigned u32x4c __attribute__((ext_vector_type(4)));
+typedef u32x4c   u32x4c_u __attribute__((aligned(2)));
 __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, int ld, const uint16_t* __restrict__ dy,
                                                             int rows_per_block, float* __restrict__ part) {
+    constexpr int    VEC = 8;
     __shared__ float sm[32][8 * VEC + 1];
     const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
     const int c0 = (blockIdx.x * 8 + cg) * VEC;
@@ -89,13 +93,17 @@ __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, 
     for (int k = 0; k < VEC; ++k) acc[k] = 0.f;
     if (c0 < cols) {
         for (int r = r0 + rl; r < r1; r += 32) {
-            if (VEC == 8) {
-                float f[8];
-                unpack8(*reinterpret_cast<const uint4*>(dy + (long long)r * ld + c0), f);
+            const uint16_t* p = dy + (long long)r * ld + c0;
+            if (c0 + VEC <= cols) {
+                const u32x4c q = *reinterpret_cast<const u32x4c_u*>(p);
+                float        f[8];
+                unpack8(make_uint4(q[0], q[1], q[2], q[3]), f);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) acc[k] += f[k];
             } else {
-                acc[0] += h2f(dy[(long long)r * ld + c0]);
+#pragma unroll
+                for (int k = 0; k < VEC - 1; ++k)
+                    if (c0 + k < cols) acc[k] += h2f(p[k]);
             }
         }
     }
@@ -494,8 +502,8 @@ static int grid_for(size_t units, int per_block, int cap) {
 }
 
 // ---- column sums
-static int colsum_row_blocks(int rows, int cols, int vec) {
-    const int col_blocks = (cols + 8 * vec - 1) / (8 * vec);
+static int colsum_row_blocks(int rows, int cols) {
+    const int col_blocks = (cols + 63) / 64;
     int       rb         = 1024 / (col_blocks > 0 ? col_blocks : 1);
     if (rb > 32) rb = 32;                 // partial rows the finish kernel has to add up
     const int max_rb = (rows + 63) / 64;  // at least 64 rows per workgroup
@@ -506,9 +514,7 @@ static int colsum_row_blocks(int rows, int cols, int vec) {
 
 extern "C" size_t mp_colsum_workspace_bytes(int rows, int cols) {
     if (rows <= 0 || cols <= 0) return 0;
-    // the scalar path (vec = 1) never uses more row blocks than the vector path allows for
-    const int rb8 = colsum_row_blocks(rows, cols, 8), rb1 = colsum_row_blocks(rows, cols, 1);
-    return (size_t)(rb8 > rb1 ? rb8 : rb1) * cols * sizeof(float);
+    return (size_t)colsum_row_blocks(rows, cols) * cols * sizeof(float);
 }
 
 int mp::finish_colsum_launch(const float* part, int nparts, int cols, mp_half* db, mp_scale_state* st, hipStream_t hs) {
@@ -523,15 +529,9 @@ int mp::finish_colsum_launch(const float* part, int nparts, int cols, mp_half* d
 // which the first launch writes before the second reads it (nothing has to start at zero).
 static int colsum_launch(int rows, int cols, const mp_half* dY, int ld, mp_half* db, mp_scale_state* st, float* part,
                          hipStream_t hs) {
-    const bool  vec = (cols % 8 == 0) && (ld % 8 == 0) && aligned16(dY);
-    const int   V   = vec ? 8 : 1;
-    const int   rb  = colsum_row_blocks(rows, cols, V);
+    const int   rb  = colsum_row_blocks(rows, cols);
     const int   rpb = (rows + rb - 1) / rb;
-    const dim3  grid((cols + 8 * V - 1) / (8 * V), rb);
-    if (vec)
-        hipLaunchKernelGGL(colsum_kernel<8>, grid, dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
-    else
-        hipLaunchKernelGGL(colsum_kernel<1>, grid, dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
+    hipLaunchKernelGGL(colsum_kernel, dim3((cols + 63) / 64, rb), dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
     MP_LAUNCH_CHECK("mp_colsum");
     FinishOuts outs{{db, nullptr, nullptr}};
     hipLaunchKernelGGL(finish_colsum_kernel, dim3((cols + 31) / 32), dim3(GL_THREADS), 0, hs, part, rb,

@@ -64,11 +64,17 @@ __global__ __launch_bounds__(LOSS_THREADS) void mse_kernel(int rows, int cols, i
 }
 
 // ------------------------------------------------------------------------------- softmax cross-entropy
-// One workgroup per row.  Cached variant (vocab a multiple of 8, at most 32 x THREADS): every lane keeps its 32
+// One workgroup per row.  Cached variant (vocab at most 32 x THREADS): every lane keeps its 32
 // logits in registers as fp32, overwrites them with exp(z - max) once and scales them on the way out, so HBM sees
 // one read and one write of the row and each exponential is computed once.  THREADS is picked from the row length
-// (256, 512 or 1024).  The generic variant re-reads the row (it then comes from L2).
+// (256, 512 or 1024).  The generic variant, for longer rows, re-reads the row (it then comes from L2).
+// RAGGED: rows of any length at any element alignment (a vocabulary as a tokenizer leaves it).  They move in 16-byte
+// pieces all the same, which the hardware takes at any address; only the lane with the row's last, partial piece goes
+// element by element.  (1021 x 12001: 46 us in the generic kernel, whose every element is a
+// 2-byte access in three passes; an iteration of that projection 216 -> 172 us together with the column sums in 16-byte pieces.)
 constexpr int XENT_VECS = 4;  // 16-byte vectors per lane
+typedef unsigned u32x4l __attribute__((ext_vector_type(4)));
+typedef u32x4l   u32x4l_u __attribute__((aligned(2)));
 
 template <int NW, bool MAX>
 __device__ __forceinline__ float block_reduce_lds(float v, float* red) {
@@ -88,15 +94,15 @@ __device__ __forceinline__ float block_reduce_lds(float v, float* red) {
 // COLSUM: every workgroup also sums the gradient values it stores (the fp16 values, as stored) per column over its
 // rows, and leaves the sums in colpart[blockIdx.x][vocab]: the bias gradient of the projection that made the logits
 // then needs no second pass over the gradient matrix, only a sum over gridDim.x partial rows.
-template <int THREADS, bool COLSUM = false>
+template <int THREADS, bool COLSUM, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld, const uint16_t* logits,
                                                               const int32_t* __restrict__ targets,
                                                               const mp_scale_state* __restrict__ st, int rows,
                                                               uint16_t* dlogits,  // may alias logits
                                                               float* __restrict__ row_loss,
-                                                              float* __restrict__ colpart = nullptr) {
+                                                              float* __restrict__ colpart) {
     __shared__ float red[THREADS / 64];
-    const int        nvec  = vocab >> 3;
+    const int        nvec  = RAGGED ? (vocab + 7) >> 3 : vocab >> 3;
     const float      coef0 = (float)((double)st->scale / (double)rows);
     // a row's packed logits, its target and the target's logit; vectors beyond the row read as -inf
     auto fetch = [&](int row, uint4* q, int& tgt, float& zt) {
@@ -107,7 +113,17 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
         for (int i = 0; i < XENT_VECS; ++i) {
             const int v = i * THREADS + threadIdx.x;
             q[i]        = make_uint4(0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u);
-            if (v < nvec) q[i] = *reinterpret_cast<const uint4*>(z + (long long)v * 8);
+            if (!RAGGED) {
+                if (v < nvec) q[i] = *reinterpret_cast<const uint4*>(z + (long long)v * 8);
+            } else if (8 * v + 8 <= vocab) {
+                const u32x4l t = *reinterpret_cast<const u32x4l_u*>(z + (long long)v * 8);
+                q[i]           = make_uint4(t[0], t[1], t[2], t[3]);
+            } else if (v < nvec) {
+                unsigned x[7];
+#pragma unroll
+                for (int k = 0; k < 7; ++k) x[k] = 8 * v + k < vocab ? z[8 * v + k] : 0xFC00u;
+                q[i] = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | 0xFC000000u);
+            }
         }
     };
     uint4 raw[XENT_VECS];
@@ -163,7 +179,7 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
             if (v < nvec) {
                 float p[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) p[k] = e[i][k] * inv;
+                for (int k = 0; k < 8; ++k) p[k] = RAGGED && !valid ? 0.f : e[i][k] * inv;
                 if (v == vt) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
@@ -172,7 +188,15 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
                 unsigned o[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) o[k] = (unsigned)f2h(coef * p[2 * k]) | ((unsigned)f2h(coef * p[2 * k + 1]) << 16);
-                *reinterpret_cast<uint4*>(dz + (long long)v * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+                if (!RAGGED) {
+                    *reinterpret_cast<uint4*>(dz + (long long)v * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+                } else if (8 * v + 8 <= vocab) {
+                    *reinterpret_cast<u32x4l_u*>(dz + (long long)v * 8) = u32x4l{o[0], o[1], o[2], o[3]};
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 7; ++k)
+                        if (8 * v + k < vocab) dz[8 * v + k] = (uint16_t)((k & 1) ? o[k >> 1] >> 16 : o[k >> 1] & 0xFFFFu);
+                }
                 if (COLSUM) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
@@ -192,7 +216,11 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
 #pragma unroll
         for (int i = 0; i < XENT_VECS; ++i) {
             const int v = i * THREADS + threadIdx.x;
-            if (v < nvec) {
+            if (RAGGED) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (8 * v + k < vocab) out[8 * v + k] = cs[i][k];
+            } else if (v < nvec) {
                 *reinterpret_cast<float4*>(out + (long long)v * 8)     = make_float4(cs[i][0], cs[i][1], cs[i][2], cs[i][3]);
                 *reinterpret_cast<float4*>(out + (long long)v * 8 + 4) = make_float4(cs[i][4], cs[i][5], cs[i][6], cs[i][7]);
             }
@@ -279,6 +307,18 @@ static int xent_grid(int rows, int threads) {
     return rows < 256 ? rows : 256;
 }
 
+template <int THREADS, bool COLSUM>
+static void launch_xent_cached(int rows, int vocab, int ld, const mp_half* logits, const int32_t* targets, const mp_scale_state* st,
+                               mp_half* dlogits, float* row_loss, float* colpart, hipStream_t hs) {
+    const dim3 grid(xent_grid(rows, THREADS)), block(THREADS);
+    if (vocab % 8 == 0 && ld % 8 == 0 && aligned16(logits) && aligned16(dlogits))
+        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, false>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
+                           row_loss, colpart);
+    else
+        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, true>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
+                           row_loss, colpart);
+}
+
 extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
                                       const mp_scale_state* st, float* loss, mp_half* dlogits, void* ws,
                                       size_t ws_bytes, mp_stream stream) {
@@ -292,18 +332,13 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
     }
     float*      row_loss = static_cast<float*>(ws);
     hipStream_t hs       = as_stream(stream);
-    const bool cache = (vocab % 8 == 0) && (ld % 8 == 0) && aligned16(logits) && aligned16(dlogits) &&
-                       (vocab / 8 <= XENT_VECS * 1024);
-    const int  nvec  = vocab / 8;
-    if (cache && nvec <= XENT_VECS * 256)
-        hipLaunchKernelGGL(xent_cached_kernel<256>, dim3(xent_grid(rows, 256)), dim3(256), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
-                           row_loss);
-    else if (cache && nvec <= XENT_VECS * 512)
-        hipLaunchKernelGGL(xent_cached_kernel<512>, dim3(xent_grid(rows, 512)), dim3(512), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
-                           row_loss);
-    else if (cache)
-        hipLaunchKernelGGL(xent_cached_kernel<1024>, dim3(xent_grid(rows, 1024)), dim3(1024), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
-                           row_loss);
+    const int   nvec     = (vocab + 7) / 8;
+    if (nvec <= XENT_VECS * 256)
+        launch_xent_cached<256, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
+    else if (nvec <= XENT_VECS * 512)
+        launch_xent_cached<512, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
+    else if (nvec <= XENT_VECS * 1024)
+        launch_xent_cached<1024, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
     else
         hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
                            row_loss);
@@ -316,9 +351,9 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
 // ---- cross-entropy that also leaves the bias gradient of the projection behind the logits
 static size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 // the fused path: rows cached in a 1024-lane workgroup, workgroups persistent over rows
-static bool xent_db_fused(int rows, int vocab, int ld, const void* logits, const void* dlogits) {
-    return (vocab % 8 == 0) && (ld % 8 == 0) && aligned16(logits) && aligned16(dlogits) && vocab / 8 <= XENT_VECS * 1024 &&
-           vocab / 8 > XENT_VECS * 512 && rows >= 1;
+static bool xent_db_fused(int vocab) {
+    const int nvec = (vocab + 7) / 8;
+    return nvec <= XENT_VECS * 1024 && nvec > XENT_VECS * 512;
 }
 
 extern "C" size_t mp_softmax_xent_db_workspace_bytes(int rows, int vocab) {
@@ -342,16 +377,15 @@ extern "C" int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* log
     const size_t head = round256(mp_loss_workspace_bytes(rows, vocab));
     float*       part = reinterpret_cast<float*>(static_cast<char*>(ws) + head);
     hipStream_t  hs   = as_stream(stream);
-    if (!xent_db_fused(rows, vocab, ld, logits, dlogits)) {
-        // small or unaligned vocabularies: the plain loss call, then a column sum over the gradient it stored
+    if (!xent_db_fused(vocab)) {
+        // small (or very large) vocabularies: the plain loss call, then a column sum over the gradient it stored
         const int rc = mp_softmax_xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, ws, head, stream);
         if (rc != MP_OK) return rc;
         return mp_colsum(rows, vocab, dlogits, ld, db, st, part, ws_bytes - head, stream);
     }
     float*    row_loss = static_cast<float*>(ws);
     const int grid     = xent_grid(rows, 1024);
-    hipLaunchKernelGGL((xent_cached_kernel<1024, true>), dim3(grid), dim3(1024), 0, hs, vocab, ld, logits, targets, st, rows,
-                       dlogits, row_loss, part);
+    launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, part, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db");
     hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(LOSS_THREADS), 0, hs, row_loss, rows, (double)rows, loss);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db(finish)");

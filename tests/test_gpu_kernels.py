@@ -627,6 +627,52 @@ def test_softmax_xent_scaled_with_bias_gradient(rows, vocab):
     assert e.value.code == ML.MP_E_WORKSPACE
 
 
+@pytest.mark.parametrize("rows,vocab", [(3, 1), (5, 7), (6, 2 ** 13 + 1), (9, 2 ** 14 - 1), (70, 2 ** 14 + 3), (300, 2 ** 15 - 3),
+                                        (4, 2 ** 15 + 1), (8, 2 ** 12)])
+def test_softmax_xent_rows_at_any_alignment(rows, vocab):
+    """Vocabularies that are no multiple of 8, in rows that start at odd elements, around the row lengths where the workgroup
+    size changes: gradient and bias gradient against the oracle, in place too, nothing written between the rows, and rows
+    with an out-of-range target get a zero gradient whatever their logits are."""
+    r = RNG(rows + vocab)
+    z = S16(r.standard_normal((rows, vocab)) * 3)
+    t = r.integers(0, vocab, rows).astype(np.int32)
+    t[1] = vocab
+    z[1, 0] = np.inf
+    S, ld = 2.0 ** 10, vocab + 3
+    clean = z.copy()
+    clean[1] = 0.0                                    # (what the row holds does not matter)
+    loss_ref, g_ref = L.softmax_xent_scaled(MIXED, clean, t, S)
+    buf = torch.full((rows * ld + 8,), 7.0, dtype=torch.float16, device="cuda")
+    zd = buf[1:1 + rows * ld].view(rows, ld)
+    zd[:, :vocab] = h16(z)
+    gbuf = torch.full_like(buf, 5.0)
+    gd = gbuf[1:1 + rows * ld].view(rows, ld)
+    st = make_state(scale=S)
+    loss, db = empty32(1), empty16(vocab)
+    mp.mp_softmax_xent_scaled(rows, vocab, zd, ld, i32(t), st, loss, gd, ws_bytes(mp.mp_loss_workspace_bytes(rows, vocab)))
+    assert abs(float(loss) - float(loss_ref)) <= 2e-6 * abs(float(loss_ref)) + 1e-6
+    assert_close16(gd[:, :vocab], g_ref, 1e-3, max_ulp=2, what="gradient")
+    assert torch.all(gd[:, vocab:] == 5.0) and float(gbuf[0]) == 5.0
+    ws = ws_bytes(mp.mp_softmax_xent_db_workspace_bytes(rows, vocab))
+    mp.mp_softmax_xent_scaled_db(rows, vocab, zd, ld, i32(t), st, loss, zd, db, ws)   # in place
+    assert np.array_equal(bits(zd[:, :vocab].contiguous()), bits(gd[:, :vocab].contiguous()))
+    assert torch.all(zd[:, vocab:] == 7.0) and float(buf[0]) == 7.0
+    assert_close16(db, MIXED.store(np32(gd[:, :vocab]).sum(0, dtype=np.float32)), 1e-3, max_ulp=1, what="bias gradient")
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (65, 7), (64, 63), (200, 65), (1021, 1001), (3, 8)])
+def test_colsum_rows_at_any_alignment(rows, cols):
+    """Column counts around the 8-column pieces and 64-column workgroups, rows that start at odd elements."""
+    r = RNG(rows + cols)
+    dy, ld = S16(r.standard_normal((rows, cols))), cols + 3
+    buf = torch.full((rows * ld + 8,), float("inf"), dtype=torch.float16, device="cuda")
+    d = buf[1:1 + rows * ld].view(rows, ld)
+    d[:, :cols] = h16(dy)
+    db = empty16(cols)
+    mp.mp_colsum(rows, cols, d, ld, db, None, ws_bytes(mp.mp_colsum_workspace_bytes(rows, cols)))
+    assert_close16(db, MIXED.store(dy.sum(0, dtype=np.float32)), 1e-3, max_ulp=1, what="colsum")
+
+
 def test_softmax_xent_bias_gradient_flags_overflow():
     """Every row has the same target and a dominant logit elsewhere: the column of the dominant class sums
     rows x S / rows = S = 2^17 > 65504, so db overflows while every stored gradient value is small."""
