@@ -190,7 +190,8 @@ int mp_gemm_bwd_dw(const mp_gemm_desc* desc /* host */, const mp_half* dY, const
  * mp_gemm_bwd_dx_ws(d_dx, dY, W, relu_src, add, ld_aux, dX, ws), whose arguments these are (same results contract; the
  * fp32 summation order may differ).  d_dx and d_dw agree in M, N and ldy; K, ldx and ldw may differ (an LSTM's input
  * gradient takes some of the columns of W that its weight gradient has).  For small unbatched products (trans_w 0) the
- * two and the bias gradient are one launch; mp_gemm_bwd_both_joint tells (1) for a pair of descriptors.  A workspace too
+ * two and the bias gradient are one launch (so dX may overlap neither dY nor X); mp_gemm_bwd_both_joint tells (1) for a
+ * pair of descriptors.  A workspace too
  * small for mp_gemm_bwd_dw is an error only where the call is not one launch. */
 int mp_gemm_bwd_both(const mp_gemm_desc* d_dx /* host */, const mp_half* dY, const mp_half* W, const mp_half* relu_src,
                      const mp_half* add, int32_t ld_aux, mp_half* dX, const mp_gemm_desc* d_dw /* host */, const mp_half* X,
@@ -320,7 +321,8 @@ int mp_softmax_bwd(int64_t rows, int cols, const mp_half* p, const mp_half* dp, 
  * with the same storage points as the unfused chain mp_gemm_fwd -> mp_softmax_fwd -> mp_gemm_fwd, but s never
  * reaches memory.  p (device fp16 [n_seq, n_heads, seq_len, seq_len]) is kept for the backward pass; ctx has the
  * heads side by side (leading dimension ld_ctx).  No mask, no dropout.
- * Supported: d_head == 64, seq_len a multiple of 8 up to 128; otherwise MP_E_UNSUPPORTED (use the unfused chain). */
+ * Supported: d_head == 64, seq_len a multiple of 8 up to 128; otherwise MP_E_UNSUPPORTED (use the calls with
+ * ld_p below, or the unfused chain). */
 int mp_attention_fwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv, float alpha,
                      mp_half* p, mp_half* ctx, int ld_ctx, mp_stream stream);
 
@@ -331,6 +333,15 @@ int mp_attention_fwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_h
 int mp_attention_bwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv, float alpha,
                      const mp_half* p, const mp_half* dctx, int ld_ctx, mp_half* dqkv, int ld_dqkv,
                      mp_stream stream);
+
+/* The same two calls for any seq_len up to 128: rows of p are ld_p >= seq_len elements apart, a multiple of 8 (p is
+ * [n_seq, n_heads, seq_len, ld_p]).  The forward call writes zeros behind a row's seq_len values up to the next multiple of
+ * 8, and the backward call expects them there. */
+int mp_attention_fwd_ldp(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv, float alpha,
+                         mp_half* p, int ld_p, mp_half* ctx, int ld_ctx, mp_stream stream);
+int mp_attention_bwd_ldp(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv, float alpha,
+                         const mp_half* p, int ld_p, const mp_half* dctx, int ld_ctx, mp_half* dqkv, int ld_dqkv,
+                         mp_stream stream);
 
 /* LSTM cell, gate blocks ordered (i, f, g, o) in gates[B, 4H] (leading dimension ldg):
  *   c = sigma(f) c_prev + sigma(i) tanh(g)   (fp32, never rounded),  h = RNE16( sigma(o) tanh(c) ).

@@ -88,6 +88,8 @@ SIGNATURES = {
     "mp_softmax_bwd": (_I, [_I64, _I, _P, _P, _P, _I, _P]),
     "mp_attention_fwd": (_I, [_I, _I, _I, _I, _P, _I, _F, _P, _P, _I, _P]),
     "mp_attention_bwd": (_I, [_I, _I, _I, _I, _P, _I, _F, _P, _P, _I, _P, _I, _P]),
+    "mp_attention_fwd_ldp": (_I, [_I, _I, _I, _I, _P, _I, _F, _P, _I, _P, _I, _P]),
+    "mp_attention_bwd_ldp": (_I, [_I, _I, _I, _I, _P, _I, _F, _P, _I, _P, _I, _P, _I, _P]),
     "mp_lstm_cell_fwd": (_I, [_I, _I, _P, _I, _P, _P, _P, _I, _P, _I, _P]),
     "mp_lstm_cell_bwd": (_I, [_I, _I, _P, _I, _P, _P, _P, _I, _P, _I, _P, _P, _P]),
     "mp_lstm_layer_workspace_bytes": (_SZ, []),

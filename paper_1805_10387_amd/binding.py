@@ -215,6 +215,15 @@ def mp_attention_bwd(n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, alpha, p, dct
                                      _p(dqkv), ld_dqkv, _stream()))
 
 
+def mp_attention_fwd_ldp(n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, alpha, p, ld_p, ctx, ld_ctx):
+    _check(L.load().mp_attention_fwd_ldp(n_seq, n_heads, seq_len, d_head, _p(qkv), ld_qkv, alpha, _p(p), ld_p, _p(ctx), ld_ctx, _stream()))
+
+
+def mp_attention_bwd_ldp(n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, alpha, p, ld_p, dctx, ld_ctx, dqkv, ld_dqkv):
+    _check(L.load().mp_attention_bwd_ldp(n_seq, n_heads, seq_len, d_head, _p(qkv), ld_qkv, alpha, _p(p), ld_p, _p(dctx), ld_ctx,
+                                         _p(dqkv), ld_dqkv, _stream()))
+
+
 def mp_lstm_cell_fwd(B, H, gates, ldg, c_prev, c, h_out, ldh, h_out2=None, ldh2=0):
     _check(L.load().mp_lstm_cell_fwd(B, H, _p(gates), ldg, _p(c_prev), _p(c), _p(h_out), ldh, _p(h_out2), ldh2, _stream()))
 

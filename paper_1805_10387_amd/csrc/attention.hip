@@ -6,6 +6,9 @@
 //     s  = RNE16(alpha q k^T)      p  = RNE16(softmax_fp32(s))      ctx = RNE16(p v)
 //     dP = RNE16(dctx v^T)         dS = RNE16(p (dP - sum_n dP p))
 //     dV = RNE16(p^T dctx)         dQ = RNE16(alpha dS k)           dK = RNE16(alpha dS^T q)
+// Any seq_len up to 128: rows of p are ld_p apart, a multiple of 8, so that every row is made of aligned 16-byte pieces; keys
+// and queries beyond seq_len read as zero rows, their probabilities are exactly 0, and nothing in the products tells them
+// from padding to the 32-row tiles, which is there anyway.
 // What is saved is HBM traffic: the unfused chain writes and re-reads the [seq, seq] score-sized
 // tensors nine times per layer.
 //
@@ -134,7 +137,7 @@ __device__ __forceinline__ void rows_product(const char* An_lds, const uint16_t*
 // ------------------------------------------------------------------------------------ forward
 __global__ __launch_bounds__(AT_THREADS, 4) void attention_fwd_kernel(int n_heads, int S, const uint16_t* __restrict__ qkv,
                                                                     int ld, int d_model, float alpha,
-                                                                    uint16_t* __restrict__ P, uint16_t* __restrict__ ctx,
+                                                                    uint16_t* __restrict__ P, int ld_p, uint16_t* __restrict__ ctx,
                                                                     int ld_ctx) {
     extern __shared__ __align__(16) char smem[];  // the rows of V (16 KB), then the rows of K (16 KB)
     char* Krows = smem + 128 * 128;
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(AT_THREADS, 4) void attention_fwd_kernel(int n_head
     const uint16_t* q = qkv + (long long)b * S * ld + h * AT_D;
     const uint16_t* k = q + d_model;
     const uint16_t* v = q + 2 * d_model;
-    uint16_t*       Pb = P + (long long)blockIdx.x * S * S;
+    uint16_t*       Pb = P + (long long)blockIdx.x * S * ld_p;
 
     {
         u32x4a rk[4], rv[4];
@@ -193,8 +196,8 @@ __global__ __launch_bounds__(AT_THREADS, 4) void attention_fwd_kernel(int n_head
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const u32x4a row8 = gather8(pk[t][4 * c], pk[t][4 * c + 1], pk[t][4 * c + 2], pk[t][4 * c + 3]);
-            const int    n    = 32 * t + 16 * c + 8 * hf;  // (S is a multiple of 8: a piece is inside or outside as a whole)
-            if (m < S && n < S) *reinterpret_cast<u32x4a*>(Pb + (long long)m * S + n) = row8;
+            const int    n    = 32 * t + 16 * c + 8 * hf;  // (a piece that straddles S lies inside ld_p; its keys beyond S are 0)
+            if (m < S && n < S) *reinterpret_cast<u32x4a*>(Pb + (long long)m * ld_p + n) = row8;
         }
     }
 
@@ -245,7 +248,7 @@ constexpr int AT_BWD_LDS = 128 * 256 + 128 * 128;
 
 __global__ __launch_bounds__(AT_THREADS, 2) void attention_bwd_kernel(int n_heads, int S, const uint16_t* __restrict__ qkv,
                                                                        int ld, int d_model, float alpha,
-                                                                       const uint16_t* __restrict__ P,
+                                                                       const uint16_t* __restrict__ P, int ld_p,
                                                                        const uint16_t* __restrict__ dctx, int ld_ctx,
                                                                        uint16_t* __restrict__ dqkv, int ld_dqkv) {
     extern __shared__ __align__(16) char smem[];
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attention_bwd_kernel(int n_head
     const uint16_t* k  = q + d_model;
     const uint16_t* v  = q + 2 * d_model;
     const uint16_t* dO = dctx + (long long)b * S * ld_ctx + h * AT_D;
-    const uint16_t* Pb = P + (long long)blockIdx.x * S * S;
+    const uint16_t* Pb = P + (long long)blockIdx.x * S * ld_p;
     uint16_t*       dq = dqkv + (long long)b * S * ld_dqkv + h * AT_D;
     uint16_t*       dk = dq + d_model;
     uint16_t*       dv = dq + 2 * d_model;
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attention_bwd_kernel(int n_head
         for (int c = 0; c < 2; ++c) {
             const int n8 = 32 * t + 16 * c + 8 * hf;  // 16 bytes = keys n8 .. n8 + 7 of query m
             pw[t][c]     = u32x4a{0u, 0u, 0u, 0u};
-            if (m < S && n8 < S) pw[t][c] = *reinterpret_cast<const u32x4a*>(Pb + (long long)m * S + n8);
+            if (m < S && n8 < S) pw[t][c] = *reinterpret_cast<const u32x4a*>(Pb + (long long)m * ld_p + n8);
         }
     u32x4a ra[4], rb[4];            // the matrix X takes next is requested a phase ahead
     load_rows_x(v, ld, S, ra);
@@ -436,14 +439,15 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attention_bwd_kernel(int n_head
 using namespace mp;
 
 static int attention_check(const char* who, int n_seq, int n_heads, int S, int d_head, const void* qkv, int ld,
-                           const void* p, const void* ctx, int ld_ctx) {
+                           const void* p, int ld_p, const void* ctx, int ld_ctx) {
     MP_REQUIRE(n_seq > 0 && n_heads > 0 && S > 0 && d_head > 0, "%s: bad shape", who);
     MP_REQUIRE(qkv && p && ctx, "%s: NULL argument", who);
-    if (d_head != AT_D || S > AT_S || (S & 7) != 0) {
-        set_error("%s: the fused kernel needs head size %d and seq_len a multiple of 8 up to %d (got %d, %d); "
-                  "use the unfused chain of mp_gemm_* and mp_softmax_* calls instead", who, AT_D, AT_S, d_head, S);
+    if (d_head != AT_D || S > AT_S || (ld_p & 7) != 0) {
+        set_error("%s: the fused kernel needs head size %d, seq_len up to %d and rows of p in multiples of 8 (got %d, %d, %d); "
+                  "use the unfused chain of mp_gemm_* and mp_softmax_* calls instead", who, AT_D, AT_S, d_head, S, ld_p);
         return MP_E_UNSUPPORTED;
     }
+    MP_REQUIRE(ld_p >= S, "%s: ld_p=%d smaller than seq_len", who, ld_p);
     const int d_model = n_heads * d_head;
     MP_REQUIRE(ld >= 3 * d_model && (ld & 7) == 0 && ld_ctx >= d_model && (ld_ctx & 7) == 0,
                "%s: leading dimensions must cover the row and be multiples of 8", who);
@@ -452,20 +456,25 @@ static int attention_check(const char* who, int n_seq, int n_heads, int S, int d
     return MP_OK;
 }
 
-extern "C" int mp_attention_fwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
-                                float alpha, mp_half* p, mp_half* ctx, int ld_ctx, mp_stream stream) {
-    int rc = attention_check("mp_attention_fwd", n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, p, ctx, ld_ctx);
+extern "C" int mp_attention_fwd_ldp(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
+                                    float alpha, mp_half* p, int ld_p, mp_half* ctx, int ld_ctx, mp_stream stream) {
+    int rc = attention_check("mp_attention_fwd", n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, p, ld_p, ctx, ld_ctx);
     if (rc) return rc;
     hipLaunchKernelGGL(attention_fwd_kernel, dim3(n_seq * n_heads), dim3(AT_THREADS), 64 * 256 + 128 * 128, as_stream(stream), n_heads,
-                       seq_len, qkv, ld_qkv, n_heads * d_head, alpha, p, ctx, ld_ctx);
+                       seq_len, qkv, ld_qkv, n_heads * d_head, alpha, p, ld_p, ctx, ld_ctx);
     MP_LAUNCH_CHECK("mp_attention_fwd");
     return MP_OK;
 }
 
-extern "C" int mp_attention_bwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
-                                float alpha, const mp_half* p, const mp_half* dctx, int ld_ctx, mp_half* dqkv,
-                                int ld_dqkv, mp_stream stream) {
-    int rc = attention_check("mp_attention_bwd", n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, p, dctx, ld_ctx);
+extern "C" int mp_attention_fwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
+                                float alpha, mp_half* p, mp_half* ctx, int ld_ctx, mp_stream stream) {
+    return mp_attention_fwd_ldp(n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, alpha, p, seq_len, ctx, ld_ctx, stream);
+}
+
+extern "C" int mp_attention_bwd_ldp(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
+                                    float alpha, const mp_half* p, int ld_p, const mp_half* dctx, int ld_ctx, mp_half* dqkv,
+                                    int ld_dqkv, mp_stream stream) {
+    int rc = attention_check("mp_attention_bwd", n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, p, ld_p, dctx, ld_ctx);
     if (rc) return rc;
     MP_REQUIRE(dqkv && aligned16(dqkv) && ld_dqkv >= 3 * n_heads * d_head && (ld_dqkv & 7) == 0,
                "mp_attention_bwd: bad dqkv / ld_dqkv");
@@ -477,7 +486,13 @@ extern "C" int mp_attention_bwd(int n_seq, int n_heads, int seq_len, int d_head,
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "mp_attention_bwd: hipFuncSetAttribute(LDS size)");
     hipLaunchKernelGGL(attention_bwd_kernel, dim3(n_seq * n_heads), dim3(AT_THREADS), AT_BWD_LDS, as_stream(stream), n_heads,
-                       seq_len, qkv, ld_qkv, n_heads * d_head, alpha, p, dctx, ld_ctx, dqkv, ld_dqkv);
+                       seq_len, qkv, ld_qkv, n_heads * d_head, alpha, p, ld_p, dctx, ld_ctx, dqkv, ld_dqkv);
     MP_LAUNCH_CHECK("mp_attention_bwd");
     return MP_OK;
+}
+
+extern "C" int mp_attention_bwd(int n_seq, int n_heads, int seq_len, int d_head, const mp_half* qkv, int ld_qkv,
+                                float alpha, const mp_half* p, const mp_half* dctx, int ld_ctx, mp_half* dqkv,
+                                int ld_dqkv, mp_stream stream) {
+    return mp_attention_bwd_ldp(n_seq, n_heads, seq_len, d_head, qkv, ld_qkv, alpha, p, seq_len, dctx, ld_ctx, dqkv, ld_dqkv, stream);
 }

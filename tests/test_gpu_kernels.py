@@ -349,6 +349,38 @@ def test_fused_attention_fwd_bwd(B, S, h):
         assert_close16(dqkv_d[:, lo:lo + d_model], dqkv_ref[:, lo:lo + d_model], 1e-3, what=f"fused {name}")
 
 
+@pytest.mark.parametrize("B,S,h,ld_p", [(3, 1, 2, 8), (2, 7, 1, 8), (2, 33, 3, 40), (3, 53, 2, 56), (2, 65, 1, 80), (2, 127, 2, 128),
+                                        (2, 40, 2, 48)])
+def test_fused_attention_rows_of_p_apart(B, S, h, ld_p):
+    """Sequence lengths that are no multiple of 8, and rows of p further apart than needed: both directions against the
+    oracle, zeros up to the next multiple of 8 behind a row of p and nothing written beyond; where the plain call takes the
+    length, the same bits as it."""
+    dk = 64
+    d_model, T, pad = h * dk, B * S, (S + 7) // 8 * 8
+    r = RNG(B * 1000 + S + h)
+    qkv, dctx = S16(r.standard_normal((T, 3 * d_model))), S16(r.standard_normal((T, d_model)))
+    ctx_ref, (q, k, v, p_ref, alpha) = L.attention_fwd(MIXED, qkv, B, S, h)
+    qkv_d, p_d, ctx_d = h16(qkv), torch.full((B, h, S, ld_p), 3.0, dtype=torch.float16, device="cuda"), empty16(T, d_model)
+    mp.mp_attention_fwd_ldp(B, h, S, dk, qkv_d, 3 * d_model, float(alpha), p_d, ld_p, ctx_d, d_model)
+    assert_close16(p_d[..., :S], p_ref, 1e-3, max_ulp=2, what="p")
+    assert torch.all(p_d[..., S:pad] == 0) and torch.all(p_d[..., pad:] == 3.0)
+    assert_close16(ctx_d, ctx_ref, 1e-3, what="ctx")
+    dqkv_ref = L.attention_bwd(MIXED, dctx, (q, k, v, np32(p_d[..., :S]), alpha))
+    dqkv_d = empty16(T, 3 * d_model)
+    mp.mp_attention_bwd_ldp(B, h, S, dk, qkv_d, 3 * d_model, float(alpha), p_d, ld_p, h16(dctx), d_model, dqkv_d, 3 * d_model)
+    for name, lo in (("dq", 0), ("dk", d_model), ("dv", 2 * d_model)):
+        # (one key: its probability is 1, dS and with it dq and dk are zero up to the rounding of dP and its sum)
+        if S > 1 or name == "dv":
+            assert_close16(dqkv_d[:, lo:lo + d_model], dqkv_ref[:, lo:lo + d_model], 1e-3, what=name)
+        else:
+            assert np.array_equal(np32(dqkv_d[:, lo:lo + d_model]), dqkv_ref[:, lo:lo + d_model])
+    if S % 8 == 0:
+        p2, ctx2, dqkv2 = empty16(B, h, S, S), empty16(T, d_model), empty16(T, 3 * d_model)
+        mp.mp_attention_fwd(B, h, S, dk, qkv_d, 3 * d_model, float(alpha), p2, ctx2, d_model)
+        mp.mp_attention_bwd(B, h, S, dk, qkv_d, 3 * d_model, float(alpha), p2, h16(dctx), d_model, dqkv2, 3 * d_model)
+        assert torch.equal(p2, p_d[..., :S]) and torch.equal(ctx2, ctx_d) and torch.equal(dqkv2, dqkv_d)
+
+
 def test_fused_attention_rejects_unsupported_shapes():
     x = empty16(64, 3 * 96)
     with pytest.raises(mp.MPError) as e:
