@@ -34,6 +34,26 @@ def _flat(wl):
     return Mo.flatten_layers(m) if isinstance(m, list) else m
 
 
+@pytest.mark.parametrize("seq_len,n_seq", [(13, 5), (64, 2), (53, 23)])
+def test_grouped_weight_gradients_with_any_token_count(seq_len, n_seq):
+    """The grouped weight-gradient launch contracts over the token count rounded up to 64 (zero rows): the same activations
+    and input gradients as with one product per weight, and weight and bias gradients that differ in fp32 order only; a
+    second iteration on another batch leaves the zero rows zero."""
+    wl = replace(I.C3_SMALL, n_layers=2, d_model=512, n_heads=8, d_ff=2048, seq_len=seq_len, n_seq=n_seq)
+    g, s = St.TransformerStep(wl), St.TransformerStep(wl, grouped_dw=False)
+    assert g.grouped_dw and not s.grouped_dw and g.T_dw == (wl.tokens + 63) // 64 * 64
+    r = np.random.default_rng(seq_len)
+    for _ in range(2):
+        batch = {k: r.standard_normal((wl.tokens, 512)).astype(np.float32) for k in ("x", "target")}
+        for step in (g, s):
+            step.set_batch(batch)
+            step.forward_backward()
+        assert torch.equal(g.act[-1]["y2"], s.act[-1]["y2"]) and torch.equal(g.dx_input, s.dx_input)
+        for k in g.P.names:
+            # (column sums of a bias gradient cancel: their order is worth more than an ulp of the result)
+            assert_close16(g.P.g16[k], np32(s.P.g16[k]), 1e-3, what=k)
+
+
 def _snapshot(step):
     P = step.P
     return dict(w16={k: np32(P.w16[k]) for k in P.names}, w32={k: np32(P.w32[k]) for k in P.names},
