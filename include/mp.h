@@ -413,6 +413,17 @@ int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d /* host */, const mp_half* w, 
                       const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
                       mp_stream stream);
 
+/* The same calls in a chain on one stream, without a launch that empties the workspace ahead of each.  A call given
+ * next_ws (4-byte aligned, next_ws_bytes bytes as for ws, apart from ws) empties it; the next call of the chain may take it
+ * as its ws with ws_is_empty nonzero, if nothing else has written to it in between.  ws_is_empty 0 and next_ws NULL: the
+ * plain calls. */
+int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d /* host */, const float* gx, const mp_half* w, const mp_half* bias,
+                            mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws, size_t ws_bytes,
+                            int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream);
+int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d /* host */, const mp_half* w, const mp_half* gates, const float* c,
+                            const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                            int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream);
+
 /* dst = RNE16(src), n elements (initial fp16 copies of masters and inputs). */
 int mp_cast_f32_to_f16(size_t n, const float* src, mp_half* dst, mp_stream stream);
 /* Fill n 32-bit words (a kernel, safe inside HIP graph capture). */

@@ -60,7 +60,16 @@ struct RlSync {
     int*      status;       // 0 on entry; set nonzero by a wave whose wait ran out
     int       never;        // tests: behave as if part of every slice never arrived
     long long limit_ticks;  // bound of one wait, in ticks of the constant 100 MHz clock
+    u32x4*    next;         // the ring of the launch behind this one, which this one fills with RL_EMPTY ...
+    unsigned  next_pieces;  // ... in 16-byte pieces (0: none)
 };
+// A launch's ring has to be empty before it starts: a fill launch (5 us of a captured chain, of the 46 to 130 us that the
+// recurrent kernels take) unless the launch ahead has done it, one or a few stores per thread that nothing waits for.
+__device__ __forceinline__ void rl_empty_next(const RlSync& s) {
+    for (unsigned i = (blockIdx.y * gridDim.x + blockIdx.x) * RL_THREADS + threadIdx.x; i < s.next_pieces;
+         i += gridDim.x * gridDim.y * RL_THREADS)
+        s.next[i] = u32x4{~0u, ~0u, ~0u, ~0u};
+}
 
 constexpr int RL_DEVICE_SCOPE = 16;  // cache-policy bit (sc1) of the buffer intrinsics: coherent across the device
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rl_ring(char* base, unsigned bytes) {
@@ -157,6 +166,7 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr unsigned slot = rl_fwd_slot(H);
     const __amdgpu_buffer_rsrc_t ring = rl_ring(a.sync.ring + (size_t)blockIdx.y * RL_RING * slot, RL_RING * slot);
     bool dead = false;
+    rl_empty_next(a.sync);
 
     // W_h fragments, resident for the whole sequence: gate g, unit lr, 8 consecutive k
     u32x4 wf[4][nks];
@@ -299,6 +309,7 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr unsigned slot = rl_bwd_slot(H);
     const __amdgpu_buffer_rsrc_t ring = rl_ring(a.sync.ring + (size_t)blockIdx.y * RL_RING * slot, RL_RING * slot);
     bool dead = false;
+    rl_empty_next(a.sync);
 
     // W_h^T fragments: unit lr, 8 consecutive gate rows n = wave H + 32 ks + 8 lq ...: W[n][I + j0 + lr].  Read as row
     // pieces of 8 units, turned by the transposing LDS read (see gemm_dtl.hpp for its lane mapping): 32 rows at a time
@@ -459,18 +470,30 @@ extern "C" size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d
     return d && d->B > 0 && d->H > 0 && d->H % 64 == 0 && d->H <= RL_MAX_H ? rl_rings(d->B, d->H) : 0;
 }
 
-static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, mp_stream stream,
-                   const char* who, RlSync* out) {
+static uintptr_t align_up16(const void* p) { return (reinterpret_cast<uintptr_t>(p) + 15) & ~(uintptr_t)15; }
+
+static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, int ws_is_empty,
+                   void* next_ws, size_t next_ws_bytes, mp_stream stream, const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
     const size_t need = d->step_rows > 0 ? rl_rings(d->B, d->H) : mp_lstm_layer_workspace_bytes();
     if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 3u)) {
         set_error("%s: 4-byte aligned workspace of %zu bytes needed, %zu given", who, need, ws_bytes);
         return MP_E_WORKSPACE;
     }
-    char* const  ring = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 15) & ~(uintptr_t)15);
+    if (next_ws != nullptr) {
+        const char *a = static_cast<const char*>(ws), *b = static_cast<const char*>(next_ws);
+        MP_REQUIRE((reinterpret_cast<uintptr_t>(next_ws) & 3u) == 0 && next_ws_bytes >= 16 && next_ws_bytes < (1ull << 32) &&
+                       (b + next_ws_bytes <= a || a + ws_bytes <= b),
+                   "%s: next_ws has to be a 4-byte aligned workspace apart from ws", who);
+        out->next        = reinterpret_cast<u32x4*>(align_up16(next_ws));
+        out->next_pieces = (unsigned)((next_ws_bytes - (align_up16(next_ws) - reinterpret_cast<uintptr_t>(next_ws))) / 16);
+    }
+    char* const  ring = reinterpret_cast<char*>(align_up16(ws));
     const size_t used = (size_t)((d->B + RL_ROWS - 1) / RL_ROWS) * RL_RING * slot;
-    const int    rc   = mp_fill_u32(used / 4, ~0u, ring, stream);  // everything starts empty (a kernel: capturable)
-    if (rc != MP_OK) return rc;
+    if (!ws_is_empty) {
+        const int rc = mp_fill_u32(used / 4, ~0u, ring, stream);  // everything starts empty (a kernel: capturable)
+        if (rc != MP_OK) return rc;
+    }
     out->ring        = ring;
     out->status      = status;
     out->never       = d->debug_extra_participants > 0;
@@ -481,6 +504,13 @@ static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, 
 extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
                                  mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
                                  size_t ws_bytes, mp_stream stream) {
+    return mp_lstm_layer_fwd_chain(d, gx, w, bias, gates, c, xh, h_up, status, ws, ws_bytes, 0, nullptr, 0, stream);
+}
+
+extern "C" int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
+                                       mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
+                                       size_t ws_bytes, int ws_is_empty, void* next_ws, size_t next_ws_bytes,
+                                       mp_stream stream) {
     int nwg = 0;
     int rc  = rl_check(d, "mp_lstm_layer_fwd", &nwg);
     if (rc) return rc;
@@ -489,7 +519,7 @@ extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, c
     MP_REQUIRE(aligned16(w) && aligned16(xh) && aligned16(gx) && aligned16(gates) && aligned16(c) && (h_up == nullptr || aligned16(h_up)),
                "mp_lstm_layer_fwd: pointers must be 16-byte aligned");
     LstmFwdArgs a{};
-    rc = rl_sync(d, rl_fwd_slot(d->H), status, ws, ws_bytes, stream, "mp_lstm_layer_fwd", &a.sync);
+    rc = rl_sync(d, rl_fwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, stream, "mp_lstm_layer_fwd", &a.sync);
     if (rc) return rc;
     a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.gx = gx; a.w = w; a.ldw = d->ldw; a.bias = bias; a.gates = gates; a.c = c; a.xh = xh; a.ldxh = d->ldxh;
@@ -504,6 +534,12 @@ extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, c
 extern "C" int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
                                  const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
                                  mp_stream stream) {
+    return mp_lstm_layer_bwd_chain(d, w, gates, c, dh_above, dgates, status, ws, ws_bytes, 0, nullptr, 0, stream);
+}
+
+extern "C" int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
+                                       const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                                       int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream) {
     int nwg = 0;
     int rc  = rl_check(d, "mp_lstm_layer_bwd", &nwg);
     if (rc) return rc;
@@ -512,7 +548,7 @@ extern "C" int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d, const mp_half* w, 
     MP_REQUIRE(aligned16(w) && aligned16(gates) && aligned16(c) && aligned16(dh_above) && aligned16(dgates),
                "mp_lstm_layer_bwd: pointers must be 16-byte aligned");
     LstmBwdArgs a{};
-    rc = rl_sync(d, rl_bwd_slot(d->H), status, ws, ws_bytes, stream, "mp_lstm_layer_bwd", &a.sync);
+    rc = rl_sync(d, rl_bwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, stream, "mp_lstm_layer_bwd", &a.sync);
     if (rc) return rc;
     a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.w = w; a.ldw = d->ldw; a.gates = gates; a.c = c; a.dh_above = dh_above; a.ld_above = d->ld_up; a.dgates = dgates;

@@ -411,8 +411,9 @@ class LSTMStep(_StepBase):
             self.dx = [z16(T * Bt, max(self.in_dims)) for _ in range(2)]     # input gradient of a layer, all steps
             self.rl_status = torch.zeros(1, dtype=torch.int32, device="cuda")
             rows = self.row_blocks[0][1]
-            self.rl_ws = torch.zeros(B.mp_lstm_layer_desc_workspace_bytes(B.lstm_layer_desc(T, rows, 0, H, H, H, H, step_rows=Bt)) // 4,
-                                     dtype=torch.int32, device="cuda")
+            # two workspaces: every recurrent call of an iteration empties the one that the next call uses
+            words = B.mp_lstm_layer_desc_workspace_bytes(B.lstm_layer_desc(T, rows, 0, H, H, H, H, step_rows=Bt)) // 4
+            self.rl_ws = [torch.zeros(words, dtype=torch.int32, device="cuda") for _ in range(2)]
             # x W_x^T and dgates W_x: the input columns [0, I) of W[4H, I+H], all T*B rows at once
             self.d_in_all = [B.gemm_desc(T * Bt, 4 * H, self.in_dims[l], ldx=self.in_dims[l] + H, ldw=self.in_dims[l] + H)
                              for l in range(NL)]
@@ -448,14 +449,17 @@ class LSTMStep(_StepBase):
     def _forward_backward_persistent(self):
         wl, w, g = self.wl, self.P.w16, self.P.g16
         T, Bt, H, NL = wl.seq_len, wl.batch_size, wl.hidden, wl.n_layers
+        ws, ws_next, ready = *self.rl_ws, False          # (nothing is taken over from an earlier iteration)
         for l in range(NL):
             B.mp_gemm_fwd(self.d_in_all[l], self.xh[l], w[f"l{l}.w"], None, None, None, self.gx)
             for d, gx, gates, c, xh, up in self.rl_fwd[l]:
-                B.mp_lstm_layer_fwd(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, self.rl_ws)
+                B.mp_lstm_layer_fwd_chain(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, ws, ready, ws_next)
+                ws, ws_next, ready = ws_next, ws, True
         B.mp_mse_scaled(T * Bt, H, self.y, self.target, H, self.st, self.loss, self.dy, self.ws)
         for l in range(NL - 1, -1, -1):
             for d, gates, c, above, dgates in self.rl_bwd[l]:
-                B.mp_lstm_layer_bwd(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, self.rl_ws)
+                B.mp_lstm_layer_bwd_chain(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, ws, ready, ws_next)
+                ws, ws_next = ws_next, ws
             B.mp_gemm_bwd_both(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2], self.d_gate_all[l], self.xh[l],
                                g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)
         self.dx_input = self.dx[0].view(-1)[:T * Bt * self.in_dims[0]].view(T * Bt, self.in_dims[0])

@@ -953,6 +953,49 @@ def test_lstm_persistent_layer_workspace_at_any_word():
     assert torch.equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("T,Bn,H", [(9, 32, 1024), (2, 3, 64), (5, 65, 192), (1, 8, 128)])
+def test_lstm_persistent_layer_chain(T, Bn, H):
+    """Calls that empty the next call's workspace: forward and backward calls in a chain of two workspaces that start full of
+    other values, the same bits as the plain calls, twice; a workspace that overlaps the call's own is refused."""
+    I = 8
+    r = RNG(T + Bn + H)
+    ld = I + H
+    w, bias, gx = h16(r.uniform(-0.1, 0.1, (4 * H, ld))), h16(np.zeros(4 * H)), f32(r.standard_normal((T * Bn, 4 * H)))
+    dh = h16(r.standard_normal((T, Bn, H)))
+    d = mp.lstm_layer_desc(T, Bn, I, H, ld, ld, H, step_rows=Bn)
+    words = mp.mp_lstm_layer_desc_workspace_bytes(d) // 4
+    # (in one buffer, at 4-byte boundaries that are no 16-byte boundaries, with guard words around them)
+    buf = torch.full((2 * words + 3,), 0x3C003C00, dtype=torch.int32, device="cuda")
+    two = [buf[1:1 + words], buf[2 + words:2 + 2 * words]]
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def run(chain):
+        out = []
+        a, b, ready = two[0], two[1], False
+        for _ in range(2):
+            gates, c = empty16(T, Bn, 4 * H), torch.zeros(T + 1, Bn, H, device="cuda")
+            xh, up, dgates = torch.zeros(T, Bn, ld, dtype=torch.float16, device="cuda"), empty16(T, Bn, H), empty16(T, Bn, 4 * H)
+            if chain:
+                mp.mp_lstm_layer_fwd_chain(d, gx, w, bias, gates, c, xh, up, status, a, ready, b)
+                mp.mp_lstm_layer_bwd_chain(d, w, gates, c, dh, dgates, status, b, True, a)
+                ready = True
+            else:
+                mp.mp_lstm_layer_fwd(d, gx, w, bias, gates, c, xh, up, status, a)
+                mp.mp_lstm_layer_bwd(d, w, gates, c, dh, dgates, status, a)
+            out += [gates, c, xh, up, dgates]
+        return out
+
+    plain = run(False)
+    buf.fill_(0x3C003C00)
+    for got, ref in zip(run(True), plain):
+        assert torch.equal(got, ref)
+    assert int(status.item()) == 0
+    assert all(int(buf[k]) == 0x3C003C00 for k in (0, 1 + words, 2 + 2 * words))
+    with pytest.raises(mp.MPError) as e:
+        mp.mp_lstm_layer_bwd_chain(d, w, plain[0], plain[1], dh, plain[4], status, two[0], False, buf[words // 2:words // 2 + words])
+    assert e.value.code == ML.MP_E_INVAL
+
+
 def test_lstm_persistent_layer_timeout_path_and_rejections():
     """The step barrier's wait is bounded: asked to wait for a flag nobody raises (debug_extra_participants) with a
     2 ms limit, every workgroup gives up, the kernels end normally and *status reports it; a poisoned status makes the
