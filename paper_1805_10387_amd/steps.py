@@ -443,7 +443,7 @@ class LSTMStep(_StepBase):
             self._forward_backward_stepwise()
 
     def recurrent_kernels_ok(self) -> bool:
-        """False if a step barrier of a persistent kernel ever ran out of time (synchronises; tests and logging)."""
+        """False if a wait of a persistent kernel ever ran out of time (synchronises; tests and logging)."""
         return (not self.persistent) or int(self.rl_status.item()) == 0
 
     def _forward_backward_persistent(self):
