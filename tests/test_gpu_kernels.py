@@ -605,6 +605,18 @@ def test_mse_scaled(rows, cols):
     assert_close16(dy, dy_ref, 1e-3, max_ulp=1, what="mse dy")
 
 
+@pytest.mark.parametrize("rows", [1, 255, 257, 4095, 4096, 4097, 8449])   # the finish kernel takes 16 x 256 at a time
+def test_softmax_xent_mean_over_any_number_of_rows(rows):
+    r = RNG(rows)
+    z, t = S16(r.standard_normal((rows, 8)) * 3), r.integers(0, 8, rows)
+    z64 = z.astype(np.float64)
+    ref = np.mean(np.log(np.exp(z64).sum(1)) - z64[np.arange(rows), t])
+    loss, zd = empty32(1), h16(z)
+    mp.mp_softmax_xent_scaled(rows, 8, zd, 8, i32(t.astype(np.int32)), make_state(scale=1.0), loss, zd, ws_bytes(mp.mp_loss_workspace_bytes(rows, 8)))
+    # row losses: about 8 roundings of values up to 16; their sum, all terms >= 0: one rounding per addition of a chain
+    assert abs(float(loss) - ref) <= 8 * 16 * 2.0 ** -24 + (rows / 256 + 10) * 2.0 ** -24 * ref
+
+
 @pytest.mark.parametrize("rows,vocab", [(16, 32768), (33, 3000), (7, 1001), (5, 40000),
                                         (600, 32768), (300, 24584)])  # the last two: several rows per persistent workgroup
 def test_softmax_xent_scaled(rows, vocab):
