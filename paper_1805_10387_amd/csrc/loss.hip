@@ -188,7 +188,7 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
             if (v < nvec) {
                 float p[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) p[k] = RAGGED && !valid ? 0.f : e[i][k] * inv;
+                for (int k = 0; k < 8; ++k) p[k] = valid ? e[i][k] * inv : 0.f;  // (the row may hold infinities: 0 x NaN)
                 if (v == vt) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k)

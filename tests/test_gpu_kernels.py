@@ -704,6 +704,31 @@ def test_softmax_xent_rows_at_any_alignment(rows, vocab):
     assert_close16(db, MIXED.store(np32(gd[:, :vocab]).sum(0, dtype=np.float32)), 1e-3, max_ulp=1, what="bias gradient")
 
 
+@pytest.mark.parametrize("vocab", [8, 3000, 8200, 16384, 24584, 32768, 32776, 1001])   # each workgroup size, the fused sums, the generic kernel
+def test_softmax_xent_rows_without_a_target_have_zero_gradient_whatever_they_hold(vocab):
+    """Rows whose target lies outside the vocabulary, holding an infinity, a NaN, only infinities: zero gradient and no loss,
+    as for finite rows, in rows of 16-byte pieces too; the bias gradient stays finite and no overflow is flagged."""
+    rows, S = 6, 2.0 ** 10
+    r = RNG(vocab)
+    z, t = S16(r.standard_normal((rows, vocab)) * 3), r.integers(0, vocab, rows).astype(np.int32)
+    t[1], t[2], t[3] = vocab, -1, vocab + 7
+    clean = z.copy()
+    clean[1:4] = 0.0
+    z[1, 0], z[2, vocab - 1], z[3] = np.inf, np.nan, -np.inf
+    loss_ref, g_ref = L.softmax_xent_scaled(MIXED, clean, t, S)
+    st, loss, db = make_state(scale=S), empty32(1), empty16(vocab)
+    g1, g2 = empty16(rows, vocab), empty16(rows, vocab)
+    mp.mp_softmax_xent_scaled(rows, vocab, h16(z), vocab, i32(t), st, loss, g1, ws_bytes(mp.mp_loss_workspace_bytes(rows, vocab)))
+    assert abs(float(loss) - float(loss_ref)) <= 2e-6 * abs(float(loss_ref)) + 1e-6
+    mp.mp_softmax_xent_scaled_db(rows, vocab, h16(z), vocab, i32(t), st, loss, g2, db, ws_bytes(mp.mp_softmax_xent_db_workspace_bytes(rows, vocab)))
+    assert abs(float(loss) - float(loss_ref)) <= 2e-6 * abs(float(loss_ref)) + 1e-6
+    for g in (g1, g2):
+        assert torch.all(g[1:4] == 0)
+        assert_close16(g, g_ref, 1e-3, max_ulp=2, what="gradient")
+    assert_close16(db, MIXED.store(np32(g2).sum(0, dtype=np.float32)), 1e-3, max_ulp=1, what="bias gradient")
+    assert mp.scale_state_read(st).found_inf == 0
+
+
 @pytest.mark.parametrize("rows,cols", [(1, 1), (65, 7), (64, 63), (200, 65), (1021, 1001), (3, 8)])
 def test_colsum_rows_at_any_alignment(rows, cols):
     """Column counts around the 8-column pieces and 64-column workgroups, rows that start at odd elements."""
