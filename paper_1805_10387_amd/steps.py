@@ -365,6 +365,19 @@ class XentStep(_StepBase):
 
 
 # ====================================================================================== config 5
+def lstm_row_blocks(batch: int, hidden: int, cus: int) -> List[tuple]:
+    """(first row, rows) of the launches that the persistent recurrent kernels of an LSTMStep take a batch in, or [] where
+    a launch has no room.
+
+    All workgroups of a launch (16 units x 8 rows each) wait for each other and have to be resident together, two to a
+    compute unit.  A launch takes no more than half of the chip, so that two models (on two streams, or in two processes)
+    never leave each other half resident."""
+    block = 8 * (cus // max(hidden // 16, 1))
+    if block <= 0:
+        return []
+    return [(r, min(block, batch - r)) for r in range(0, batch, block)]
+
+
 class LSTMStep(_StepBase):
     """Stacked LSTM unrolled over time with an MSE loss on the top layer's outputs (config 5).
 
@@ -375,7 +388,13 @@ class LSTMStep(_StepBase):
       on chip (mp_lstm_layer_fwd); backward likewise one recurrent kernel per layer (mp_lstm_layer_bwd) followed by
       the large input-gradient and weight-gradient products over all T*B rows.
     step by step: per time step one gate product with W[4H, I+H] (mp_gemm_fwd_ws) and one cell kernel; the cell
-      kernel writes h_t both into xh[l][t+1] (recurrence) and into the next layer's xh[l+1][t] (or the output)."""
+      kernel writes h_t both into xh[l][t+1] (recurrence) and into the next layer's xh[l+1][t] (or the output).
+
+    A persistent launch may take half of the GPU's workgroup slots until it is done, so at most two models whose iterations
+    may overlap (other streams, other processes on the GPU) run this plan safely; more of them need persistent=False.  Where
+    that is not kept, a wait ends after 2 s.  What had not arrived by then reads as NaN: the iteration's gradients are
+    flagged and its update is skipped, as those of later iterations are until rl_status, which recurrent_kernels_ok()
+    looks at, is cleared."""
 
     def __init__(self, wl, masters=None, persistent=True, **kw):
         if masters is None:
@@ -386,11 +405,9 @@ class LSTMStep(_StepBase):
         z16 = lambda *s: torch.zeros(s, dtype=torch.float16, device="cuda")
         z32 = lambda *s: torch.zeros(s, dtype=torch.float32, device="cuda")
         self.in_dims = [wl.d_in if l == 0 else H for l in range(NL)]
-        # batch rows one launch of the recurrent kernels takes: all its workgroups (16 units x 8 rows each) run at once,
-        # two to a compute unit; a larger batch takes several launches
-        block = 8 * (2 * torch.cuda.get_device_properties(0).multi_processor_count // max(H // 16, 1))
-        self.persistent = persistent and H % 64 == 0 and H <= 1024 and all(i % 8 == 0 for i in self.in_dims) and block > 0
-        self.row_blocks = [(r, min(block, Bt - r)) for r in range(0, Bt, block)] if self.persistent else []
+        blocks = lstm_row_blocks(Bt, H, torch.cuda.get_device_properties(0).multi_processor_count)
+        self.persistent = persistent and H % 64 == 0 and H <= 1024 and all(i % 8 == 0 for i in self.in_dims) and bool(blocks)
+        self.row_blocks = blocks if self.persistent else []
         self.xh = [z16(T, Bt, self.in_dims[l] + H) for l in range(NL)]      # h_0 = 0 stays in xh[l][0][:, I:]
         self.gates = [z16(T, Bt, 4 * H) for _ in range(NL)]
         self.c = [z32(T + 1, Bt, H) for _ in range(NL)]                      # c_0 = 0

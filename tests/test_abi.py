@@ -115,6 +115,21 @@ def test_workspace_queries_are_consistent():
     assert lib.mp_layernorm_bwd_workspace_bytes(8192, 1024) % (2 * 1024 * 4) == 0
 
 
+@pytest.mark.parametrize("cus", [256, 128, 32])
+def test_recurrent_launches_leave_half_of_the_gpu(cus):
+    """The blocks of batch rows that LSTMStep takes: in order, whole, each launch with at most one of the two workgroups
+    per compute unit (16 units x 8 rows a workgroup)."""
+    from paper_1805_10387_amd.steps import lstm_row_blocks
+    for hidden in range(64, 1025, 64):
+        for batch in (1, 7, 8, 32, 33, 40, 64, 65, 100, 128, 200, 256, 500, 1024, 4096):
+            blocks = lstm_row_blocks(batch, hidden, cus)
+            assert blocks or hidden // 16 > cus
+            if blocks:
+                assert [r for r, _ in blocks] == [sum(n for _, n in blocks[:k]) for k in range(len(blocks))]
+                assert sum(n for _, n in blocks) == batch and all(n >= 1 for _, n in blocks)
+                assert all(hidden // 16 * ((n + 7) // 8) <= cus and (r % 8 == 0) for r, n in blocks)
+
+
 def test_product_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_1805_10387_amd")
     for fn in os.listdir(pkg):

@@ -530,6 +530,63 @@ def test_config5_reduced_size(persistent):
     assert step.recurrent_kernels_ok() and step2.recurrent_kernels_ok()
 
 
+def test_two_lstm_models_on_two_streams():
+    """Two models whose recurrent launches each take all the workgroup slots a launch may have run at the same time: no wait
+    runs out and both give the bits of a model that runs alone."""
+    wl = replace(I.C5_SMALL, n_layers=1, hidden=1024, d_in=64, batch_size=64, seq_len=12)
+    batch = wl.batch()
+    models = [St.LSTMStep(wl) for _ in range(3)]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert all(m.persistent and len(m.row_blocks) == 2 and 1024 // 16 * (m.row_blocks[0][1] // 8) <= cus for m in models)
+    for m in models:
+        m.set_batch(batch)
+        m.step()
+    graphs = [_graph_step(m) for m in models]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(6):
+        graphs[2].replay()
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for g, s in zip(graphs, streams):
+            with torch.cuda.stream(s):
+                g.replay()
+    torch.cuda.synchronize()
+    assert all(m.recurrent_kernels_ok() and m.state().skipped_steps == 0 for m in models)
+    for m in models[:2]:
+        assert torch.equal(m.P.w32_arena, models[2].P.w32_arena) and torch.equal(m.y, models[2].y)
+
+
+def test_lstm_step_without_waits_changes_no_weight():
+    """With the status word set the recurrent kernels stop waiting, as after a wait that ran out: what had not arrived reads
+    as NaN, so the iteration either has the right bits (everything had arrived) or is flagged and skipped; with the word
+    cleared the next one is right again."""
+    wl = replace(I.C5_SMALL, n_layers=2, hidden=512, d_in=64, batch_size=20, seq_len=12)
+    batch = wl.batch()
+    a, b = St.LSTMStep(wl), St.LSTMStep(wl)
+    for m in (a, b):
+        assert m.persistent
+        m.set_batch(batch)
+    before = [t.clone() for t in (a.P.w32_arena, a.P.w16_arena, a.P.m_arena, a.P.v_arena)]
+    a.rl_status.fill_(1)
+    a.step()
+    b.step()
+    torch.cuda.synchronize()
+    assert not a.recurrent_kernels_ok() and b.recurrent_kernels_ok()
+    if a.state().skipped_steps:
+        assert all(torch.equal(x, y) for x, y in zip(before, (a.P.w32_arena, a.P.w16_arena, a.P.m_arena, a.P.v_arena)))
+        a.rl_status.zero_()
+        c = St.LSTMStep(wl)                       # the skipped iteration halved the scale: so does this one, by hand
+        c.set_batch(batch)
+        c.st.copy_(a.st)
+        for m in (a, c):
+            m.step()
+        assert a.recurrent_kernels_ok() and a.state().skipped_steps == 1
+        assert torch.equal(a.P.w32_arena, c.P.w32_arena) and torch.equal(a.y, c.y)
+    else:
+        assert torch.equal(a.P.w32_arena, b.P.w32_arena)
+
+
 # ------------------------------------------------------------------ full sizes, in the configuration bench.py times
 def test_config3_full_size_bench_configuration():
     """Config 3 at full size exactly as bench.py launches it (producer-side overflow inspection, one flat update
