@@ -367,13 +367,16 @@ class XentStep(_StepBase):
 # ====================================================================================== config 5
 def lstm_row_blocks(batch: int, hidden: int, cus: int) -> List[tuple]:
     """(first row, rows) of the launches that the persistent recurrent kernels of an LSTMStep take a batch in, or [] where
-    a launch has no room.
+    the step-by-step plan is the faster one.
 
     All workgroups of a launch (16 units x 8 rows each) wait for each other and have to be resident together, two to a
     compute unit.  A launch takes no more than half of the chip, so that two models (on two streams, or in two processes)
-    never leave each other half resident."""
+    never leave each other half resident.  Launches follow one another, so their number bounds the gain: us per iteration
+    of two layers x 10 steps, persistent / step by step, 512 units: 256 rows (4 launches) 527 / 561, 512 rows (8) 935 / 690;
+    1024 units: 64 rows (2) 467 / 640, 128 rows (4) 741 / 784, 256 rows (8) 1295 / 918; 256 units, whose step-by-step
+    products have less to do: 256 rows (2) 267 / 348, 512 rows (4) 442 / 384."""
     block = 8 * (cus // max(hidden // 16, 1))
-    if block <= 0:
+    if block <= 0 or -(-batch // block) > (4 if hidden >= 512 else 2):
         return []
     return [(r, min(block, batch - r)) for r in range(0, batch, block)]
 

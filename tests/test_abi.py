@@ -118,16 +118,20 @@ def test_workspace_queries_are_consistent():
 @pytest.mark.parametrize("cus", [256, 128, 32])
 def test_recurrent_launches_leave_half_of_the_gpu(cus):
     """The blocks of batch rows that LSTMStep takes: in order, whole, each launch with at most one of the two workgroups
-    per compute unit (16 units x 8 rows a workgroup)."""
+    per compute unit (16 units x 8 rows a workgroup), never many launches in a row; a batch of 32 always is persistent
+    on the full chip."""
     from paper_1805_10387_amd.steps import lstm_row_blocks
     for hidden in range(64, 1025, 64):
         for batch in (1, 7, 8, 32, 33, 40, 64, 65, 100, 128, 200, 256, 500, 1024, 4096):
             blocks = lstm_row_blocks(batch, hidden, cus)
-            assert blocks or hidden // 16 > cus
+            assert len(blocks) <= 4 and (blocks or batch > 32 or cus < 256)
             if blocks:
                 assert [r for r, _ in blocks] == [sum(n for _, n in blocks[:k]) for k in range(len(blocks))]
                 assert sum(n for _, n in blocks) == batch and all(n >= 1 for _, n in blocks)
                 assert all(hidden // 16 * ((n + 7) // 8) <= cus and (r % 8 == 0) for r, n in blocks)
+    # step by step is the faster plan beyond these
+    assert lstm_row_blocks(128, 1024, 256) and not lstm_row_blocks(129, 1024, 256)
+    assert lstm_row_blocks(256, 256, 256) and not lstm_row_blocks(257, 256, 256)
 
 
 def test_product_never_imports_the_oracle():
