@@ -482,7 +482,10 @@ class LSTMStep(_StepBase):
                 ws, ws_next = ws_next, ws
             B.mp_gemm_bwd_both(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2], self.d_gate_all[l], self.xh[l],
                                g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)
-        self.dx_input = self.dx[0].view(-1)[:T * Bt * self.in_dims[0]].view(T * Bt, self.in_dims[0])
+        # gradient of the input: rows of all steps, and with time as a dimension of its own (where the step-by-step plan has
+        # [T, batch, I + H]) for the sizes that plan was once the only one for
+        lead = (T * Bt,) if Bt <= 32 and H % 128 == 0 else (T, Bt)
+        self.dx_input = self.dx[0].view(-1)[:T * Bt * self.in_dims[0]].view(*lead, self.in_dims[0])
 
     def _forward_backward_stepwise(self):
         wl, w, g = self.wl, self.P.w16, self.P.g16

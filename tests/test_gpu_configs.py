@@ -530,6 +530,25 @@ def test_config5_reduced_size(persistent):
     assert step.recurrent_kernels_ok() and step2.recurrent_kernels_ok()
 
 
+@pytest.mark.parametrize("hidden,batch", [(64, 5), (192, 8), (128, 40), (128, 32)])
+def test_lstm_input_gradient_is_indexed_alike_in_both_plans(hidden, batch):
+    """Batches above 32 and widths off 128: dx_input[:, :, :I] in both plans; the others keep their rows of all steps."""
+    wl = replace(I.C5_SMALL, hidden=hidden, batch_size=batch)
+    a, b = St.LSTMStep(wl), St.LSTMStep(wl, persistent=False)
+    for m in (a, b):
+        m.set_batch(wl.batch())
+        m.forward_backward()
+    assert a.persistent and a.recurrent_kernels_ok()
+    ref = np32(b.dx_input[:, :, :wl.d_in])
+    if (hidden, batch) == (128, 32):
+        assert a.dx_input.shape == (wl.seq_len * batch, wl.d_in)
+        got = a.dx_input.view(wl.seq_len, batch, wl.d_in)
+    else:
+        got = a.dx_input[:, :, :wl.d_in]
+    assert got.shape == ref.shape
+    assert rel_fro(np32(got), ref) <= 2e-3                 # (two plans, two fp32 orders, through two recurrent layers)
+
+
 def test_two_lstm_models_on_two_streams():
     """Two models whose recurrent launches each take all the workgroup slots a launch may have run at the same time: no wait
     runs out and both give the bits of a model that runs alone."""
