@@ -440,7 +440,9 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 // of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
-    if (g_force_tile >= 0 || !plain(dx) || !plain(dw)) return false;
+    if (g_force_tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;
+    // (as matrix_path_ok, for both: stored rows of at least 8 elements, offsets inside a tile within the buffer size)
+    if (dx->N < 8 || dx->K < 8 || dw->K < 8 || std::max(std::max(dx->ldy, dx->ldw), dw->ldx) >= LD_BUFFER_64) return false;
     return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M) &&
            small_tiles(dx->M, dx->K) + small_tiles(dw->N, dw->K) + (dw->N + SM_STRIP - 1) / SM_STRIP <= 3 * kCUs;
 }
@@ -469,15 +471,13 @@ extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, con
         w.A = dY; w.B = X; w.C = dW; w.found_inf = st ? &st->found_inf : nullptr;
         w.M = d_dw->N; w.N = d_dw->K; w.K = d_dw->M;
         w.lda = d_dw->ldy; w.ldb = d_dw->ldx; w.ldc = d_dw->ldw; w.alpha = d_dw->alpha; w.batch_inner = 1;
-        if (std::max(std::max(x.lda, x.ldb), w.ldb) < LD_BUFFER_64 && matrix_path_ok(x, true, false) && matrix_path_ok(w, false, false)) {
-            for (GemmArgs* g : {&x, &w}) {
-                g->tiles_m = (g->M + 31) / 32;
-                g->tiles_n = (g->N + 31) / 32;
-            }
-            b.dY = dY; b.db = db; b.rows = d_dw->M; b.cols = d_dw->N; b.ld = d_dw->ldy;
-            return launch_small_both(small_waves((long long)x.tiles_m * x.tiles_n + (long long)w.tiles_m * w.tiles_n, std::max(x.K, w.K)), b,
-                                     as_stream(stream));
+        for (GemmArgs* g : {&x, &w}) {
+            g->tiles_m = (g->M + 31) / 32;
+            g->tiles_n = (g->N + 31) / 32;
         }
+        b.dY = dY; b.db = db; b.rows = d_dw->M; b.cols = d_dw->N; b.ld = d_dw->ldy;
+        return launch_small_both(small_waves((long long)x.tiles_m * x.tiles_n + (long long)w.tiles_m * w.tiles_n, std::max(x.K, w.K)), b,
+                                 as_stream(stream));
     }
     rc = mp_gemm_bwd_dw(d_dw, dY, X, dW, db, st, ws, ws_bytes, stream);
     if (rc) return rc;

@@ -115,6 +115,32 @@ def test_workspace_queries_are_consistent():
     assert lib.mp_layernorm_bwd_workspace_bytes(8192, 1024) % (2 * 1024 * 4) == 0
 
 
+def test_joint_gradients_query_says_what_the_call_does():
+    """mp_gemm_bwd_both_joint is 1 only where mp_gemm_bwd_both is one launch: a pair it names needs no workspace, and any
+    other pair is refused without one before anything is launched."""
+    from paper_1805_10387_amd import _lib
+    lib = _lib.load()
+
+    def desc(M, N, K, ldx=None, ldw=None, ldy=None, trans_w=0):
+        d = _lib.GemmDesc()
+        d.M, d.N, d.K, d.ldx, d.ldw, d.ldy = M, N, K, ldx or K, ldw or (N if trans_w else K), ldy or N
+        d.batch_outer = d.batch_inner = 1
+        d.trans_w, d.alpha = trans_w, 1.0
+        return d
+
+    joint = lambda x, w: lib.mp_gemm_bwd_both_joint(C.byref(x), C.byref(w))  # noqa: E731
+    call = lambda x, w: lib.mp_gemm_bwd_both(C.byref(x), 256, 256, None, None, 0, 256, C.byref(w), 256, 256, None, None, None, 0, None)  # noqa: E731
+    ok = desc(64, 256, 128)
+    assert joint(ok, ok) == 1 and joint(desc(8, 8, 8), desc(8, 8, 8)) == 1 and joint(desc(100, 64, 40, ldw=104), desc(100, 64, 104)) == 1
+    # rows of fewer than 8 elements, rows too far apart, a stored [K, N] weight, products that are not small
+    for d in (desc(64, 256, 7), desc(64, 7, 256), desc(64, 4, 4), desc(64, 256, 128, ldx=1 << 24), desc(64, 256, 128, ldw=1 << 24),
+              desc(64, 256, 128, ldy=1 << 24), desc(64, 256, 128, trans_w=1), desc(8192, 1024, 1024)):
+        assert joint(d, d) == 0 and call(d, d) == _lib.MP_E_WORKSPACE
+    assert joint(ok, desc(64, 256, 7)) == 0 and joint(desc(64, 256, 7), ok) == 0
+    for w in (desc(65, 256, 128), desc(64, 248, 128, ldy=256), desc(64, 256, 128, ldy=264)):    # another dY: no pair
+        assert joint(ok, w) == 0 and call(ok, w) == _lib.MP_E_INVAL
+
+
 @pytest.mark.parametrize("cus", [256, 128, 32])
 def test_recurrent_launches_leave_half_of_the_gpu(cus):
     """The blocks of batch rows that LSTMStep takes: in order, whole, each launch with at most one of the two workgroups
