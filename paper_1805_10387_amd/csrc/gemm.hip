@@ -104,8 +104,10 @@ constexpr int   kCUs      = 256;
 
 // Products for the small kernel: up to two workgroups per compute unit, and not so long a contraction that reading the
 // operand panels anew for every 32 x 32 tile outweighs the short chain.  us alone, larger tiles against this kernel:
-// 64 x 1024 over 256 4.1 / 3.0, 64 x 256 over 1024 6.7 / 4.4, 520 x 256 over 3000 16.3 / 8.3, 1024 x 161 over 1500 15.2 / 7.9;
-// beyond the line 512 x 512 over 4096 13.0 / 16.8, 1024 x 1024 over 1024 7.3 / 10.0.
+// 64 x 1024 over 256 4.1 / 3.0, 64 x 256 over 1024 6.7 / 4.4, 520 x 256 over 3000 16.3 / 8.3, 1024 x 161 over 1500 15.2 / 7.9.
+// At the line, forward, input gradient, weight gradient: 512 x 512 over 3072 14.9 / 8.9, 16.6 / 10.7, 12.1 / 11.9;
+// 256 x 2048 over 1536 9.7 / 8.7, 10.5 / 10.1, 12.1 / 11.3; the least gain of 288 sizes inside it: 1024 x 512 over 1024 7.7 / 7.0,
+// 8.3 / 8.6, 10.9 / 9.5.  Beyond it 512 x 512 over 4096 13.0 / 16.8, 1024 x 1024 over 1024 7.3 / 10.0.
 static long long small_tiles(int M, int N) { return ((M + 31) / 32) * (long long)((N + 31) / 32); }
 static bool      small_wins(int M, int N, int K) {
     const long long t = small_tiles(M, N);
