@@ -65,7 +65,10 @@ enum {
 };
 
 const char* mp_last_error(void);
-int         mp_version(void);
+/* Version of this interface; mp_version() is that of the library.  2: the last field of mp_lstm_layer_desc, which version 1
+ * had as `reserved` and did not look at, is step_rows; a caller written for version 1 sets it to 0. */
+#define MP_VERSION 2
+int mp_version(void);
 
 /* ------------------------------------------------------------------------------------------
  * Loss-scale state (Section 3.1, item 1).  Lives in device memory; every kernel that needs

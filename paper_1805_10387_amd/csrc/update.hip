@@ -286,7 +286,7 @@ static int launch_update(const std::vector<UpdBatch>& batches, const UpdScalars&
 using namespace mp;
 
 extern "C" const char* mp_last_error(void) { return g_err; }
-extern "C" int         mp_version(void) { return 1; }
+extern "C" int         mp_version(void) { return MP_VERSION; }
 
 extern "C" int mp_scale_state_init(mp_scale_state* st, int mode, float init_scale, int growth_interval,
                                    float min_scale, float max_scale, mp_stream stream) {

@@ -48,6 +48,16 @@ def test_struct_layouts_match_the_header():
     assert f"#define MP_HISTORY {_lib.MP_HISTORY}" in hdr
 
 
+def test_version_tells_a_recurrent_layer_description_with_step_rows():
+    """Version 1 had an unused last field in mp_lstm_layer_desc; what it holds has a meaning since version 2, which header,
+    library and binding agree on."""
+    from paper_1805_10387_amd import _lib
+    assert "#define MP_VERSION 2\n" in open(HEADER).read() and _lib.load().mp_version() == 2
+    assert _lib.LstmLayerDesc.step_rows.offset + 4 == C.sizeof(_lib.LstmLayerDesc) == 40
+    d = _lib.LstmLayerDesc(4, 8, 0, 128, 128, 128, 128)
+    assert d.step_rows == 0
+
+
 def test_validation_errors_enqueue_nothing():
     """NULL / malformed arguments are rejected on the host (no HIP call is made on these paths)."""
     from paper_1805_10387_amd import _lib
