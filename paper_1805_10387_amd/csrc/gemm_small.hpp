@@ -64,8 +64,7 @@ struct WaveOperand {
                 for (int p = 0; p < NV / 2; ++p)
                     t[p] = __builtin_amdgcn_perm(v[2 * p + 1][i >> 1], v[2 * p][i >> 1], (i & 1) ? 0x07060302u : 0x05040100u);
                 char* const row = lds + lo() * 1024 + i * 128;
-                if constexpr (NV == 8) *reinterpret_cast<u32x4*>(row + ((hi() ^ i ^ lo()) << 4)) = u32x4{t[0], t[1], t[2], t[3]};
-                else *reinterpret_cast<u32x2g*>(row + (((hi() >> 1) ^ i ^ lo()) << 4) + (hi() & 1) * 8) = u32x2g{t[0], t[1]};
+                *reinterpret_cast<u32x2g*>(row + (((hi() >> 1) ^ i ^ lo()) << 4) + (hi() & 1) * 8) = u32x2g{t[0], t[1]};
             });
         }
     }
@@ -79,15 +78,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
-    constexpr int T = E / 32;
     const int m0 = tm * E, n0 = tn * E;
     char* const own = smem + wave * SM_WAVE;
 
-    f32x16 acc[T][T];
-#pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int j = 0; j < T; ++j) acc[i][j] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
     WaveOperand<A_KC, MODE> a[SM_DEPTH];  // k-tiles on their way
     WaveOperand<B_KC, MODE> b[SM_DEPTH];
@@ -101,7 +95,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
         a.load(A_KC ? g.A + (long long)m0 * g.lda + k : g.A + k * g.lda + m0, g.lda, g.M - m0, g.K - (int)k);
         b.load(B_KC ? g.B + (long long)n0 * g.ldb + k : g.B + k * g.ldb + n0, g.ldb, g.N - n0, g.K - (int)k);
     };
-    // fragment of slice kk: row r (+ 32), k-slot 2 kk + h; swz(row + 32) = swz(row) ^ 4
+    // fragment of slice kk: row r, k-slot 2 kk + h
     int off[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) off[c] = r * 128 + ((((2 * c) | h) ^ swz(r)) << 4);
@@ -111,16 +105,9 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
         if (kt + NW * SM_DEPTH < kt1) load(a, b, kt + NW * SM_DEPTH);
         static_for<4>([&](auto kc) {
             constexpr int kk = decltype(kc)::value;
-            f16x8         af[T], bf[T];
-#pragma unroll
-            for (int f = 0; f < T; ++f) {
-                af[f] = *reinterpret_cast<const f16x8*>(own + off[kk ^ (f << 1)] + f * 4096);
-                bf[f] = *reinterpret_cast<const f16x8*>(own + E * 128 + off[kk ^ (f << 1)] + f * 4096);
-            }
-#pragma unroll
-            for (int i = 0; i < T; ++i)
-#pragma unroll
-                for (int j = 0; j < T; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[j], af[i], acc[i][j], 0, 0, 0);
+            const f16x8   af = *reinterpret_cast<const f16x8*>(own + off[kk]);
+            const f16x8   bf = *reinterpret_cast<const f16x8*>(own + E * 128 + off[kk]);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, af, acc, 0, 0, 0);
         });
     };
     int kt = kt0 + wave;
@@ -133,16 +120,12 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
             if (kt + NW * d < kt1) step(a[d], b[d], kt + NW * d);
     }
 
-    // partial sums, row-major fp32 in 16-byte slots ^ (row % (E / 4)): lane (r, h) holds row 32 i + r, columns 32 j + 8 q + 4 h ...
+    // partial sums, row-major fp32 in 16-byte slots ^ (row % 8): lane (r, h) holds row r, columns 8 q + 4 h ...
     constexpr int SX = E / 4 - 1;
 #pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int j = 0; j < T; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<f32x4*>(own + (32 * i + r) * (4 * E) + (((8 * j + 2 * q + h) ^ (r & SX)) << 4)) =
-                    f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4*>(own + r * (4 * E) + (((2 * q + h) ^ (r & SX)) << 4)) =
+            f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
     __syncthreads();
     // wave w finishes rows E / NW w ..., a lane (of the first E E / 8 / NW) 8 consecutive columns of one
     const uint16_t* const aux = g.relu_src ? g.relu_src : g.add;
