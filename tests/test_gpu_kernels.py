@@ -286,9 +286,10 @@ def test_gemm_fp32_addend_and_fp32_output():
     assert_close16(y, ref, 1e-3, max_ulp=1, what="split contraction")
 
 
-def test_gemm_attention_batched_strided():
-    """Q K^T, P V and their gradients on a fused qkv buffer, batch = (sequence, head), no copies."""
-    B, S, h, dk = 3, 40, 4, 64
+@pytest.mark.parametrize("B,S,h,dk", [(3, 40, 4, 64), (2, 53, 3, 64), (2, 131, 2, 40), (3, 37, 2, 33), (1, 65, 5, 17), (2, 9, 3, 9)])
+def test_gemm_attention_batched_strided(B, S, h, dk):
+    """Q K^T, P V and their gradients on a fused qkv buffer, batch = (sequence, head), no copies.  Lengths and head sizes
+    off 8: pieces that straddle the border, at odd batch strides and leading dimensions."""
     d_model, T = h * dk, B * S
     r = RNG(10)
     qkv = S16(r.standard_normal((T, 3 * d_model)))
@@ -419,17 +420,96 @@ def test_gemm_split_k_weight_gradient():
     assert_close16(db, db_ref, 1e-3, max_ulp=1, what="db")
 
 
-@pytest.mark.parametrize("shapes", [
-    [(192, 256, 128), (192, 128, 384), (192, 384, 256)],      # multiples of 128 only: 128 x 128 tiles
-    [(128, 256, 512), (128, 512, 256), (128, 256, 256)],      # multiples of 256: 256 x 256 tiles
-    [(320, 1024, 256)] * 5,                                     # more tiles than workgroups resident at once
+def odd16(a):
+    """A matrix inside a wider one of 7.0 with an odd row length, starting at an odd element -> (view, leading dimension)."""
+    rows, cols = a.shape
+    ld = cols + (3 if cols % 2 == 0 else 2)
+    buf = torch.full((rows * ld + 9,), 7.0, dtype=torch.float16, device="cuda")
+    v = buf[1:1 + rows * ld].view(rows, ld)
+    v[:, :cols] = h16(a)
+    return v, ld
+
+
+@pytest.mark.parametrize("aligned", [False, True])
+@pytest.mark.parametrize("joint,M,N,Kx,Kw", [
+    (1, 8, 8, 8, 8), (1, 8, 9, 9, 8), (1, 1, 40, 33, 8),            # one tile, one straddling piece, one row
+    (1, 65, 31, 63, 70), (1, 64, 256, 104, 128),                    # 4 waves: contractions of at most 512 ...
+    (1, 521, 521, 321, 321), (1, 520, 520, 320, 328),               # ... or more than 256 tiles
+    (1, 33, 523, 65, 129), (1, 600, 136, 72, 72), (1, 1500, 41, 29, 33),   # 8 waves; column sums in several rounds
+    (1, 7, 40, 24, 24), (0, 70, 7, 24, 24), (0, 70, 24, 7, 24), (0, 70, 24, 24, 7),   # stored rows of fewer than 8 elements ...
+    (0, 4128, 136, 520, 264),                                       # ... and products that are not small: separate calls
 ])
-def test_gemm_grouped_weight_gradients(shapes):
-    """Several dW = dY^T X in one launch: each equals the oracle and, bit for bit, the single-problem entry point."""
+def test_gemm_both_gradients_of_a_layer(joint, M, N, Kx, Kw, aligned):
+    """mp_gemm_bwd_both: input, weight and bias gradient against the oracle, with every epilogue of the input gradient,
+    with and without the bias gradient, widths of the two products that differ, any extent, leading dimension and
+    alignment, nothing written outside the output columns; one launch where mp_gemm_bwd_both_joint says so (it then takes
+    no workspace), separate calls elsewhere.  Bounds as for the separate calls: fp32 order only."""
+    r = RNG(M + 3 * N + 7 * Kx + 11 * Kw)
+    x, w, dy = S16(r.standard_normal((M, Kw))), S16(r.standard_normal((N, Kx)) * 0.1), S16(r.standard_normal((M, N)) * 0.1)
+    other = S16(r.standard_normal((M, Kx)))
+    src = S16(np.maximum(other, 0))
+    put = (lambda a: (h16(a), a.shape[1])) if aligned else odd16
+    (xd, ldx), (wd, ldw), (dyd, ldy), (od, lda), (sd, _) = put(x), put(w), put(dy), put(other), put(src)
+    (dx, ldo), (dw, ldg) = put(np.zeros((M, Kx))), put(np.zeros((N, Kw)))
+    d_dx = mp.gemm_desc(M, N, Kx, ldx=ldo, ldw=ldw, ldy=ldy)
+    d_dw = mp.gemm_desc(M, N, Kw, ldx=ldx, ldw=ldg, ldy=ldy)
+    assert mp.mp_gemm_bwd_both_joint(d_dx, d_dw) == bool(joint)
+    ws = None if joint else ws_bytes(max(mp.mp_gemm_bwd_dw_workspace_bytes(d_dw, True), mp.mp_gemm_split_workspace_bytes(d_dx)))
+    dx_ref = MIXED.store(dy @ w)
+    _, dw_ref, db_ref = L.linear_bwd(MIXED, dy, x, np.zeros((N, Kw), np.float32))
+    st = make_state()
+    bias = torch.full((N + 9,), 7.0, dtype=torch.float16, device="cuda")
+    lead = 8 if aligned else 1
+    for k, (kw, ref, ulp) in enumerate([({}, dx_ref, 1), (dict(relu_src=sd, ld_aux=lda), L.relu_mask(MIXED, dx_ref, src), 1),
+                                        (dict(add=od, ld_aux=lda), L.add_store(MIXED, dx_ref, other), None)]):
+        dx[:, :Kx] = float("nan")
+        dw[:, :Kw] = float("nan")
+        db = None if k == 1 else bias[lead:lead + N]
+        mp.mp_gemm_bwd_both(d_dx, dyd, wd, dx, d_dw, xd, dw, db, st, ws, **kw)
+        assert_close16(dx[:, :Kx], ref, 1e-3, max_ulp=ulp, what=f"dx {k}")
+        assert_close16(dw[:, :Kw], dw_ref, 1e-3, max_ulp=1, what=f"dw {k}")
+        if db is not None:
+            assert_close16(db, db_ref, 1e-3, max_ulp=1, what=f"db {k}")
+            bias[lead:lead + N] = 7.0
+        assert torch.all(bias == 7.0)
+    assert torch.all(dx[:, Kx:] == 7.0) and torch.all(dw[:, Kw:] == 7.0)
+    assert mp.scale_state_read(st).found_inf == 0
+
+
+@pytest.mark.parametrize("M,N,K", [(128, 64, 40), (130, 65, 41), (640, 131, 67)])
+def test_gemm_both_gradients_flag_what_the_separate_calls_flag(M, N, K):
+    """A joint launch raises found_inf for the weight gradient alone and for the bias gradient alone, not for the input
+    gradient (an activation gradient has no flag of its own), and not for finite results."""
+    full = lambda rows, cols, v: torch.full((rows, cols), v, dtype=torch.float16, device="cuda")  # noqa: E731
+    d = mp.gemm_desc(M, N, K)
+    assert mp.mp_gemm_bwd_both_joint(d, d)
+    for dy, w, x, flag, inf in ((60.0, 0.0, 2.0 ** 14, 1, "dw"), (600.0, 0.0, 0.0, 1, "db"), (60.0, 2.0 ** 14, 0.0, 0, "dx"),
+                                (1.0, 1.0, 1.0, 0, "")):
+        st = make_state()
+        dx, dw, db = empty16(M, K), empty16(N, K), empty16(N)
+        mp.mp_gemm_bwd_both(d, full(M, N, dy), full(N, K, w), dx, d, full(M, K, x), dw, db, st)
+        assert mp.scale_state_read(st).found_inf == flag, inf
+        for name, t in (("dx", dx), ("dw", dw), ("db", db)):
+            assert bool(torch.isinf(t).all() if name == inf else torch.isfinite(t).all()), (inf, name)
+
+
+@pytest.mark.parametrize("tile,shapes", [
+    (3, [(192, 256, 128), (192, 128, 384), (192, 384, 256)]),      # few tiles: 128 x 128
+    (3, [(128, 256, 512), (128, 512, 256), (128, 256, 256)]),      # ... whatever the extents divide by
+    (3, [(320, 1024, 256)] * 5),
+    (3, [(64, 1152, 1152)] * 7),                                   # 567 tiles and 54 strips: workgroups take several, in both families
+    (1, [(64, 1024, 1024)] * 5),                                   # one round of 160 tiles of 256 x 128 against two of 320
+    (1, [(64, 1024, 1152)] * 4),                                   # ... and where 256 x 256 does not divide
+    (0, [(64, 1024, 4096), (64, 4096, 1024), (64, 3072, 1024), (64, 1024, 1024)]),   # one round of 192 tiles of 256 x 256
+    (0, [(64, 2048, 4096)] * 3),                                   # 384 tiles of 256 x 256: workgroups take several
+])
+def test_gemm_grouped_weight_gradients(tile, shapes):
+    """Several dW = dY^T X in one launch: each equals the oracle and, bit for bit, the single-problem entry point.
+    `tile` is the shape the rule takes (of 256 x 256, 256 x 128 and 128 x 128 the one whose rounds of one work item per
+    compute unit cost least; the register-staged kernels have no 256 x 128 and take 128 x 128 there)."""
     r = RNG(len(shapes) * 7 + shapes[0][1])
     items, refs, singles, db_refs = [], [], [], []
     st = make_state()
-    all256 = all(n % 256 == 0 and k % 256 == 0 for (_, n, k) in shapes)
     for j, (M, N, K) in enumerate(shapes):
         x, dy = S16(r.standard_normal((M, K))), S16(r.standard_normal((M, N)) * 0.1)
         d = mp.gemm_desc(M, N, K)
@@ -439,7 +519,7 @@ def test_gemm_grouped_weight_gradients(shapes):
         _, dw_ref, db_ref = L.linear_bwd(MIXED, dy, x, np.zeros((N, K), np.float32))
         refs.append(dw_ref)
         db_refs.append(db_ref)
-        mp.mp_gemm_tuning_override(0 if all256 else 3, 1)         # the tile the grouped launch takes, no k-split
+        mp.mp_gemm_tuning_override(tile, 1)                       # the tile the grouped launch takes, no k-split
         mp.mp_gemm_bwd_dw(d, items[-1][1], items[-1][2], dw1, None, None, ws_bytes(mp.mp_gemm_bwd_dw_workspace_bytes(d, False)))
         mp.mp_gemm_tuning_override(-1, 0)
         singles.append(dw1)
