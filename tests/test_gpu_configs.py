@@ -352,9 +352,10 @@ def test_config3_reduced_size_two_layers():
     _transformer(I.C3_SMALL, 3, 3)
 
 
-def test_unfused_attention_path_reduced_size():
-    """The chain of batched products and softmax kernels (used where the fused kernel does not apply)."""
-    wl = I.C3_SMALL
+@pytest.mark.parametrize("seq_len,n_heads", [(48, 4), (53, 4), (131, 8)])
+def test_unfused_attention_path_reduced_size(seq_len, n_heads):
+    """The chain of batched products and softmax kernels (used where the fused kernel does not apply), lengths off 8 too."""
+    wl = replace(I.C3_SMALL, seq_len=seq_len, n_heads=n_heads)
     batch = wl.batch()
     step = St.TransformerStep(wl, fused_attention=False)
     step.set_batch(batch)
@@ -384,8 +385,8 @@ def _assert_clean_steps_have_margin(step, lo=0.55, hi=0.8):
 
 
 def test_config3_reduced_overflowing_run_in_the_bench_configuration():
-    """Producer-side overflow inspection + one flat update descriptor + second stream (the configuration bench.py
-    times) on a run that overflows NATURALLY: the start scale 2^24 is three halvings too high, and with a growth
+    """Producer-side overflow inspection + one flat update descriptor, asked for a second stream (the configuration
+    bench.py times; a model this small has both gradients of a layer in one launch and leaves that stream empty) on a run that overflows NATURALLY: the start scale 2^24 is three halvings too high, and with a growth
     interval of 3 every fourth clean step doubles the scale back into overflow.  Flags, skipped steps and the scale
     sequence must equal the free-running oracle's; a graph replay of the same run must give the eager run's bits."""
     wl = replace(I.C3_SMALL, scale=I.ScaleCfg(init_scale=2.0 ** 24, growth_interval=3))
@@ -457,15 +458,38 @@ def test_config5_reduced_prechecked_configuration_matches_default():
     assert torch.equal(a.P.w32_arena, b.P.w32_arena) and a.state().opt_step == b.state().opt_step == 3
 
 
-def test_second_stream_for_weight_gradients_gives_the_same_bits():
-    wl, batch = I.C3_SMALL, I.C3_SMALL.batch()
-    a, b = St.TransformerStep(wl), St.TransformerStep(wl, two_streams=True)
-    for s in (a, b):
-        s.set_batch(batch)
-        for _ in range(3):
-            s.step()
-    torch.cuda.synchronize()
-    assert torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.P.g16_arena, b.P.g16_arena)
+@pytest.mark.parametrize("kind,d_model,n_heads,d_ff,seq_len,n_seq", [
+    ("joint", 256, 4, 512, 48, 6),          # one launch for both gradients of a layer: nothing is left for a second stream
+    ("grouped", 256, 4, 512, 48, 32),       # the grouped launch of a layer on the second stream
+    ("separate", 192, 3, 768, 61, 66),      # every weight gradient by itself on the second stream
+])
+def test_second_stream_for_weight_gradients_gives_the_same_bits(kind, d_model, n_heads, d_ff, seq_len, n_seq):
+    """Three layers, so that each of the alternating temporaries is taken again while the second stream may still read it;
+    a run that starts with overflowing scales, so that the streams also agree on flags raised there; call by call and as a
+    graph replay."""
+    wl = replace(I.C3_SMALL, n_layers=3, d_model=d_model, n_heads=n_heads, d_ff=d_ff, seq_len=seq_len, n_seq=n_seq,
+                 scale=I.ScaleCfg(init_scale=2.0 ** 27, growth_interval=3, max_scale=2.0 ** 27))
+    batch, n = wl.batch(), 12
+    for kw in ({}, dict(prechecked=True, flat_update=True)):
+        a, b, c = St.TransformerStep(wl, **kw), St.TransformerStep(wl, two_streams=True, **kw), St.TransformerStep(wl, two_streams=True, **kw)
+        for s in (a, b, c):
+            assert (s.joint_bwd, s.grouped_dw) == (kind == "joint", kind == "grouped")
+            s.set_batch(batch)
+        for s in (a, b):
+            for _ in range(n):
+                s.step()
+        c.step()
+        graph = _graph_step(c)
+        for _ in range(n - 1):
+            graph.replay()
+        torch.cuda.synchronize()
+        flags = [a.state().hist_found_inf[i] for i in range(n)]
+        assert flags[0] == 1 and 0 in flags
+        for s in (b, c):
+            assert [s.state().hist_found_inf[i] for i in range(n)] == flags
+            assert torch.equal(a.P.w32_arena, s.P.w32_arena)
+            for x, y in ((a.P.g16_arena, s.P.g16_arena), (a.dx_input, s.dx_input)):
+                assert torch.equal(x.view(torch.int16), y.view(torch.int16))       # (bits: the last step may overflow)
 
 
 def test_config2_full_size():
