@@ -6,24 +6,31 @@
 namespace mp {
 
 constexpr int LOSS_THREADS = 256;
-constexpr int FM_LOADS     = 16;  // partials a thread of the finish kernel has on their way
+constexpr int FM_LOADS     = 16;  // partials a thread of the finish kernel has on their way, where there are that many
 
 // Sum `n` fp32 partials with one workgroup (fixed order), divide by `denom`, store to *out.
 // Bound by memory latency: a thread has 16 loads on their way at a time and adds them in index order, so 8192 row losses
 // cost two round trips and not 32 (8192 x 32768 vocabulary iteration 1840 -> 1834 us; the kernel took 12.7 us before).
+// LOADS 1 is for up to one partial per thread, where 16 loads each cost 0.2 us more than one (losses of 1 to 100 rows).
+template <int LOADS>
 __global__ __launch_bounds__(LOSS_THREADS) void finish_mean_kernel(const float* __restrict__ part, int n, double denom,
                                                                    float* __restrict__ out) {
     __shared__ float red[LOSS_THREADS / 64];
     float            acc = 0.f;
-    for (long long i = threadIdx.x; i < n; i += FM_LOADS * LOSS_THREADS) {
-        float v[FM_LOADS];
+    for (long long i = threadIdx.x; i < n; i += LOADS * LOSS_THREADS) {
+        float v[LOADS];
 #pragma unroll
-        for (int k = 0; k < FM_LOADS; ++k) v[k] = part[min(i + k * LOSS_THREADS, (long long)n - 1)];
+        for (int k = 0; k < LOADS; ++k) v[k] = part[min(i + k * LOSS_THREADS, (long long)n - 1)];
 #pragma unroll
-        for (int k = 0; k < FM_LOADS; ++k) acc += i + k * LOSS_THREADS < n ? v[k] : 0.f;
+        for (int k = 0; k < LOADS; ++k) acc += i + k * LOSS_THREADS < n ? v[k] : 0.f;
     }
     const float tot = block_sum<LOSS_THREADS / 64>(acc, red);
     if (threadIdx.x == 0) *out = tot / (float)denom;
+}
+
+static void launch_finish_mean(const float* part, int n, double denom, float* out, hipStream_t hs) {
+    if (n <= LOSS_THREADS) hipLaunchKernelGGL(finish_mean_kernel<1>, dim3(1), dim3(LOSS_THREADS), 0, hs, part, n, denom, out);
+    else hipLaunchKernelGGL(finish_mean_kernel<FM_LOADS>, dim3(1), dim3(LOSS_THREADS), 0, hs, part, n, denom, out);
 }
 
 // ------------------------------------------------------------------------------- MSE
@@ -303,7 +310,7 @@ extern "C" int mp_mse_scaled(int rows, int cols, const mp_half* y, const mp_half
     else
         hipLaunchKernelGGL(mse_kernel<false>, dim3(nb), dim3(LOSS_THREADS), 0, hs, rows, cols, ld, y, target, st, dy, part);
     MP_LAUNCH_CHECK("mp_mse_scaled");
-    hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(LOSS_THREADS), 0, hs, part, nb, (double)rows * (double)cols, loss);
+    launch_finish_mean(part, nb, (double)rows * (double)cols, loss, hs);
     MP_LAUNCH_CHECK("mp_mse_scaled(finish)");
     return MP_OK;
 }
@@ -316,11 +323,20 @@ static int xent_grid(int rows, int threads) {
     return rows < 256 ? rows : 256;
 }
 
+// rows made of aligned 16-byte pieces
+static bool xent_pieces(int vocab, int ld, const mp_half* logits, const mp_half* dlogits) {
+    return vocab % 8 == 0 && ld % 8 == 0 && aligned16(logits) && aligned16(dlogits);
+}
+// Other rows of up to this length go through the generic kernel: it has up to 5 elements per thread, and the cached one works
+// on 32 per thread whatever the row holds.  us, cached / generic, with the finish launch: 4096 x 29 15.6 / 7.5, 4096 x 1001
+// 16.3 / 12.4, 1021 x 1201 8.0 / 7.1, 1 x 1201 5.4 / 5.5; beyond 4096 x 2001 18.7 / 20, 100 x 1501 6.1 / 6.4.
+constexpr int XENT_SHORT = 1280;
+
 template <int THREADS, bool COLSUM>
 static void launch_xent_cached(int rows, int vocab, int ld, const mp_half* logits, const int32_t* targets, const mp_scale_state* st,
                                mp_half* dlogits, float* row_loss, float* colpart, hipStream_t hs) {
     const dim3 grid(xent_grid(rows, THREADS)), block(THREADS);
-    if (vocab % 8 == 0 && ld % 8 == 0 && aligned16(logits) && aligned16(dlogits))
+    if (xent_pieces(vocab, ld, logits, dlogits))
         hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, false>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
                            row_loss, colpart);
     else
@@ -342,7 +358,9 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
     float*      row_loss = static_cast<float*>(ws);
     hipStream_t hs       = as_stream(stream);
     const int   nvec     = (vocab + 7) / 8;
-    if (nvec <= XENT_VECS * 256)
+    if (vocab <= XENT_SHORT && !xent_pieces(vocab, ld, logits, dlogits))
+        hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, row_loss);
+    else if (nvec <= XENT_VECS * 256)
         launch_xent_cached<256, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
     else if (nvec <= XENT_VECS * 512)
         launch_xent_cached<512, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
@@ -352,7 +370,7 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
         hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
                            row_loss);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled");
-    hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(LOSS_THREADS), 0, hs, row_loss, rows, (double)rows, loss);
+    launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled(finish)");
     return MP_OK;
 }
@@ -396,7 +414,7 @@ extern "C" int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* log
     const int grid     = xent_grid(rows, 1024);
     launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, part, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db");
-    hipLaunchKernelGGL(finish_mean_kernel, dim3(1), dim3(LOSS_THREADS), 0, hs, row_loss, rows, (double)rows, loss);
+    launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db(finish)");
     return finish_colsum_launch(part, grid, vocab, db, st, hs);
 }

@@ -752,7 +752,7 @@ def test_softmax_xent_scaled_with_bias_gradient(rows, vocab):
 
 
 @pytest.mark.parametrize("rows,vocab", [(3, 1), (5, 7), (6, 2 ** 13 + 1), (9, 2 ** 14 - 1), (70, 2 ** 14 + 3), (300, 2 ** 15 - 3),
-                                        (4, 2 ** 15 + 1), (8, 2 ** 12)])
+                                        (4, 2 ** 15 + 1), (8, 2 ** 12), (300, 1280), (300, 1281)])
 def test_softmax_xent_rows_at_any_alignment(rows, vocab):
     """Vocabularies that are no multiple of 8, in rows that start at odd elements, around the row lengths where the workgroup
     size changes: gradient and bias gradient against the oracle, in place too, nothing written between the rows, and rows
