@@ -74,36 +74,36 @@ __global__ __launch_bounds__(GL_THREADS) void finish_colsum_kernel(const float* 
 }
 
 // --------------------------------------------------------------------------- column sums
-// Workgroup = 8 column-groups x 32 row-lanes, 8 columns per column-group (a row piece of 8 x 16 B = one 128-byte line per
-// row).  Rows may start at any element and have any length: the pieces are loaded as they lie (the hardware takes any
-// address), and only a last, partial piece goes element by element.  (1021 x 12001 with 2-byte loads, one column per
+// Workgroup = 8 column-groups x 32 row-lanes, VEC columns per column-group: 8 (a row piece of 8 x 16 B = one 128-byte line
+// per row) or 1.  Rows may start at any element and have any length: the pieces are loaded as they lie (the hardware takes any
+// address).  RAGGED: the last, partial piece of a row is loaded so that it ends with the row, and the columns it then shares
+// with the piece ahead are left to that one, so the row loop has no branch.  (1021 x 12001 with 2-byte loads, one column per
 // column-group: 27 us; for the iteration's gain see xent_cached_kernel.)
 typedef unsigned u32x4c __attribute__((ext_vector_type(4)));
 typedef u32x4c   u32x4c_u __attribute__((aligned(2)));
+template <int VEC, bool RAGGED>
 __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, int ld, const uint16_t* __restrict__ dy,
                                                             int rows_per_block, float* __restrict__ part) {
-    constexpr int    VEC = 8;
     __shared__ float sm[32][8 * VEC + 1];
     const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
     const int c0 = (blockIdx.x * 8 + cg) * VEC;
     const int r0 = blockIdx.y * rows_per_block;
     const int r1 = min(rows, r0 + rows_per_block);
+    const int early = RAGGED && c0 < cols ? max(0, c0 + VEC - cols) : 0;
     float     acc[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) acc[k] = 0.f;
     if (c0 < cols) {
         for (int r = r0 + rl; r < r1; r += 32) {
-            const uint16_t* p = dy + (long long)r * ld + c0;
-            if (c0 + VEC <= cols) {
+            const uint16_t* p = dy + (long long)r * ld + (c0 - early);
+            if constexpr (VEC == 8) {
                 const u32x4c q = *reinterpret_cast<const u32x4c_u*>(p);
                 float        f[8];
                 unpack8(make_uint4(q[0], q[1], q[2], q[3]), f);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) acc[k] += f[k];
             } else {
-#pragma unroll
-                for (int k = 0; k < VEC - 1; ++k)
-                    if (c0 + k < cols) acc[k] += h2f(p[k]);
+                acc[0] += h2f(*p);
             }
         }
     }
@@ -111,11 +111,13 @@ __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, 
     for (int k = 0; k < VEC; ++k) sm[rl][cg * VEC + k] = acc[k];
     __syncthreads();
     for (int c = threadIdx.x; c < 8 * VEC; c += GL_THREADS) {
-        float t = 0.f;
-#pragma unroll
-        for (int j = 0; j < 32; ++j) t += sm[j][c];
         const int gc = blockIdx.x * 8 * VEC + c;
-        if (gc < cols) part[(long long)blockIdx.y * cols + gc] = t;
+        if (gc >= cols) break;
+        const int src = c + (RAGGED && gc >= cols / VEC * VEC ? VEC - cols % VEC : 0);  // (where the partial piece has the column)
+        float     t   = 0.f;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) t += sm[j][src];
+        part[(long long)blockIdx.y * cols + gc] = t;
     }
 }
 
@@ -531,7 +533,14 @@ static int colsum_launch(int rows, int cols, const mp_half* dY, int ld, mp_half*
                          hipStream_t hs) {
     const int   rb  = colsum_row_blocks(rows, cols);
     const int   rpb = (rows + rb - 1) / rb;
-    hipLaunchKernelGGL(colsum_kernel, dim3((cols + 63) / 64, rb), dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
+    // few columns that are no whole pieces: one column per column-group, which makes eight times the workgroups (us, VEC 8 / 1:
+    // 8192 x 29 5.7 / 5.0, 8192 x 130 6.2 / 5.8, 60 x 65 4.2 / 4.1; beyond 8192 x 300 6.3 / 9.8, 1021 x 1001 4.9 / 5.0)
+    if (cols % 8 == 0)
+        hipLaunchKernelGGL((colsum_kernel<8, false>), dim3((cols + 63) / 64, rb), dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
+    else if (cols > 256)
+        hipLaunchKernelGGL((colsum_kernel<8, true>), dim3((cols + 63) / 64, rb), dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
+    else
+        hipLaunchKernelGGL((colsum_kernel<1, false>), dim3((cols + 7) / 8, rb), dim3(GL_THREADS), 0, hs, rows, cols, ld, dY, rpb, part);
     MP_LAUNCH_CHECK("mp_colsum");
     FinishOuts outs{{db, nullptr, nullptr}};
     hipLaunchKernelGGL(finish_colsum_kernel, dim3((cols + 31) / 32), dim3(GL_THREADS), 0, hs, part, rb,

@@ -809,7 +809,8 @@ def test_softmax_xent_rows_without_a_target_have_zero_gradient_whatever_they_hol
     assert mp.scale_state_read(st).found_inf == 0
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 1), (65, 7), (64, 63), (200, 65), (1021, 1001), (3, 8)])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (65, 7), (64, 63), (200, 65), (1021, 1001), (3, 8), (300, 255), (65, 257), (70, 260),
+                                       (1, 319), (130, 321)])
 def test_colsum_rows_at_any_alignment(rows, cols):
     """Column counts around the 8-column pieces and 64-column workgroups, rows that start at odd elements."""
     r = RNG(rows + cols)
