@@ -47,7 +47,8 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
     }
 }
 
-// Scalar kernel with the same contract, for the few shapes the matrix-core path does not take (see matrix_path_ok).
+// Scalar kernel with the same contract, for the few shapes the matrix-core path does not take or is slower on (see
+// matrix_path_ok, scalar_wins).
 __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g, int a_kc, int b_kc) {
     const long long mn  = (long long)g.M * g.N;
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -195,12 +196,21 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
     return interior || std::max(g.lda, g.ldb) < LD_BUFFER_64;
 }
 
+// Few ragged outputs over a contraction that short cost the scalar kernel less than the matrix cores' chain of loads, LDS and
+// final sum (us, matrix cores / scalar, forward: 1500 x 29 over 9 4.2 / 3.3, over 12 4.2 / 3.6, over 17 4.2 / 4.1; 512 x 512 over 9
+// 4.0 / 4.3; 64 products 37 x 37 over 9 4.6 / 3.3, over 17 4.7 / 4.2; 512 of 20 x 20 over 9 5.5 / 5.2.  Input gradients:
+// 1500 x 29 over 12 4.0 / 3.5, over 17 4.0 / 4.0; 512 products 9 x 40 over 9 5.7 / 4.1, 20 x 40 over 20 5.8 / 7.1).
+static bool scalar_wins(const GemmArgs& g, long long batches) {
+    const long long outs = (long long)g.M * g.N * batches;
+    return g_force_tile < 0 && !g.aligned && (batches == 1 ? g.K <= 12 && outs <= 65536 : g.K <= 16 && outs * g.K <= 1 << 21);
+}
+
 // ws: split-K partial buffer (may be NULL when !allow_split).
 static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool allow_split, float* ws, size_t ws_floats,
                     hipStream_t hs) {
     if (g.M == 0 || g.N == 0 || batches == 0) return MP_OK;
     g.aligned = fast_path_ok(g);
-    if (!matrix_path_ok(g, a_kc, b_kc) || batches > 65535) {
+    if (!matrix_path_ok(g, a_kc, b_kc) || scalar_wins(g, batches) || batches > 65535) {
         if (batches > 65535) {
             set_error("gemm: more than 65535 batches");
             return MP_E_UNSUPPORTED;

@@ -255,6 +255,44 @@ def test_gemm_extents_and_strides_of_any_parity(tile, M, N, K):
     assert mp.scale_state_read(st).found_inf == 0
 
 
+@pytest.mark.parametrize("M,N,K", [(33, 45, 8), (33, 45, 12), (33, 45, 13), (17, 3855, 12), (17, 3856, 12), (1, 8, 9), (9, 40, 1)])
+def test_gemm_short_ragged_contractions(M, N, K):
+    """Contractions around the length, and outputs around the number, up to which ragged products take the scalar kernel, in
+    each of the three products, at odd elements and leading dimensions; bounds as for the other shapes."""
+    r = RNG(M + 3 * N + 7 * K)
+    x, w, b = S16(r.standard_normal((M, K))), S16(r.standard_normal((N, K))), S16(r.standard_normal(N))
+    (xd, ldx), (wd, ldw), (xt, ldxt), (wt, ldwt) = odd16(x), odd16(w), odd16(np.ascontiguousarray(x.T)), odd16(np.ascontiguousarray(w.T))
+    ref = MIXED.store(x @ w.T)
+    for what in ("fwd", "dx", "dw"):
+        y, ldy = odd16(np.zeros((M, N)))
+        y[:, :N] = float("nan")
+        if what == "fwd":
+            mp.mp_gemm_fwd(mp.gemm_desc(M, N, K, ldx=ldx, ldw=ldw, ldy=ldy, epilogue=1), xd, wd, h16(b), None, y)
+        elif what == "dx":     # dY [M, K] W [K, N]
+            mp.mp_gemm_bwd_dx(mp.gemm_desc(M, K, N, ldx=ldy, ldw=ldwt, ldy=ldx), xd, wt, y)
+        else:                  # dY [K, M], X [K, N]
+            d = mp.gemm_desc(K, M, N, ldx=ldwt, ldw=ldy, ldy=ldxt)
+            mp.mp_gemm_bwd_dw(d, xt, wt, y, None, None, ws_bytes(mp.mp_gemm_bwd_dw_workspace_bytes(d, False)))
+        assert_close16(y[:, :N], L.linear_fwd(MIXED, x, w, b) if what == "fwd" else ref, 1e-3, max_ulp=1, what=what)
+        assert torch.all(y[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("outer,inner,M,N,K", [(3, 4, 13, 9, 16), (3, 4, 13, 9, 17), (16, 56, 16, 16, 9), (16, 57, 16, 16, 9)])
+def test_gemm_short_ragged_batched_contractions(outer, inner, M, N, K):
+    """The same rule over batches (outputs counted over all of them), batches side by side in rows of odd length."""
+    r = RNG(outer + inner + M + K)
+    x, w = S16(r.standard_normal((outer, M, inner * K))), S16(r.standard_normal((outer, N, inner * K)))
+    pad = lambda a: np.concatenate([a, np.zeros(a.shape[:2] + (1 - a.shape[2] % 2,), np.float32)], 2)  # noqa: E731
+    x, w = pad(x), pad(w)
+    ld = x.shape[2]
+    y = empty16(outer, inner, M, N)
+    d = mp.gemm_desc(M, N, K, ldx=ld, ldw=ld, ldy=N, alpha=0.5, batch_outer=outer, batch_inner=inner, sx=(M * ld, K), sw=(N * ld, K),
+                     sy=(inner * M * N, M * N))
+    mp.mp_gemm_fwd(d, h16(x), h16(w), None, None, y)
+    split = lambda a: a[:, :, :inner * K].reshape(outer, -1, inner, K).transpose(0, 2, 1, 3)  # noqa: E731
+    assert_close16(y, MIXED.store(np.float32(0.5) * (split(x) @ split(w).transpose(0, 1, 3, 2))), 1e-3, max_ulp=1, what="batched")
+
+
 def test_gemm_leading_dimensions_and_unaligned_fallback():
     r = RNG(8)
     M, N, K = 70, 90, 50                      # K, N not multiples of 8: slow path
