@@ -121,8 +121,8 @@ int mp_loss_scale_update(mp_scale_state* st, mp_stream stream);
  * entry points.  Batched use: batch_outer x batch_inner independent problems; operand t of batch
  * (o, i) starts at t + o*s?_outer + i*s?_inner (elements).  Strides of 0 broadcast.
  * Any pointer (element-aligned), leading dimension and stride runs on the matrix cores as long as a row of each operand,
- * as stored, has at least 8 elements (and N is a multiple of 4 where an fp32 addend or output is given); anything else
- * runs a slow scalar kernel with the same results contract.  16-byte aligned pointers with extents, leading dimensions
+ * as stored, has at least 8 elements (and N is a multiple of 4 where an fp32 addend or output is given); anything else, and
+ * few ragged outputs over a contraction of at most 12 to 16, runs a scalar kernel with the same results contract.  16-byte aligned pointers with extents, leading dimensions
  * and strides in multiples of 8 (better: of the tile shapes, 128 or 256) are the fastest case.
  * ------------------------------------------------------------------------------------------ */
 enum { MP_EPI_NONE = 0, MP_EPI_BIAS = 1, MP_EPI_BIAS_RELU = 2 };
@@ -279,8 +279,8 @@ int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits, int ld, c
 
 /* mp_softmax_xent_scaled that also returns the bias gradient of the projection behind the logits (Section 3.2: the
  * gradients are fp16 tensors): db[vocab] = RNE16( fp32 column sums over the rows of the dlogits values as stored ).
- * For vocabularies of more than 16384 classes (multiples of 8, 16-byte aligned rows) the sums are taken in the pass
- * that writes dlogits, so the gradient matrix is not read again; other shapes run the plain call followed by mp_colsum.
+ * For vocabularies of 16385 to 32768 classes the sums are taken in the pass that writes dlogits (rows of any alignment), so
+ * the gradient matrix is not read again; others run the plain call followed by mp_colsum.
  * st is read for S as above; its overflow flag is set if a stored db value is non-finite (dlogits itself is bounded
  * by S / rows and is covered by whoever consumes it).  Workspace: mp_softmax_xent_db_workspace_bytes(rows, vocab),
  * 16-byte aligned.  Same results contract as the two separate calls (fp32 summation order differs). */

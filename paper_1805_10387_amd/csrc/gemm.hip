@@ -448,8 +448,12 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 }
 
 // One launch for both gradients: each product for the small kernel by itself, and together no more than three workgroups
-// per compute unit.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and the small tiles,
-// of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained then.)
+// per compute unit.  us, separate calls / one launch, with the bias gradient: 64 x 256 over 1024 (328 workgroups) 10.0 / 3.7,
+// 704 x 504 over 512 (624) 14.3 / 8.4, 1500 x 300 over 300 (580) 18.1 / 13.6; without it the last, whose weight gradient is
+// a long chain, 12.9 / 13.7.  The line lies short of where the gain ends: 512 x 1024 over 512 (800) 14.9 / 10.3,
+// 704 x 704 over 704 (990) 17.1 / 11.2.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and
+// the small tiles, of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained
+// then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
     if (g_force_tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;

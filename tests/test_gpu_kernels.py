@@ -150,7 +150,7 @@ def test_gemm_bwd_dx_and_dw(M, N, K):
     assert mp.scale_state_read(st).found_inf == 0
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 128, 64), (300, 264, 136), (70, 90, 50)])   # matrix-core interior, ragged, scalar path
+@pytest.mark.parametrize("M,N,K", [(64, 128, 64), (300, 264, 136), (70, 90, 50), (70, 90, 10)])   # aligned, ragged, straddling, scalar kernel
 def test_gemm_relu_epilogue_keeps_nonfinite_values(M, N, K):
     """max(x, 0) on a non-finite pre-activation: +inf stays +inf, -inf becomes 0 and NaN stays NaN, as in the
     oracle's definition.  A NaN that the epilogue dropped would hide a forward overflow from the gradient
@@ -295,7 +295,7 @@ def test_gemm_short_ragged_batched_contractions(outer, inner, M, N, K):
 
 def test_gemm_leading_dimensions_and_unaligned_fallback():
     r = RNG(8)
-    M, N, K = 70, 90, 50                      # K, N not multiples of 8: slow path
+    M, N, K = 70, 90, 50                      # K, N not multiples of 8: pieces that straddle the rows' ends
     x, w = S16(r.standard_normal((M, K))), S16(r.standard_normal((N, K)))
     y = empty16(M, N)
     mp.mp_gemm_fwd(mp.gemm_desc(M, N, K), h16(x), h16(w), None, None, y)
