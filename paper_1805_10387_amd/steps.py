@@ -365,7 +365,7 @@ class XentStep(_StepBase):
 
 
 # ====================================================================================== config 5
-def lstm_row_blocks(batch: int, hidden: int, cus: int) -> List[tuple]:
+def lstm_row_blocks(batch: int, hidden: int, cus: int, seq_len: int) -> List[tuple]:
     """(first row, rows) of the launches that the persistent recurrent kernels of an LSTMStep take a batch in, or [] where
     the step-by-step plan is the faster one.
 
@@ -374,9 +374,13 @@ def lstm_row_blocks(batch: int, hidden: int, cus: int) -> List[tuple]:
     never leave each other half resident.  Launches follow one another, so their number bounds the gain: us per iteration
     of two layers x 10 steps, persistent / step by step, 512 units: 256 rows (4 launches) 527 / 561, 512 rows (8) 935 / 690;
     1024 units: 64 rows (2) 467 / 640, 128 rows (4) 741 / 784, 256 rows (8) 1295 / 918; 256 units, whose step-by-step
-    products have less to do: 256 rows (2) 267 / 348, 512 rows (4) 442 / 384."""
+    products have less to do: 256 rows (2) 267 / 348, 512 rows (4) 442 / 384.  Each launch reads the weights anew, which
+    short sequences do not make up for: 2, 3 and 4 launches need 3, 5 and 9 time steps (one layer of 1024 units: 64 rows
+    (2) x 2 steps 119 / 103, x 3 130 / 126, x 4 142 / 148; 96 rows (3) x 4 172 / 160, x 6 204 / 214; 128 rows (4) x 8
+    289 / 276; of 512 units: 128 rows (2) x 2 79 / 68, x 3 88 / 88, 256 rows (4) x 8 214 / 196)."""
     block = 8 * (cus // max(hidden // 16, 1))
-    if block <= 0 or -(-batch // block) > (4 if hidden >= 512 else 2):
+    most = min(max(1, (seq_len - 1).bit_length()), 4 if hidden >= 512 else 2)
+    if block <= 0 or -(-batch // block) > most:
         return []
     return [(r, min(block, batch - r)) for r in range(0, batch, block)]
 
@@ -408,7 +412,7 @@ class LSTMStep(_StepBase):
         z16 = lambda *s: torch.zeros(s, dtype=torch.float16, device="cuda")
         z32 = lambda *s: torch.zeros(s, dtype=torch.float32, device="cuda")
         self.in_dims = [wl.d_in if l == 0 else H for l in range(NL)]
-        blocks = lstm_row_blocks(Bt, H, torch.cuda.get_device_properties(0).multi_processor_count)
+        blocks = lstm_row_blocks(Bt, H, torch.cuda.get_device_properties(0).multi_processor_count, T)
         self.persistent = persistent and H % 64 == 0 and H <= 1024 and all(i % 8 == 0 for i in self.in_dims) and bool(blocks)
         self.row_blocks = blocks if self.persistent else []
         self.xh = [z16(T, Bt, self.in_dims[l] + H) for l in range(NL)]      # h_0 = 0 stays in xh[l][0][:, I:]

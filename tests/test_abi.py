@@ -159,15 +159,19 @@ def test_recurrent_launches_leave_half_of_the_gpu(cus):
     from paper_1805_10387_amd.steps import lstm_row_blocks
     for hidden in range(64, 1025, 64):
         for batch in (1, 7, 8, 32, 33, 40, 64, 65, 100, 128, 200, 256, 500, 1024, 4096):
-            blocks = lstm_row_blocks(batch, hidden, cus)
+            blocks = lstm_row_blocks(batch, hidden, cus, 50)
             assert len(blocks) <= 4 and (blocks or batch > 32 or cus < 256)
             if blocks:
                 assert [r for r, _ in blocks] == [sum(n for _, n in blocks[:k]) for k in range(len(blocks))]
                 assert sum(n for _, n in blocks) == batch and all(n >= 1 for _, n in blocks)
                 assert all(hidden // 16 * ((n + 7) // 8) <= cus and (r % 8 == 0) for r, n in blocks)
     # step by step is the faster plan beyond these
-    assert lstm_row_blocks(128, 1024, 256) and not lstm_row_blocks(129, 1024, 256)
-    assert lstm_row_blocks(256, 256, 256) and not lstm_row_blocks(257, 256, 256)
+    assert lstm_row_blocks(128, 1024, 256, 50) and not lstm_row_blocks(129, 1024, 256, 50)
+    assert lstm_row_blocks(256, 256, 256, 50) and not lstm_row_blocks(257, 256, 256, 50)
+    # ... and several launches for sequences shorter than these
+    for launches, steps in ((1, 1), (2, 3), (3, 5), (4, 9)):
+        assert len(lstm_row_blocks(32 * launches, 1024, 256, steps)) == launches
+        assert launches == 1 or not lstm_row_blocks(32 * launches, 1024, 256, steps - 1)
 
 
 def test_product_never_imports_the_oracle():
