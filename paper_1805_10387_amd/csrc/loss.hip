@@ -186,7 +186,13 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
                 se += e[i][k];
             }
         se = block_reduce_lds<THREADS / 64, false>(se, red);
-        const float inv = 1.0f / se;
+        const float inv = valid ? 1.0f / se : 0.f;
+        if (!valid) {  // (the row may hold infinities, so its exponentials NaN: 0 x NaN)
+#pragma unroll
+            for (int i = 0; i < XENT_VECS; ++i)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) e[i][k] = 0.f;
+        }
         if (threadIdx.x == 0) row_loss[row] = valid ? (mx + __logf(se)) - zt : 0.f;
         const int vt = valid ? (tgt >> 3) : -1;  // the vector that holds the target class
 #pragma unroll
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
             if (v < nvec) {
                 float p[8];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) p[k] = valid ? e[i][k] * inv : 0.f;  // (the row may hold infinities: 0 x NaN)
+                for (int k = 0; k < 8; ++k) p[k] = e[i][k] * inv;
                 if (v == vt) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k)
