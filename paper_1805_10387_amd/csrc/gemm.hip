@@ -12,9 +12,9 @@ namespace mp {
 extern template int launch_tile<true, true>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
-extern template int launch_dtl_tile<true, true>(int, const GemmArgs&, int, hipStream_t);
-extern template int launch_dtl_tile<true, false>(int, const GemmArgs&, int, hipStream_t);
-extern template int launch_dtl_tile<false, false>(int, const GemmArgs&, int, hipStream_t);
+extern template int launch_dtl_tile<true, true>(int, const GemmArgs&, dim3, hipStream_t);
+extern template int launch_dtl_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
+extern template int launch_dtl_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
 extern template int launch_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
 extern template int launch_dtl_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
@@ -88,20 +88,39 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g, int a_kc,
 }
 
 // ------------------------------------------------------------------------------------ host side
-struct TileCfg {
-    int   bm, bn;
-    float eff;  // relative per-flop efficiency of the tile shape (bigger tiles reuse LDS data more)
+// Tile shapes and what they cost.  A workgroup's time is fixed + per_kt x its k-tiles (of 64), us, with one workgroup on every
+// compute unit; fixed2 + per_kt2 is that of a pair sharing one.  Fitted to 3000 launches of one card (M 512 to 8192, N and K 320 to
+// 4096, the three products, N(0,1) operands, every shape forced in turn): 3 us + the sum over the rounds is off by 5 to 9 % on average.
+struct TileTime {
+    float fixed, per_kt, fixed2, per_kt2;   // (per_kt2 0: a pair does not fit)
 };
-static const TileCfg kTiles[] = {{256, 256, 1.00f}, {256, 128, 0.85f}, {128, 256, 0.85f}, {128, 128, 0.65f},
-                                 {128, 64, 0.45f},  {64, 128, 0.45f},  {64, 64, 0.30f},   {32, 128, 0.25f},
+struct TileCfg {
+    int      bm, bn;
+    TileTime reg, dtl;  // register-staged kernel; kernel that loads straight into LDS (gemm_dtl.hpp; per_kt 0: not built)
+};
+static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
+                                 {256, 128, {3.68f, 0.75f}, {3.13f, 0.63f}},
+                                 {128, 256, {3.75f, 0.76f}, {3.30f, 0.64f}},
+                                 {128, 128, {1.99f, 0.50f, 3.02f, 1.08f}, {1.26f, 0.42f, 2.69f, 0.88f}},
+                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {}},
+                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {}},
+                                 {64, 64, {0.57f, 0.30f, 1.00f, 0.46f}, {}},
+                                 {32, 128, {1.00f, 0.34f, 1.60f, 0.63f}, {}},   // (not fitted: 0.9 of 128 x 64)
                                  // only when both operands are stored contraction-contiguous (the transposing loader
                                  // wants a power-of-two tile edge): fills the chip evenly when N is a multiple of 192 only
-                                 {256, 192, 0.88f}};
+                                 {256, 192, {5.98f, 0.88f}, {6.19f, 0.81f}}};
+constexpr int kCUs = 256;
+// us of `wgs` workgroups with k_tiles k-tiles each, without the launch
+static double rounds_us(const TileTime& t, long long wgs, double k_tiles) {
+    const double one = t.fixed + t.per_kt * k_tiles, two = t.fixed2 + t.per_kt2 * k_tiles;
+    if (t.per_kt2 == 0.f) return (double)((wgs + kCUs - 1) / kCUs) * one;
+    const long long rest = wgs % (2 * kCUs);
+    return (double)(wgs / (2 * kCUs)) * two + (rest == 0 ? 0. : rest <= kCUs ? one : two);
+}
 constexpr int   kTileKcOnly = 8;  // first index of the shapes restricted to that operand layout
 constexpr int   kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 // then 32 x 32 with the contraction dealt to 4 or to 8 waves (gemm_small.hpp), unbatched only
 constexpr int   kTileSmall4 = kNumTiles, kTileSmall8 = kNumTiles + 1;
-constexpr int   kCUs      = 256;
 
 // Products for the small kernel: up to two workgroups per compute unit, and not so long a contraction that reading the
 // operand panels anew for every 32 x 32 tile outweighs the short chain.  us alone, larger tiles against this kernel:
@@ -119,18 +138,22 @@ static bool      small_wins(int M, int N, int K) {
 static int small_waves(long long tiles, int K) { return tiles <= kCUs && K > 512 ? 8 : 4; }
 
 struct Plan {
-    int tile, splits, k_per_split;
+    int  tile, splits, k_per_split;
+    bool dtl;  // on the kernel that loads straight into LDS
 };
 static int g_force_tile = -1, g_force_splits = 1;
 
-// Which products take the direct-to-LDS kernels (mp_gemm_tuning_dtl): 0 = none, 1 (default) = weight-gradient products
-// (both operands output-contiguous), 2 = every product they are built for.
+// Which products take the direct-to-LDS kernels (mp_gemm_tuning_dtl): 0 = none, 1 (default) = where the plan finds them the
+// faster ones, 2 = every product they are built for.
 static int g_dtl_mode = 1;
 static int dtl_mode() { return g_dtl_mode; }
+// (contraction K in parts of kps: each has to hold the load stream's lead)
+static bool dtl_takes(int tile, int K, int splits, int kps) {
+    return tile < kNumTiles && kTiles[tile].dtl.per_kt > 0.f && (splits == 1 ? K : std::min(kps, K - (splits - 1) * kps)) >= DTL_MIN_K;
+}
 
-// Pick the tile shape (and split count when allowed) that minimises an estimate of run time:
-// rounds of 256 workgroups x work per workgroup / shape efficiency.
-static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool kc_kc = false) {
+// Pick the tile shape (and split count when allowed) that minimises the estimate of run time.  dtl: the operands are fit for the direct-to-LDS kernels
+static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool kc_kc, bool dtl) {
     // tuning aid (mp_gemm_tuning_override): force a tile shape / split count
     if (g_force_tile >= 0) {
         int t = g_force_tile < (kc_kc ? kNumTiles : kTileKcOnly) || g_force_tile >= kTileSmall4 ? g_force_tile : 0, sp = allow_split ? g_force_splits : 1;
@@ -142,11 +165,12 @@ static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
             --sp;
             kps = ((K + sp - 1) / sp + BK - 1) / BK * BK;
         }
-        return Plan{t, sp, kps > 0 ? kps : BK};
+        return Plan{t, sp, kps > 0 ? kps : BK, dtl && dtl_takes(t, K, sp, kps)};
     }
-    if (batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
-        return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK};
-    Plan   best{0, 1, 0};
+    const bool dtl_only = dtl && dtl_mode() == 2;
+    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
+        return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK, false};
+    Plan   best{0, 1, 0, false};
     double best_cost = 1e300;
     for (int t = 0; t < (kc_kc ? kNumTiles : kTileKcOnly); ++t) {
         const long long tm = (M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (N + kTiles[t].bn - 1) / kTiles[t].bn;
@@ -155,13 +179,14 @@ static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
         for (int s = 1; s <= max_s; s *= 2) {
             const int kps = ((K + s - 1) / s + BK - 1) / BK * BK;
             if (s > 1 && (kps < 4 * BK || (long long)(s - 1) * kps >= K)) break;
-            const long long wgs    = tiles * s;
-            const long long rounds = (wgs + kCUs - 1) / kCUs;
-            double cost = (double)rounds * kTiles[t].bm * kTiles[t].bn * ((double)kps + 2.0 * BK) / kTiles[t].eff;
-            if (s > 1) cost += (double)M * N * s * 6.0;  // writing and re-reading fp32 partials
+            const bool      d      = dtl && dtl_takes(t, K, s, kps);
+            if (dtl_only && !d) continue;
+            double cost = rounds_us(d ? kTiles[t].dtl : kTiles[t].reg, tiles * s, kps / (double)BK);
+            // the finish launch, and the fp32 partials written and read again (1024 x 1024 over 8192 in 4: 10.5 us, 512 x 512 in 8: 6.7)
+            if (s > 1) cost += 2.5 + 2.0e-6 * M * N * s;
             if (cost < best_cost) {
                 best_cost = cost;
-                best      = Plan{t, s, kps};
+                best      = Plan{t, s, kps, d};
             }
         }
     }
@@ -196,6 +221,13 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
     return interior || std::max(g.lda, g.ldb) < LD_BUFFER_64;
 }
 
+// What the direct-to-LDS kernels take: rows that are whole 16-byte pieces, a contraction of whole k-tiles and long enough for
+// the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
+static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
+    return dtl_mode() != 0 && g.aligned && batches == 1 && g.K % BK == 0 && g.K >= DTL_MIN_K && (a_kc || (!b_kc && g.M % 8 == 0)) &&
+           std::max(g.lda, g.ldb) < LD_BUFFER_256;
+}
+
 // Few ragged outputs over a contraction that short cost the scalar kernel less than the matrix cores' chain of loads, LDS and
 // final sum (us, matrix cores / scalar, forward: 1500 x 29 over 9 4.2 / 3.3, over 12 4.2 / 3.6, over 17 4.2 / 4.1; 512 x 512 over 9
 // 4.0 / 4.3; 64 products 37 x 37 over 9 4.6 / 3.3, over 17 4.7 / 4.2; 512 of 20 x 20 over 9 5.5 / 5.2.  Input gradients:
@@ -222,39 +254,27 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
         MP_LAUNCH_CHECK("gemm (generic)");
         return MP_OK;
     }
-    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc && b_kc);
-    if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc && b_kc);
+    const bool dtl = dtl_ok(g, a_kc, b_kc, batches);
+    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc && b_kc, dtl);
+    if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc && b_kc, dtl);
     // very long rows: 64 x 64 tiles, unless all loads are plain ones
     if (std::max(g.lda, g.ldb) >= LD_BUFFER_256 && !(g.aligned && g.M % 256 == 0 && g.N % 256 == 0 && g.K % BK == 0 && p.tile < kTileKcOnly))
-        p = Plan{6, 1, (g.K + BK - 1) / BK * BK};
+        p = Plan{6, 1, (g.K + BK - 1) / BK * BK, false};
     g.k_per_split = p.k_per_split;
     if (p.tile >= kTileSmall4 && (batches != 1 || (!a_kc && b_kc))) p.tile = 6;
     const bool    small = p.tile >= kTileSmall4;
     const int     waves = p.tile == kTileSmall4 ? 4 : 8;
-    const TileCfg tile  = small ? TileCfg{32, 32, 0.f} : kTiles[p.tile];
+    const TileCfg tile  = small ? TileCfg{32, 32, {}, {}} : kTiles[p.tile];
     g.tiles_m     = (g.M + tile.bm - 1) / tile.bm;
     g.tiles_n     = (g.N + tile.bn - 1) / tile.bn;
     // persistent along x: at most as many workgroups as fit on the chip at once (a multiple of 8, see the tile
     // mapping); batches and splits keep their own grid dimensions
     const int  ntiles   = g.tiles_m * g.tiles_n;
-    const int  lds_kib  = 2 * (tile.bm + tile.bn) * 128 / 1024;
-    const int  resident = kCUs * (lds_kib > 80 ? 1 : 2);
+    const int  resident = small ? ntiles : kCUs * ((p.dtl ? tile.dtl : tile.reg).per_kt2 > 0.f ? 2 : 1);
     const long long others = batches * p.splits;
     const int  gx = (others == 1 && ntiles > resident) ? resident : ntiles;
     const dim3 grid((unsigned)gx, (unsigned)batches, (unsigned)p.splits);
 
-    // interior, unbatched, unsplit problems on the large tiles: operands go straight from global memory into LDS
-    // (built for all three operand layouts, used where it is the faster one: both operands output-contiguous, i.e. the
-    // weight gradients.  A contraction-contiguous operand arrives there in 64-byte row pieces, which costs what the
-    // saved LDS stores gain, so forward and input-gradient products stay on the register-staged kernel)
-    const int bm = tile.bm, bn = tile.bn;
-    if (dtl_mode() != 0 && g.aligned && others == 1 && bm >= 128 && bn >= 128 && g.M % bm == 0 && g.N % bn == 0 && g.K % DK == 0 && g.K >= DK &&
-        (a_kc || !b_kc) && (dtl_mode() == 2 || (!a_kc && !b_kc))) {
-        const int gxd = ntiles > kCUs ? kCUs : ntiles;   // one workgroup per compute unit (its ring of stages fills the LDS)
-        if (a_kc && b_kc) return launch_dtl_tile<true, true>(p.tile, g, gxd, hs);
-        if (a_kc && !b_kc) return launch_dtl_tile<true, false>(p.tile, g, gxd, hs);
-        return launch_dtl_tile<false, false>(p.tile, g, gxd, hs);
-    }
     GemmArgs k = g;
     if (p.splits > 1) {  // partials to workspace, epilogue (scale, bias, rounding, flag) in the finish kernel
         k.C32       = ws;
@@ -264,6 +284,9 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     }
     int rc;
     if (small) rc = launch_small_tile(waves, a_kc, b_kc, k, p.splits, hs);
+    else if (p.dtl && a_kc && b_kc) rc = launch_dtl_tile<true, true>(p.tile, k, grid, hs);
+    else if (p.dtl && a_kc) rc = launch_dtl_tile<true, false>(p.tile, k, grid, hs);
+    else if (p.dtl) rc = launch_dtl_tile<false, false>(p.tile, k, grid, hs);
     else if (a_kc && b_kc) rc = launch_tile<true, true>(p.tile, k, grid, hs);
     else if (a_kc && !b_kc) rc = launch_tile<true, false>(p.tile, k, grid, hs);
     else if (!a_kc && !b_kc) rc = launch_tile<false, false>(p.tile, k, grid, hs);
@@ -302,18 +325,14 @@ static void zero_args(GemmArgs& g) { g = GemmArgs{}; }
 
 using namespace mp;
 
-// fp32 partial-sum floats the weight-gradient product [M,N] with contraction K will use
-// (0 when the plan does not split the contraction).
-static size_t splitk_floats(int M, int N, int K) {
+// fp32 partial-sum floats the product [M,N] with contraction K may use (0 when no plan splits the contraction): the
+// pointers and leading dimensions, which decide between the kernels, are not known yet.
+static size_t splitk_floats(int M, int N, int K, bool kc_kc) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const Plan p = make_plan(M, N, K, 1, true);
-    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N : 0;
-}
-
-static size_t splitk_floats_any(int M, int N, int K, bool allow, bool kc_kc) {
-    if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const Plan p = make_plan(M, N, K, 1, allow, kc_kc);
-    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N : 0;
+    const bool dtl = dtl_mode() != 0 && K % BK == 0 && K >= DTL_MIN_K;
+    const Plan p = make_plan(M, N, K, 1, true, kc_kc, false), q = make_plan(M, N, K, 1, true, kc_kc, dtl);
+    const int  splits = std::max(p.splits, q.splits);
+    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;
 }
 
 extern "C" int mp_gemm_tuning_override(int tile, int splits) {
@@ -334,7 +353,7 @@ extern "C" size_t mp_gemm_bwd_dw_workspace_bytes(const mp_gemm_desc* d, int with
     if (!d) return 0;
     const int rows = d->trans_w ? d->K : d->N, cols = d->trans_w ? d->N : d->K;
     size_t    b    = 0;
-    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats(rows, cols, d->M) * sizeof(float);
+    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats(rows, cols, d->M, false) * sizeof(float);
     if (with_db) b += mp_colsum_workspace_bytes(d->M, d->N);
     return b + 256;
 }
@@ -348,8 +367,8 @@ static bool split_ok(const GemmArgs& g, long long batches, const void* ws) {
 extern "C" size_t mp_gemm_split_workspace_bytes(const mp_gemm_desc* d) {
     if (!d || d->M <= 0 || d->N <= 0 || d->K <= 0) return 0;
     // the larger of the forward (M x N over K) and dX (M x K over N) plans; 0 when neither would split
-    const size_t a = splitk_floats_any(d->M, d->N, d->K, true, d->trans_w == 0);
-    const size_t b = splitk_floats_any(d->M, d->K, d->N, true, d->trans_w == 1);
+    const size_t a = splitk_floats(d->M, d->N, d->K, d->trans_w == 0);
+    const size_t b = splitk_floats(d->M, d->K, d->N, d->trans_w == 1);
     return (a > b ? a : b) * sizeof(float);
 }
 
@@ -436,7 +455,7 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
         g.B = dY; g.ldb = d->ldy; g.sb_o = d->sy_outer; g.sb_i = d->sy_inner; g.N = d->N;
     }
     float*       wsf       = static_cast<float*>(ws);
-    const size_t sk_floats = batches == 1 ? splitk_floats(g.M, g.N, g.K) : 0;
+    const size_t sk_floats = batches == 1 ? splitk_floats(g.M, g.N, g.K, false) : 0;
     rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? wsf : nullptr, sk_floats, as_stream(stream));
     if (rc) return rc;
     if (db) {
@@ -503,7 +522,7 @@ extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, con
 extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_state* st, mp_stream stream) {
     MP_REQUIRE(items != nullptr && count >= 1 && count <= GROUP_MAX, "mp_gemm_bwd_dw_grouped: 1..%d items", GROUP_MAX);
     GemmArgs args[GROUP_MAX];
-    bool     m256 = true, n256 = true, k32 = true;
+    bool     m256 = true, n256 = true, dtl = dtl_mode() != 0;
     for (int i = 0; i < count; ++i) {
         const mp_gemm_desc* d = &items[i].desc;
         int rc = check_desc(d, "mp_gemm_bwd_dw_grouped");
@@ -511,7 +530,7 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
         MP_REQUIRE(items[i].dY && items[i].X && items[i].dW, "mp_gemm_bwd_dw_grouped: item %d has a NULL operand", i);
         GemmArgs& g = args[i];
         zero_args(g);
-        g.C = items[i].dW; g.found_inf = st ? &st->found_inf : nullptr;
+        g.C = items[i].dW;
         g.K = d->M; g.ldc = d->ldw; g.batch_inner = 1; g.alpha = d->alpha;
         if (!d->trans_w) {  // dW[N,K] = dY^T X
             g.A = items[i].dY; g.lda = d->ldy; g.M = d->N;
@@ -530,22 +549,23 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
         }
         m256 = m256 && g.M % 256 == 0;
         n256 = n256 && g.N % 256 == 0;
-        k32  = k32 && g.K % DK == 0;
+        dtl  = dtl && g.K >= DTL_MIN_K && std::max(g.lda, g.ldb) < LD_BUFFER_256;
     }
-    // Tile shape: the one with the least estimated time, rounds of one work item per compute unit times the tile's time
-    // (relative efficiencies as in kTiles).  Large tiles win once they fill the chip (a layer with d_model 1024: 192 tiles
-    // of 256 x 256 and 56 strips in one round); with fewer, most compute units would idle through a long contraction
-    // (d_model 512, 4096 tokens: 48 such tiles, 92 us, against 192 of 128 x 128, 49 us).
-    const bool dtl = dtl_mode() != 0 && k32;
-    int        bm = 128, bn = 128;
-    double     best_cost = 1e300;
+    // Tile shape: the one with the least estimated time (a strip of a bias gradient counted as a tile).  Large tiles win once
+    // they fill the chip (a layer with d_model 1024: 192 tiles of 256 x 256 and 56 strips in one round); with fewer, most
+    // compute units would idle through a long contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the
+    // register-staged kernels, against 192 of 128 x 128, 49 us).
+    int    k_max = 0;
+    for (int i = 0; i < count; ++i) k_max = std::max(k_max, args[i].K);
+    int    bm = 128, bn = 128;
+    double best_cost = 1e300;
     for (int t : {0, 1, 3}) {
         const int tm = kTiles[t].bm, tn = kTiles[t].bn;
         if ((tm == 256 && !m256) || (tn == 256 && !n256) || (t == 1 && !dtl)) continue;
         long long n_items = 0;
         for (int i = 0; i < count; ++i)
             n_items += (long long)(args[i].M / tm) * (args[i].N / tn) + (items[i].db ? items[i].desc.N / BIAS_COLS : 0);
-        const double cost = (double)((n_items + kCUs - 1) / kCUs) * tm * tn / kTiles[t].eff;
+        const double cost = rounds_us(dtl ? kTiles[t].dtl : kTiles[t].reg, n_items, k_max / (double)BK);
         if (cost < best_cost) {
             best_cost = cost;
             bm        = tm;
@@ -561,13 +581,12 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
     ga.count = count;
     long long total = 0;
     for (int i = 0; i < count; ++i) {
-        GemmArgs g = args[order[i]];
-        g.tiles_m  = g.M / bm;
-        g.tiles_n  = g.N / bn;
-        ga.p[i]          = g;
+        const GemmArgs& g = args[order[i]];
+        ga.p[i]          = GroupItem{g.A, g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.M / bm, g.N / bn, g.alpha};
         ga.tile_start[i] = (int)total;
-        total += (long long)g.tiles_m * g.tiles_n;
+        total += (long long)(g.M / bm) * (g.N / bn);
     }
+    ga.found_inf = st ? &st->found_inf : nullptr;
     MP_REQUIRE(total < (1 << 24), "mp_gemm_bwd_dw_grouped: too many tiles");
     for (int i = count; i <= GROUP_MAX; ++i) ga.tile_start[i] = (int)total;
     // bias gradients: strips of BIAS_COLS columns of dY[M, N], numbered after the product tiles (same item order)
@@ -585,7 +604,7 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
     for (int i = ga.nbias; i <= GROUP_MAX; ++i) ga.strip_start[i] = strips;
     if (dtl) {
         if (bn == 256) return launch_dtl_grouped<256, 256>(ga, kCUs, as_stream(stream));
-        return bm == 256 ? launch_dtl_grouped<256, 128>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, kCUs, as_stream(stream));
+        return bm == 256 ? launch_dtl_grouped<256, 128>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
     }
     return bm == 256 ? launch_grouped<256, 256>(ga, kCUs, as_stream(stream)) : launch_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
 }

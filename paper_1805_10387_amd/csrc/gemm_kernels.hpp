@@ -706,8 +706,16 @@ struct BiasItem {
     unsigned short*       db;
     int                   ld, rows;
 };
+// (what such a problem needs of GemmArgs, no more: all of them sit in scalar registers while a tile's is chosen)
+struct GroupItem {
+    const uint16_t *A, *B;
+    uint16_t*       C;
+    int             M, N, K, lda, ldb, ldc, tiles_m, tiles_n;
+    float           alpha;
+};
 struct GroupArgs {
-    GemmArgs p[GROUP_MAX];
+    GroupItem p[GROUP_MAX];
+    int*     found_inf;  // one flag for the whole group
     int      tile_start[GROUP_MAX + 1];
     int      count;
     BiasItem b[GROUP_MAX];
@@ -758,6 +766,27 @@ __device__ inline void colsum_strip(const BiasItem it, int strip, char* smem, bo
     __syncthreads();
 }
 
+// The problem that tile vb belongs to, chosen with wave-uniform selects over statically indexed entries, so that the
+// descriptor stays in scalar registers; `first`: its first tile.
+__device__ inline GemmArgs group_problem(const GroupArgs& ga, const int vb, int& first) {
+    GroupItem p = ga.p[0];
+    first       = 0;
+#pragma unroll
+    for (int q = 1; q < GROUP_MAX; ++q) {
+        if (q < ga.count && vb >= ga.tile_start[q]) {
+            p     = ga.p[q];
+            first = ga.tile_start[q];
+        }
+    }
+    GemmArgs g{};
+    g.A = p.A; g.B = p.B; g.C = p.C; g.found_inf = ga.found_inf;
+    g.M = p.M; g.N = p.N; g.K = p.K;
+    g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc;
+    g.tiles_m = p.tiles_m; g.tiles_n = p.tiles_n;
+    g.batch_inner = 1; g.alpha = p.alpha; g.k_per_split = p.K;
+    return g;
+}
+
 // the strips of a grouped launch, work items total .. total + strips - 1
 __device__ inline void group_bias_item(const GroupArgs& ga, int s, char* smem, bool& bad) {
     BiasItem it    = ga.b[0];
@@ -776,7 +805,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_grouped_kernel(GroupArgs ga) {
     extern __shared__ __align__(16) char smem[];
     bool      bad_any = false;
-    int*      flag    = ga.p[0].found_inf;  // one flag for the whole group
+    int*      flag    = ga.found_inf;
     const int total   = ga.tile_start[ga.count];
     const int items   = total + ga.strip_start[ga.nbias];
     for (int vb0 = blockIdx.x; vb0 < items; vb0 += gridDim.x) {
@@ -790,17 +819,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_grouped_kernel(GroupArgs ga
         // tiles (neighbouring tiles share operand panels)
         const int xq = total >> 3, xrem = total & 7, xx = vb0 & 7;
         const int vb = xx * xq + min(xx, xrem) + (vb0 >> 3);
-        // the problem this tile belongs to: chosen with wave-uniform selects over statically indexed entries, so
-        // the descriptor stays in scalar registers
-        GemmArgs g     = ga.p[0];
-        int      first = 0;
-#pragma unroll
-        for (int q = 1; q < GROUP_MAX; ++q) {
-            if (q < ga.count && vb >= ga.tile_start[q]) {
-                g     = ga.p[q];
-                first = ga.tile_start[q];
-            }
-        }
+        int            first;
+        const GemmArgs g = group_problem(ga, vb, first);
         bool bad = false;
         OperandStream<BM, BN, A_KC, B_KC> S;
         S.init(g.lda, g.ldb);

@@ -3,5 +3,5 @@
 
 namespace mp {
 template int launch_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
-template int launch_dtl_tile<true, false>(int, const GemmArgs&, int, hipStream_t);
+template int launch_dtl_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
 }  // namespace mp

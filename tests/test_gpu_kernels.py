@@ -89,11 +89,11 @@ def test_gemm_workgroups_that_take_several_tiles(tile, M, N, K):
 @pytest.mark.parametrize("tile,M,N,K", [(0, 4352, 4096, 256), (0, 512, 512, 32), (0, 256, 768, 1056), (1, 2304, 1152, 96),
                                         (2, 1152, 2304, 160), (3, 2560, 3456, 512), (3, 128, 128, 32), (8, 512, 384, 224)])
 def test_gemm_direct_to_lds_kernels_all_layouts(tile, M, N, K):
-    """The kernels whose operand tiles go from global memory straight into LDS (ring of 32-deep k-tiles; transposing LDS
-    reads for output-contiguous operands), forced for every product they are built for: forward (both operands
+    """The kernels whose operand tiles go from global memory straight into LDS (transposing LDS reads for output-contiguous
+    operands), forced for every product they are built for: forward (both operands
     contraction-contiguous), dX (second operand output-contiguous) and dW (both output-contiguous), every tile shape,
-    one and several tiles per workgroup (the ring then runs on from tile to tile), k-tile counts below, at and above the
-    ring depth, with the epilogues that read a second operand and the overflow flag."""
+    one and several tiles per workgroup (the load stream then runs on from tile to tile), contractions below (register-staged
+    kernels), at and above the shortest they take, with the epilogues that read a second operand and the overflow flag."""
     r = RNG(M + N + K + tile + 3)
     x, w, b = S16(r.standard_normal((M, K))), S16(r.standard_normal((N, K)) * 0.1), S16(r.standard_normal(N))
     dy, src, other = S16(r.standard_normal((M, N))), S16(np.maximum(r.standard_normal((M, K)), 0)), S16(r.standard_normal((M, K)))
@@ -129,6 +129,65 @@ def test_gemm_direct_to_lds_kernels_all_layouts(tile, M, N, K):
     assert_close16(dw0, MIXED.store(dy.T @ x), 1e-3, max_ulp=1, what="dw, register-staged")
     with pytest.raises(mp.MPError):
         mp.mp_gemm_tuning_dtl(3)
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 8])
+@pytest.mark.parametrize("rows,cols,depth,splits", [(264, 200, 192, 1), (1, 8, 256, 1), (257, 392, 320, 1), (3233, 1544, 448, 1),
+                                                    (128, 256, 1024, 3), (136, 264, 1344, 4), (512, 384, 192, 1)])
+def test_gemm_direct_to_lds_borders(tile, rows, cols, depth, splits):
+    """The same kernels where output tiles stick out of the matrix (rows and columns just past a tile, far below one, several
+    tiles per workgroup), at the shortest contraction they take (three k-tiles), with odd k-tile counts and with a split
+    contraction whose last part is shorter.  Operands and outputs are blocks of larger arrays: NaN around the operands must not
+    get in, nothing around an output may change.  mp_gemm_tuning_dtl(2) keeps the call on these kernels."""
+    r = RNG(rows + cols + depth + tile)
+
+    def block(a, pad):
+        big = np.full((a.shape[0] + 3, a.shape[1] + pad), np.nan, np.float32)
+        big[:a.shape[0], :a.shape[1]] = a
+        return h16(big)[:a.shape[0], :a.shape[1]]
+
+    def out(m, n, pad, dtype=torch.float16):
+        big = torch.full((m + 3, n + pad), 7.0, dtype=dtype, device="cuda")
+        return big, big[:m, :n]
+
+    a, b, bias = S16(r.standard_normal((rows, depth))), S16(r.standard_normal((cols, depth)) * 0.1), S16(r.standard_normal(cols))
+    other = S16(r.standard_normal((rows, cols)))
+    ref = MIXED.store(a @ b.T)
+    ws = ws_bytes(16 * rows * cols * 4 + 4096)
+    mp.mp_gemm_tuning_override(tile, splits)
+    mp.mp_gemm_tuning_dtl(2)
+    try:
+        big_y, y = out(rows, cols, 16)
+        d = mp.gemm_desc(rows, cols, depth, ldx=depth + 8, ldw=depth + 16, ldy=cols + 16, epilogue=1)
+        mp.mp_gemm_fwd_ws(d, block(a, 8), block(b, 16), h16(bias), None, y, ws=ws)
+        big_x, dx = out(rows, cols, 8)
+        d = mp.gemm_desc(rows, depth, cols, ldx=cols + 8, ldw=cols + 8, ldy=depth + 8)
+        mp.mp_gemm_bwd_dx(d, block(a, 8), block(b.T, 8), dx, add=block(other, 24), ld_aux=cols + 24)
+        dw_ok = rows % 8 == 0
+        big_w, dw = out(rows, cols, 8)
+        st = make_state()
+        if dw_ok:
+            d = mp.gemm_desc(depth, rows, cols, ldx=cols + 8, ldw=cols + 8, ldy=rows + 8)
+            mp.mp_gemm_bwd_dw(d, block(a.T, 8), block(b.T, 8), dw, None, st, ws)
+        f32 = torch.full((rows + 1, cols), 7.0, dtype=torch.float32, device="cuda")
+        acc = torch.from_numpy(r.standard_normal((rows, cols)).astype(np.float32)).cuda()
+        d = mp.gemm_desc(rows, cols, depth, ldx=depth + 8, ldw=depth + 16, alpha=0.5)
+        mp.mp_gemm_fwd(d, block(a, 8), block(b, 16), None, acc, None, f32)
+    finally:
+        mp.mp_gemm_tuning_override(-1, 0)
+        mp.mp_gemm_tuning_dtl(1)
+    assert_close16(y, MIXED.store(a @ b.T + bias), 1e-3, max_ulp=1, what="fwd")
+    assert_close16(dx, L.add_store(MIXED, ref, other), 1e-3, what="dx add")
+    # fp32: sums of `depth` products in any order
+    got, want = f32[:rows].cpu().numpy(), 0.5 * (a.astype(np.float64) @ b.T.astype(np.float64)) + acc.cpu().numpy()
+    bound = 2.0 ** -24 * depth * (0.5 * (np.abs(a).astype(np.float64) @ np.abs(b).T) + np.abs(acc.cpu().numpy())) + 2.0 ** -23 * np.abs(want)
+    assert np.all(np.abs(got - want) <= bound)
+    assert torch.all(f32[rows:] == 7.0)
+    for big in [big_y, big_x] + ([big_w] if dw_ok else []):
+        assert torch.all(big[rows:] == 7.0) and torch.all(big[:, cols:] == 7.0)
+    if dw_ok:
+        assert_close16(dw, ref, 1e-3, max_ulp=1, what="dw")
+        assert mp.scale_state_read(st).found_inf == 0
 
 
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
