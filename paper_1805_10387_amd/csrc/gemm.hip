@@ -102,8 +102,8 @@ static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
                                  {256, 128, {3.68f, 0.75f}, {3.13f, 0.63f}},
                                  {128, 256, {3.75f, 0.76f}, {3.30f, 0.64f}},
                                  {128, 128, {1.99f, 0.50f, 3.02f, 1.08f}, {1.26f, 0.42f, 2.69f, 0.88f}},
-                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {}},
-                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {}},
+                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {1.74f, 0.27f}},
+                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {1.45f, 0.27f}},
                                  {64, 64, {0.57f, 0.30f, 1.00f, 0.46f}, {}},
                                  {32, 128, {1.00f, 0.34f, 1.60f, 0.63f}, {}},   // (not fitted: 0.9 of 128 x 64)
                                  // only when both operands are stored contraction-contiguous (the transposing loader

@@ -51,7 +51,7 @@ constexpr size_t dtl_lds(int bm, int bn) { return 2 * (size_t)dtl_stage(bm, bn) 
 // block and then the others.  GUARD: rows may lie outside the matrix (see rsrc below).
 template <int R, int WR, bool KC, bool SPLIT, bool GUARD>
 struct DtlOperand {
-    static_assert(R % 64 == 0 && (KC || R == 128 || R == 256), "tile edge");
+    static_assert(R % 64 == 0 && (KC || R == 64 || R == 128 || R == 256), "tile edge");
     static constexpr int BYTES = R * 128;             // one k-tile: R rows x 64 k x 2 bytes
     static constexpr int NL    = R / 32;              // loads per wave and k-tile (1 KB each)
     static constexpr int UR    = SPLIT ? R / 2 : R;   // rows of a unit
@@ -265,6 +265,33 @@ __device__ __forceinline__ void dtl_epilogue(const GemmArgs& g, f32x4 (&acc)[TM]
     bad |= mag[0] >= 0x7C00 || mag[1] >= 0x7C00;
 }
 
+// tile numbering: XCD-contiguous runs, bands of 4 tile rows (as gemm_kernel)
+__device__ __forceinline__ int dtl_tile_of(const int vb, const int ntiles) {
+    const int q = ntiles >> 3, rem = ntiles & 7, x = vb & 7, local = vb >> 3;
+    return x * q + min(x, rem) + local;
+}
+template <int BM, int BN>
+__device__ __forceinline__ void dtl_tile_origin(const GemmArgs& g, const int p, int& mm, int& nn) {
+    constexpr int GROUP = 4;
+    const int     band  = p / (GROUP * g.tiles_n);
+    const int     first = band * GROUP;
+    const int     gsz   = min(GROUP, g.tiles_m - first);
+    const int     inb   = p - band * GROUP * g.tiles_n;
+    mm                  = (first + inb % gsz) * BM;
+    nn                  = (inb / gsz) * BN;
+}
+// buffer descriptors (words 0 and 1: address, word 2: size)
+__device__ __forceinline__ void buffer_move(u32x4& r, const long long d) {
+    const unsigned long long a = (((unsigned long long)r[1] << 32) | r[0]) + d;
+    r[0] = (unsigned)a;
+    r[1] = (unsigned)(a >> 32);
+}
+__device__ __forceinline__ u32x4 buffer_at(const uint16_t* p, const long long bytes, const unsigned size) {
+    u32x4 r = {0u, 0u, size, 0x00020000u};
+    buffer_move(r, (long long)reinterpret_cast<unsigned long long>(p) + bytes);
+    return r;
+}
+
 // The output tiles vb0, vb0 + vb_step, ... (< tiles_m * tiles_n) of problem g, one after the other, with the load stream
 // running on from tile to tile.  remap: number the tiles so that each XCD gets a contiguous run (a launch of one problem);
 // otherwise vb is the tile number itself (the caller has placed the tiles).  split: g describes one part of a split contraction.
@@ -297,21 +324,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
     const int nkt    = g.K / BK;
     const int ntiles = g.tiles_m * g.tiles_n;
 
-    // tile numbering: XCD-contiguous runs, bands of 4 tile rows (as gemm_kernel)
-    auto tile_of = [&](const int vb) {
-        if (!remap) return vb;
-        const int q = ntiles >> 3, rem = ntiles & 7, x = vb & 7, local = vb >> 3;
-        return x * q + min(x, rem) + local;
-    };
-    auto tile_origin = [&](const int p, int& mm, int& nn) {
-        constexpr int GROUP = 4;
-        const int     band  = p / (GROUP * g.tiles_n);
-        const int     first = band * GROUP;
-        const int     gsz   = min(GROUP, g.tiles_m - first);
-        const int     inb   = p - band * GROUP * g.tiles_n;
-        mm                  = (first + inb % gsz) * BM;
-        nn                  = (inb / gsz) * BN;
-    };
+    auto tile_origin = [&](const int vb, int& mm, int& nn) { dtl_tile_origin<BM, BN>(g, remap ? dtl_tile_of(vb, ntiles) : vb, mm, nn); };
 
     OpA oa;
     OpB ob;
@@ -322,15 +335,9 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
 
     // ---- the load stream: k-tile after k-tile, output tile after output tile, two k-tiles ahead of the matrix cores
     int m0, n0;
-    tile_origin(tile_of(vb0), m0, n0);
-    auto move = [](u32x4& r, const long long d) {   // (words 0 and 1 of a buffer descriptor are its address)
-        const unsigned long long a = (((unsigned long long)r[1] << 32) | r[0]) + d;
-        r[0] = (unsigned)a;
-        r[1] = (unsigned)(a >> 32);
-    };
-    u32x4 ra = {0u, 0u, OpA::span(min(g.M - m0, BM), g.lda), 0x00020000u}, rb = {0u, 0u, OpB::span(min(g.N - n0, BN), g.ldb), 0x00020000u};
-    move(ra, (long long)reinterpret_cast<unsigned long long>(g.A) + OpA::origin(m0, g.lda));
-    move(rb, (long long)reinterpret_cast<unsigned long long>(g.B) + OpB::origin(n0, g.ldb));
+    tile_origin(vb0, m0, n0);
+    u32x4 ra = buffer_at(g.A, OpA::origin(m0, g.lda), OpA::span(min(g.M - m0, BM), g.lda));
+    u32x4 rb = buffer_at(g.B, OpB::origin(n0, g.ldb), OpB::span(min(g.N - n0, BN), g.ldb));
     int      left = nkt;      // k-tiles of its output tile from where the stream stands
     unsigned l_st = 0;        // LDS offset of the stage it writes
     // load q of a phase: its LDS destination (SET), or the load itself
@@ -370,8 +377,8 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         static_for<L1>([&](auto qc) { load1(qc, Set{}); asm volatile("s_nop 0"); load1(qc, Load{}); });
         l_st = STAGE - l_st;
         --left;
-        move(ra, step_a);
-        move(rb, step_b);
+        buffer_move(ra, step_a);
+        buffer_move(rb, step_b);
     });
     // the bias starts the accumulators; a tile's values are requested ahead of the previous tile's output stores (a wait for
     // a load behind them would be a wait for the stores)
@@ -397,7 +404,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         // from the last k-tile of this tile to the first of the next (or back to this tile's own first: those loads go to
         // stages nobody reads any more, are in bounds, and keep the count of loads in flight uniform)
         int m1 = m0, n1 = n0;
-        if (vb + vb_step < ntiles) tile_origin(tile_of(vb + vb_step), m1, n1);
+        if (vb + vb_step < ntiles) tile_origin(vb + vb_step, m1, n1);
         const long long jump_a = OpA::origin(m1, g.lda) - OpA::origin(m0, g.lda) - (nkt - 1) * step_a;
         const long long jump_b = OpB::origin(n1, g.ldb) - OpB::origin(n0, g.ldb) - (nkt - 1) * step_b;
         f32x4 acc[TM][TN];
@@ -471,8 +478,8 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             l_st = STAGE - l_st;
             const bool last = left == 1;
             left = last ? nkt : left - 1;
-            move(ra, last ? jump_a : step_a);
-            move(rb, last ? jump_b : step_b);
+            buffer_move(ra, last ? jump_a : step_a);
+            buffer_move(rb, last ? jump_b : step_b);
             if (MODE != INTERIOR && last) {
                 ra[2] = OpA::span(min(g.M - m1, BM), g.lda);
                 rb[2] = OpB::span(min(g.N - n1, BN), g.ldb);
@@ -484,6 +491,167 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         n0 = n1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last (unused) loads have landed before the LDS is reused
+    __syncthreads();
+}
+
+// The same for tiles of 128 x 64 and 64 x 128, which have a quarter of the matrix-core work per k-tile: a k-tile's loads need
+// several k-tiles of lead, so the stages form a ring (six, all of a compute unit's LDS) and each is worked on as a whole; a
+// stage is free once its fragments are in registers, one k-tile ahead of its use.  One barrier per k-tile.  What bounds a
+// k-tile is the LDS (48 KB read and 24 KB written against 16 matrix-core instructions per wave) and the barrier: 0.27 us, the
+// register-staged kernel 0.38 (4096 x 512 over 2048: 16.4 -> 13.5 us; input gradient 1600 x 1024 over 4096: 29.5 -> 23.2).
+constexpr int    DEEP_STAGES = 6;
+constexpr size_t deep_lds(int bm, int bn) { return DEEP_STAGES * (size_t)dtl_stage(bm, bn) + 4 * dtl_out_bytes(bn / 2); }
+template <int BM, int BN, bool A_KC, bool B_KC, int MODE>
+__device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, const int vb_step, const bool split, char* smem, bool& bad) {
+    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+    typedef DtlOperand<BM, WM, A_KC, false, MODE != INTERIOR> OpA;
+    typedef DtlOperand<BN, WN, B_KC, false, MODE != INTERIOR> OpB;
+    constexpr int STAGE = dtl_stage(BM, BN), MS = TM * TN * 2, NA = OpA::NL, NL = NA + OpB::NL, NR = 2 * (TM + TN);
+    constexpr int PI = MS / NL;   // matrix-core instructions per load
+    static_assert(PI >= 2 && (DEEP_STAGES - 1) * NL <= 63, "loads in flight must fit the counter");
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned lds_a = (unsigned)(size_t)MP_LDS_PTR(smem) + wave * 1024, lds_b = lds_a + OpA::BYTES;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int eh = lane >> 4;
+    const int nkt    = g.K / BK;
+    const int ntiles = g.tiles_m * g.tiles_n;
+    auto tile_origin = [&](const int vb, int& mm, int& nn) { dtl_tile_origin<BM, BN>(g, dtl_tile_of(vb, ntiles), mm, nn); };
+
+    OpA oa;
+    OpB ob;
+    oa.init(g.lda, wave, lane, wm);
+    ob.init(g.ldb, wave, lane, wn);
+    const long long step_a = A_KC ? 2 * BK : 2ll * BK * g.lda, step_b = B_KC ? 2 * BK : 2ll * BK * g.ldb;
+
+    // the load stream: k-tile after k-tile, output tile after output tile (past the last k-tile of all it starts that tile
+    // again: in bounds, into stages nobody reads any more)
+    u32x4    ra, rb;
+    int      l_vb = vb0, left = nkt;
+    unsigned l_st = 0;
+    auto stand = [&] {
+        int m, n;
+        tile_origin(l_vb, m, n);
+        ra = buffer_at(g.A, OpA::origin(m, g.lda), OpA::span(min(g.M - m, BM), g.lda));
+        rb = buffer_at(g.B, OpB::origin(n, g.ldb), OpB::span(min(g.N - n, BN), g.ldb));
+    };
+    stand();
+    auto load = [&](auto qc, auto setc) {
+        constexpr int  q   = decltype(qc)::value;
+        constexpr bool set = decltype(setc)::value;
+        if constexpr (q < NA) {
+            if constexpr (set) OpA::template target<q>(lds_a + l_st);
+            else oa.template issue<q>(ra);
+        } else {
+            if constexpr (set) OpB::template target<q - NA>(lds_b + l_st);
+            else ob.template issue<q - NA>(rb);
+        }
+    };
+    auto advance = [&] {
+        l_st = l_st + STAGE == DEEP_STAGES * STAGE ? 0 : l_st + STAGE;
+        if (__builtin_expect(--left > 0, 1)) {
+            buffer_move(ra, step_a);
+            buffer_move(rb, step_b);
+        } else {
+            if (l_vb + vb_step < ntiles) l_vb += vb_step;
+            left = nkt;
+            stand();
+        }
+    };
+    typedef std::true_type  Set;
+    typedef std::false_type Load;
+    f16x8 af[2][2][TM], bf[2][2][TN];  // fragments [k-tile parity][slice][tile]
+    auto  read = [&](const char* st, auto pc, auto fc) {
+        constexpr int p = decltype(pc)::value, f = decltype(fc)::value, s = f / (TM + TN), t = f % (TM + TN);
+        if constexpr (t < TN) bf[p][s][t] = ob.template frag<s, 0, t>(st + OpA::BYTES);
+        else af[p][s][t - TN] = oa.template frag<s, 0, t - TN>(st);
+    };
+    typedef unsigned u32x2b __attribute__((ext_vector_type(2)));
+    u32x2b     braw[TN];
+    const bool fold_bias = g.bias != nullptr && g.C32 == nullptr && g.alpha == 1.f;
+    auto load_bias = [&](const int nn) {
+        static_for<TN>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const int     n = nn + wn * WN + 16 * j + 4 * eh;
+            braw[j] = {0u, 0u};
+            if (MODE == INTERIOR || n < g.N) braw[j] = *reinterpret_cast<const u32x2b*>(g.bias + n);
+        });
+    };
+    int m0, n0;
+    tile_origin(vb0, m0, n0);
+    if (fold_bias) load_bias(n0);
+    static_for<DEEP_STAGES>([&](auto) {
+        static_for<NL>([&](auto qc) { load(qc, Set{}); asm volatile("s_nop 0"); load(qc, Load{}); });
+        advance();
+    });
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DEEP_STAGES - 1) * NL) : "memory");
+    __syncthreads();
+    unsigned c_st = 0;
+    static_for<NR>([&](auto fc) { read(smem, std::integral_constant<int, 0>{}, fc); });
+
+    for (int vb = vb0; vb < ntiles; vb += vb_step) {
+        int m1 = m0, n1 = n0;
+        if (vb + vb_step < ntiles) tile_origin(vb + vb_step, m1, n1);
+        f32x4 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (fold_bias) {
+            static_for<TN>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float b = h2f((uint16_t)((e & 1) ? (braw[j][e >> 1] >> 16) : (braw[j][e >> 1] & 0xFFFFu)));
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) acc[i][j][e] = acc_put(b);
+                }
+            });
+        }
+        auto ktile = [&](auto pc) {
+            constexpr int p = decltype(pc)::value;
+            c_st = c_st + STAGE == DEEP_STAGES * STAGE ? 0 : c_st + STAGE;
+            const char* st = smem + c_st;   // of the next k-tile
+            __builtin_amdgcn_sched_barrier(0);
+            // the next k-tile has landed, and every wave has this one's fragments in registers
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((DEEP_STAGES - 2) * NL) : "memory");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<MS>([&](auto mc) {
+                constexpr int m = decltype(mc)::value, s = m / (TM * TN), i = m / TN % TM, j = m % TN;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[p][s][j], af[p][s][i], acc[i][j], 0, 0, 0);
+                constexpr int f0 = m * NR / (MS - 2), f1 = (m + 1) * NR / (MS - 2);
+                static_for<(f1 < NR ? f1 : NR) - (f0 < NR ? f0 : NR)>([&](auto fc) { read(st, std::integral_constant<int, 1 - p>{}, std::integral_constant<int, f0 + decltype(fc)::value>{}); });
+                if constexpr (m / PI < NL && m % PI == 0) load(std::integral_constant<int, m / PI>{}, Set{});
+                if constexpr (m / PI < NL && m % PI == 1) load(std::integral_constant<int, m / PI>{}, Load{});
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            advance();
+        };
+        typedef std::integral_constant<int, 0> P0;
+        typedef std::integral_constant<int, 1> P1;
+        int kt = 0;
+        for (; kt + 1 < nkt; kt += 2) {
+            ktile(P0{});
+            ktile(P1{});
+        }
+        if (kt < nkt) {
+            ktile(P0{});
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {   // (a tile starts with its first fragments in set 0)
+#pragma unroll
+                for (int i = 0; i < TM; ++i) af[0][s][i] = af[1][s][i];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) bf[0][s][j] = bf[1][s][j];
+            }
+        }
+        if (fold_bias) load_bias(n1);
+        dtl_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM, n0 + wn * WN, split, fold_bias, smem + DEEP_STAGES * STAGE + wave * dtl_out_bytes(WN), bad);
+        m0 = m1;
+        n0 = n1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 }
 
@@ -500,7 +668,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_kernel(GemmArgs g) {
         g.C32 += (long long)blockIdx.z * g.M * g.N;
         g.K = min(g.k_per_split, g.K - (int)k0);
     }
-    dtl_tiles<BM, BN, A_KC, B_KC, MODE>(g, blockIdx.x, gridDim.x, true, split, smem, bad);
+    if constexpr (BM * BN < 128 * 128) deep_tiles<BM, BN, A_KC, B_KC, MODE>(g, blockIdx.x, gridDim.x, split, smem, bad);
+    else dtl_tiles<BM, BN, A_KC, B_KC, MODE>(g, blockIdx.x, gridDim.x, true, split, smem, bad);
     if (g.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(g.found_inf, 1);
     }
@@ -554,7 +723,7 @@ int launch_dtl_grouped(const GroupArgs& ga, int resident, hipStream_t hs) {
 // Launch (host): the caller has checked dtl_ok.
 template <int BM, int BN, bool AKC, bool BKC, int MODE>
 int launch_dtl_mode(const GemmArgs& g, dim3 grid, hipStream_t hs) {
-    constexpr size_t  lds = dtl_lds(BM, BN);
+    constexpr size_t  lds = BM * BN < 128 * 128 ? deep_lds(BM, BN) : dtl_lds(BM, BN);
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
     std::call_once(once, [] {
@@ -579,6 +748,8 @@ int launch_dtl_tile(int t, const GemmArgs& g, dim3 grid, hipStream_t hs) {
         case 1: return launch_dtl<256, 128, AKC, BKC>(g, grid, hs);
         case 2: return launch_dtl<128, 256, AKC, BKC>(g, grid, hs);
         case 3: return launch_dtl<128, 128, AKC, BKC>(g, grid, hs);
+        case 4: return launch_dtl<128, 64, AKC, BKC>(g, grid, hs);
+        case 5: return launch_dtl<64, 128, AKC, BKC>(g, grid, hs);
         case 8:
             if constexpr (AKC && BKC) return launch_dtl<256, 192, AKC, BKC>(g, grid, hs);
             [[fallthrough]];

@@ -87,7 +87,8 @@ def test_gemm_workgroups_that_take_several_tiles(tile, M, N, K):
 
 
 @pytest.mark.parametrize("tile,M,N,K", [(0, 4352, 4096, 256), (0, 512, 512, 32), (0, 256, 768, 1056), (1, 2304, 1152, 96),
-                                        (2, 1152, 2304, 160), (3, 2560, 3456, 512), (3, 128, 128, 32), (8, 512, 384, 224)])
+                                        (2, 1152, 2304, 160), (3, 2560, 3456, 512), (3, 128, 128, 32), (4, 4352, 704, 320), (5, 704, 4352, 320),
+                                        (8, 512, 384, 224)])
 def test_gemm_direct_to_lds_kernels_all_layouts(tile, M, N, K):
     """The kernels whose operand tiles go from global memory straight into LDS (transposing LDS reads for output-contiguous
     operands), forced for every product they are built for: forward (both operands
@@ -131,7 +132,7 @@ def test_gemm_direct_to_lds_kernels_all_layouts(tile, M, N, K):
         mp.mp_gemm_tuning_dtl(3)
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 8])
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 8])
 @pytest.mark.parametrize("rows,cols,depth,splits", [(264, 200, 192, 1), (1, 8, 256, 1), (257, 392, 320, 1), (3233, 1544, 448, 1),
                                                     (128, 256, 1024, 3), (136, 264, 1344, 4), (512, 384, 192, 1)])
 def test_gemm_direct_to_lds_borders(tile, rows, cols, depth, splits):
