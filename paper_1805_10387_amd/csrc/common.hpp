@@ -4,6 +4,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <stdarg.h>
+#include <type_traits>
 
 #include "mp.h"
 
@@ -54,15 +55,32 @@ __device__ __forceinline__ float round16(float x) { return (float)(f16)x; }
 __device__ __forceinline__ bool half_nonfinite(uint16_t b) { return (b & 0x7C00u) == 0x7C00u; }
 
 // ---- wave / block reductions (wave64) -----------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Butterflies over lane distances 32, 16, 8, 4, 2, 1 without a trip through LDS: the halves and the 16-lane rows trade places
+// by register swaps, the rest are rotations and permutations that ride on the additions.  (A distance through
+// ds_bpermute is an LDS round trip, six of them one after the other in every row reduction.)
+template <typename F>
+__device__ __forceinline__ float wave_butterfly(float v, F&& op) {
+    const auto swap = [&](const auto r) {
+        const unsigned a = r[0], b = r[1];  // (bit_cast wants whole objects, not vector elements)
+        v = op(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+    };
+    swap(__builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false));
+    swap(__builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false));
+    const auto with = [&](auto ctrl) {
+        const int i = __builtin_bit_cast(int, v);
+        v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xF, 0xF, false)));
+    };
+    with(std::integral_constant<int, 0x128>{});  // rotate a row of 16 by 8
+    with(std::integral_constant<int, 0x124>{});  // by 4 (halves of a row are alike by now)
+    with(std::integral_constant<int, 0x4E>{});   // quad: lanes 2 3 0 1
+    with(std::integral_constant<int, 0xB1>{});   // quad: lanes 1 0 3 2
     return v;
 }
+__device__ __forceinline__ float wave_sum(float v) {
+    return wave_butterfly(v, [](float a, float b) { return a + b; });
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_butterfly(v, [](float a, float b) { return fmaxf(a, b); });
 }
 // Sum over a block of NW waves; every thread gets the result.  `red` is NW floats of LDS.
 // Workgroup barrier that waits for the wave's LDS traffic only.  __syncthreads() is also a release fence: with global

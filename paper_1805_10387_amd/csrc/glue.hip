@@ -6,6 +6,7 @@
 #include "cell_math.hpp"
 #include "common.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace mp {
@@ -124,6 +125,7 @@ __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, 
 // --------------------------------------------------------------------------- LayerNorm
 // One wave per row.  MAXV 16-byte vectors per lane are kept in registers (d <= 64*8*MAXV).
 constexpr int LN_MAXV = 4;
+constexpr int LN_MAX_LDS = 160 * 1024;
 
 __global__ __launch_bounds__(GL_THREADS) void layernorm_fwd_kernel(int rows, int d, const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ a,
@@ -192,18 +194,22 @@ __global__ __launch_bounds__(GL_THREADS) void layernorm_fwd_kernel(int rows, int
 // which is the bias gradient of the linear layer whose output fed this LayerNorm).
 // MAXV = 16-byte vectors per lane (d <= 64 * 8 * MAXV).  The raw vectors of the wave's next row are requested
 // before the current row is reduced, so the two cross-lane reductions of a row overlap the next row's loads.
-template <bool ZSUM, int MAXV>
-__global__ __launch_bounds__(GL_THREADS) void layernorm_bwd_kernel(int rows, int d, const uint16_t* __restrict__ dy,
+// NW = waves of a workgroup: 8 where that leaves a workgroup for every compute unit, which halves the partials
+// (8192 x 1024 with the finish launch 23.0 -> 19.8 us, with 16-byte LDS accesses and reductions in registers).
+// In LDS the first and the second four of a lane's 8 columns lie apart (and 64 bytes off the banks' period), so that both
+// directions move 16 bytes per lane without conflicts.
+template <bool ZSUM, int MAXV, int NW>
+__global__ __launch_bounds__(64 * NW) void layernorm_bwd_kernel(int rows, int d, const uint16_t* __restrict__ dy,
                                                                    const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ a,
                                                                    const uint16_t* __restrict__ gamma,
                                                                    const float* __restrict__ mean_i,
                                                                    const float* __restrict__ rstd_i,
                                                                    uint16_t* __restrict__ dz, float* __restrict__ part) {
-    extern __shared__ float sm[];  // [GL_WAVES][NS][d]
+    extern __shared__ float sm[];  // [NW][NS][2][d / 2 + 16]
     constexpr int NS = ZSUM ? 3 : 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nvec = d >> 3;
+    const int nvec = d >> 3, half = d / 2 + 16;
     float     gam[MAXV][8], sg[MAXV][8], sb[MAXV][8], sz[ZSUM ? MAXV : 1][8];
 #pragma unroll
     for (int i = 0; i < MAXV; ++i) {
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(GL_THREADS) void layernorm_bwd_kernel(int rows, int
         }
         if (v < nvec) unpack8(*reinterpret_cast<const uint4*>(gamma + v * 8), gam[i]);
     }
-    const int stride = gridDim.x * GL_WAVES;
+    const int stride = gridDim.x * NW;
     uint4     rdy[MAXV], rx[MAXV], ra[MAXV];  // raw vectors of the row being worked on
     float     mean = 0.f, rstd = 0.f;
     auto fetch = [&](int row, uint4* qdy, uint4* qx, uint4* qa, float& mu, float& rs) {
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(GL_THREADS) void layernorm_bwd_kernel(int rows, int
         mu = mean_i[row];
         rs = rstd_i[row];
     };
-    int row = blockIdx.x * GL_WAVES + wave;
+    int row = blockIdx.x * NW + wave;
     if (row < rows) fetch(row, rdy, rx, ra, mean, rstd);
     for (; row < rows; row += stride) {
         uint4 ndy[MAXV], nx[MAXV], na[MAXV];
@@ -296,21 +302,26 @@ __global__ __launch_bounds__(GL_THREADS) void layernorm_bwd_kernel(int rows, int
     for (int i = 0; i < MAXV; ++i) {
         const int v = i * 64 + lane;
         if (v < nvec) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                sm[(wave * NS + 0) * d + v * 8 + k] = sg[i][k];
-                sm[(wave * NS + 1) * d + v * 8 + k] = sb[i][k];
-                if (ZSUM) sm[(wave * NS + 2) * d + v * 8 + k] = sz[i][k];
-            }
+            auto put = [&](const int q, const float* f) {
+                float* o = sm + (long long)(wave * NS + q) * 2 * half + v * 4;
+                *reinterpret_cast<float4*>(o)        = make_float4(f[0], f[1], f[2], f[3]);
+                *reinterpret_cast<float4*>(o + half) = make_float4(f[4], f[5], f[6], f[7]);
+            };
+            put(0, sg[i]);
+            put(1, sb[i]);
+            if (ZSUM) put(2, sz[i]);
         }
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < NS * d; c += GL_THREADS) {
-        const int which = c / d, col = c - which * d;
-        float     t     = 0.f;
+    for (int c = threadIdx.x; c < NS * d / 4; c += 64 * NW) {  // four columns each
+        const int which = c / (d / 4), r = c - which * (d / 4);
+        float4    t     = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int w = 0; w < GL_WAVES; ++w) t += sm[(w * NS + which) * d + col];
-        part[(long long)blockIdx.x * NS * d + c] = t;
+        for (int w = 0; w < NW; ++w) {
+            const float4 u = *reinterpret_cast<const float4*>(sm + ((long long)(w * NS + which) * 2 + (r & 1)) * half + (r >> 1) * 4);
+            t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+        }
+        *reinterpret_cast<float4*>(part + (long long)blockIdx.x * NS * d + c * 4) = t;
     }
 }
 
@@ -627,16 +638,16 @@ extern "C" int mp_layernorm_fwd(int rows, int d, const mp_half* x, const mp_half
     return MP_OK;
 }
 
-static int ln_bwd_blocks(int rows) {
-    int nb = (rows + GL_WAVES * 4 - 1) / (GL_WAVES * 4);  // about 4 rows per wave
-    if (nb > 512) nb = 512;
-    if (nb < 1) nb = 1;
-    return nb;
+// about 4 rows per wave
+static int ln_bwd_waves(int rows, int d) { return rows >= 256 * 8 * 4 && d <= 64 * 8 * 2 ? 8 : GL_WAVES; }
+static int ln_bwd_blocks(int rows, int d) {
+    const int nw = ln_bwd_waves(rows, d);
+    return std::max(1, std::min((rows + nw * 4 - 1) / (nw * 4), 2048 / nw));
 }
 
 extern "C" size_t mp_layernorm_bwd_workspace_bytes(int rows, int d) {
     if (rows <= 0 || d <= 0) return 0;
-    return (size_t)ln_bwd_blocks(rows) * 3 * d * sizeof(float);
+    return (size_t)ln_bwd_blocks(rows, d) * 3 * d * sizeof(float);
 }
 
 extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
@@ -656,27 +667,29 @@ extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_hal
                   ws_bytes);
         return MP_E_WORKSPACE;
     }
-    const int   nb   = ln_bwd_blocks(rows);
+    const int   nb   = ln_bwd_blocks(rows, d);
     const int   ns   = dz_colsum ? 3 : 2;
     float*      part = static_cast<float*>(ws);
     hipStream_t hs   = as_stream(stream);
-    const size_t lds = (size_t)GL_WAVES * ns * d * sizeof(float);
+    const int    nw  = ln_bwd_waves(rows, d);
+    const size_t lds = (size_t)nw * ns * (d + 32) * sizeof(float);
     const bool small = d <= 64 * 8 * 2;  // two vectors per lane are enough: fewer registers, more waves per CU
-    if (dz_colsum) {
-        if (small)
-            hipLaunchKernelGGL((layernorm_bwd_kernel<true, 2>), dim3(nb), dim3(GL_THREADS), lds, hs, rows, d, dy, x, a, gamma,
-                               mean, rstd, dz, part);
-        else
-            hipLaunchKernelGGL((layernorm_bwd_kernel<true, LN_MAXV>), dim3(nb), dim3(GL_THREADS), lds, hs, rows, d, dy, x, a,
-                               gamma, mean, rstd, dz, part);
-    } else {
-        if (small)
-            hipLaunchKernelGGL((layernorm_bwd_kernel<false, 2>), dim3(nb), dim3(GL_THREADS), lds, hs, rows, d, dy, x, a, gamma,
-                               mean, rstd, dz, part);
-        else
-            hipLaunchKernelGGL((layernorm_bwd_kernel<false, LN_MAXV>), dim3(nb), dim3(GL_THREADS), lds, hs, rows, d, dy, x, a,
-                               gamma, mean, rstd, dz, part);
-    }
+    auto launch = [&](auto zsum, auto maxv, auto waves) {
+        constexpr auto kernel = &layernorm_bwd_kernel<decltype(zsum)::value, decltype(maxv)::value, decltype(waves)::value>;
+        static std::once_flag once;
+        static hipError_t     attr_err = hipSuccess;
+        std::call_once(once, [&] { attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LN_MAX_LDS); });
+        if (attr_err != hipSuccess) return hip_fail(attr_err, "mp_layernorm_bwd: hipFuncSetAttribute(LDS size)");
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * decltype(waves)::value), lds, hs, rows, d, dy, x, a, gamma, mean, rstd, dz, part);
+        return (int)MP_OK;
+    };
+    auto by_width = [&](auto zsum) {
+        typedef std::integral_constant<int, 2> V2;
+        if (!small) return launch(zsum, std::integral_constant<int, LN_MAXV>{}, std::integral_constant<int, GL_WAVES>{});
+        return nw == 8 ? launch(zsum, V2{}, std::integral_constant<int, 8>{}) : launch(zsum, V2{}, std::integral_constant<int, GL_WAVES>{});
+    };
+    const int rc = dz_colsum ? by_width(std::true_type{}) : by_width(std::false_type{});
+    if (rc != MP_OK) return rc;
     MP_LAUNCH_CHECK("mp_layernorm_bwd");
     FinishOuts outs{{dgamma, dbeta, dz_colsum}};
     hipLaunchKernelGGL(finish_colsum_kernel, dim3((ns * d + 31) / 32), dim3(GL_THREADS), 0, hs, part, nb, (long long)ns * d,
