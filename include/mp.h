@@ -221,6 +221,20 @@ typedef struct mp_gemm_group_item {
 } mp_gemm_group_item;
 int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_state* st, mp_stream stream);
 
+/* Column sums that another call left as partial sums (mp_layernorm_bwd_parts): part (device) has nparts rows of nseg x cols
+ * fp32 values; out[s][c] = RNE16( sum over the rows of column s cols + c ), s < nseg <= 3.  cols a multiple of 128, part
+ * 16-byte aligned. */
+typedef struct mp_colsum_parts {
+    const float* part;
+    int32_t      nparts, cols, nseg, reserved;
+    mp_half*     out[3];
+} mp_colsum_parts;
+
+/* mp_gemm_bwd_dw_grouped that also finishes nsums (0..4, host array) such column sums, on compute units that the product
+ * tiles leave idle: same results and bits as the finish launch that mp_layernorm_bwd ends with.  st covers them too. */
+int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int count, const mp_colsum_parts* sums /* host */, int nsums,
+                                mp_scale_state* st, mp_stream stream);
+
 /* Tuning aid for sweeps and tests, process-wide and not thread-safe (the one piece of mutable library state;
  * a training step never calls it): force every following contraction onto tile shape `tile`
  * (index into the library's tile table: 0 = 256x256, 1 = 256x128, 2 = 128x256, 3 = 128x128, 4 = 128x64,
@@ -310,6 +324,14 @@ int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const
                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,
                      mp_half* dgamma, mp_half* dbeta, mp_half* dz_colsum, mp_scale_state* st, void* ws,
                      size_t ws_bytes, mp_stream stream);
+
+/* mp_layernorm_bwd without its last launch: dz is written, the column sums stay in ws as mp_layernorm_bwd_nparts(rows, d) rows
+ * of partial sums (d for dgamma, d for dbeta and, with_dz_colsum != 0, d for dz_colsum, side by side) that
+ * mp_gemm_bwd_dw_grouped_sums finishes; ws must stay untouched until then. */
+int mp_layernorm_bwd_nparts(int rows, int d);
+int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a, const mp_half* gamma,
+                           const float* mean, const float* rstd, mp_half* dz, int with_dz_colsum, void* ws, size_t ws_bytes,
+                           mp_stream stream);
 
 /* Row softmax of attention scores: p = RNE16( softmax_fp32(s) ), rows x cols, contiguous rows of
  * length cols with leading dimension ld (p may alias s). */

@@ -36,6 +36,11 @@ class GemmGroupItem(C.Structure):
     _fields_ = [("desc", GemmDesc), ("dY", C.c_void_p), ("X", C.c_void_p), ("dW", C.c_void_p), ("db", C.c_void_p)]
 
 
+class ColsumParts(C.Structure):
+    _fields_ = [("part", C.c_void_p), ("nparts", C.c_int32), ("cols", C.c_int32), ("nseg", C.c_int32), ("reserved", C.c_int32),
+                ("out", C.c_void_p * 3)]
+
+
 class LstmLayerDesc(C.Structure):
     _fields_ = [("T", C.c_int32), ("B", C.c_int32), ("I", C.c_int32), ("H", C.c_int32),
                 ("ldw", C.c_int32), ("ldxh", C.c_int32), ("ld_up", C.c_int32), ("wait_limit_us", C.c_int32),
@@ -70,6 +75,7 @@ SIGNATURES = {
     "mp_gemm_bwd_both": (_I, [C.POINTER(GemmDesc), _P, _P, _P, _P, C.c_int32, _P, C.POINTER(GemmDesc), _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_gemm_bwd_both_joint": (_I, [C.POINTER(GemmDesc), C.POINTER(GemmDesc)]),
     "mp_gemm_bwd_dw_grouped": (_I, [C.POINTER(GemmGroupItem), _I, _P, _P]),
+    "mp_gemm_bwd_dw_grouped_sums": (_I, [C.POINTER(GemmGroupItem), _I, C.POINTER(ColsumParts), _I, _P, _P]),
     "mp_gemm_tuning_override": (_I, [_I, _I]),
     "mp_gemm_tuning_dtl": (_I, [_I]),
     "mp_colsum_workspace_bytes": (_SZ, [_I, _I]),
@@ -84,6 +90,8 @@ SIGNATURES = {
     "mp_layernorm_fwd": (_I, [_I, _I, _P, _P, _P, _P, _F, _P, _P, _P, _P]),
     "mp_layernorm_bwd_workspace_bytes": (_SZ, [_I, _I]),
     "mp_layernorm_bwd": (_I, [_I, _I, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
+    "mp_layernorm_bwd_nparts": (_I, [_I, _I]),
+    "mp_layernorm_bwd_parts": (_I, [_I, _I, _P, _P, _P, _P, _P, _P, _P, _I, _P, _SZ, _P]),
     "mp_softmax_fwd": (_I, [_I64, _I, _P, _P, _I, _P]),
     "mp_softmax_bwd": (_I, [_I64, _I, _P, _P, _P, _I, _P]),
     "mp_attention_fwd": (_I, [_I, _I, _I, _I, _P, _I, _F, _P, _P, _I, _P]),

@@ -135,6 +135,21 @@ def mp_gemm_bwd_dw_grouped(group, st=None):
     _check(L.load().mp_gemm_bwd_dw_grouped(group, len(group), _p(st), _stream()))
 
 
+def colsum_parts(entries):
+    """Host array for mp_gemm_bwd_dw_grouped_sums from (part, nparts, cols, (out, ...)) tuples; keeps the tensors alive."""
+    arr = (L.ColsumParts * len(entries))()
+    for k, (part, nparts, cols, outs) in enumerate(entries):
+        arr[k].part, arr[k].nparts, arr[k].cols, arr[k].nseg = _p(part), nparts, cols, len(outs)
+        for s, o in enumerate(outs):
+            arr[k].out[s] = _p(o)
+    arr._keep = [(e[0], e[3]) for e in entries]
+    return arr
+
+
+def mp_gemm_bwd_dw_grouped_sums(group, sums, st=None):
+    _check(L.load().mp_gemm_bwd_dw_grouped_sums(group, len(group), sums, len(sums), _p(st), _stream()))
+
+
 def mp_gemm_tuning_override(tile: int, splits: int = 1):
     _check(L.load().mp_gemm_tuning_override(tile, splits))
 
@@ -196,6 +211,15 @@ def mp_layernorm_bwd_workspace_bytes(rows: int, d: int) -> int:
 def mp_layernorm_bwd(rows, d, dy, x, a, gamma, mean, rstd, dz, dgamma, dbeta, st, ws, dz_colsum=None):
     _check(L.load().mp_layernorm_bwd(rows, d, _p(dy), _p(x), _p(a), _p(gamma), _p(mean), _p(rstd), _p(dz), _p(dgamma),
                                      _p(dbeta), _p(dz_colsum), _p(st), _p(ws), ws.numel() * ws.element_size(), _stream()))
+
+
+def mp_layernorm_bwd_nparts(rows: int, d: int) -> int:
+    return L.load().mp_layernorm_bwd_nparts(rows, d)
+
+
+def mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, dz, with_dz_colsum, ws):
+    _check(L.load().mp_layernorm_bwd_parts(rows, d, _p(dy), _p(x), _p(a), _p(gamma), _p(mean), _p(rstd), _p(dz), int(with_dz_colsum),
+                                           _p(ws), ws.numel() * ws.element_size(), _stream()))
 
 
 def mp_softmax_fwd(rows, cols, s, p, ld):

@@ -15,11 +15,11 @@ extern template int launch_tile<false, false>(int, const GemmArgs&, dim3, hipStr
 extern template int launch_dtl_tile<true, true>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_dtl_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_dtl_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
-extern template int launch_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
-extern template int launch_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
-extern template int launch_dtl_grouped<256, 256>(const GroupArgs&, int, hipStream_t);
-extern template int launch_dtl_grouped<256, 128>(const GroupArgs&, int, hipStream_t);
-extern template int launch_dtl_grouped<128, 128>(const GroupArgs&, int, hipStream_t);
+extern template int launch_grouped<256, 256>(GroupArgs, int, hipStream_t);
+extern template int launch_grouped<128, 128>(GroupArgs, int, hipStream_t);
+extern template int launch_dtl_grouped<256, 256>(GroupArgs, int, hipStream_t);
+extern template int launch_dtl_grouped<256, 128>(GroupArgs, int, hipStream_t);
+extern template int launch_dtl_grouped<128, 128>(GroupArgs, int, hipStream_t);
 
 // Sum split-K partials in split order, scale, round once, optional non-finite flag.
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ part, int splits, long long mn,
@@ -520,6 +520,12 @@ extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, con
 }
 
 extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count, mp_scale_state* st, mp_stream stream) {
+    return mp_gemm_bwd_dw_grouped_sums(items, count, nullptr, 0, st, stream);
+}
+
+extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int count, const mp_colsum_parts* sums, int nsums,
+                                           mp_scale_state* st, mp_stream stream) {
+    MP_REQUIRE(nsums >= 0 && nsums <= SUMS_MAX && (nsums == 0 || sums != nullptr), "mp_gemm_bwd_dw_grouped_sums: 0..%d sums", SUMS_MAX);
     MP_REQUIRE(items != nullptr && count >= 1 && count <= GROUP_MAX, "mp_gemm_bwd_dw_grouped: 1..%d items", GROUP_MAX);
     GemmArgs args[GROUP_MAX];
     bool     m256 = true, n256 = true, dtl = dtl_mode() != 0;
@@ -602,6 +608,20 @@ extern "C" int mp_gemm_bwd_dw_grouped(const mp_gemm_group_item* items, int count
         strips += it.desc.N / BIAS_COLS;      // N is a multiple of 128 here (checked above for either orientation)
     }
     for (int i = ga.nbias; i <= GROUP_MAX; ++i) ga.strip_start[i] = strips;
+    for (int i = 0; i < nsums; ++i) {
+        const mp_colsum_parts& c = sums[i];
+        MP_REQUIRE(c.part && aligned16(c.part) && c.nparts > 0 && c.cols > 0 && c.cols % BIAS_COLS == 0 && c.nseg >= 1 && c.nseg <= 3,
+                   "mp_gemm_bwd_dw_grouped_sums: sum %d: bad shape or pointer", i);
+        SumItem& s = ga.s[i];
+        s.part = c.part; s.nparts = c.nparts; s.cols = c.cols; s.nseg = c.nseg;
+        for (int k = 0; k < c.nseg; ++k) {
+            MP_REQUIRE(c.out[k], "mp_gemm_bwd_dw_grouped_sums: sum %d has a NULL output", i);
+            s.out[k] = reinterpret_cast<unsigned short*>(c.out[k]);
+        }
+        ga.sum_start[i + 1] = ga.sum_start[i] + c.nseg * (c.cols / BIAS_COLS);
+    }
+    ga.nsums = nsums;
+    for (int i = nsums; i < SUMS_MAX; ++i) ga.sum_start[i + 1] = ga.sum_start[i];
     if (dtl) {
         if (bn == 256) return launch_dtl_grouped<256, 256>(ga, kCUs, as_stream(stream));
         return bm == 256 ? launch_dtl_grouped<256, 128>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));

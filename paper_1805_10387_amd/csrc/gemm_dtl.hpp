@@ -680,32 +680,22 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_kernel(GemmArgs g) {
 template <int BM, int BN>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_grouped_kernel(GroupArgs ga) {
     extern __shared__ __align__(16) char smem[];
-    bool      bad_any = false;
-    int*      flag    = ga.found_inf;
-    const int total   = ga.tile_start[ga.count];
-    const int items   = total + ga.strip_start[ga.nbias];
-    for (int vb0 = blockIdx.x; vb0 < items; vb0 += gridDim.x) {
-        if (vb0 >= total) {  // a bias-gradient strip (no loads in flight between tiles here)
-            bool bad = false;
-            group_bias_item(ga, vb0 - total, smem, bad);
-            bad_any |= bad;
-            continue;
-        }
-        const int xq = total >> 3, xrem = total & 7, xx = vb0 & 7;
-        const int vb = xx * xq + min(xx, xrem) + (vb0 >> 3);
+    bool bad_any = false;
+    int* flag    = ga.found_inf;
+    group_run(ga, smem, bad_any, [&](const int vb) {
         int            first;
         const GemmArgs g = group_problem(ga, vb, first);
-        bool bad = false;
+        bool           bad = false;
         dtl_tiles<BM, BN, false, false, INTERIOR>(g, vb - first, 1 << 30, false, false, smem, bad);
         bad_any |= bad;
-    }
+    });
     if (flag && __any(bad_any)) {
         if ((threadIdx.x & 63) == 0) atomicOr(flag, 1);
     }
 }
 
 template <int BM, int BN>
-int launch_dtl_grouped(const GroupArgs& ga, int resident, hipStream_t hs) {
+int launch_dtl_grouped(GroupArgs ga, int resident, hipStream_t hs) {
     constexpr size_t  lds = dtl_lds(BM, BN);
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
@@ -714,8 +704,7 @@ int launch_dtl_grouped(const GroupArgs& ga, int resident, hipStream_t hs) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    const int total = ga.tile_start[ga.count] + ga.strip_start[ga.nbias];
-    hipLaunchKernelGGL((gemm_dtl_grouped_kernel<BM, BN>), dim3(total < resident ? total : resident), dim3(GEMM_THREADS), lds, hs, ga);
+    hipLaunchKernelGGL((gemm_dtl_grouped_kernel<BM, BN>), dim3(group_workgroups(ga, resident)), dim3(GEMM_THREADS), lds, hs, ga);
     MP_LAUNCH_CHECK("grouped gemm launch (direct-to-LDS)");
     return MP_OK;
 }

@@ -706,6 +706,13 @@ struct BiasItem {
     unsigned short*       db;
     int                   ld, rows;
 };
+// Column sums whose partial sums are there (rows of nseg x cols fp32 values), finished by the same launch.
+constexpr int SUMS_MAX = 4;
+struct SumItem {
+    const float*    part;
+    int             nparts, cols, nseg;
+    unsigned short* out[3];
+};
 // (what such a problem needs of GemmArgs, no more: all of them sit in scalar registers while a tile's is chosen)
 struct GroupItem {
     const uint16_t *A, *B;
@@ -721,6 +728,10 @@ struct GroupArgs {
     BiasItem b[GROUP_MAX];
     int      strip_start[GROUP_MAX + 1];  // strip_start[nbias] = number of strips
     int      nbias;
+    SumItem  s[SUMS_MAX];
+    int      sum_start[SUMS_MAX + 1];     // in columns of BIAS_COLS; sum_start[nsums] = their number
+    int      nsums;
+    int      tile_wgs;                    // workgroups 0 .. tile_wgs - 1 take tiles
 };
 
 // db[strip] = RNE16(fp32 column sums of a 128-column strip of dY), by one workgroup of 256 threads: 16 lanes x 8
@@ -801,33 +812,91 @@ __device__ inline void group_bias_item(const GroupArgs& ga, int s, char* smem, b
     colsum_strip(it, s - first, smem, bad);
 }
 
+// BIAS_COLS columns, starting at `col`, of a sum's partials: 32 lanes x 4 columns by 8 groups, eight loads in flight per
+// lane, in the order of finish_colsum_kernel (glue.hip): group q adds rows q, q + 8, ..., then the groups in order.
+__device__ inline void finish_sums(const SumItem it, const int col, char* smem, bool& bad) {
+    const int       cl = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const long long stride = (long long)it.nseg * it.cols;
+    const float*    src = it.part + col + 4 * cl;
+    f32x4           acc = {0.f, 0.f, 0.f, 0.f};
+    int             p = q;
+    for (; p + 56 < it.nparts; p += 64) {
+        f32x4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const f32x4*>(src + (p + 8 * u) * stride);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += t[u];
+    }
+    for (; p < it.nparts; p += 8) acc += *reinterpret_cast<const f32x4*>(src + p * stride);
+    float* red = reinterpret_cast<float*>(smem);
+    __syncthreads();
+    *reinterpret_cast<f32x4*>(red + q * BIAS_COLS + 4 * cl) = acc;
+    __syncthreads();
+    if (threadIdx.x < BIAS_COLS) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += red[j * BIAS_COLS + threadIdx.x];
+        const unsigned short h = __builtin_bit_cast(unsigned short, (_Float16)s);  // round to nearest even
+        const int            seg = col / it.cols;
+        unsigned short*      o = seg == 0 ? it.out[0] : seg == 1 ? it.out[1] : it.out[2];
+        o[col - seg * it.cols + threadIdx.x] = h;
+        bad |= (h & 0x7fffu) >= 0x7c00u;
+    }
+    __syncthreads();
+}
+
+// What a grouped launch does besides its tiles, item j: the bias-gradient strips, then the sums.
+__device__ inline void group_small_item(const GroupArgs& ga, int j, char* smem, bool& bad) {
+    const int strips = ga.strip_start[ga.nbias];
+    if (j < strips) {
+        group_bias_item(ga, j, smem, bad);
+        return;
+    }
+    j -= strips;
+    SumItem it    = ga.s[0];
+    int     first = 0;
+#pragma unroll
+    for (int q = 1; q < SUMS_MAX; ++q) {
+        if (q < ga.nsums && j >= ga.sum_start[q]) {
+            it    = ga.s[q];
+            first = ga.sum_start[q];
+        }
+    }
+    finish_sums(it, (j - first) * BIAS_COLS, smem, bad);
+}
+// Work of one workgroup: the first tile_wgs take tiles, the others (where the tiles leave compute units idle) the small
+// items, which are short against a tile; where there are no others, everybody takes some after its tiles.
+template <typename TILE>
+__device__ __forceinline__ void group_run(const GroupArgs& ga, char* smem, bool& bad, TILE&& tile) {
+    const int total = ga.tile_start[ga.count], small = ga.strip_start[ga.nbias] + ga.sum_start[ga.nsums];
+    const int others = gridDim.x - ga.tile_wgs;
+    if ((int)blockIdx.x < ga.tile_wgs) {
+        for (int vb = blockIdx.x; vb < total; vb += ga.tile_wgs) {
+            // consecutive workgroup ids go round-robin over the 8 XCDs: give each XCD, and its L2, a contiguous run of
+            // tiles (neighbouring tiles share operand panels)
+            const int q = total >> 3, rem = total & 7, x = vb & 7;
+            tile(x * q + min(x, rem) + (vb >> 3));
+        }
+        if (others > 0) return;
+    }
+    for (int j = others > 0 ? blockIdx.x - ga.tile_wgs : blockIdx.x; j < small; j += others > 0 ? others : (int)gridDim.x) group_small_item(ga, j, smem, bad);
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_grouped_kernel(GroupArgs ga) {
     extern __shared__ __align__(16) char smem[];
-    bool      bad_any = false;
-    int*      flag    = ga.found_inf;
-    const int total   = ga.tile_start[ga.count];
-    const int items   = total + ga.strip_start[ga.nbias];
-    for (int vb0 = blockIdx.x; vb0 < items; vb0 += gridDim.x) {
-        if (vb0 >= total) {  // a bias-gradient strip
-            bool bad = false;
-            group_bias_item(ga, vb0 - total, smem, bad);
-            bad_any |= bad;
-            continue;
-        }
-        // consecutive workgroup ids go round-robin over the 8 XCDs: give each XCD, and its L2, a contiguous run of
-        // tiles (neighbouring tiles share operand panels)
-        const int xq = total >> 3, xrem = total & 7, xx = vb0 & 7;
-        const int vb = xx * xq + min(xx, xrem) + (vb0 >> 3);
+    bool bad_any = false;
+    int* flag    = ga.found_inf;
+    group_run(ga, smem, bad_any, [&](const int vb) {
         int            first;
         const GemmArgs g = group_problem(ga, vb, first);
-        bool bad = false;
+        bool           bad = false;
         OperandStream<BM, BN, A_KC, B_KC> S;
         S.init(g.lda, g.ldb);
         gemm_tile<BM, BN, WAVES_M, WAVES_N, A_KC, B_KC, INTERIOR>(g, vb - first, -1, 0, 0, 1, smem, S, bad);
         bad_any |= bad;
         __syncthreads();  // (tiles of different problems: keep the LDS stages of one tile apart from the next)
-    }
+    });
     if (flag && __any(bad_any)) {
         if ((threadIdx.x & 63) == 0) atomicOr(flag, 1);
     }
@@ -879,8 +948,14 @@ int launch_tile(int t, const GemmArgs& g, dim3 grid, hipStream_t hs) {
     }
 }
 
+// sets tile_wgs; returns the number of workgroups
+inline int group_workgroups(GroupArgs& ga, int resident) {
+    const int total = ga.tile_start[ga.count], small = ga.strip_start[ga.nbias] + ga.sum_start[ga.nsums];
+    ga.tile_wgs = total < resident ? total : resident;
+    return ga.tile_wgs + (small < resident - ga.tile_wgs ? small : resident - ga.tile_wgs);
+}
 template <int BM, int BN>
-int launch_grouped(const GroupArgs& ga, int resident, hipStream_t hs) {
+int launch_grouped(GroupArgs ga, int resident, hipStream_t hs) {
     constexpr size_t  lds = 2 * (size_t)(BM + BN) * 128;
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
@@ -889,9 +964,7 @@ int launch_grouped(const GroupArgs& ga, int resident, hipStream_t hs) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    const int total = ga.tile_start[ga.count] + ga.strip_start[ga.nbias];
-    hipLaunchKernelGGL((gemm_grouped_kernel<BM, BN, 2, 2, false, false>), dim3(total < resident ? total : resident),
-                       dim3(GEMM_THREADS), lds, hs, ga);
+    hipLaunchKernelGGL((gemm_grouped_kernel<BM, BN, 2, 2, false, false>), dim3(group_workgroups(ga, resident)), dim3(GEMM_THREADS), lds, hs, ga);
     MP_LAUNCH_CHECK("grouped gemm launch");
     return MP_OK;
 }

@@ -650,12 +650,13 @@ extern "C" size_t mp_layernorm_bwd_workspace_bytes(int rows, int d) {
     return (size_t)ln_bwd_blocks(rows, d) * 3 * d * sizeof(float);
 }
 
-extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
-                                const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz, mp_half* dgamma,
-                                mp_half* dbeta, mp_half* dz_colsum, mp_scale_state* st, void* ws, size_t ws_bytes,
-                                mp_stream stream) {
+extern "C" int mp_layernorm_bwd_nparts(int rows, int d) { return rows > 0 && d > 0 ? ln_bwd_blocks(rows, d) : 0; }
+
+extern "C" int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
+                                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,
+                                      int with_dz_colsum, void* ws, size_t ws_bytes, mp_stream stream) {
     MP_REQUIRE(rows > 0 && d > 0, "mp_layernorm_bwd: bad shape rows=%d d=%d", rows, d);
-    MP_REQUIRE(dy && x && gamma && mean && rstd && dz && dgamma && dbeta, "mp_layernorm_bwd: NULL argument");
+    MP_REQUIRE(dy && x && gamma && mean && rstd && dz, "mp_layernorm_bwd: NULL argument");
     if (!ln_shape_ok(d)) {
         set_error("mp_layernorm_bwd: d=%d unsupported (need a multiple of 8, at most %d)", d, 64 * 8 * LN_MAXV);
         return MP_E_UNSUPPORTED;
@@ -668,7 +669,7 @@ extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_hal
         return MP_E_WORKSPACE;
     }
     const int   nb   = ln_bwd_blocks(rows, d);
-    const int   ns   = dz_colsum ? 3 : 2;
+    const int   ns   = with_dz_colsum ? 3 : 2;
     float*      part = static_cast<float*>(ws);
     hipStream_t hs   = as_stream(stream);
     const int    nw  = ln_bwd_waves(rows, d);
@@ -688,12 +689,23 @@ extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_hal
         if (!small) return launch(zsum, std::integral_constant<int, LN_MAXV>{}, std::integral_constant<int, GL_WAVES>{});
         return nw == 8 ? launch(zsum, V2{}, std::integral_constant<int, 8>{}) : launch(zsum, V2{}, std::integral_constant<int, GL_WAVES>{});
     };
-    const int rc = dz_colsum ? by_width(std::true_type{}) : by_width(std::false_type{});
+    const int rc = with_dz_colsum ? by_width(std::true_type{}) : by_width(std::false_type{});
     if (rc != MP_OK) return rc;
     MP_LAUNCH_CHECK("mp_layernorm_bwd");
+    return MP_OK;
+}
+
+extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
+                                const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz, mp_half* dgamma,
+                                mp_half* dbeta, mp_half* dz_colsum, mp_scale_state* st, void* ws, size_t ws_bytes,
+                                mp_stream stream) {
+    MP_REQUIRE(dgamma && dbeta, "mp_layernorm_bwd: NULL argument");
+    const int rc = mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, dz, dz_colsum != nullptr, ws, ws_bytes, stream);
+    if (rc != MP_OK) return rc;
+    const int  ns = dz_colsum ? 3 : 2;
     FinishOuts outs{{dgamma, dbeta, dz_colsum}};
-    hipLaunchKernelGGL(finish_colsum_kernel, dim3((ns * d + 31) / 32), dim3(GL_THREADS), 0, hs, part, nb, (long long)ns * d,
-                       d, ns, outs, st);
+    hipLaunchKernelGGL(finish_colsum_kernel, dim3((ns * d + 31) / 32), dim3(GL_THREADS), 0, as_stream(stream), static_cast<const float*>(ws),
+                       ln_bwd_blocks(rows, d), (long long)ns * d, d, ns, outs, st);
     MP_LAUNCH_CHECK("mp_layernorm_bwd(finish)");
     return MP_OK;
 }

@@ -211,6 +211,12 @@ class TransformerStep(_StepBase):
                  B.mp_layernorm_bwd_workspace_bytes(T, d), B.mp_loss_workspace_bytes(T, d)]
         self._alloc_ws(max(need))
         self.ws_side = torch.empty_like(self.ws)
+        # partial column sums of a layer's two LayerNorm backwards, finished by its grouped launch (which alternate by layer)
+        self.ln_parts = []
+        if self.grouped_dw:
+            n = B.mp_layernorm_bwd_workspace_bytes(T, d) // 4
+            self.ln_parts = [[e32(n), e32(n)] for _ in range(2)]
+            self.ln_nparts = B.mp_layernorm_bwd_nparts(T, d)
 
     def set_batch(self, batch):
         self.x0.copy_(_h16(batch["x"]))
@@ -278,20 +284,27 @@ class TransformerStep(_StepBase):
             a, p = self.act[l], f"l{l}."
             tb = self.tmp[i % 2]
             dz2, df, dz1, dqkv = tb["dz2"], tb["df"], tb["dz1"], tb["dqkv"]
+            parts = self.ln_parts[i % 2] if self.grouped_dw else None
+
+            def layernorm_bwd(k, dy, xin, ain, ln, mean, rstd, dz, bname):
+                """One LayerNorm backward; its column sums are finished by the layer's grouped launch where there is one."""
+                if self.grouped_dw:
+                    B.mp_layernorm_bwd_parts(T, d, dy, xin, ain, w[p + ln + "_g"], mean, rstd, dz, True, parts[k])
+                else:
+                    B.mp_layernorm_bwd(T, d, dy, xin, ain, w[p + ln + "_g"], mean, rstd, dz, g[p + ln + "_g"], g[p + ln + "_b"], st, ws,
+                                       dz_colsum=None if self.joint_bwd else g[p + bname])
             if side is not None and i >= 2:
                 main.wait_event(done[i - 2])        # side stream finished reading this parity's temporaries
             x = self.x0 if l == 0 else self.act[l - 1]["y2"]
             # dz2 is the gradient of g = W2 f + b2 too, so its column sums are b2's gradient
-            B.mp_layernorm_bwd(T, d, dy2, a["y1"], a["g"], w[p + "ln2_g"], a["mean2"], a["rstd2"], dz2,
-                               g[p + "ln2_g"], g[p + "ln2_b"], st, ws, dz_colsum=None if self.joint_bwd else g[p + "b2"])
+            layernorm_bwd(0, dy2, a["y1"], a["g"], "ln2", a["mean2"], a["rstd2"], dz2, "b2")
             self._t("dy2", l, dy2)
             self._t("dz2", l, dz2)
             linear_bwd(self.d_f2, dz2, p + "w2", p + "b2", a["f"], df, False, relu_src=a["f"], ld_aux=f)
             self._t("df", l, df)
             linear_bwd(self.d_f1, df, p + "w1", p + "b1", a["y1"], self.dy1, True, add=dz2, ld_aux=d)
             self._t("dy1", l, self.dy1)
-            B.mp_layernorm_bwd(T, d, self.dy1, x, a["a"], w[p + "ln1_g"], a["mean1"], a["rstd1"], dz1,
-                               g[p + "ln1_g"], g[p + "ln1_b"], st, ws, dz_colsum=None if self.joint_bwd else g[p + "bo"])
+            layernorm_bwd(1, self.dy1, x, a["a"], "ln1", a["mean1"], a["rstd1"], dz1, "bo")
             self._t("dz1", l, dz1)
             linear_bwd(self.d_o, dz1, p + "wo", p + "bo", a["ctx"], self.dctx, False)
             self._t("dctx", l, self.dctx)
@@ -316,11 +329,13 @@ class TransformerStep(_StepBase):
                 key = (l, i % 2)
                 if key not in self._groups:
                     over = lambda x: B.gemm_desc(self.T_dw, x.N, x.K)  # noqa: E731  (the zero rows too)
+                    sums = B.colsum_parts([(parts[k], self.ln_nparts, d, (g[p + ln + "_g"], g[p + ln + "_b"], g[p + bias]))
+                                           for k, (ln, bias) in enumerate((("ln2", "b2"), ("ln1", "bo")))])
                     self._groups[key] = B.gemm_group([(over(self.d_f2), dz2, a["f"], g[p + "w2"]),
                                                       (over(self.d_f1), df, a["y1"], g[p + "w1"], g[p + "b1"]),
                                                       (over(self.d_qkv), dqkv, x, g[p + "wqkv"], g[p + "bqkv"]),
-                                                      (over(self.d_o), dz1, a["ctx"], g[p + "wo"])])
-                fork(lambda wsx: B.mp_gemm_bwd_dw_grouped(self._groups[key], st))
+                                                      (over(self.d_o), dz1, a["ctx"], g[p + "wo"])]), sums
+                fork(lambda wsx: B.mp_gemm_bwd_dw_grouped_sums(*self._groups[key], st))
             if side is not None:
                 done[i] = torch.cuda.Event()
                 done[i].record(side)

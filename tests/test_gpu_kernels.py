@@ -638,6 +638,46 @@ def test_gemm_grouped_weight_gradients(tile, shapes):
     assert mp.scale_state_read(st).found_inf == 0
 
 
+@pytest.mark.parametrize("rows,d,with_dz", [(3, 128, True), (200, 256, False), (4096, 512, True), (8191, 384, True), (8200, 1024, True),
+                                            (300, 2048, True)])
+def test_grouped_launch_finishes_layernorm_sums(rows, d, with_dz):
+    """mp_layernorm_bwd_parts and the sums of a grouped launch (few and many partial rows, 4 and 8 waves to a workgroup, every
+    register width) give the bits of mp_layernorm_bwd, whether the launch has idle compute units for them or not, and raise
+    its flag."""
+    r = RNG(rows + d)
+    up = lambda *s: h16(S16(r.standard_normal(s)))  # noqa: E731
+    dy, x, a, gamma = up(rows, d), up(rows, d), up(rows, d), up(d)
+    mean, rstd = torch.randn(rows, device="cuda") * 0.1, torch.rand(rows, device="cuda") + 0.5
+    ws = ws_bytes(mp.mp_layernorm_bwd_workspace_bytes(rows, d))
+    n = 3 if with_dz else 2
+    want = [empty16(rows, d)] + [empty16(d) for _ in range(n)]
+    st = make_state()
+    mp.mp_layernorm_bwd(rows, d, dy, x, a, gamma, mean, rstd, want[0], want[1], want[2], st, ws, dz_colsum=want[3] if with_dz else None)
+    for tiles in (1, 300):                      # idle compute units for the sums; none (128 x 128 tiles)
+        M, N, K = 192, 128, 128 * tiles
+        gy, gx, dw = up(M, N), up(M, K), empty16(N, K)
+        for mode in (1, 0):
+            got = [empty16(rows, d)] + [empty16(d) for _ in range(n)]
+            part = ws_bytes(mp.mp_layernorm_bwd_workspace_bytes(rows, d))
+            mp.mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, got[0], with_dz, part)
+            sums = mp.colsum_parts([(part, mp.mp_layernorm_bwd_nparts(rows, d), d, got[1:])] * 2)
+            mp.mp_gemm_tuning_dtl(mode)
+            try:
+                mp.mp_gemm_bwd_dw_grouped_sums(mp.gemm_group([(mp.gemm_desc(M, N, K), gy, gx, dw)]), sums, st)
+            finally:
+                mp.mp_gemm_tuning_dtl(1)
+            for k in range(n + 1):
+                assert torch.equal(got[k], want[k]), (tiles, mode, k)
+    assert mp.scale_state_read(st).found_inf == 0
+    dy[0, 0] = float("inf")
+    mp.mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, got[0], with_dz, part)
+    mp.mp_gemm_bwd_dw_grouped_sums(mp.gemm_group([(mp.gemm_desc(M, N, K), gy, gx, dw)]), sums, st)
+    assert mp.scale_state_read(st).found_inf != 0
+    with pytest.raises(mp.MPError):             # columns off 128
+        mp.mp_gemm_bwd_dw_grouped_sums(mp.gemm_group([(mp.gemm_desc(M, N, K), gy, gx, dw)]),
+                                       mp.colsum_parts([(part, 1, d - 8, got[1:])]), st)
+
+
 def test_gemm_grouped_transposed_weight_layout_with_bias_gradient():
     """A grouped item whose weight is stored [K, N] (trans_w): dW[K, N] = X^T dY, and db = column sums of dY, next to an
     ordinary item; both kernel families."""
