@@ -221,11 +221,13 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
     return interior || std::max(g.lda, g.ldb) < LD_BUFFER_64;
 }
 
-// What the direct-to-LDS kernels take: rows that are whole 16-byte pieces, a contraction of whole k-tiles and long enough for
+// What the direct-to-LDS kernels take: operand rows that are whole 16-byte pieces (the output's too unless both operands are
+// contraction-contiguous), a contraction of whole k-tiles and long enough for
 // the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
 static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
-    return dtl_mode() != 0 && g.aligned && batches == 1 && g.K % BK == 0 && g.K >= DTL_MIN_K && (a_kc || (!b_kc && g.M % 8 == 0)) &&
-           std::max(g.lda, g.ldb) < LD_BUFFER_256;
+    const bool operands = aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0;
+    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K % BK == 0 && g.K >= DTL_MIN_K &&
+           (a_kc || (!b_kc && g.M % 8 == 0)) && std::max(g.lda, g.ldb) < LD_BUFFER_256;
 }
 
 // Few ragged outputs over a contraction that short cost the scalar kernel less than the matrix cores' chain of loads, LDS and

@@ -191,6 +191,37 @@ def test_gemm_direct_to_lds_borders(tile, rows, cols, depth, splits):
         assert mp.scale_state_read(st).found_inf == 0
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("rows,cols,depth", [(33, 9, 192), (257, 391, 320), (1021, 2051, 256), (128, 258, 192)])
+def test_gemm_direct_to_lds_ragged_outputs(tile, rows, cols, depth):
+    """Forward products on aligned operands whose output has any width and element alignment (columns straddling a 16-byte piece
+    by 1 to 7, odd leading dimensions, an odd bias address), with each epilogue, and no byte outside the
+    output changes."""
+    r = RNG(rows + cols + depth + tile)
+    a, b, bias = S16(r.standard_normal((rows, depth))), S16(r.standard_normal((cols, depth)) * 0.1), S16(r.standard_normal(cols))
+    bias_d = torch.zeros(cols + 1, dtype=torch.float16, device="cuda")
+    bias_d[1:] = h16(bias)
+    big = torch.full((rows + 2, cols + 3), 7.0, dtype=torch.float16, device="cuda")
+    y = big.view(-1)[1:1 + rows * (cols + 3)].view(rows, cols + 3)[:, :cols]
+    mp.mp_gemm_tuning_override(tile, 1)
+    mp.mp_gemm_tuning_dtl(2)
+    try:
+        for epi, ref in ((0, a @ b.T), (1, a @ b.T + bias), (2, np.maximum(a @ b.T + bias, 0))):
+            y.fill_(float("nan"))
+            mp.mp_gemm_fwd(mp.gemm_desc(rows, cols, depth, ldy=cols + 3, epilogue=epi), h16(a), h16(b), bias_d[1:] if epi else None, None, y)
+            assert_close16(y, MIXED.store(ref), 1e-3, max_ulp=1, what=f"epilogue {epi}")
+        y.fill_(float("nan"))
+        mp.mp_gemm_fwd(mp.gemm_desc(rows, cols, depth, ldy=cols + 3, alpha=0.5, epilogue=1), h16(a), h16(b), bias_d[1:], None, y)
+    finally:
+        mp.mp_gemm_tuning_override(-1, 0)
+        mp.mp_gemm_tuning_dtl(1)
+    assert_close16(y, MIXED.store(0.5 * (a @ b.T) + bias), 1e-3, max_ulp=1, what="scaled")
+    flat = big.view(-1)
+    keep = torch.ones(flat.numel(), dtype=torch.bool, device="cuda")
+    keep[1:1 + rows * (cols + 3)].view(rows, cols + 3)[:, :cols] = False
+    assert torch.all(flat[keep] == 7.0)
+
+
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm_bwd_dx_and_dw(M, N, K):
     r = RNG(M * 3 + N + K)
