@@ -222,12 +222,12 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
 }
 
 // What the direct-to-LDS kernels take: operand rows that are whole 16-byte pieces (the output's too unless both operands are
-// contraction-contiguous), a contraction of whole k-tiles and long enough for
-// the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
+// contraction-contiguous), a contraction of whole k-tiles (any where both are
+// output-contiguous: their k-rows beyond it read as zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
 static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
     const bool operands = aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0;
-    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K % BK == 0 && g.K >= DTL_MIN_K &&
-           (a_kc || (!b_kc && g.M % 8 == 0)) && std::max(g.lda, g.ldb) < LD_BUFFER_256;
+    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % BK == 0 : !b_kc) &&
+           std::max(g.lda, g.ldb) < LD_BUFFER_256;
 }
 
 // Few ragged outputs over a contraction that short cost the scalar kernel less than the matrix cores' chain of loads, LDS and
@@ -331,7 +331,7 @@ using namespace mp;
 // pointers and leading dimensions, which decide between the kernels, are not known yet.
 static size_t splitk_floats(int M, int N, int K, bool kc_kc) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const bool dtl = dtl_mode() != 0 && K % BK == 0 && K >= DTL_MIN_K;
+    const bool dtl = dtl_mode() != 0 && K >= DTL_MIN_K;
     const Plan p = make_plan(M, N, K, 1, true, kc_kc, false), q = make_plan(M, N, K, 1, true, kc_kc, dtl);
     const int  splits = std::max(p.splits, q.splits);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;

@@ -1,6 +1,6 @@
 // Contraction kernel whose operand tiles go from global memory straight into LDS (`buffer_load ... lds`: no staging
-// registers, no LDS store instructions), for products whose contraction is a multiple of 64 and whose rows are 16-byte
-// aligned.  Same arithmetic as gemm_kernels.hpp (paper Section 3.1: fp16 operands, fp32 sums, one rounding); what differs
+// registers, no LDS store instructions), for products whose rows are 16-byte aligned and whose contraction is a multiple of 64
+// (any, where both operands are output-contiguous).  Same arithmetic as gemm_kernels.hpp (paper Section 3.1: fp16 operands, fp32 sums, one rounding); what differs
 // is how the operands reach the matrix cores and how the results leave them.
 //
 // What bounds it.  Under a full-chip load the matrix cores' clock follows the power that the operands draw, so both the
@@ -124,11 +124,12 @@ struct DtlOperand {
             return __builtin_bit_cast(f16x8, v);
         }
     }
-    // Bytes a tile's buffer spans from the origin of its k-tile, `left` of its rows being inside the matrix.  Loads beyond it
-    // give zeros.  Output-contiguous: columns beyond `left` of the k-tile's last row; those of the other k-rows are
-    // elements of the row that follows.  No stored result depends on either.
-    static __device__ __forceinline__ unsigned span(int left, int ld) {
-        return KC ? (left - 1) * (unsigned)ld * 2u + 2u * BK : (BK - 1) * (unsigned)ld * 2u + 2u * left;
+    // Bytes a tile's buffer spans from the origin of its k-tile, `left` of its rows and `k_left` of its k being inside the
+    // matrix.  Loads beyond it give zeros.  Output-contiguous: k-rows beyond the contraction, and columns beyond `left` (whole
+    // words: a piece may straddle) of the last k-row; those of the other k-rows are elements behind the row's end or of the row
+    // that follows, and no stored result depends on them.
+    static __device__ __forceinline__ unsigned span(int left, int ld, int k_left) {
+        return KC ? (left - 1) * (unsigned)ld * 2u + 2u * BK : (unsigned)(min(k_left, BK) - 1) * (unsigned)ld * 2u + ((2u * left + 3u) & ~3u);
     }
     static __device__ __forceinline__ long long origin(int row, int ld) { return KC ? (long long)row * ld * 2 : 2ll * row; }  // bytes
 };
@@ -344,7 +345,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
     const unsigned lds_a = (unsigned)(size_t)MP_LDS_PTR(smem) + wave * 1024, lds_b = lds_a + OpA::BYTES;
     const int wm = wave >> 1, wn = wave & 1;
     const int eh = lane >> 4;
-    const int nkt    = g.K / BK;
+    const int nkt    = (g.K + BK - 1) / BK;
     const int ntiles = g.tiles_m * g.tiles_n;
 
     auto tile_origin = [&](const int vb, int& mm, int& nn) { dtl_tile_origin<BM, BN>(g, remap ? dtl_tile_of(vb, ntiles) : vb, mm, nn); };
@@ -359,8 +360,13 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
     // ---- the load stream: k-tile after k-tile, output tile after output tile, two k-tiles ahead of the matrix cores
     int m0, n0;
     tile_origin(vb0, m0, n0);
-    u32x4 ra = buffer_at(g.A, OpA::origin(m0, g.lda), OpA::span(min(g.M - m0, BM), g.lda));
-    u32x4 rb = buffer_at(g.B, OpB::origin(n0, g.ldb), OpB::span(min(g.N - n0, BN), g.ldb));
+    u32x4 ra = buffer_at(g.A, OpA::origin(m0, g.lda), OpA::span(min(g.M - m0, BM), g.lda, BK));
+    u32x4 rb = buffer_at(g.B, OpB::origin(n0, g.ldb), OpB::span(min(g.N - n0, BN), g.ldb, BK));
+    auto  size_to = [&](const int m, const int n, const int k_left) {
+        ra[2] = OpA::span(min(g.M - m, BM), g.lda, k_left);
+        rb[2] = OpB::span(min(g.N - n, BN), g.ldb, k_left);
+    };
+    const int k_last = g.K - (nkt - 1) * BK;   // k of a tile's last k-tile
     int      left = nkt;      // k-tiles of its output tile from where the stream stands
     unsigned l_st = 0;        // LDS offset of the stage it writes
     // load q of a phase: its LDS destination (SET), or the load itself
@@ -403,6 +409,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         buffer_move(ra, step_a);
         buffer_move(rb, step_b);
     });
+    if (MODE != INTERIOR && !A_KC && left == 1) size_to(m0, n0, k_last);
     // the bias starts the accumulators; a tile's values are requested ahead of the previous tile's output stores (a wait for
     // a load behind them would be a wait for the stores)
     u32x2g     braw[TN];
@@ -501,10 +508,8 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             left = last ? nkt : left - 1;
             buffer_move(ra, last ? jump_a : step_a);
             buffer_move(rb, last ? jump_b : step_b);
-            if (MODE != INTERIOR && last) {
-                ra[2] = OpA::span(min(g.M - m1, BM), g.lda);
-                rb[2] = OpB::span(min(g.N - n1, BN), g.ldb);
-            }
+            if (MODE != INTERIOR && last) size_to(m1, n1, BK);
+            if (MODE != INTERIOR && !A_KC && left == 1) size_to(m0, n0, k_last);
         }
         if (fold_bias) load_bias(n1);
         dtl_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM, n0 + wn * WN, split, fold_bias, smem + 2 * STAGE + wave * dtl_out_bytes(WN), bad);
@@ -536,7 +541,7 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
     const unsigned lds_a = (unsigned)(size_t)MP_LDS_PTR(smem) + wave * 1024, lds_b = lds_a + OpA::BYTES;
     const int wm = wave >> 1, wn = wave & 1;
     const int eh = lane >> 4;
-    const int nkt    = g.K / BK;
+    const int nkt    = (g.K + BK - 1) / BK;
     const int ntiles = g.tiles_m * g.tiles_n;
     auto tile_origin = [&](const int vb, int& mm, int& nn) { dtl_tile_origin<BM, BN>(g, dtl_tile_of(vb, ntiles), mm, nn); };
 
@@ -554,8 +559,8 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
     auto stand = [&] {
         int m, n;
         tile_origin(l_vb, m, n);
-        ra = buffer_at(g.A, OpA::origin(m, g.lda), OpA::span(min(g.M - m, BM), g.lda));
-        rb = buffer_at(g.B, OpB::origin(n, g.ldb), OpB::span(min(g.N - n, BN), g.ldb));
+        ra = buffer_at(g.A, OpA::origin(m, g.lda), OpA::span(min(g.M - m, BM), g.lda, g.K));
+        rb = buffer_at(g.B, OpB::origin(n, g.ldb), OpB::span(min(g.N - n, BN), g.ldb, g.K));
     };
     stand();
     auto load = [&](auto qc, auto setc) {
@@ -574,6 +579,12 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
         if (__builtin_expect(--left > 0, 1)) {
             buffer_move(ra, step_a);
             buffer_move(rb, step_b);
+            if (MODE != INTERIOR && !A_KC && left == 1) {   // the last k-tile may be short
+                int m, n;
+                tile_origin(l_vb, m, n);
+                ra[2] = OpA::span(min(g.M - m, BM), g.lda, g.K - (nkt - 1) * BK);
+                rb[2] = OpB::span(min(g.N - n, BN), g.ldb, g.K - (nkt - 1) * BK);
+            }
         } else {
             if (l_vb + vb_step < ntiles) l_vb += vb_step;
             left = nkt;
@@ -750,7 +761,7 @@ int launch_dtl(const GemmArgs& g, dim3 grid, hipStream_t hs) {
     if constexpr (AKC && BKC) {
         if (!g.aligned) return launch_dtl_mode<BM, BN, AKC, BKC, TAIL>(g, grid, hs);
     }
-    return g.M % BM || g.N % BN ? launch_dtl_mode<BM, BN, AKC, BKC, EDGE>(g, grid, hs) : launch_dtl_mode<BM, BN, AKC, BKC, INTERIOR>(g, grid, hs);
+    return g.M % BM || g.N % BN || g.K % BK ? launch_dtl_mode<BM, BN, AKC, BKC, EDGE>(g, grid, hs) : launch_dtl_mode<BM, BN, AKC, BKC, INTERIOR>(g, grid, hs);
 }
 
 // tile index as in the planner's table; returns MP_E_UNSUPPORTED for shapes this kernel is not built for

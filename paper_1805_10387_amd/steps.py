@@ -360,9 +360,12 @@ class XentStep(_StepBase):
         T, d, V = wl.tokens, wl.d_model, wl.vocab
         self.h = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.targets = torch.empty(T, dtype=torch.int32, device="cuda")
-        self.logits = torch.empty(T, V, dtype=torch.float16, device="cuda")   # overwritten by dlogits
+        # overwritten by dlogits; rows a multiple of 8 elements apart, which every kernel reads in whole 16-byte pieces (pieces at
+        # odd addresses arrive at a third of the rate)
+        self.ld_v = _round_up(V, 8)
+        self.logits = torch.empty(T, self.ld_v, dtype=torch.float16, device="cuda")[:, :V]
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
-        self.desc = B.gemm_desc(T, V, d, epilogue=ML.MP_EPI_BIAS)
+        self.desc = B.gemm_desc(T, V, d, ldy=self.ld_v, epilogue=ML.MP_EPI_BIAS)
         self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, False), B.mp_gemm_split_workspace_bytes(self.desc),
                            B.mp_softmax_xent_db_workspace_bytes(T, V)))
 
@@ -375,7 +378,7 @@ class XentStep(_StepBase):
         T, V = wl.tokens, wl.vocab
         B.mp_gemm_fwd(self.desc, self.h, w["w"], w["b"], None, self.logits)
         # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits
-        B.mp_softmax_xent_scaled_db(T, V, self.logits, V, self.targets, self.st, self.loss, self.logits, g["b"], self.ws)
+        B.mp_softmax_xent_scaled_db(T, V, self.logits, self.ld_v, self.targets, self.st, self.loss, self.logits, g["b"], self.ws)
         B.mp_gemm_bwd_both(self.desc, self.logits, w["w"], self.dh, self.desc, self.h, g["w"], None, self.st_grad, self.ws)
 
 

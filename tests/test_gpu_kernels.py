@@ -222,6 +222,35 @@ def test_gemm_direct_to_lds_ragged_outputs(tile, rows, cols, depth):
     assert torch.all(flat[keep] == 7.0)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5])
+@pytest.mark.parametrize("tokens,N,K,splits", [(193, 391, 264, 1), (255, 130, 8, 1), (321, 1, 200, 1), (1021, 2051, 392, 1), (1021, 135, 264, 3), (200, 256, 256, 1)])
+def test_weight_gradients_of_any_token_count_direct_to_lds(tile, tokens, N, K, splits):
+    """Weight gradients whose contraction is no multiple of 64 and whose output rows are no multiple of 8, on rows that are 16-byte
+    pieces: NaN in the rows' padding and in the token rows beyond must not get in, nothing around the output may change."""
+    r = RNG(tokens + N + K + tile)
+    ld = (N + 7) // 8 * 8
+    dy, x = S16(r.standard_normal((tokens, N)) * 0.1), S16(r.standard_normal((tokens, K)))
+
+    def block(a, ldim):
+        big = np.full((a.shape[0] + 70, ldim), np.nan, np.float32)
+        big[:a.shape[0], :a.shape[1]] = a
+        return h16(big)[:a.shape[0], :a.shape[1]]
+
+    big = torch.full((N + 3, K + 8), 7.0, dtype=torch.float16, device="cuda")
+    st = make_state()
+    mp.mp_gemm_tuning_override(tile, splits)
+    mp.mp_gemm_tuning_dtl(2)
+    try:
+        mp.mp_gemm_bwd_dw(mp.gemm_desc(tokens, N, K, ldx=K + 8, ldw=K + 8, ldy=ld), block(dy, ld), block(x, K + 8), big[:N, :K], None, st,
+                          ws_bytes(16 * N * K * 4 + 4096))
+    finally:
+        mp.mp_gemm_tuning_override(-1, 0)
+        mp.mp_gemm_tuning_dtl(1)
+    assert_close16(big[:N, :K], MIXED.store(dy.T @ x), 1e-3, max_ulp=1, what="dw")
+    assert torch.all(big[N:] == 7.0) and torch.all(big[:, K:] == 7.0)
+    assert mp.scale_state_read(st).found_inf == 0
+
+
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm_bwd_dx_and_dw(M, N, K):
     r = RNG(M * 3 + N + K)
