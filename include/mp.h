@@ -247,8 +247,8 @@ int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int count, cons
 int mp_gemm_tuning_override(int tile, int splits);
 
 /* Tuning aid of the same kind (process-wide, not thread-safe, never called by a training step): which unbatched products
- * run on the kernels whose operand tiles go from global memory straight into LDS (16-byte aligned rows, a contraction that is a
- * multiple of 64 and at least 192).
+ * run on the kernels whose operand tiles go from global memory straight into LDS (16-byte aligned rows, a contraction of at least
+ * 192 that is a multiple of 8, or any where both operands are output-contiguous).
  * 0 = none, 1 = those where that is estimated to be the faster one (the built-in choice), 2 = every product they are built for
  * (all three operand layouts).  Same results contract either way (fp32 summation order may differ).  Other values: MP_E_INVAL. */
 int mp_gemm_tuning_dtl(int mode);

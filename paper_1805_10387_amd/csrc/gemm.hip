@@ -90,7 +90,9 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g, int a_kc,
 // ------------------------------------------------------------------------------------ host side
 // Tile shapes and what they cost.  A workgroup's time is fixed + per_kt x its k-tiles (of 64), us, with one workgroup on every
 // compute unit; fixed2 + per_kt2 is that of a pair sharing one.  Fitted to 3000 launches of one card (M 512 to 8192, N and K 320 to
-// 4096, the three products, N(0,1) operands, every shape forced in turn): 3 us + the sum over the rounds is off by 5 to 9 % on average.
+// 4096, the three products, N(0,1) operands, every shape forced in turn): 3 us + the sum over the rounds is off by 5 to 9 % on average.  (The two six-stage shapes, 128 x 64 and 64 x 128 straight into LDS:
+// fixed time raised by 0.3 so that they start where they win, 1718 x 768 over 256 5.9 register-staged / 6.8, 802 x 1536 over 384
+// 6.4 / 7.0, 4096 x 512 over 512 7.3 / 6.8.)
 struct TileTime {
     float fixed, per_kt, fixed2, per_kt2;   // (per_kt2 0: a pair does not fit)
 };
@@ -102,8 +104,8 @@ static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
                                  {256, 128, {3.68f, 0.75f}, {3.13f, 0.63f}},
                                  {128, 256, {3.75f, 0.76f}, {3.30f, 0.64f}},
                                  {128, 128, {1.99f, 0.50f, 3.02f, 1.08f}, {1.26f, 0.42f, 2.69f, 0.88f}},
-                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {1.74f, 0.27f}},
-                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {1.45f, 0.27f}},
+                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {2.05f, 0.27f}},
+                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {1.80f, 0.27f}},
                                  {64, 64, {0.57f, 0.30f, 1.00f, 0.46f}, {}},
                                  {32, 128, {1.00f, 0.34f, 1.60f, 0.63f}, {}},   // (not fitted: 0.9 of 128 x 64)
                                  // only when both operands are stored contraction-contiguous (the transposing loader
@@ -111,10 +113,10 @@ static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
                                  {256, 192, {5.98f, 0.88f}, {6.19f, 0.81f}}};
 constexpr int kCUs = 256;
 // us of `wgs` workgroups with k_tiles k-tiles each, without the launch
-static double rounds_us(const TileTime& t, long long wgs, double k_tiles) {
+static double rounds_us(const TileTime& t, int wgs, double k_tiles) {
     const double one = t.fixed + t.per_kt * k_tiles, two = t.fixed2 + t.per_kt2 * k_tiles;
     if (t.per_kt2 == 0.f) return (double)((wgs + kCUs - 1) / kCUs) * one;
-    const long long rest = wgs % (2 * kCUs);
+    const int rest = wgs % (2 * kCUs);
     return (double)(wgs / (2 * kCUs)) * two + (rest == 0 ? 0. : rest <= kCUs ? one : two);
 }
 constexpr int   kTileKcOnly = 8;  // first index of the shapes restricted to that operand layout
@@ -172,21 +174,27 @@ static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
         return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK, false};
     Plan   best{0, 1, 0, false};
     double best_cost = 1e300;
+    // Operands that do not fit the memory-side cache: the two stages of 128 x 128 tiles straight into LDS are too few for a
+    // contraction-transposing operand out of HBM (weight gradient 27448 x 128 over 7260: 109 us, register-staged 99;
+    // 32768 x 192 over 8192: 190 / 164)
+    const bool streamed = !kc_kc && ((double)M + N) * K > 100e6;
     for (int t = 0; t < (kc_kc ? kNumTiles : kTileKcOnly); ++t) {
         const long long tm = (M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (N + kTiles[t].bn - 1) / kTiles[t].bn;
         const long long tiles = tm * tn * batches;
         const int       max_s = allow_split ? 16 : 1;
         for (int s = 1; s <= max_s; s *= 2) {
             const int kps = ((K + s - 1) / s + BK - 1) / BK * BK;
-            if (s > 1 && (kps < 4 * BK || (long long)(s - 1) * kps >= K)) break;
-            const bool      d      = dtl && dtl_takes(t, K, s, kps);
-            if (dtl_only && !d) continue;
-            double cost = rounds_us(d ? kTiles[t].dtl : kTiles[t].reg, tiles * s, kps / (double)BK);
+            if (s > 1 && (kps < 4 * BK || (long long)(s - 1) * kps >= K || tiles > 2 * kCUs)) break;
             // the finish launch, and the fp32 partials written and read again (1024 x 1024 over 8192 in 4: 10.5 us, 512 x 512 in 8: 6.7)
-            if (s > 1) cost += 2.5 + 2.0e-6 * M * N * s;
-            if (cost < best_cost) {
-                best_cost = cost;
-                best      = Plan{t, s, kps, d};
+            const double parts = s > 1 ? 2.5 + 2.0e-6 * M * N * s : 0.;
+            for (int v = 0; v < 2; ++v) {
+                const bool d = v == 0;
+                if (d ? !dtl || !dtl_takes(t, K, s, kps) || (streamed && t == 3 && !dtl_only) : dtl_only) continue;
+                const double cost = parts + rounds_us(d ? kTiles[t].dtl : kTiles[t].reg, (int)std::min(tiles * s, 1ll << 30), kps / (double)BK);
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best      = Plan{t, s, kps, d};
+                }
             }
         }
     }
@@ -222,11 +230,11 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
 }
 
 // What the direct-to-LDS kernels take: operand rows that are whole 16-byte pieces (the output's too unless both operands are
-// contraction-contiguous), a contraction of whole k-tiles (any where both are
-// output-contiguous: their k-rows beyond it read as zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
+// contraction-contiguous), a contraction of whole pieces (any where both are
+// output-contiguous: what lies beyond it reads as zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
 static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
     const bool operands = aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0;
-    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % BK == 0 : !b_kc) &&
+    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % 8 == 0 : !b_kc) &&
            std::max(g.lda, g.ldb) < LD_BUFFER_256;
 }
 
@@ -332,8 +340,8 @@ using namespace mp;
 static size_t splitk_floats(int M, int N, int K, bool kc_kc) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
     const bool dtl = dtl_mode() != 0 && K >= DTL_MIN_K;
-    const Plan p = make_plan(M, N, K, 1, true, kc_kc, false), q = make_plan(M, N, K, 1, true, kc_kc, dtl);
-    const int  splits = std::max(p.splits, q.splits);
+    int        splits = make_plan(M, N, K, 1, true, kc_kc, false).splits;
+    if (dtl) splits = std::max(splits, make_plan(M, N, K, 1, true, kc_kc, true).splits);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;
 }
 
@@ -437,7 +445,9 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
     MP_REQUIRE(dY && X && dW, "mp_gemm_bwd_dw: NULL operand");
     const long long batches = (long long)d->batch_outer * d->batch_inner;
     MP_REQUIRE(!(db && batches != 1), "mp_gemm_bwd_dw: db is not available for batched problems");
-    const size_t need = mp_gemm_bwd_dw_workspace_bytes(d, db != nullptr);
+    const int    w_rows = d->trans_w ? d->K : d->N, w_cols = d->trans_w ? d->N : d->K;
+    const size_t sk_floats = batches == 1 ? splitk_floats(w_rows, w_cols, d->M, false) : 0;
+    const size_t need = sk_floats * sizeof(float) + (db ? mp_colsum_workspace_bytes(d->M, d->N) : 0) + 256;
     if (!ws || ws_bytes < need || !aligned16(ws)) {
         set_error("mp_gemm_bwd_dw: 16-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
         return MP_E_WORKSPACE;
@@ -457,7 +467,6 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
         g.B = dY; g.ldb = d->ldy; g.sb_o = d->sy_outer; g.sb_i = d->sy_inner; g.N = d->N;
     }
     float*       wsf       = static_cast<float*>(ws);
-    const size_t sk_floats = batches == 1 ? splitk_floats(g.M, g.N, g.K, false) : 0;
     rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? wsf : nullptr, sk_floats, as_stream(stream));
     if (rc) return rc;
     if (db) {
@@ -573,7 +582,7 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
         long long n_items = 0;
         for (int i = 0; i < count; ++i)
             n_items += (long long)(args[i].M / tm) * (args[i].N / tn) + (items[i].db ? items[i].desc.N / BIAS_COLS : 0);
-        const double cost = rounds_us(dtl ? kTiles[t].dtl : kTiles[t].reg, n_items, k_max / (double)BK);
+        const double cost = rounds_us(dtl ? kTiles[t].dtl : kTiles[t].reg, (int)std::min(n_items, 1ll << 30), k_max / (double)BK);
         if (cost < best_cost) {
             best_cost = cost;
             bm        = tm;

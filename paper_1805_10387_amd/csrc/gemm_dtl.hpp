@@ -1,5 +1,5 @@
 // Contraction kernel whose operand tiles go from global memory straight into LDS (`buffer_load ... lds`: no staging
-// registers, no LDS store instructions), for products whose rows are 16-byte aligned and whose contraction is a multiple of 64
+// registers, no LDS store instructions), for products whose rows are 16-byte aligned and whose contraction is a multiple of 8
 // (any, where both operands are output-contiguous).  Same arithmetic as gemm_kernels.hpp (paper Section 3.1: fp16 operands, fp32 sums, one rounding); what differs
 // is how the operands reach the matrix cores and how the results leave them.
 //
@@ -59,6 +59,7 @@ struct DtlOperand {
     static constexpr int RB    = 2 * UR;              // ... and bytes of a k-row
     unsigned voff[GUARD ? NL : 1];                    // this lane's byte offset from the k-tile's origin, load q (INTERIOR: load 0)
     unsigned ld;
+    int      piece;                                   // contraction-contiguous: which piece of a k-tile's row this lane fetches
     int      foff[KC ? 1 : 4];                        // fragment read offsets
 
     // output-contiguous: what a k-row's piece numbers are XOR-ed with, so that the 4 k-rows x 32 bytes of a transposing read
@@ -96,6 +97,21 @@ struct DtlOperand {
         }
         if constexpr (GUARD) {
             static_for<NL - 1>([&](auto qc) { voff[decltype(qc)::value + 1] = voff[0] + q_off<decltype(qc)::value + 1>(); });
+        }
+        piece = (lane & 7) ^ ((8 * wave + (lane >> 3)) >> 1 & 7);   // (contraction-contiguous: the same for every load)
+    }
+    // Contraction-contiguous rows whose last k-tile holds only k_last (a multiple of 8) of the contraction: while the load
+    // stream stands at it, the lanes whose piece lies beyond fetch from outside the buffer, which gives zeros.
+    __device__ __forceinline__ void tail_on(int k_last) {
+        if constexpr (KC && GUARD) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) voff[q] |= 8 * piece >= k_last ? BUF_OUT : 0u;
+        }
+    }
+    __device__ __forceinline__ void tail_off() {
+        if constexpr (KC && GUARD) {
+#pragma unroll
+            for (int q = 0; q < NL; ++q) voff[q] &= ~BUF_OUT;
         }
     }
     // Load Q of a k-tile, in two instructions of their own: its LDS destination (base: this wave's part of the stage) and, no
@@ -366,7 +382,13 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         ra[2] = OpA::span(min(g.M - m, BM), g.lda, k_left);
         rb[2] = OpB::span(min(g.N - n, BN), g.ldb, k_left);
     };
-    const int k_last = g.K - (nkt - 1) * BK;   // k of a tile's last k-tile
+    const int k_last  = g.K - (nkt - 1) * BK;   // k of a tile's last k-tile
+    int       l_m = m0, l_n = n0;               // its tile (with three k-tiles to a tile the stream is a whole tile ahead by then)
+    auto      to_last = [&] {
+        size_to(l_m, l_n, k_last);
+        oa.tail_on(k_last);
+        ob.tail_on(k_last);
+    };
     int      left = nkt;      // k-tiles of its output tile from where the stream stands
     unsigned l_st = 0;        // LDS offset of the stage it writes
     // load q of a phase: its LDS destination (SET), or the load itself
@@ -409,7 +431,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
         buffer_move(ra, step_a);
         buffer_move(rb, step_b);
     });
-    if (MODE != INTERIOR && !A_KC && left == 1) size_to(m0, n0, k_last);
+    if (MODE != INTERIOR && left == 1) to_last();
     // the bias starts the accumulators; a tile's values are requested ahead of the previous tile's output stores (a wait for
     // a load behind them would be a wait for the stores)
     u32x2g     braw[TN];
@@ -508,8 +530,14 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             left = last ? nkt : left - 1;
             buffer_move(ra, last ? jump_a : step_a);
             buffer_move(rb, last ? jump_b : step_b);
-            if (MODE != INTERIOR && last) size_to(m1, n1, BK);
-            if (MODE != INTERIOR && !A_KC && left == 1) size_to(m0, n0, k_last);
+            if (MODE != INTERIOR && last) {
+                l_m = m1;
+                l_n = n1;
+                size_to(l_m, l_n, BK);
+                oa.tail_off();
+                ob.tail_off();
+            }
+            if (MODE != INTERIOR && left == 1) to_last();
         }
         if (fold_bias) load_bias(n1);
         dtl_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM, n0 + wn * WN, split, fold_bias, smem + 2 * STAGE + wave * dtl_out_bytes(WN), bad);
@@ -579,13 +607,18 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
         if (__builtin_expect(--left > 0, 1)) {
             buffer_move(ra, step_a);
             buffer_move(rb, step_b);
-            if (MODE != INTERIOR && !A_KC && left == 1) {   // the last k-tile may be short
-                int m, n;
+            if (MODE != INTERIOR && left == 1) {   // the last k-tile may be short
+                const int k_last = g.K - (nkt - 1) * BK;
+                int       m, n;
                 tile_origin(l_vb, m, n);
-                ra[2] = OpA::span(min(g.M - m, BM), g.lda, g.K - (nkt - 1) * BK);
-                rb[2] = OpB::span(min(g.N - n, BN), g.ldb, g.K - (nkt - 1) * BK);
+                ra[2] = OpA::span(min(g.M - m, BM), g.lda, k_last);
+                rb[2] = OpB::span(min(g.N - n, BN), g.ldb, k_last);
+                oa.tail_on(k_last);
+                ob.tail_on(k_last);
             }
         } else {
+            oa.tail_off();
+            ob.tail_off();
             if (l_vb + vb_step < ntiles) l_vb += vb_step;
             left = nkt;
             stand();

@@ -278,33 +278,33 @@ class TransformerStep(_StepBase):
             with torch.cuda.stream(side):
                 fn(self.ws_side)
 
+        def layernorm_bwd(part, dy, xin, ain, ln, mean, rstd, dz, bname):
+            """One LayerNorm backward; its column sums are finished by the layer's grouped launch where there is one."""
+            if part is not None:
+                B.mp_layernorm_bwd_parts(T, d, dy, xin, ain, w[ln + "_g"], mean, rstd, dz, True, part)
+            else:
+                B.mp_layernorm_bwd(T, d, dy, xin, ain, w[ln + "_g"], mean, rstd, dz, g[ln + "_g"], g[ln + "_b"], st, ws,
+                                   dz_colsum=None if self.joint_bwd else g[bname])
+
         # the layer-output gradient ping-pongs between two [T, d] buffers; the loss wrote gbuf[0]
         for i, l in enumerate(range(wl.n_layers - 1, -1, -1)):
             dy2, dx = self.gbuf[i % 2], self.gbuf[(i + 1) % 2]
             a, p = self.act[l], f"l{l}."
             tb = self.tmp[i % 2]
             dz2, df, dz1, dqkv = tb["dz2"], tb["df"], tb["dz1"], tb["dqkv"]
-            parts = self.ln_parts[i % 2] if self.grouped_dw else None
-
-            def layernorm_bwd(k, dy, xin, ain, ln, mean, rstd, dz, bname):
-                """One LayerNorm backward; its column sums are finished by the layer's grouped launch where there is one."""
-                if self.grouped_dw:
-                    B.mp_layernorm_bwd_parts(T, d, dy, xin, ain, w[p + ln + "_g"], mean, rstd, dz, True, parts[k])
-                else:
-                    B.mp_layernorm_bwd(T, d, dy, xin, ain, w[p + ln + "_g"], mean, rstd, dz, g[p + ln + "_g"], g[p + ln + "_b"], st, ws,
-                                       dz_colsum=None if self.joint_bwd else g[p + bname])
+            parts = self.ln_parts[i % 2] if self.grouped_dw else (None, None)
             if side is not None and i >= 2:
                 main.wait_event(done[i - 2])        # side stream finished reading this parity's temporaries
             x = self.x0 if l == 0 else self.act[l - 1]["y2"]
             # dz2 is the gradient of g = W2 f + b2 too, so its column sums are b2's gradient
-            layernorm_bwd(0, dy2, a["y1"], a["g"], "ln2", a["mean2"], a["rstd2"], dz2, "b2")
+            layernorm_bwd(parts[0], dy2, a["y1"], a["g"], p + "ln2", a["mean2"], a["rstd2"], dz2, p + "b2")
             self._t("dy2", l, dy2)
             self._t("dz2", l, dz2)
             linear_bwd(self.d_f2, dz2, p + "w2", p + "b2", a["f"], df, False, relu_src=a["f"], ld_aux=f)
             self._t("df", l, df)
             linear_bwd(self.d_f1, df, p + "w1", p + "b1", a["y1"], self.dy1, True, add=dz2, ld_aux=d)
             self._t("dy1", l, self.dy1)
-            layernorm_bwd(1, self.dy1, x, a["a"], "ln1", a["mean1"], a["rstd1"], dz1, "bo")
+            layernorm_bwd(parts[1], self.dy1, x, a["a"], p + "ln1", a["mean1"], a["rstd1"], dz1, p + "bo")
             self._t("dz1", l, dz1)
             linear_bwd(self.d_o, dz1, p + "wo", p + "bo", a["ctx"], self.dctx, False)
             self._t("dctx", l, self.dctx)

@@ -134,11 +134,12 @@ def test_gemm_direct_to_lds_kernels_all_layouts(tile, M, N, K):
 
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 8])
 @pytest.mark.parametrize("rows,cols,depth,splits", [(264, 200, 192, 1), (1, 8, 256, 1), (257, 392, 320, 1), (3233, 1544, 448, 1),
-                                                    (128, 256, 1024, 3), (136, 264, 1344, 4), (512, 384, 192, 1)])
+                                                    (128, 256, 1024, 3), (136, 264, 1344, 4), (512, 384, 192, 1), (257, 256, 200, 1), (264, 392, 264, 1),
+                                                    (4360, 4104, 192, 1), (4360, 4104, 200, 1), (136, 264, 1000, 3)])
 def test_gemm_direct_to_lds_borders(tile, rows, cols, depth, splits):
     """The same kernels where output tiles stick out of the matrix (rows and columns just past a tile, far below one, several
-    tiles per workgroup), at the shortest contraction they take (three k-tiles), with odd k-tile counts and with a split
-    contraction whose last part is shorter.  Operands and outputs are blocks of larger arrays: NaN around the operands must not
+    tiles per workgroup), at the shortest contraction they take (three k-tiles), with odd k-tile counts, with a last k-tile of 1, 5
+    and 7 pieces, and with a split contraction whose last part is shorter.  Operands and outputs are blocks of larger arrays: NaN around the operands must not
     get in, nothing around an output may change.  mp_gemm_tuning_dtl(2) keeps the call on these kernels."""
     r = RNG(rows + cols + depth + tile)
 
