@@ -366,7 +366,7 @@ def main():
         "step_gemm_tflops": wl.gemm_flops_per_step() / (ms_per_step * 1e-3) * 1e-12,
         "step_mfma_util_pct": 100.0 * wl.gemm_flops_per_step() / (ms_per_step * 1e-3) * 1e-12 / PEAK_FP16_TFLOPS,
         "final_loss": loss, "loss_scale": st.scale, "opt_steps": st.opt_step, "skipped": st.skipped_steps,
-        "roofline": {"bound": "mfma", "kernel": "gemm_kernel / gemm_dtl_grouped_kernel (every dense fp16 contraction of the step: per layer 4 fwd, 4 dX, and the 4 dW in one grouped launch)",
+        "roofline": {"bound": "mfma", "kernel": "gemm_dtl_kernel / gemm_dtl_grouped_kernel (every dense fp16 contraction of the step: per layer 4 fwd, 4 dX, and the 4 dW in one grouped launch)",
                      "achieved": flops / secs * 1e-12, "peak": PEAK_FP16_TFLOPS, "unit": "TFLOP/s",
                      "frac": flops / secs * 1e-12 / PEAK_FP16_TFLOPS,
                      "traffic": traffic["gemm"],
