@@ -15,11 +15,11 @@ extern template int launch_tile<false, false>(int, const GemmArgs&, dim3, hipStr
 extern template int launch_dtl_tile<true, true>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_dtl_tile<true, false>(int, const GemmArgs&, dim3, hipStream_t);
 extern template int launch_dtl_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
-extern template int launch_grouped<256, 256>(GroupArgs, int, hipStream_t);
-extern template int launch_grouped<128, 128>(GroupArgs, int, hipStream_t);
-extern template int launch_dtl_grouped<256, 256>(GroupArgs, int, hipStream_t);
-extern template int launch_dtl_grouped<256, 128>(GroupArgs, int, hipStream_t);
-extern template int launch_dtl_grouped<128, 128>(GroupArgs, int, hipStream_t);
+extern template int launch_grouped<256, 256>(const GroupArgs&, hipStream_t);
+extern template int launch_grouped<128, 128>(const GroupArgs&, hipStream_t);
+extern template int launch_dtl_grouped<256, 256>(const GroupArgs&, hipStream_t);
+extern template int launch_dtl_grouped<256, 128>(const GroupArgs&, hipStream_t);
+extern template int launch_dtl_grouped<128, 128>(const GroupArgs&, hipStream_t);
 
 // Sum split-K partials in split order, scale, round once, optional non-finite flag.
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ part, int splits, long long mn,
@@ -568,57 +568,15 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
         n256 = n256 && g.N % 256 == 0;
         dtl  = dtl && g.K >= DTL_MIN_K && std::max(g.lda, g.ldb) < LD_BUFFER_256;
     }
-    // Tile shape: the one with the least estimated time (a strip of a bias gradient counted as a tile).  Large tiles win once
-    // they fill the chip (a layer with d_model 1024: 192 tiles of 256 x 256 and 56 strips in one round); with fewer, most
-    // compute units would idle through a long contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the
-    // register-staged kernels, against 192 of 128 x 128, 49 us).
-    int    k_max = 0;
-    for (int i = 0; i < count; ++i) k_max = std::max(k_max, args[i].K);
-    int    bm = 128, bn = 128;
-    double best_cost = 1e300;
-    for (int t : {0, 1, 3}) {
-        const int tm = kTiles[t].bm, tn = kTiles[t].bn;
-        if ((tm == 256 && !m256) || (tn == 256 && !n256) || (t == 1 && !dtl)) continue;
-        long long n_items = 0;
-        for (int i = 0; i < count; ++i)
-            n_items += (long long)(args[i].M / tm) * (args[i].N / tn) + (items[i].db ? items[i].desc.N / BIAS_COLS : 0);
-        const double cost = rounds_us(dtl ? kTiles[t].dtl : kTiles[t].reg, (int)std::min(n_items, 1ll << 30), k_max / (double)BK);
-        if (cost < best_cost) {
-            best_cost = cost;
-            bm        = tm;
-            bn        = tn;
-        }
-    }
-    // longest contraction first, so that the tiles that take longest start first
-    int order[GROUP_MAX];
-    for (int i = 0; i < count; ++i) order[i] = i;
-    for (int i = 1; i < count; ++i)
-        for (int j = i; j > 0 && args[order[j]].K > args[order[j - 1]].K; --j) std::swap(order[j], order[j - 1]);
+    // what rides along: strips of bias gradients and columns of the other sums
     GroupArgs ga{};
-    ga.count = count;
-    long long total = 0;
+    int       strips = 0, strip_rows = 0, sum_rows = 0, k_max = 0;
     for (int i = 0; i < count; ++i) {
-        const GemmArgs& g = args[order[i]];
-        ga.p[i]          = GroupItem{g.A, g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.M / bm, g.N / bn, g.alpha};
-        ga.tile_start[i] = (int)total;
-        total += (long long)(g.M / bm) * (g.N / bn);
+        k_max = std::max(k_max, args[i].K);
+        if (!items[i].db) continue;
+        strips += items[i].desc.N / BIAS_COLS;      // N is a multiple of 128 here (checked above for either orientation)
+        strip_rows = std::max(strip_rows, items[i].desc.M);
     }
-    ga.found_inf = st ? &st->found_inf : nullptr;
-    MP_REQUIRE(total < (1 << 24), "mp_gemm_bwd_dw_grouped: too many tiles");
-    for (int i = count; i <= GROUP_MAX; ++i) ga.tile_start[i] = (int)total;
-    // bias gradients: strips of BIAS_COLS columns of dY[M, N], numbered after the product tiles (same item order)
-    int strips = 0;
-    for (int i = 0; i < count; ++i) {
-        const mp_gemm_group_item& it = items[order[i]];
-        if (!it.db) continue;
-        BiasItem& b = ga.b[ga.nbias];
-        b.dY = reinterpret_cast<const unsigned short*>(it.dY);
-        b.db = reinterpret_cast<unsigned short*>(it.db);
-        b.ld = it.desc.ldy; b.rows = it.desc.M;
-        ga.strip_start[ga.nbias++] = strips;
-        strips += it.desc.N / BIAS_COLS;      // N is a multiple of 128 here (checked above for either orientation)
-    }
-    for (int i = ga.nbias; i <= GROUP_MAX; ++i) ga.strip_start[i] = strips;
     for (int i = 0; i < nsums; ++i) {
         const mp_colsum_parts& c = sums[i];
         MP_REQUIRE(c.part && aligned16(c.part) && c.nparts > 0 && c.cols > 0 && c.cols % BIAS_COLS == 0 && c.nseg >= 1 && c.nseg <= 3,
@@ -630,12 +588,67 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
             s.out[k] = reinterpret_cast<unsigned short*>(c.out[k]);
         }
         ga.sum_start[i + 1] = ga.sum_start[i] + c.nseg * (c.cols / BIAS_COLS);
+        sum_rows            = std::max(sum_rows, c.nparts);
     }
     ga.nsums = nsums;
     for (int i = nsums; i < SUMS_MAX; ++i) ga.sum_start[i + 1] = ga.sum_start[i];
-    if (dtl) {
-        if (bn == 256) return launch_dtl_grouped<256, 256>(ga, kCUs, as_stream(stream));
-        return bm == 256 ? launch_dtl_grouped<256, 128>(ga, kCUs, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
+    const int columns = ga.sum_start[nsums];
+    // Tile shape: the one with the least estimated time (a strip of a bias gradient counted as a tile).  Large tiles win once
+    // they fill the chip (a layer with d_model 1024: 192 tiles of 256 x 256 and 56 strips in one round); with fewer, most
+    // compute units would idle through a long contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the
+    // register-staged kernels, against 192 of 128 x 128, 49 us).
+    int    bm = 128, bn = 128;
+    double best_cost = 1e300;
+    for (int t : {0, 1, 3}) {
+        const int tm = kTiles[t].bm, tn = kTiles[t].bn;
+        if ((tm == 256 && !m256) || (tn == 256 && !n256) || (t == 1 && !dtl)) continue;
+        long long tiles = 0;
+        for (int i = 0; i < count; ++i) tiles += (long long)(args[i].M / tm) * (args[i].N / tn);
+        if (tiles >= (1 << 24)) continue;
+        const TileTime&  time     = dtl ? kTiles[t].dtl : kTiles[t].reg;
+        const int        resident = kCUs * (time.per_kt2 > 0.f ? 2 : 1);
+        const double     kt = k_max / (double)BK, last_us = rounds_us(time, ((int)tiles - 1) % resident + 1, kt);
+        const GroupShare share = group_share((int)tiles, strips, strip_rows, columns, sum_rows, resident, last_us);
+        const double     cost = rounds_us(time, (int)std::min(tiles + strips, 1ll << 30), kt);
+        if (cost < best_cost) {
+            best_cost = cost;
+            bm        = tm;
+            bn        = tn;
+            ga.share  = share;
+        }
     }
-    return bm == 256 ? launch_grouped<256, 256>(ga, kCUs, as_stream(stream)) : launch_grouped<128, 128>(ga, 2 * kCUs, as_stream(stream));
+    MP_REQUIRE(best_cost < 1e300, "mp_gemm_bwd_dw_grouped: too many tiles");
+    // longest contraction first, so that the tiles that take longest start first
+    int order[GROUP_MAX];
+    for (int i = 0; i < count; ++i) order[i] = i;
+    for (int i = 1; i < count; ++i)
+        for (int j = i; j > 0 && args[order[j]].K > args[order[j - 1]].K; --j) std::swap(order[j], order[j - 1]);
+    ga.count = count;
+    long long total = 0;
+    for (int i = 0; i < count; ++i) {
+        const GemmArgs& g = args[order[i]];
+        ga.p[i]          = GroupItem{g.A, g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, g.M / bm, g.N / bn, g.alpha};
+        ga.tile_start[i] = (int)total;
+        total += (long long)(g.M / bm) * (g.N / bn);
+    }
+    ga.found_inf = st ? &st->found_inf : nullptr;
+    for (int i = count; i <= GROUP_MAX; ++i) ga.tile_start[i] = (int)total;
+    // bias gradients: strips of BIAS_COLS columns of dY[M, N], numbered after the product tiles (same item order)
+    strips = 0;
+    for (int i = 0; i < count; ++i) {
+        const mp_gemm_group_item& it = items[order[i]];
+        if (!it.db) continue;
+        BiasItem& b = ga.b[ga.nbias];
+        b.dY = reinterpret_cast<const unsigned short*>(it.dY);
+        b.db = reinterpret_cast<unsigned short*>(it.db);
+        b.ld = it.desc.ldy; b.rows = it.desc.M;
+        ga.strip_start[ga.nbias++] = strips;
+        strips += it.desc.N / BIAS_COLS;
+    }
+    for (int i = ga.nbias; i <= GROUP_MAX; ++i) ga.strip_start[i] = strips;
+    if (dtl) {
+        if (bn == 256) return launch_dtl_grouped<256, 256>(ga, as_stream(stream));
+        return bm == 256 ? launch_dtl_grouped<256, 128>(ga, as_stream(stream)) : launch_dtl_grouped<128, 128>(ga, as_stream(stream));
+    }
+    return bm == 256 ? launch_grouped<256, 256>(ga, as_stream(stream)) : launch_grouped<128, 128>(ga, as_stream(stream));
 }

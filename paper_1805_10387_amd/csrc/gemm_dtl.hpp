@@ -758,7 +758,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_grouped_kernel(GroupArg
 }
 
 template <int BM, int BN>
-int launch_dtl_grouped(GroupArgs ga, int resident, hipStream_t hs) {
+int launch_dtl_grouped(const GroupArgs& ga, hipStream_t hs) {
     constexpr size_t  lds = dtl_lds(BM, BN);
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
@@ -767,7 +767,7 @@ int launch_dtl_grouped(GroupArgs ga, int resident, hipStream_t hs) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    hipLaunchKernelGGL((gemm_dtl_grouped_kernel<BM, BN>), dim3(group_workgroups(ga, resident)), dim3(GEMM_THREADS), lds, hs, ga);
+    hipLaunchKernelGGL((gemm_dtl_grouped_kernel<BM, BN>), dim3(ga.share.wgs), dim3(GEMM_THREADS), lds, hs, ga);
     MP_LAUNCH_CHECK("grouped gemm launch (direct-to-LDS)");
     return MP_OK;
 }

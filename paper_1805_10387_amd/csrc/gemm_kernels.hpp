@@ -19,6 +19,7 @@
 //     lane l, accumulator register r  ->  row m = l % 32,  col n = 8*(r/4) + 4*(l/32) + r%4.
 #pragma once
 #include "common.hpp"
+#include "group_rule.hpp"
 
 #include <mutex>
 #include <type_traits>
@@ -698,8 +699,8 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_kernel(GemmArgs g) {
 // alone has too few tiles for the chip).  Tiles of all problems are numbered one after the other, largest problem
 // first; no batches, no k-splits.
 constexpr int GROUP_MAX = 8;
-// A bias gradient riding in a grouped launch: column sums of dY[rows, cols], cut into strips of BIAS_COLS columns
-// that are numbered after the product tiles (a strip is one work item for a workgroup, like a tile).
+// A bias gradient riding in a grouped launch: column sums of dY[rows, cols], cut into strips of BIAS_COLS columns, each a work
+// item for a workgroup (group_rule.hpp says for which).
 constexpr int BIAS_COLS = 128;
 struct BiasItem {
     const unsigned short* dY;  // fp16 bits
@@ -731,7 +732,7 @@ struct GroupArgs {
     SumItem  s[SUMS_MAX];
     int      sum_start[SUMS_MAX + 1];     // in columns of BIAS_COLS; sum_start[nsums] = their number
     int      nsums;
-    int      tile_wgs;                    // workgroups 0 .. tile_wgs - 1 take tiles
+    GroupShare share;
 };
 
 // db[strip] = RNE16(fp32 column sums of a 128-column strip of dY), by one workgroup of 256 threads: 16 lanes x 8
@@ -864,22 +865,18 @@ __device__ inline void group_small_item(const GroupArgs& ga, int j, char* smem, 
     }
     finish_sums(it, (j - first) * BIAS_COLS, smem, bad);
 }
-// Work of one workgroup: the first tile_wgs take tiles, the others (where the tiles leave compute units idle) the small
-// items, which are short against a tile; where there are no others, everybody takes some after its tiles.
+// work of one workgroup
 template <typename TILE>
 __device__ __forceinline__ void group_run(const GroupArgs& ga, char* smem, bool& bad, TILE&& tile) {
     const int total = ga.tile_start[ga.count], small = ga.strip_start[ga.nbias] + ga.sum_start[ga.nsums];
-    const int others = gridDim.x - ga.tile_wgs;
-    if ((int)blockIdx.x < ga.tile_wgs) {
-        for (int vb = blockIdx.x; vb < total; vb += ga.tile_wgs) {
-            // consecutive workgroup ids go round-robin over the 8 XCDs: give each XCD, and its L2, a contiguous run of
-            // tiles (neighbouring tiles share operand panels)
-            const int q = total >> 3, rem = total & 7, x = vb & 7;
-            tile(x * q + min(x, rem) + (vb >> 3));
-        }
-        if (others > 0) return;
-    }
-    for (int j = others > 0 ? blockIdx.x - ga.tile_wgs : blockIdx.x; j < small; j += others > 0 ? others : (int)gridDim.x) group_small_item(ga, j, smem, bad);
+    group_walk(ga.share, total, small, blockIdx.x,
+               [&](const int vb) {
+                   // consecutive workgroup ids go round-robin over the 8 XCDs: give each XCD, and its L2, a contiguous run of
+                   // tiles (neighbouring tiles share operand panels)
+                   const int q = total >> 3, rem = total & 7, x = vb & 7;
+                   tile(x * q + min(x, rem) + (vb >> 3));
+               },
+               [&](const int j) { group_small_item(ga, j, smem, bad); });
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC>
@@ -948,14 +945,8 @@ int launch_tile(int t, const GemmArgs& g, dim3 grid, hipStream_t hs) {
     }
 }
 
-// sets tile_wgs; returns the number of workgroups
-inline int group_workgroups(GroupArgs& ga, int resident) {
-    const int total = ga.tile_start[ga.count], small = ga.strip_start[ga.nbias] + ga.sum_start[ga.nsums];
-    ga.tile_wgs = total < resident ? total : resident;
-    return ga.tile_wgs + (small < resident - ga.tile_wgs ? small : resident - ga.tile_wgs);
-}
 template <int BM, int BN>
-int launch_grouped(GroupArgs ga, int resident, hipStream_t hs) {
+int launch_grouped(const GroupArgs& ga, hipStream_t hs) {
     constexpr size_t  lds = 2 * (size_t)(BM + BN) * 128;
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
@@ -964,7 +955,7 @@ int launch_grouped(GroupArgs ga, int resident, hipStream_t hs) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    hipLaunchKernelGGL((gemm_grouped_kernel<BM, BN, 2, 2, false, false>), dim3(group_workgroups(ga, resident)), dim3(GEMM_THREADS), lds, hs, ga);
+    hipLaunchKernelGGL((gemm_grouped_kernel<BM, BN, 2, 2, false, false>), dim3(ga.share.wgs), dim3(GEMM_THREADS), lds, hs, ga);
     MP_LAUNCH_CHECK("grouped gemm launch");
     return MP_OK;
 }

@@ -4,9 +4,9 @@
 namespace mp {
 template int launch_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
 template int launch_dtl_tile<false, false>(int, const GemmArgs&, dim3, hipStream_t);
-template int launch_grouped<256, 256>(GroupArgs, int, hipStream_t);
-template int launch_grouped<128, 128>(GroupArgs, int, hipStream_t);
-template int launch_dtl_grouped<256, 256>(GroupArgs, int, hipStream_t);
-template int launch_dtl_grouped<256, 128>(GroupArgs, int, hipStream_t);
-template int launch_dtl_grouped<128, 128>(GroupArgs, int, hipStream_t);
+template int launch_grouped<256, 256>(const GroupArgs&, hipStream_t);
+template int launch_grouped<128, 128>(const GroupArgs&, hipStream_t);
+template int launch_dtl_grouped<256, 256>(const GroupArgs&, hipStream_t);
+template int launch_dtl_grouped<256, 128>(const GroupArgs&, hipStream_t);
+template int launch_dtl_grouped<128, 128>(const GroupArgs&, hipStream_t);
 }  // namespace mp

@@ -324,8 +324,7 @@ class TransformerStep(_StepBase):
             self._t("dx", l, dx)
             if self.grouped_dw:
                 # all four operand pairs of this layer are still in place (the temporaries alternate by layer); the
-                # two bias gradients that no LayerNorm backward produced ride in the same launch, on CUs that the
-                # product tiles (fewer than the chip has CUs) leave idle
+                # two bias gradients that no LayerNorm backward produced ride in the same launch
                 key = (l, i % 2)
                 if key not in self._groups:
                     over = lambda x: B.gemm_desc(self.T_dw, x.N, x.K)  # noqa: E731  (the zero rows too)
