@@ -593,10 +593,12 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
     ga.nsums = nsums;
     for (int i = nsums; i < SUMS_MAX; ++i) ga.sum_start[i + 1] = ga.sum_start[i];
     const int columns = ga.sum_start[nsums];
-    // Tile shape: the one with the least estimated time (a strip of a bias gradient counted as a tile).  Large tiles win once
-    // they fill the chip (a layer with d_model 1024: 192 tiles of 256 x 256 and 56 strips in one round); with fewer, most
-    // compute units would idle through a long contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the
-    // register-staged kernels, against 192 of 128 x 128, 49 us).
+    // Tile shape: the one with the least estimated time.  Large tiles win once they fill the chip (a layer with d_model 1024: 192
+    // tiles of 256 x 256 in one round, the strips beside them); with fewer, most compute units would idle through a long
+    // contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the register-staged kernels, against 192 of 128 x 128, 49 us).
+    // Strips beside tiles count nothing (us, 256 x 256 / 256 x 128 / 128 x 128, 8192 rows: d_model 1024, 4096 wide 171 / 217 / 267,
+    // with a bias gradient for each of the four 199 / - / 236; d_model 768, 3072 wide - / 167 / 150; d_model 512, 2048 wide, 4096
+    // rows 75 / 52 / 36).
     int    bm = 128, bn = 128;
     double best_cost = 1e300;
     for (int t : {0, 1, 3}) {
@@ -607,9 +609,9 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
         if (tiles >= (1 << 24)) continue;
         const TileTime&  time     = dtl ? kTiles[t].dtl : kTiles[t].reg;
         const int        resident = kCUs * (time.per_kt2 > 0.f ? 2 : 1);
-        const double     kt = k_max / (double)BK, last_us = rounds_us(time, ((int)tiles - 1) % resident + 1, kt);
+        const double     kt = k_max / (double)BK, all_us = rounds_us(time, (int)tiles, kt), last_us = rounds_us(time, ((int)tiles - 1) % resident + 1, kt);
         const GroupShare share = group_share((int)tiles, strips, strip_rows, columns, sum_rows, resident, last_us);
-        const double     cost = rounds_us(time, (int)std::min(tiles + strips, 1ll << 30), kt);
+        const double     cost = group_us(share, strips, strip_rows, columns, sum_rows, all_us);
         if (cost < best_cost) {
             best_cost = cost;
             bm        = tm;

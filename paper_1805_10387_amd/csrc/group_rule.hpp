@@ -58,5 +58,10 @@ inline GroupShare group_share(const int tiles, const int strips, const int strip
     }
     return s;
 }
+// us of the launch whose tiles take tiles_us: items beside tiles cost nothing, those behind them a round each
+inline double group_us(const GroupShare& s, const int strips, const int strip_rows, const int sums, const int sum_rows, const double tiles_us) {
+    const int left = strips + sums - s.first;
+    return tiles_us + (left + s.wgs - 1) / s.wgs * item_us_alone(s.first < strips ? strip_rows : sum_rows);
+}
 
 }  // namespace mp

@@ -18,6 +18,7 @@ extern "C" int walk(int tiles, int strips, int strip_rows, int sums, int sum_row
         mp::group_walk(s, tiles, strips + sums, w, [&](int t) { tile_wg[t] = tile_wg[t] == -1 ? w : -2; },
                        [&](int j) { item_wg[j] = item_wg[j] == -1 ? w : -2; });
     us[0] = mp::item_us_beside(strip_rows); us[1] = mp::item_us_beside(sum_rows); us[2] = mp::item_us_alone(strip_rows); us[3] = mp::item_us_alone(sum_rows);
+    us[4] = mp::group_us(s, strips, strip_rows, sums, sum_rows, 1000. * round_us);
     return s.wgs;
 }
 """
@@ -47,7 +48,7 @@ def test_small_items_of_a_grouped_launch(group, strips, sums, resident, round_fi
     one more than any other; so the launch ends soon after its tiles."""
     round_us = round_fixed + round_row * rows
     for tiles in (1, 48, 192, 255, 256, 257, 432, 496, 504, 510, 511, 512, 513, 588, 600, 1023, 1024, 5000):
-        tile_wg, item_wg, us = (C.c_int * tiles)(*[-1] * tiles), (C.c_int * (strips + sums + 1))(*[-1] * (strips + sums + 1)), (C.c_double * 4)()
+        tile_wg, item_wg, us = (C.c_int * tiles)(*[-1] * tiles), (C.c_int * (strips + sums + 1))(*[-1] * (strips + sums + 1)), (C.c_double * 5)()
         wgs = group.walk(tiles, strips, rows, sums, 256, resident, round_us, tile_wg, item_wg, us)
         assert 1 <= wgs <= resident and all(0 <= w < wgs for w in tile_wg) and all(0 <= w < wgs for w in item_wg[:strips + sums])
         n_tiles, n_strips, n_sums = [0] * wgs, [0] * wgs, [0] * wgs
@@ -68,3 +69,7 @@ def test_small_items_of_a_grouped_launch(group, strips, sums, resident, round_fi
             assert behind <= -(-items // wgs)
         if idle and -(-strips // len(idle)) * us[0] + -(-sums // len(idle)) * us[1] <= round_us:
             assert behind == 0           # the idle ones have the time
+        # the estimate the tile shape is chosen by: items beside tiles cost nothing (strips counted as tiles made a second round of
+        # 192 tiles of 256 x 256 and 72 strips), items behind them a round each
+        assert us[4] >= 1000 * round_us - 1e-9 and (us[4] <= 1000 * round_us + 1e-9) == (behind == 0 or items == 0)
+        assert us[4] <= 1000 * round_us + -(-items // wgs) * max(us[2], us[3]) + 1e-9
