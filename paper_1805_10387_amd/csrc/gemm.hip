@@ -1,5 +1,5 @@
-// Contractions: planner, split-K finish, generic fallback and the C entry points.  The matrix-core kernel templates are
-// in gemm_kernels.hpp and are instantiated in gemm_kk.hip / gemm_ko.hip / gemm_oo.hip.
+// Contractions: split-K finish, generic fallback and the C entry points.  The matrix-core kernel templates are in gemm_kernels.hpp and
+// are instantiated in gemm_kk.hip / gemm_ko.hip / gemm_oo.hip; gemm_plan.hpp picks among them.
 #include "gemm_dtl.hpp"
 #include "gemm_small.hpp"
 
@@ -88,120 +88,7 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmArgs g, int a_kc,
 }
 
 // ------------------------------------------------------------------------------------ host side
-// Tile shapes and what they cost.  A workgroup's time is fixed + per_kt x its k-tiles (of 64), us, with one workgroup on every
-// compute unit; fixed2 + per_kt2 is that of a pair sharing one.  Fitted to 3000 launches of one card (M 512 to 8192, N and K 320 to
-// 4096, the three products, N(0,1) operands, every shape forced in turn): 3 us + the sum over the rounds is off by 5 to 9 % on average.  (The two six-stage shapes, 128 x 64 and 64 x 128 straight into LDS:
-// fixed time raised by 0.3 so that they start where they win, 1718 x 768 over 256 5.9 register-staged / 6.8, 802 x 1536 over 384
-// 6.4 / 7.0, 4096 x 512 over 512 7.3 / 6.8.)
-struct TileTime {
-    float fixed, per_kt, fixed2, per_kt2;   // (per_kt2 0: a pair does not fit)
-};
-struct TileCfg {
-    int      bm, bn;
-    TileTime reg, dtl;  // register-staged kernel; kernel that loads straight into LDS (gemm_dtl.hpp; per_kt 0: not built)
-};
-static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
-                                 {256, 128, {3.68f, 0.75f}, {3.13f, 0.63f}},
-                                 {128, 256, {3.75f, 0.76f}, {3.30f, 0.64f}},
-                                 {128, 128, {1.99f, 0.50f, 3.02f, 1.08f}, {1.26f, 0.42f, 2.69f, 0.88f}},
-                                 {128, 64, {1.09f, 0.38f, 1.73f, 0.70f}, {2.05f, 0.27f}},
-                                 {64, 128, {1.08f, 0.39f, 1.84f, 0.69f}, {1.80f, 0.27f}},
-                                 {64, 64, {0.57f, 0.30f, 1.00f, 0.46f}, {}},
-                                 {32, 128, {1.00f, 0.34f, 1.60f, 0.63f}, {}},   // (not fitted: 0.9 of 128 x 64)
-                                 // only when both operands are stored contraction-contiguous (the transposing loader
-                                 // wants a power-of-two tile edge): fills the chip evenly when N is a multiple of 192 only
-                                 {256, 192, {5.98f, 0.88f}, {6.19f, 0.81f}}};
-constexpr int kCUs = 256;
-// us of `wgs` workgroups with k_tiles k-tiles each, without the launch
-static double rounds_us(const TileTime& t, int wgs, double k_tiles) {
-    const double one = t.fixed + t.per_kt * k_tiles, two = t.fixed2 + t.per_kt2 * k_tiles;
-    if (t.per_kt2 == 0.f) return (double)((wgs + kCUs - 1) / kCUs) * one;
-    const int rest = wgs % (2 * kCUs);
-    return (double)(wgs / (2 * kCUs)) * two + (rest == 0 ? 0. : rest <= kCUs ? one : two);
-}
-constexpr int   kTileKcOnly = 8;  // first index of the shapes restricted to that operand layout
-constexpr int   kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-// then 32 x 32 with the contraction dealt to 4 or to 8 waves (gemm_small.hpp), unbatched only
-constexpr int   kTileSmall4 = kNumTiles, kTileSmall8 = kNumTiles + 1;
-
-// Products for the small kernel: up to two workgroups per compute unit, and not so long a contraction that reading the
-// operand panels anew for every 32 x 32 tile outweighs the short chain.  us alone, larger tiles against this kernel:
-// 64 x 1024 over 256 4.1 / 3.0, 64 x 256 over 1024 6.7 / 4.4, 520 x 256 over 3000 16.3 / 8.3, 1024 x 161 over 1500 15.2 / 7.9.
-// At the line, forward, input gradient, weight gradient: 512 x 512 over 3072 14.9 / 8.9, 16.6 / 10.7, 12.1 / 11.9;
-// 256 x 2048 over 1536 9.7 / 8.7, 10.5 / 10.1, 12.1 / 11.3; the least gain of 288 sizes inside it: 1024 x 512 over 1024 7.7 / 7.0,
-// 8.3 / 8.6, 10.9 / 9.5.  Beyond it 512 x 512 over 4096 13.0 / 16.8, 1024 x 1024 over 1024 7.3 / 10.0.
-static long long small_tiles(int M, int N) { return ((M + 31) / 32) * (long long)((N + 31) / 32); }
-static bool      small_wins(int M, int N, int K) {
-    const long long t = small_tiles(M, N);
-    return t <= 2 * kCUs && K <= 4096 && t * K <= 3072ll * kCUs;
-}
-// 8 waves (64 KB of LDS) when a workgroup has its compute unit to itself and each wave several k-tiles: 512 x 512 over
-// 4096 20.7 -> 16.8 us, 1500 x 29 over 1024 6.6 -> 5.7; shorter contractions lose 0.2 us in the longer final sum.
-static int small_waves(long long tiles, int K) { return tiles <= kCUs && K > 512 ? 8 : 4; }
-
-struct Plan {
-    int  tile, splits, k_per_split;
-    bool dtl;  // on the kernel that loads straight into LDS
-};
-static int g_force_tile = -1, g_force_splits = 1;
-
-// Which products take the direct-to-LDS kernels (mp_gemm_tuning_dtl): 0 = none, 1 (default) = where the plan finds them the
-// faster ones, 2 = every product they are built for.
-static int g_dtl_mode = 1;
-static int dtl_mode() { return g_dtl_mode; }
-// (contraction K in parts of kps: each has to hold the load stream's lead)
-static bool dtl_takes(int tile, int K, int splits, int kps) {
-    return tile < kNumTiles && kTiles[tile].dtl.per_kt > 0.f && (splits == 1 ? K : std::min(kps, K - (splits - 1) * kps)) >= DTL_MIN_K;
-}
-
-// Pick the tile shape (and split count when allowed) that minimises the estimate of run time.  dtl: the operands are fit for the direct-to-LDS kernels
-static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool kc_kc, bool dtl) {
-    // tuning aid (mp_gemm_tuning_override): force a tile shape / split count
-    if (g_force_tile >= 0) {
-        int t = g_force_tile < (kc_kc ? kNumTiles : kTileKcOnly) || g_force_tile >= kTileSmall4 ? g_force_tile : 0, sp = allow_split ? g_force_splits : 1;
-        if (sp < 1) sp = 1;
-        if (sp > 16) sp = 16;
-        // every split must own at least one k-tile: (sp - 1) * k_per_split < K, as in the planner's own search
-        int kps = ((K + sp - 1) / sp + BK - 1) / BK * BK;
-        while (sp > 1 && (long long)(sp - 1) * kps >= K) {
-            --sp;
-            kps = ((K + sp - 1) / sp + BK - 1) / BK * BK;
-        }
-        return Plan{t, sp, kps > 0 ? kps : BK, dtl && dtl_takes(t, K, sp, kps)};
-    }
-    const bool dtl_only = dtl && dtl_mode() == 2;
-    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
-        return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK, false};
-    Plan   best{0, 1, 0, false};
-    double best_cost = 1e300;
-    // Operands that do not fit the memory-side cache: the two stages of 128 x 128 tiles straight into LDS are too few for a
-    // contraction-transposing operand out of HBM (weight gradient 27448 x 128 over 7260: 109 us, register-staged 99;
-    // 32768 x 192 over 8192: 190 / 164)
-    const bool streamed = !kc_kc && ((double)M + N) * K > 100e6;
-    for (int t = 0; t < (kc_kc ? kNumTiles : kTileKcOnly); ++t) {
-        const long long tm = (M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (N + kTiles[t].bn - 1) / kTiles[t].bn;
-        const long long tiles = tm * tn * batches;
-        const int       max_s = allow_split ? 16 : 1;
-        for (int s = 1; s <= max_s; s *= 2) {
-            const int kps = ((K + s - 1) / s + BK - 1) / BK * BK;
-            if (s > 1 && (kps < 4 * BK || (long long)(s - 1) * kps >= K || tiles > 2 * kCUs)) break;
-            // the finish launch, and the fp32 partials written and read again (1024 x 1024 over 8192 in 4: 10.5 us, 512 x 512 in 8: 6.7)
-            const double parts = s > 1 ? 2.5 + 2.0e-6 * M * N * s : 0.;
-            for (int v = 0; v < 2; ++v) {
-                const bool d = v == 0;
-                if (d ? !dtl || !dtl_takes(t, K, s, kps) || (streamed && t == 3 && !dtl_only) : dtl_only) continue;
-                const double cost = parts + rounds_us(d ? kTiles[t].dtl : kTiles[t].reg, (int)std::min(tiles * s, 1ll << 30), kps / (double)BK);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best      = Plan{t, s, kps, d};
-                }
-            }
-        }
-    }
-    if (best.splits == 1) best.k_per_split = (K + BK - 1) / BK * BK;
-    if (best.k_per_split == 0) best.k_per_split = BK;
-    return best;
-}
+static PlanTuning g_tuning;
 
 static bool fast_path_ok(const GemmArgs& g) {
     auto m8 = [](long long v) { return (v & 7) == 0; };
@@ -234,7 +121,7 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
 // output-contiguous: what lies beyond it reads as zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
 static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
     const bool operands = aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0;
-    return dtl_mode() != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % 8 == 0 : !b_kc) &&
+    return g_tuning.dtl != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % 8 == 0 : !b_kc) &&
            std::max(g.lda, g.ldb) < LD_BUFFER_256;
 }
 
@@ -244,7 +131,7 @@ static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
 // 1500 x 29 over 12 4.0 / 3.5, over 17 4.0 / 4.0; 512 products 9 x 40 over 9 5.7 / 4.1, 20 x 40 over 20 5.8 / 7.1).
 static bool scalar_wins(const GemmArgs& g, long long batches) {
     const long long outs = (long long)g.M * g.N * batches;
-    return g_force_tile < 0 && !g.aligned && (batches == 1 ? g.K <= 12 && outs <= 65536 : g.K <= 16 && outs * g.K <= 1 << 21);
+    return g_tuning.tile < 0 && !g.aligned && (batches == 1 ? g.K <= 12 && outs <= 65536 : g.K <= 16 && outs * g.K <= 1 << 21);
 }
 
 // ws: split-K partial buffer (may be NULL when !allow_split).
@@ -265,8 +152,8 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
         return MP_OK;
     }
     const bool dtl = dtl_ok(g, a_kc, b_kc, batches);
-    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc && b_kc, dtl);
-    if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc && b_kc, dtl);
+    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc, b_kc, dtl, g_tuning);
+    if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
     // very long rows: 64 x 64 tiles, unless all loads are plain ones
     if (std::max(g.lda, g.ldb) >= LD_BUFFER_256 && !(g.aligned && g.M % 256 == 0 && g.N % 256 == 0 && g.K % BK == 0 && p.tile < kTileKcOnly))
         p = Plan{6, 1, (g.K + BK - 1) / BK * BK, false};
@@ -337,25 +224,25 @@ using namespace mp;
 
 // fp32 partial-sum floats the product [M,N] with contraction K may use (0 when no plan splits the contraction): the
 // pointers and leading dimensions, which decide between the kernels, are not known yet.
-static size_t splitk_floats(int M, int N, int K, bool kc_kc) {
+static size_t splitk_floats(int M, int N, int K, bool a_kc, bool b_kc) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const bool dtl = dtl_mode() != 0 && K >= DTL_MIN_K;
-    int        splits = make_plan(M, N, K, 1, true, kc_kc, false).splits;
-    if (dtl) splits = std::max(splits, make_plan(M, N, K, 1, true, kc_kc, true).splits);
+    const bool dtl = g_tuning.dtl != 0 && K >= DTL_MIN_K;
+    int        splits = make_plan(M, N, K, 1, true, a_kc, b_kc, false, g_tuning).splits;
+    if (dtl) splits = std::max(splits, make_plan(M, N, K, 1, true, a_kc, b_kc, true, g_tuning).splits);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;
 }
 
 extern "C" int mp_gemm_tuning_override(int tile, int splits) {
     MP_REQUIRE(tile <= kTileSmall8, "mp_gemm_tuning_override: tile index %d out of range (%d shapes)", tile, kTileSmall8 + 1);
     MP_REQUIRE(tile < 0 || (splits >= 0 && splits <= 16), "mp_gemm_tuning_override: splits %d outside 0..16", splits);
-    g_force_tile   = tile;
-    g_force_splits = splits > 0 ? splits : 1;
+    g_tuning.tile   = tile;
+    g_tuning.splits = splits > 0 ? splits : 1;
     return MP_OK;
 }
 
 extern "C" int mp_gemm_tuning_dtl(int mode) {
     MP_REQUIRE(mode >= 0 && mode <= 2, "mp_gemm_tuning_dtl: mode %d outside 0..2", mode);
-    g_dtl_mode = mode;
+    g_tuning.dtl = mode;
     return MP_OK;
 }
 
@@ -363,7 +250,7 @@ extern "C" size_t mp_gemm_bwd_dw_workspace_bytes(const mp_gemm_desc* d, int with
     if (!d) return 0;
     const int rows = d->trans_w ? d->K : d->N, cols = d->trans_w ? d->N : d->K;
     size_t    b    = 0;
-    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats(rows, cols, d->M, false) * sizeof(float);
+    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats(rows, cols, d->M, false, false) * sizeof(float);
     if (with_db) b += mp_colsum_workspace_bytes(d->M, d->N);
     return b + 256;
 }
@@ -377,8 +264,8 @@ static bool split_ok(const GemmArgs& g, long long batches, const void* ws) {
 extern "C" size_t mp_gemm_split_workspace_bytes(const mp_gemm_desc* d) {
     if (!d || d->M <= 0 || d->N <= 0 || d->K <= 0) return 0;
     // the larger of the forward (M x N over K) and dX (M x K over N) plans; 0 when neither would split
-    const size_t a = splitk_floats(d->M, d->N, d->K, d->trans_w == 0);
-    const size_t b = splitk_floats(d->M, d->K, d->N, d->trans_w == 1);
+    const size_t a = splitk_floats(d->M, d->N, d->K, true, d->trans_w == 0);
+    const size_t b = splitk_floats(d->M, d->K, d->N, true, d->trans_w == 1);
     return (a > b ? a : b) * sizeof(float);
 }
 
@@ -446,7 +333,7 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
     const long long batches = (long long)d->batch_outer * d->batch_inner;
     MP_REQUIRE(!(db && batches != 1), "mp_gemm_bwd_dw: db is not available for batched problems");
     const int    w_rows = d->trans_w ? d->K : d->N, w_cols = d->trans_w ? d->N : d->K;
-    const size_t sk_floats = batches == 1 ? splitk_floats(w_rows, w_cols, d->M, false) : 0;
+    const size_t sk_floats = batches == 1 ? splitk_floats(w_rows, w_cols, d->M, false, false) : 0;
     const size_t need = sk_floats * sizeof(float) + (db ? mp_colsum_workspace_bytes(d->M, d->N) : 0) + 256;
     if (!ws || ws_bytes < need || !aligned16(ws)) {
         set_error("mp_gemm_bwd_dw: 16-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
@@ -486,7 +373,7 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 // then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
-    if (g_force_tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;
+    if (g_tuning.tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;
     // (as matrix_path_ok, for both: stored rows of at least 8 elements, offsets inside a tile within the buffer size)
     if (dx->N < 8 || dx->K < 8 || dw->K < 8 || std::max(std::max(dx->ldy, dx->ldw), dw->ldx) >= LD_BUFFER_64) return false;
     return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M) &&
@@ -539,7 +426,7 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
     MP_REQUIRE(nsums >= 0 && nsums <= SUMS_MAX && (nsums == 0 || sums != nullptr), "mp_gemm_bwd_dw_grouped_sums: 0..%d sums", SUMS_MAX);
     MP_REQUIRE(items != nullptr && count >= 1 && count <= GROUP_MAX, "mp_gemm_bwd_dw_grouped: 1..%d items", GROUP_MAX);
     GemmArgs args[GROUP_MAX];
-    bool     m256 = true, n256 = true, dtl = dtl_mode() != 0;
+    bool     m256 = true, n256 = true, dtl = g_tuning.dtl != 0;
     for (int i = 0; i < count; ++i) {
         const mp_gemm_desc* d = &items[i].desc;
         int rc = check_desc(d, "mp_gemm_bwd_dw_grouped");

@@ -39,9 +39,6 @@ namespace mp {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// least contraction: the loads run two k-tiles ahead and cross at most one tile border
-constexpr int DTL_MIN_K = 3 * BK;
-
 constexpr int    dtl_stage(int bm, int bn) { return (bm + bn) * 128; }            // LDS bytes of one k-tile
 constexpr int    dtl_out_pitch(int wn) { return wn > 64 ? 256 : 128; }            // bytes of an output row on its way out
 constexpr int    dtl_out_bytes(int wn) { return 16 * dtl_out_pitch(wn); }         // of one wave

@@ -19,6 +19,7 @@
 //     lane l, accumulator register r  ->  row m = l % 32,  col n = 8*(r/4) + 4*(l/32) + r%4.
 #pragma once
 #include "common.hpp"
+#include "gemm_plan.hpp"
 #include "group_rule.hpp"
 
 #include <mutex>
@@ -28,7 +29,6 @@
 namespace mp {
 
 constexpr int GEMM_THREADS = 256;
-constexpr int BK           = 64;  // halves per LDS row = 128 bytes = 8 slots of 16 bytes
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 struct GemmArgs {
