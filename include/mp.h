@@ -184,7 +184,8 @@ int    mp_gemm_bwd_dx_ws(const mp_gemm_desc* desc, const mp_half* dY, const mp_h
  * if db != NULL, db[N] = RNE16( column sums of dY ) (unbatched only).
  *   st        device, or NULL: if given, st->found_inf is set when any value written to dW or db
  *             is inf/NaN (the gradient inspection of Section 3.1 done where the gradient is made).
- *   ws        device workspace of at least mp_gemm_bwd_dw_workspace_bytes(desc, db != NULL). */
+ *   ws        device workspace; mp_gemm_bwd_dw_workspace_bytes(desc, db != NULL) are enough whatever the pointers' alignment.
+ *             Fewer are taken where they hold the partial sums of the plan that runs, MP_E_WORKSPACE where they do not. */
 int mp_gemm_bwd_dw(const mp_gemm_desc* desc /* host */, const mp_half* dY, const mp_half* X,
                    mp_half* dW, mp_half* db, mp_scale_state* st, void* ws, size_t ws_bytes,
                    mp_stream stream);

@@ -153,7 +153,13 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     }
     const bool dtl = dtl_ok(g, a_kc, b_kc, batches);
     Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc, b_kc, dtl, g_tuning);
-    if (p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
+    // a workspace too small for that: the register-staged kernel's plan if it holds that one, else unsplit
+    const auto too_small = [&] { return p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats; };
+    if (dtl && too_small()) {
+        p = make_plan(g.M, g.N, g.K, batches, true, a_kc, b_kc, false, g_tuning);
+        if (p.splits == 1) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
+    }
+    if (too_small()) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
     // very long rows: 64 x 64 tiles, unless all loads are plain ones
     if (std::max(g.lda, g.ldb) >= LD_BUFFER_256 && !(g.aligned && g.M % 256 == 0 && g.N % 256 == 0 && g.K % BK == 0 && p.tile < kTileKcOnly))
         p = Plan{6, 1, (g.K + BK - 1) / BK * BK, false};
@@ -222,14 +228,16 @@ static void zero_args(GemmArgs& g) { g = GemmArgs{}; }
 
 using namespace mp;
 
-// fp32 partial-sum floats the product [M,N] with contraction K may use (0 when no plan splits the contraction): the
-// pointers and leading dimensions, which decide between the kernels, are not known yet.
-static size_t splitk_floats(int M, int N, int K, bool a_kc, bool b_kc) {
+// fp32 partial-sum floats the product [M,N] with contraction K uses (0 when the plan does not split the contraction)
+static size_t splitk_floats(int M, int N, int K, bool a_kc, bool b_kc, bool dtl) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const bool dtl = g_tuning.dtl != 0 && K >= DTL_MIN_K;
-    int        splits = make_plan(M, N, K, 1, true, a_kc, b_kc, false, g_tuning).splits;
-    if (dtl) splits = std::max(splits, make_plan(M, N, K, 1, true, a_kc, b_kc, true, g_tuning).splits);
+    const int splits = make_plan(M, N, K, 1, true, a_kc, b_kc, dtl, g_tuning).splits;
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;
+}
+// ... where the pointers and leading dimensions, which decide between the kernels, are not known yet
+static size_t splitk_floats_any(int M, int N, int K, bool a_kc, bool b_kc) {
+    const size_t staged = splitk_floats(M, N, K, a_kc, b_kc, false);
+    return g_tuning.dtl != 0 && K >= DTL_MIN_K ? std::max(staged, splitk_floats(M, N, K, a_kc, b_kc, true)) : staged;
 }
 
 extern "C" int mp_gemm_tuning_override(int tile, int splits) {
@@ -250,7 +258,7 @@ extern "C" size_t mp_gemm_bwd_dw_workspace_bytes(const mp_gemm_desc* d, int with
     if (!d) return 0;
     const int rows = d->trans_w ? d->K : d->N, cols = d->trans_w ? d->N : d->K;
     size_t    b    = 0;
-    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats(rows, cols, d->M, false, false) * sizeof(float);
+    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats_any(rows, cols, d->M, false, false) * sizeof(float);
     if (with_db) b += mp_colsum_workspace_bytes(d->M, d->N);
     return b + 256;
 }
@@ -264,8 +272,8 @@ static bool split_ok(const GemmArgs& g, long long batches, const void* ws) {
 extern "C" size_t mp_gemm_split_workspace_bytes(const mp_gemm_desc* d) {
     if (!d || d->M <= 0 || d->N <= 0 || d->K <= 0) return 0;
     // the larger of the forward (M x N over K) and dX (M x K over N) plans; 0 when neither would split
-    const size_t a = splitk_floats(d->M, d->N, d->K, true, d->trans_w == 0);
-    const size_t b = splitk_floats(d->M, d->K, d->N, true, d->trans_w == 1);
+    const size_t a = splitk_floats_any(d->M, d->N, d->K, true, d->trans_w == 0);
+    const size_t b = splitk_floats_any(d->M, d->K, d->N, true, d->trans_w == 1);
     return (a > b ? a : b) * sizeof(float);
 }
 
@@ -332,13 +340,6 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
     MP_REQUIRE(dY && X && dW, "mp_gemm_bwd_dw: NULL operand");
     const long long batches = (long long)d->batch_outer * d->batch_inner;
     MP_REQUIRE(!(db && batches != 1), "mp_gemm_bwd_dw: db is not available for batched problems");
-    const int    w_rows = d->trans_w ? d->K : d->N, w_cols = d->trans_w ? d->N : d->K;
-    const size_t sk_floats = batches == 1 ? splitk_floats(w_rows, w_cols, d->M, false, false) : 0;
-    const size_t need = sk_floats * sizeof(float) + (db ? mp_colsum_workspace_bytes(d->M, d->N) : 0) + 256;
-    if (!ws || ws_bytes < need || !aligned16(ws)) {
-        set_error("mp_gemm_bwd_dw: 16-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
-        return MP_E_WORKSPACE;
-    }
     GemmArgs g;
     zero_args(g);
     g.C = dW; g.found_inf = st ? &st->found_inf : nullptr;
@@ -353,8 +354,20 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
         g.A = X;  g.lda = d->ldx; g.sa_o = d->sx_outer; g.sa_i = d->sx_inner; g.M = d->K;
         g.B = dY; g.ldb = d->ldy; g.sb_o = d->sy_outer; g.sb_i = d->sy_inner; g.N = d->N;
     }
-    float*       wsf       = static_cast<float*>(ws);
-    rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? wsf : nullptr, sk_floats, as_stream(stream));
+    // the partial sums of the plan that runs, or of the register-staged kernel's plan where the workspace holds only those (run_gemm)
+    const size_t cs_bytes = db ? mp_colsum_workspace_bytes(d->M, d->N) : 0;
+    const auto   need = [&](size_t floats) { return floats * sizeof(float) + cs_bytes + 256; };
+    size_t       sk_floats = 0;
+    if (batches == 1) {
+        g.aligned = fast_path_ok(g);
+        sk_floats = splitk_floats(g.M, g.N, g.K, false, false, dtl_ok(g, false, false, 1));
+        if (ws_bytes < need(sk_floats)) sk_floats = std::min(sk_floats, splitk_floats(g.M, g.N, g.K, false, false, false));
+    }
+    if (!ws || ws_bytes < need(sk_floats) || !aligned16(ws)) {
+        set_error("mp_gemm_bwd_dw: 16-byte aligned workspace of %zu bytes needed, %zu given", need(sk_floats), ws_bytes);
+        return MP_E_WORKSPACE;
+    }
+    rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? static_cast<float*>(ws) : nullptr, sk_floats, as_stream(stream));
     if (rc) return rc;
     if (db) {
         char*  cs_ws = static_cast<char*>(ws) + ((sk_floats * sizeof(float) + 255) / 256) * 256;

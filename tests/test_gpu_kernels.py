@@ -824,6 +824,34 @@ def test_gemm_few_rows_with_workspace(M, N, K):
         assert_close16(dx, L.linear_bwd(MIXED, dy, x, w)[0], 1e-3, max_ulp=1, what="few rows dx")
 
 
+@pytest.mark.parametrize("tokens,N,K", [(4096, 1024, 1024), (3240, 2048, 512), (8192, 384, 1024), (8192, 2048, 1024)])
+def test_weight_gradient_takes_a_workspace_that_holds_its_plan(tokens, N, K):
+    """The two kernel families split such a contraction differently.  A workspace that holds either plan of a call is taken, and no byte
+    behind it changes; operands off 16 bytes, which only the register-staged kernels take, need their plan's; less is refused."""
+    r = RNG(tokens + N)
+    x, dy = S16(r.standard_normal((tokens, K))), S16(r.standard_normal((tokens, N)) * 0.1)
+    ref, d = L.linear_bwd(MIXED, dy, x, np.zeros((N, K), np.float32))[1], mp.gemm_desc(tokens, N, K)
+
+    def off(a, elements):
+        t = torch.zeros(a.size + 8, dtype=torch.float16, device="cuda")[elements:elements + a.size].view(a.shape)
+        return t.copy_(h16(a))
+
+    both = mp.mp_gemm_bwd_dw_workspace_bytes(d, False)
+    mp.mp_gemm_tuning_dtl(0)
+    staged = mp.mp_gemm_bwd_dw_workspace_bytes(d, False)
+    mp.mp_gemm_tuning_dtl(1)
+    for elements, sizes in ((0, (both, staged)), (1, (staged,))):
+        dyd, xd = off(dy, elements), off(x, elements)
+        for size in sizes:
+            ws = torch.full((size // 4 + 64,), 7.0, dtype=torch.float32, device="cuda")
+            dw = empty16(N, K)
+            mp.mp_gemm_bwd_dw(d, dyd, xd, dw, None, None, ws[:size // 4])
+            assert_close16(dw, ref, 1e-3, max_ulp=1, what=f"dw {elements} {size}")
+            assert torch.all(ws[size // 4:] == 7.0)
+        with pytest.raises(mp.MPError):
+            mp.mp_gemm_bwd_dw(d, dyd, xd, dw, None, None, ws[:staged // 4 - 1 if elements else 60])
+
+
 def test_empty_and_degenerate_inputs():
     """Zero rows: nothing is launched and the output is untouched.  Zero-length contraction: the sum is empty, the
     epilogue still applies (Y = bias).  An empty tensor list and zero-length tensors in the optimizer wrapper: the step
