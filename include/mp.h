@@ -319,7 +319,7 @@ int mp_layernorm_fwd(int rows, int d, const mp_half* x, const mp_half* a, const 
  * dgamma[d] = RNE16( sum_rows dy xhat ), dbeta[d] = RNE16( sum_rows dy ).  dz is the gradient of both
  * x and a.  If dz_colsum != NULL it also receives RNE16( column sums over rows of the stored dz ): the bias
  * gradient of the linear layer whose output entered this LayerNorm, at no extra pass over memory.
- * Optional overflow flag on dgamma / dbeta / dz_colsum.  Workspace: mp_layernorm_bwd_workspace_bytes. */
+ * Optional overflow flag on dgamma / dbeta / dz_colsum.  Workspace: mp_layernorm_bwd_workspace_bytes, at any 4-byte boundary. */
 size_t mp_layernorm_bwd_workspace_bytes(int rows, int d);
 int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,
@@ -328,7 +328,7 @@ int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const
 
 /* mp_layernorm_bwd without its last launch: dz is written, the column sums stay in ws as mp_layernorm_bwd_nparts(rows, d) rows
  * of partial sums (d for dgamma, d for dbeta and, with_dz_colsum != 0, d for dz_colsum, side by side) that
- * mp_gemm_bwd_dw_grouped_sums finishes; ws must stay untouched until then. */
+ * mp_gemm_bwd_dw_grouped_sums finishes (which wants them at a 16-byte boundary); ws must stay untouched until then. */
 int mp_layernorm_bwd_nparts(int rows, int d);
 int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a, const mp_half* gamma,
                            const float* mean, const float* rstd, mp_half* dz, int with_dz_colsum, void* ws, size_t ws_bytes,

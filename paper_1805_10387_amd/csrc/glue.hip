@@ -126,6 +126,7 @@ __global__ __launch_bounds__(GL_THREADS) void colsum_kernel(int rows, int cols, 
 // One wave per row.  MAXV 16-byte vectors per lane are kept in registers (d <= 64*8*MAXV).
 constexpr int LN_MAXV = 4;
 constexpr int LN_MAX_LDS = 160 * 1024;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // (a caller's workspace may start at any word)
 
 __global__ __launch_bounds__(GL_THREADS) void layernorm_fwd_kernel(int rows, int d, const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ a,
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(64 * NW) void layernorm_bwd_kernel(int rows, int d,
                                                                    const float* __restrict__ mean_i,
                                                                    const float* __restrict__ rstd_i,
                                                                    uint16_t* __restrict__ dz, float* __restrict__ part) {
-    extern __shared__ float sm[];  // [NW][NS][2][d / 2 + 16]
+    extern __shared__ __align__(16) float sm[];  // [NW][NS][2][d / 2 + 16]
     constexpr int NS = ZSUM ? 3 : 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nvec = d >> 3, half = d / 2 + 16;
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(64 * NW) void layernorm_bwd_kernel(int rows, int d,
             const float4 u = *reinterpret_cast<const float4*>(sm + ((long long)(w * NS + which) * 2 + (r & 1)) * half + (r >> 1) * 4);
             t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
         }
-        *reinterpret_cast<float4*>(part + (long long)blockIdx.x * NS * d + c * 4) = t;
+        *reinterpret_cast<f32x4_any*>(part + (long long)blockIdx.x * NS * d + c * 4) = f32x4_any{t.x, t.y, t.z, t.w};
     }
 }
 

@@ -1104,6 +1104,26 @@ def test_layernorm_fwd_bwd(rows, d):
     assert mp.scale_state_read(st).found_inf == 0
 
 
+@pytest.mark.parametrize("rows,d", [(3, 8), (200, 264), (8200, 1024), (300, 2048)])
+def test_layernorm_bwd_workspace_at_any_word(rows, d):
+    """A workspace that starts at a 4-byte boundary which is no 16-byte boundary gives the bits of an aligned one, and nothing around it
+    changes; 4 and 8 waves to a workgroup, every register width."""
+    r = RNG(rows + d + 1)
+    up = lambda *s: h16(S16(r.standard_normal(s)))  # noqa: E731
+    dy, x, gam = up(rows, d), up(rows, d), up(d)
+    mean, rstd = torch.randn(rows, device="cuda") * 0.1, torch.rand(rows, device="cuda") + 0.5
+    words = mp.mp_layernorm_bwd_workspace_bytes(rows, d) // 4
+    outs = []
+    for at in (0, 1, 2, 3):
+        ws = torch.full((words + 16,), 7.0, dtype=torch.float32, device="cuda")
+        out = [empty16(rows, d)] + [empty16(d) for _ in range(3)]
+        mp.mp_layernorm_bwd(rows, d, dy, x, None, gam, mean, rstd, out[0], out[1], out[2], None, ws[at:at + words], dz_colsum=out[3])
+        assert torch.all(ws[:at] == 7.0) and torch.all(ws[at + words:] == 7.0)
+        outs.append(out)
+    for out in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out, outs[0]))
+
+
 @pytest.mark.parametrize("rows,cols", [(64, 64), (1000, 128), (77, 40), (50, 256), (9, 512), (13, 301), (6, 1000)])
 def test_softmax_fwd_bwd(rows, cols):
     r = RNG(rows + cols)
