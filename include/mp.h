@@ -304,6 +304,11 @@ size_t mp_softmax_xent_db_workspace_bytes(int rows, int vocab);
 int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
                               mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* db, void* ws,
                               size_t ws_bytes, mp_stream stream);
+/* The same, with dlogits also in `copy` (device, may be NULL; vocab contiguous elements a row, overlapping no other argument), for a
+ * caller whose products want rows a multiple of 8 elements apart and whose user wants them side by side. */
+int mp_softmax_xent_scaled_db_copy(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                   mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* copy, mp_half* db, void* ws,
+                                   size_t ws_bytes, mp_stream stream);
 
 /* ------------------------------------------------------------------------------------------
  * Bandwidth-bound layer pieces (fp32 arithmetic between fp16 storage points, Section 3.2).

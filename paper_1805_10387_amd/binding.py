@@ -199,6 +199,11 @@ def mp_softmax_xent_scaled_db(rows, vocab, logits, ld, targets, st, loss, dlogit
                                               _p(db), _p(ws), ws.numel() * ws.element_size(), _stream()))
 
 
+def mp_softmax_xent_scaled_db_copy(rows, vocab, logits, ld, targets, st, loss, dlogits, copy, db, ws):
+    _check(L.load().mp_softmax_xent_scaled_db_copy(rows, vocab, _p(logits), ld, _p(targets), _p(st), _p(loss), _p(dlogits), _p(copy),
+                                                   _p(db), _p(ws), ws.numel() * ws.element_size(), _stream()))
+
+
 # ------------------------------------------------------------------ bandwidth-bound pieces
 def mp_layernorm_fwd(rows, d, x, a, gamma, beta, eps, y, mean, rstd):
     _check(L.load().mp_layernorm_fwd(rows, d, _p(x), _p(a), _p(gamma), _p(beta), eps, _p(y), _p(mean), _p(rstd), _stream()))

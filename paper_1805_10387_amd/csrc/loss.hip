@@ -110,11 +110,13 @@ __device__ __forceinline__ float block_reduce_lds(float v, float* red) {
 // COLSUM: every workgroup also sums the gradient values it stores (the fp16 values, as stored) per column over its
 // rows, and leaves the sums in colpart[blockIdx.x][vocab]: the bias gradient of the projection that made the logits
 // then needs no second pass over the gradient matrix, only a sum over gridDim.x partial rows.
+// RAGGED writes the gradient to `copy` as well, rows vocab apart, if that is given.
 template <int THREADS, bool COLSUM, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld, const uint16_t* logits,
                                                               const int32_t* __restrict__ targets,
                                                               const mp_scale_state* __restrict__ st, int rows,
                                                               uint16_t* dlogits,  // may alias logits
+                                                              uint16_t* __restrict__ copy,
                                                               float* __restrict__ row_loss,
                                                               float* __restrict__ colpart) {
     __shared__ float red[THREADS / 64];
@@ -210,14 +212,20 @@ __global__ __launch_bounds__(THREADS) void xent_cached_kernel(int vocab, int ld,
                 unsigned o[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) o[k] = (unsigned)f2h(coef * p[2 * k]) | ((unsigned)f2h(coef * p[2 * k + 1]) << 16);
+                auto put = [&](uint16_t* z) {
+                    if (8 * v + 8 <= vocab) {
+                        *reinterpret_cast<u32x4l_u*>(z + (long long)v * 8) = u32x4l{o[0], o[1], o[2], o[3]};
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 7; ++k)
+                            if (8 * v + k < vocab) z[8 * v + k] = (uint16_t)((k & 1) ? o[k >> 1] >> 16 : o[k >> 1] & 0xFFFFu);
+                    }
+                };
                 if (!RAGGED) {
                     *reinterpret_cast<uint4*>(dz + (long long)v * 8) = make_uint4(o[0], o[1], o[2], o[3]);
-                } else if (8 * v + 8 <= vocab) {
-                    *reinterpret_cast<u32x4l_u*>(dz + (long long)v * 8) = u32x4l{o[0], o[1], o[2], o[3]};
                 } else {
-#pragma unroll
-                    for (int k = 0; k < 7; ++k)
-                        if (8 * v + k < vocab) dz[8 * v + k] = (uint16_t)((k & 1) ? o[k >> 1] >> 16 : o[k >> 1] & 0xFFFFu);
+                    put(dz);
+                    if (copy) put(copy + (long long)row * vocab);
                 }
                 if (COLSUM) {
 #pragma unroll
@@ -254,7 +262,7 @@ __global__ __launch_bounds__(LOSS_THREADS) void xent_kernel(int vocab, int ld, c
                                                             const int32_t* __restrict__ targets,
                                                             const mp_scale_state* __restrict__ st, int rows,
                                                             uint16_t* dlogits,  // may alias logits
-                                                            float* __restrict__ row_loss) {
+                                                            uint16_t* __restrict__ copy, float* __restrict__ row_loss) {
     __shared__ float red[LOSS_THREADS / 64];
     const int        row  = blockIdx.x;
     const uint16_t*  z    = logits + (long long)row * ld;
@@ -276,7 +284,9 @@ __global__ __launch_bounds__(LOSS_THREADS) void xent_kernel(int vocab, int ld, c
         float p = __expf(h2f(z[e]) - mx) * inv;
         if (e == tgt) p -= 1.0f;
         if (!valid) p = 0.f;
-        dz[e] = f2h(coef * p);
+        const uint16_t h = f2h(coef * p);
+        dz[e] = h;
+        if (copy) copy[(long long)row * vocab + e] = h;
     }
 }
 
@@ -340,19 +350,18 @@ constexpr int XENT_SHORT = 1280;
 
 template <int THREADS, bool COLSUM>
 static void launch_xent_cached(int rows, int vocab, int ld, const mp_half* logits, const int32_t* targets, const mp_scale_state* st,
-                               mp_half* dlogits, float* row_loss, float* colpart, hipStream_t hs) {
+                               mp_half* dlogits, mp_half* copy, float* row_loss, float* colpart, hipStream_t hs) {
     const dim3 grid(xent_grid(rows, THREADS)), block(THREADS);
-    if (xent_pieces(vocab, ld, logits, dlogits))
-        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, false>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
+    if (!copy && xent_pieces(vocab, ld, logits, dlogits))
+        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, false>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy,
                            row_loss, colpart);
     else
-        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, true>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
+        hipLaunchKernelGGL((xent_cached_kernel<THREADS, COLSUM, true>), grid, block, 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy,
                            row_loss, colpart);
 }
 
-extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
-                                      const mp_scale_state* st, float* loss, mp_half* dlogits, void* ws,
-                                      size_t ws_bytes, mp_stream stream) {
+static int xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets, const mp_scale_state* st, float* loss,
+                       mp_half* dlogits, mp_half* copy, void* ws, size_t ws_bytes, mp_stream stream) {
     MP_REQUIRE(rows > 0 && vocab > 0 && ld >= vocab, "mp_softmax_xent_scaled: bad shape rows=%d vocab=%d ld=%d", rows,
                vocab, ld);
     MP_REQUIRE(logits && targets && st && loss && dlogits, "mp_softmax_xent_scaled: NULL argument");
@@ -365,20 +374,25 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
     hipStream_t hs       = as_stream(stream);
     const int   nvec     = (vocab + 7) / 8;
     if (vocab <= XENT_SHORT && !xent_pieces(vocab, ld, logits, dlogits))
-        hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, row_loss);
+        hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy, row_loss);
     else if (nvec <= XENT_VECS * 256)
-        launch_xent_cached<256, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
+        launch_xent_cached<256, false>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, nullptr, hs);
     else if (nvec <= XENT_VECS * 512)
-        launch_xent_cached<512, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
+        launch_xent_cached<512, false>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, nullptr, hs);
     else if (nvec <= XENT_VECS * 1024)
-        launch_xent_cached<1024, false>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, nullptr, hs);
+        launch_xent_cached<1024, false>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, nullptr, hs);
     else
-        hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits,
-                           row_loss);
+        hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy, row_loss);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled");
     launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled(finish)");
     return MP_OK;
+}
+
+extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                      const mp_scale_state* st, float* loss, mp_half* dlogits, void* ws,
+                                      size_t ws_bytes, mp_stream stream) {
+    return xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, nullptr, ws, ws_bytes, stream);
 }
 
 // ---- cross-entropy that also leaves the bias gradient of the projection behind the logits
@@ -399,6 +413,12 @@ extern "C" size_t mp_softmax_xent_db_workspace_bytes(int rows, int vocab) {
 extern "C" int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
                                          mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* db, void* ws,
                                          size_t ws_bytes, mp_stream stream) {
+    return mp_softmax_xent_scaled_db_copy(rows, vocab, logits, ld, targets, st, loss, dlogits, nullptr, db, ws, ws_bytes, stream);
+}
+
+extern "C" int mp_softmax_xent_scaled_db_copy(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                              mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* copy, mp_half* db, void* ws,
+                                              size_t ws_bytes, mp_stream stream) {
     MP_REQUIRE(rows > 0 && vocab > 0 && ld >= vocab, "mp_softmax_xent_scaled_db: bad shape rows=%d vocab=%d ld=%d", rows,
                vocab, ld);
     MP_REQUIRE(logits && targets && st && loss && dlogits && db, "mp_softmax_xent_scaled_db: NULL argument");
@@ -412,13 +432,13 @@ extern "C" int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* log
     hipStream_t  hs   = as_stream(stream);
     if (!xent_db_fused(vocab)) {
         // small (or very large) vocabularies: the plain loss call, then a column sum over the gradient it stored
-        const int rc = mp_softmax_xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, ws, head, stream);
+        const int rc = xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, copy, ws, head, stream);
         if (rc != MP_OK) return rc;
         return mp_colsum(rows, vocab, dlogits, ld, db, st, part, ws_bytes - head, stream);
     }
     float*    row_loss = static_cast<float*>(ws);
     const int grid     = xent_grid(rows, 1024);
-    launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, row_loss, part, hs);
+    launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, part, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db");
     launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db(finish)");

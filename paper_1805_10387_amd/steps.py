@@ -351,7 +351,8 @@ class TransformerStep(_StepBase):
 
 # ====================================================================================== config 4
 class XentStep(_StepBase):
-    """Hidden states -> vocabulary logits -> softmax cross-entropy (config 4)."""
+    """Hidden states -> vocabulary logits -> softmax cross-entropy (config 4).  After forward_backward() `logits` [T, V],
+    contiguous, holds their gradient."""
 
     def __init__(self, wl, masters=None, **kw):
         super().__init__(masters or wl.masters(), wl.opt, wl.scale, **kw)
@@ -359,10 +360,12 @@ class XentStep(_StepBase):
         T, d, V = wl.tokens, wl.d_model, wl.vocab
         self.h = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.targets = torch.empty(T, dtype=torch.int32, device="cuda")
-        # overwritten by dlogits; rows a multiple of 8 elements apart, which every kernel reads in whole 16-byte pieces (pieces at
-        # odd addresses arrive at a third of the rate)
+        # the products work on rows a multiple of 8 elements apart, which every kernel reads in whole 16-byte pieces (pieces at odd
+        # addresses arrive at a third of the rate); `logits` then takes dlogits from the pass that writes them
+        # (1021 x 12001: an iteration with products on rows of 12001 156 us, so 149)
         self.ld_v = _round_up(V, 8)
-        self.logits = torch.empty(T, self.ld_v, dtype=torch.float16, device="cuda")[:, :V]
+        self.rows16 = torch.empty(T, self.ld_v, dtype=torch.float16, device="cuda")
+        self.logits = self.rows16 if V == self.ld_v else torch.empty(T, V, dtype=torch.float16, device="cuda")
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.desc = B.gemm_desc(T, V, d, ldy=self.ld_v, epilogue=ML.MP_EPI_BIAS)
         self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, False), B.mp_gemm_split_workspace_bytes(self.desc),
@@ -375,10 +378,11 @@ class XentStep(_StepBase):
     def forward_backward(self):
         wl, w, g = self.wl, self.P.w16, self.P.g16
         T, V = wl.tokens, wl.vocab
-        B.mp_gemm_fwd(self.desc, self.h, w["w"], w["b"], None, self.logits)
+        B.mp_gemm_fwd(self.desc, self.h, w["w"], w["b"], None, self.rows16)
         # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits
-        B.mp_softmax_xent_scaled_db(T, V, self.logits, self.ld_v, self.targets, self.st, self.loss, self.logits, g["b"], self.ws)
-        B.mp_gemm_bwd_both(self.desc, self.logits, w["w"], self.dh, self.desc, self.h, g["w"], None, self.st_grad, self.ws)
+        B.mp_softmax_xent_scaled_db_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16,
+                                         None if V == self.ld_v else self.logits, g["b"], self.ws)
+        B.mp_gemm_bwd_both(self.desc, self.rows16, w["w"], self.dh, self.desc, self.h, g["w"], None, self.st_grad, self.ws)
 
 
 # ====================================================================================== config 5

@@ -1064,6 +1064,44 @@ def test_softmax_xent_bias_gradient_flags_overflow():
     assert torch.isinf(db[7]) and torch.isfinite(z).all()
 
 
+@pytest.mark.parametrize("rows,vocab", [(60, 29), (7, 1279), (33, 5003), (100, 8192), (1021, 12001), (300, 20001), (5, 32771)])
+def test_xent_gradient_also_side_by_side(rows, vocab):
+    """mp_softmax_xent_scaled_db_copy: the bits of the plain call, and dlogits once more with rows `vocab` apart, in every kernel and row
+    length (generic, cached, with the column sums), nothing around either changed; rows without a target are zero in both."""
+    r = RNG(rows + vocab)
+    ld = (vocab + 7) // 8 * 8
+    t = r.integers(0, vocab, rows).astype(np.int32)
+    t[rows // 2] = -1
+    z = torch.full((rows, ld), 7.0, dtype=torch.float16, device="cuda")
+    z[:, :vocab] = h16(S16(r.standard_normal((rows, vocab)) * 3))
+    z2, st = z.clone(), make_state(scale=1024.0)
+    loss, loss2, db, db2 = empty32(1), empty32(1), empty16(vocab), empty16(vocab)
+    ws = ws_bytes(mp.mp_softmax_xent_db_workspace_bytes(rows, vocab))
+    mp.mp_softmax_xent_scaled_db(rows, vocab, z, ld, i32(t), st, loss, z, db, ws)
+    flat = torch.full((rows * vocab + 64,), 7.0, dtype=torch.float16, device="cuda")
+    mp.mp_softmax_xent_scaled_db_copy(rows, vocab, z2, ld, i32(t), st, loss2, z2, flat[:rows * vocab], db2, ws)
+    assert torch.equal(z2, z) and torch.equal(loss2, loss) and torch.equal(db2, db)
+    assert torch.equal(flat[:rows * vocab].view(rows, vocab), z[:, :vocab]) and torch.all(flat[rows * vocab:] == 7.0)
+    assert torch.all(z[rows // 2, :vocab] == 0) and torch.all(z[:, vocab:] == 7.0)
+
+
+@pytest.mark.parametrize("vocab", [1000, 1001, 12001])
+def test_xent_step_leaves_the_logits_gradient_contiguous(vocab):
+    """XentStep.logits is one [T, V] block for every vocabulary, live over iterations."""
+    import mp_inputs as I
+    from dataclasses import replace
+    from paper_1805_10387_amd import steps as St
+    wl = replace(I.C4_SMALL, vocab=vocab)
+    step = St.XentStep(wl)
+    step.set_batch(wl.batch())
+    held = step.logits
+    assert held.is_contiguous() and held.shape == (wl.tokens, vocab)
+    for _ in range(2):
+        step.step()
+        assert torch.equal(held.view(-1), step.rows16[:, :vocab].reshape(-1)) and torch.any(held != 0)
+        held.fill_(1.0)
+
+
 def test_xent_uniform_logits_closed_form():
     rows, vocab = 8, 32768
     st = make_state(scale=2.0 ** 15)
