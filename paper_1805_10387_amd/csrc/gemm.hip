@@ -439,7 +439,7 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
     MP_REQUIRE(nsums >= 0 && nsums <= SUMS_MAX && (nsums == 0 || sums != nullptr), "mp_gemm_bwd_dw_grouped_sums: 0..%d sums", SUMS_MAX);
     MP_REQUIRE(items != nullptr && count >= 1 && count <= GROUP_MAX, "mp_gemm_bwd_dw_grouped: 1..%d items", GROUP_MAX);
     GemmArgs args[GROUP_MAX];
-    bool     m256 = true, n256 = true, dtl = g_tuning.dtl != 0;
+    bool     dtl = g_tuning.dtl != 0;
     for (int i = 0; i < count; ++i) {
         const mp_gemm_desc* d = &items[i].desc;
         int rc = check_desc(d, "mp_gemm_bwd_dw_grouped");
@@ -464,8 +464,6 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
                       "(weights) / 64 (rows); use mp_gemm_bwd_dw", i);
             return MP_E_UNSUPPORTED;
         }
-        m256 = m256 && g.M % 256 == 0;
-        n256 = n256 && g.N % 256 == 0;
         dtl  = dtl && g.K >= DTL_MIN_K && std::max(g.lda, g.ldb) < LD_BUFFER_256;
     }
     // what rides along: strips of bias gradients and columns of the other sums
@@ -493,33 +491,15 @@ extern "C" int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int 
     ga.nsums = nsums;
     for (int i = nsums; i < SUMS_MAX; ++i) ga.sum_start[i + 1] = ga.sum_start[i];
     const int columns = ga.sum_start[nsums];
-    // Tile shape: the one with the least estimated time.  Large tiles win once they fill the chip (a layer with d_model 1024: 192
-    // tiles of 256 x 256 in one round, the strips beside them); with fewer, most compute units would idle through a long
-    // contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us with the register-staged kernels, against 192 of 128 x 128, 49 us).
-    // Strips beside tiles count nothing (us, 256 x 256 / 256 x 128 / 128 x 128, 8192 rows: d_model 1024, 4096 wide 171 / 217 / 267,
-    // with a bias gradient for each of the four 199 / - / 236; d_model 768, 3072 wide - / 167 / 150; d_model 512, 2048 wide, 4096
-    // rows 75 / 52 / 36).
-    int    bm = 128, bn = 128;
-    double best_cost = 1e300;
-    for (int t : {0, 1, 3}) {
-        const int tm = kTiles[t].bm, tn = kTiles[t].bn;
-        if ((tm == 256 && !m256) || (tn == 256 && !n256) || (t == 1 && !dtl)) continue;
-        long long tiles = 0;
-        for (int i = 0; i < count; ++i) tiles += (long long)(args[i].M / tm) * (args[i].N / tn);
-        if (tiles >= (1 << 24)) continue;
-        const TileTime&  time     = dtl ? kTiles[t].dtl : kTiles[t].reg;
-        const int        resident = kCUs * (time.per_kt2 > 0.f ? 2 : 1);
-        const double     kt = k_max / (double)BK, all_us = rounds_us(time, (int)tiles, kt), last_us = rounds_us(time, ((int)tiles - 1) % resident + 1, kt);
-        const GroupShare share = group_share((int)tiles, strips, strip_rows, columns, sum_rows, resident, last_us);
-        const double     cost = group_us(share, strips, strip_rows, columns, sum_rows, all_us);
-        if (cost < best_cost) {
-            best_cost = cost;
-            bm        = tm;
-            bn        = tn;
-            ga.share  = share;
-        }
+    int m_of[GROUP_MAX], n_of[GROUP_MAX];
+    for (int i = 0; i < count; ++i) {
+        m_of[i] = args[i].M;
+        n_of[i] = args[i].N;
     }
-    MP_REQUIRE(best_cost < 1e300, "mp_gemm_bwd_dw_grouped: too many tiles");
+    const GroupPlan plan = group_plan(m_of, n_of, count, k_max, dtl, strips, strip_rows, columns, sum_rows);
+    MP_REQUIRE(plan.tile >= 0, "mp_gemm_bwd_dw_grouped: too many tiles");
+    const int bm = kTiles[plan.tile].bm, bn = kTiles[plan.tile].bn;
+    ga.share = plan.share;
     // longest contraction first, so that the tiles that take longest start first
     int order[GROUP_MAX];
     for (int i = 0; i < count; ++i) order[i] = i;

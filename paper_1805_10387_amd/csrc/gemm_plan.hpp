@@ -32,7 +32,7 @@ static const TileCfg kTiles[] = {{256, 256, {6.45f, 1.15f}, {5.96f, 1.03f}},
                                  {256, 192, {5.98f, 0.88f}, {6.19f, 0.81f}}};
 constexpr int kCUs = 256;
 // us of `wgs` workgroups with k_tiles k-tiles each, without the launch
-static double rounds_us(const TileTime& t, int wgs, double k_tiles) {
+inline double rounds_us(const TileTime& t, int wgs, double k_tiles) {
     const double one = t.fixed + t.per_kt * k_tiles, two = t.fixed2 + t.per_kt2 * k_tiles;
     if (t.per_kt2 == 0.f) return (double)((wgs + kCUs - 1) / kCUs) * one;
     const int rest = wgs % (2 * kCUs);
@@ -49,14 +49,14 @@ constexpr int   kTileSmall4 = kNumTiles, kTileSmall8 = kNumTiles + 1;
 // At the line, forward, input gradient, weight gradient: 512 x 512 over 3072 14.9 / 8.9, 16.6 / 10.7, 12.1 / 11.9;
 // 256 x 2048 over 1536 9.7 / 8.7, 10.5 / 10.1, 12.1 / 11.3; the least gain of 288 sizes inside it: 1024 x 512 over 1024 7.7 / 7.0,
 // 8.3 / 8.6, 10.9 / 9.5.  Beyond it 512 x 512 over 4096 13.0 / 16.8, 1024 x 1024 over 1024 7.3 / 10.0.
-static long long small_tiles(int M, int N) { return ((M + 31) / 32) * (long long)((N + 31) / 32); }
-static bool      small_wins(int M, int N, int K) {
+inline long long small_tiles(int M, int N) { return ((M + 31) / 32) * (long long)((N + 31) / 32); }
+inline bool      small_wins(int M, int N, int K) {
     const long long t = small_tiles(M, N);
     return t <= 2 * kCUs && K <= 4096 && t * K <= 3072ll * kCUs;
 }
 // 8 waves (64 KB of LDS) when a workgroup has its compute unit to itself and each wave several k-tiles: 512 x 512 over
 // 4096 20.7 -> 16.8 us, 1500 x 29 over 1024 6.6 -> 5.7; shorter contractions lose 0.2 us in the longer final sum.
-static int small_waves(long long tiles, int K) { return tiles <= kCUs && K > 512 ? 8 : 4; }
+inline int small_waves(long long tiles, int K) { return tiles <= kCUs && K > 512 ? 8 : 4; }
 
 struct Plan {
     int  tile, splits, k_per_split;
@@ -69,7 +69,7 @@ struct PlanTuning {
 };
 
 // (contraction K in parts of kps: each has to hold the load stream's lead)
-static bool dtl_takes(int tile, int K, int splits, int kps) {
+inline bool dtl_takes(int tile, int K, int splits, int kps) {
     return tile < kNumTiles && kTiles[tile].dtl.per_kt > 0.f && (splits == 1 ? K : std::min(kps, K - (splits - 1) * kps)) >= DTL_MIN_K;
 }
 
@@ -98,7 +98,7 @@ inline double arrival(const int t, const int M, const int N, const int K, const 
 
 // Pick the tile shape (and split count when allowed) that minimises the estimate of run time.  a_kc, b_kc: contraction-contiguous
 // operands; dtl: the operands are fit for the direct-to-LDS kernels
-static Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool a_kc, bool b_kc, bool dtl, const PlanTuning& tuning) {
+inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool a_kc, bool b_kc, bool dtl, const PlanTuning& tuning) {
     const bool kc_kc = a_kc && b_kc;
     if (tuning.tile >= 0) {
         int t = tuning.tile < (kc_kc ? kNumTiles : kTileKcOnly) || tuning.tile >= kTileSmall4 ? tuning.tile : 0, sp = allow_split ? tuning.splits : 1;

@@ -1,7 +1,7 @@
 // Which workgroup of a grouped launch does what: the product tiles and the small items (strips of a bias gradient, columns of
 // other column sums) that ride along.  Plain C++, so that a test can walk it without a GPU.
 #pragma once
-#include <algorithm>
+#include "gemm_plan.hpp"
 
 #if defined(__HIPCC__)
 #define MP_HOST_DEVICE __host__ __device__ __forceinline__
@@ -62,6 +62,44 @@ inline GroupShare group_share(const int tiles, const int strips, const int strip
 inline double group_us(const GroupShare& s, const int strips, const int strip_rows, const int sums, const int sum_rows, const double tiles_us) {
     const int left = strips + sums - s.first;
     return tiles_us + (left + s.wgs - 1) / s.wgs * item_us_alone(s.first < strips ? strip_rows : sum_rows);
+}
+
+// Tile shape of a grouped launch of weight gradients M[i] x N[i] (multiples of 128) over at most k_max: the one with the least
+// estimated time; tile < 0: too many tiles.  dtl: on the kernels that load straight into LDS (the others have no 256 x 128).
+// Large tiles win once they fill the chip (a layer with d_model 1024: 192 tiles of 256 x 256 in one round, the strips beside
+// them); with fewer, most compute units would idle through a long contraction (d_model 512, 4096 tokens: 48 such tiles, 92 us
+// with the register-staged kernels, against 192 of 128 x 128, 49 us).
+// Strips beside tiles count nothing (us, 256 x 256 / 256 x 128 / 128 x 128, 8192 rows: d_model 1024, 4096 wide 171 / 217 / 267,
+// with a bias gradient for each of the four 199 / - / 236; d_model 768, 3072 wide - / 167 / 150; d_model 512, 2048 wide, 4096
+// rows 75 / 52 / 36).
+struct GroupPlan {
+    int        tile;
+    GroupShare share;
+};
+inline GroupPlan group_plan(const int* M, const int* N, const int count, const int k_max, const bool dtl, const int strips, const int strip_rows,
+                            const int sums, const int sum_rows) {
+    GroupPlan best{-1, {}};
+    double    best_us = 1e300;
+    for (int t : {0, 1, 3}) {
+        const int tm = kTiles[t].bm, tn = kTiles[t].bn;
+        long long tiles = 0;
+        bool      fits = t != 1 || dtl;
+        for (int i = 0; i < count; ++i) {
+            fits = fits && M[i] % tm == 0 && N[i] % tn == 0;
+            tiles += (long long)(M[i] / tm) * (N[i] / tn);
+        }
+        if (!fits || tiles >= (1 << 24)) continue;
+        const TileTime&  time     = dtl ? kTiles[t].dtl : kTiles[t].reg;
+        const int        resident = kCUs * (time.per_kt2 > 0.f ? 2 : 1);
+        const double     kt = k_max / (double)BK, all_us = rounds_us(time, (int)tiles, kt), last_us = rounds_us(time, ((int)tiles - 1) % resident + 1, kt);
+        const GroupShare share = group_share((int)tiles, strips, strip_rows, sums, sum_rows, resident, last_us);
+        const double     us = group_us(share, strips, strip_rows, sums, sum_rows, all_us);
+        if (us < best_us) {
+            best_us = us;
+            best    = GroupPlan{t, share};
+        }
+    }
+    return best;
 }
 
 }  // namespace mp

@@ -7,6 +7,30 @@ from oracle import MIXED
 from oracle.numerics import half_bits
 
 
+# Grouped weight gradients: tile shape that the launch takes straight into LDS, or with fewer than 192 rows through registers (index
+# into the library's table: 0 = 256 x 256, 1 = 256 x 128, 3 = 128 x 128), items (rows, N, K); every item but the second asks for its
+# bias gradient as well.  test_dispatch_rules.py holds the rule to these shapes.
+GROUPED = [
+    (3, [(192, 256, 128), (192, 128, 384), (192, 384, 256)]),      # few tiles: 128 x 128
+    (3, [(128, 256, 512), (128, 512, 256), (128, 256, 256)]),      # ... whatever the extents divide by
+    (3, [(320, 1024, 256)] * 5),
+    (3, [(64, 1152, 1152)] * 7),                                   # 567 tiles and 54 strips: workgroups take several
+    (3, [(64, 1024, 1024)] * 5),
+    (3, [(64, 1024, 1152)] * 4),
+    (3, [(64, 1024, 4096), (64, 4096, 1024), (64, 3072, 1024), (64, 1024, 1024)]),
+    (3, [(64, 2048, 4096)] * 3),                                   # 1536 tiles: three rounds, nobody idle
+    # the same at contractions that the direct-to-LDS kernels take, from their least one on
+    (3, [(192, 1152, 1152)] * 7),                                  # 567 tiles, the strips beside the second round
+    (3, [(192, 1152, 1152)] * 6 + [(192, 128, 2560)]),             # 506 tiles, 46 strips: a few beside them, then everybody
+    (1, [(320, 1024, 1024)] * 5),                                  # one round of 160 tiles of 256 x 128 against 320
+    (1, [(320, 1024, 1152)] * 4),                                  # ... and where 256 x 256 does not divide
+    (1, [(192, 1024, 4608)] * 3 + [(192, 1024, 1152)]),            # 468 tiles of 256 x 128: workgroups take several
+    (0, [(640, 1024, 4096), (640, 4096, 1024), (640, 3072, 1024), (640, 1024, 1024)]),   # one round of 192 tiles of 256 x 256
+    (0, [(640, 2048, 4096)] * 3),                                  # 384 tiles of 256 x 256: workgroups take several
+    (0, [(192, 4096, 2048)] * 3 + [(192, 4096, 1792)]),            # 496 tiles of 256 x 256, strips beside and behind
+]
+
+
 def h16(x) -> torch.Tensor:
     """fp32/fp64 NumPy values -> device fp16 tensor holding RNE16(x) (rounded by NumPy)."""
     with np.errstate(over="ignore"):

@@ -135,3 +135,36 @@ def test_plan_parts_hold_the_contraction(plan, a_kc, b_kc):
                             assert min(per, K - (splits - 1) * per) >= 192
                         if not (a_kc and b_kc):
                             assert tile != 8
+
+
+GROUPED_TILE = r"""
+#include "group_rule.hpp"
+extern "C" int grouped_tile(const int* M, const int* N, int count, int k_max, int dtl, int strips, int strip_rows, int* wgs) {
+    const mp::GroupPlan p = mp::group_plan(M, N, count, k_max, dtl, strips, strip_rows, 0, 0);
+    wgs[0] = p.share.wgs; wgs[1] = p.share.busy; wgs[2] = p.share.first;
+    return p.tile;
+}
+"""
+
+
+def test_tile_of_a_grouped_launch(tmp_path):
+    """The tile shape that each case of the GPU test of grouped launches is there for, and that the cases cover what a launch can
+    do: every shape of both kernel families, in one round and in several, items beside the tiles only, behind them as well, and
+    behind them only."""
+    from gpu_util import GROUPED
+    lib, share = _compile(str(tmp_path), "tile", GROUPED_TILE), (C.c_int * 3)()
+    seen = set()
+    for tile, shapes in GROUPED:
+        rows, n = shapes[0][0], len(shapes)
+        assert all(s[0] == rows for s in shapes)
+        ints = lambda k: (C.c_int * n)(*[s[k] for s in shapes])  # noqa: E731
+        strips = sum(s[1] // 128 for j, s in enumerate(shapes) if j != 1)
+        for dtl in ([1, 0] if rows >= 192 else [0]):
+            got = lib.grouped_tile(ints(1), ints(2), n, rows, dtl, strips, rows, share)
+            assert got == tile or (not dtl and rows >= 192 and got in (0, 3)), (shapes, dtl, got)
+            wgs, busy, first = share
+            tm, tn = {0: (256, 256), 1: (256, 128), 3: (128, 128)}[got]
+            several = sum(s[1] // tm * (s[2] // tn) for s in shapes) > wgs
+            seen |= {(dtl, got, several), "beside" if first >= strips else "both" if first else "behind"}
+    assert seen >= {(1, 0, False), (1, 0, True), (1, 1, False), (1, 1, True), (1, 3, False), (1, 3, True), (0, 0, False), (0, 0, True),
+                    (0, 3, False), (0, 3, True), "beside", "both", "behind"}, seen

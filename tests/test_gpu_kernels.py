@@ -652,20 +652,10 @@ def test_gemm_both_gradients_flag_what_the_separate_calls_flag(M, N, K):
             assert bool(torch.isinf(t).all() if name == inf else torch.isfinite(t).all()), (inf, name)
 
 
-@pytest.mark.parametrize("tile,shapes", [
-    (3, [(192, 256, 128), (192, 128, 384), (192, 384, 256)]),      # few tiles: 128 x 128
-    (3, [(128, 256, 512), (128, 512, 256), (128, 256, 256)]),      # ... whatever the extents divide by
-    (3, [(320, 1024, 256)] * 5),
-    (3, [(64, 1152, 1152)] * 7),                                   # 567 tiles and 54 strips: workgroups take several, in both families
-    (1, [(64, 1024, 1024)] * 5),                                   # one round of 160 tiles of 256 x 128 against two of 320
-    (1, [(64, 1024, 1152)] * 4),                                   # ... and where 256 x 256 does not divide
-    (0, [(64, 1024, 4096), (64, 4096, 1024), (64, 3072, 1024), (64, 1024, 1024)]),   # one round of 192 tiles of 256 x 256
-    (0, [(64, 2048, 4096)] * 3),                                   # 384 tiles of 256 x 256: workgroups take several
-])
+@pytest.mark.parametrize("tile,shapes", GROUPED)
 def test_gemm_grouped_weight_gradients(tile, shapes):
     """Several dW = dY^T X in one launch: each equals the oracle and, bit for bit, the single-problem entry point.
-    `tile` is the shape the rule takes (of 256 x 256, 256 x 128 and 128 x 128 the one whose rounds of one work item per
-    compute unit cost least; the register-staged kernels have no 256 x 128 and take 128 x 128 there)."""
+    `tile` is the shape the rule takes (of 256 x 256, 256 x 128 and 128 x 128 the one with the least estimated time)."""
     r = RNG(len(shapes) * 7 + shapes[0][1])
     items, refs, singles, db_refs = [], [], [], []
     st = make_state()
@@ -703,8 +693,9 @@ def test_gemm_grouped_weight_gradients(tile, shapes):
                                             (300, 2048, True)])
 def test_grouped_launch_finishes_layernorm_sums(rows, d, with_dz):
     """mp_layernorm_bwd_parts and the sums of a grouped launch (few and many partial rows, 4 and 8 waves to a workgroup, every
-    register width) give the bits of mp_layernorm_bwd, whether the launch has idle compute units for them or not, and raise
-    its flag."""
+    register width) give the bits of mp_layernorm_bwd, and raise its flag: beside the tiles of a launch with as many idle workgroups as
+    items, with a few (508 tiles of 128 x 128 on 512 workgroups: several items to each of them, the others behind the tiles), with idle
+    ones in the second round only (600) and with none (1024), bias-gradient strips in front of the sums."""
     r = RNG(rows + d)
     up = lambda *s: h16(S16(r.standard_normal(s)))  # noqa: E731
     dy, x, a, gamma = up(rows, d), up(rows, d), up(rows, d), up(d)
@@ -714,21 +705,23 @@ def test_grouped_launch_finishes_layernorm_sums(rows, d, with_dz):
     want = [empty16(rows, d)] + [empty16(d) for _ in range(n)]
     st = make_state()
     mp.mp_layernorm_bwd(rows, d, dy, x, a, gamma, mean, rstd, want[0], want[1], want[2], st, ws, dz_colsum=want[3] if with_dz else None)
-    for tiles in (1, 300):                      # idle compute units for the sums; none (128 x 128 tiles)
+    for tiles in (1, 300, 508, 600, 1024):      # of 128 x 128
         M, N, K = 192, 128, 128 * tiles
-        gy, gx, dw = up(M, N), up(M, K), empty16(N, K)
+        gy, gx, dw, db = up(M, N), up(M, K), empty16(N, K), empty16(N)
         for mode in (1, 0):
+            db.fill_(float("nan"))
             got = [empty16(rows, d)] + [empty16(d) for _ in range(n)]
             part = ws_bytes(mp.mp_layernorm_bwd_workspace_bytes(rows, d))
             mp.mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, got[0], with_dz, part)
             sums = mp.colsum_parts([(part, mp.mp_layernorm_bwd_nparts(rows, d), d, got[1:])] * 2)
             mp.mp_gemm_tuning_dtl(mode)
             try:
-                mp.mp_gemm_bwd_dw_grouped_sums(mp.gemm_group([(mp.gemm_desc(M, N, K), gy, gx, dw)]), sums, st)
+                mp.mp_gemm_bwd_dw_grouped_sums(mp.gemm_group([(mp.gemm_desc(M, N, K), gy, gx, dw, db)]), sums, st)
             finally:
                 mp.mp_gemm_tuning_dtl(1)
             for k in range(n + 1):
                 assert torch.equal(got[k], want[k]), (tiles, mode, k)
+            assert_close16(db, MIXED.store(np32(gy).sum(0, dtype=np.float32)), 1e-3, max_ulp=1, what=f"db {tiles} {mode}")
     assert mp.scale_state_read(st).found_inf == 0
     dy[0, 0] = float("inf")
     mp.mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, got[0], with_dz, part)
