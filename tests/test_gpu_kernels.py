@@ -755,8 +755,9 @@ def test_gemm_grouped_transposed_weight_layout_with_bias_gradient():
         assert_close16(dbt, db_ref, 1e-3, max_ulp=1, what=f"grouped db (mode {mode})")
 
 
-def test_gemm_grouped_flags_overflow_and_rejects_ragged_shapes():
-    M, N, K = 128, 128, 128
+@pytest.mark.parametrize("M", [128, 192])     # register-staged, straight into LDS
+def test_gemm_grouped_flags_overflow_and_rejects_ragged_shapes(M):
+    N, K = 128, 128
     big = torch.full((M, N), 300.0, dtype=torch.float16, device="cuda")
     x = torch.full((M, K), 300.0, dtype=torch.float16, device="cuda")
     ok_dy, ok_x = torch.ones(M, N, dtype=torch.float16, device="cuda"), torch.ones(M, K, dtype=torch.float16, device="cuda")
@@ -765,7 +766,7 @@ def test_gemm_grouped_flags_overflow_and_rejects_ragged_shapes():
     dw0, dw1 = empty16(N, K), empty16(N, K)
     mp.mp_gemm_bwd_dw_grouped(mp.gemm_group([(d, ok_dy, ok_x, dw0), (d, big, x, dw1)]), st)
     assert mp.scale_state_read(st).found_inf == 1          # 128 * 300 * 300 overflows fp16
-    assert torch.all(dw0 == 128.0) and torch.all(torch.isinf(dw1))
+    assert torch.all(dw0 == float(M)) and torch.all(torch.isinf(dw1))
     # a bias gradient that overflows while the product stays finite: 128 rows of 600 sum to 76800 > 65504
     st2 = make_state()
     dy600 = torch.full((M, N), 600.0, dtype=torch.float16, device="cuda")
