@@ -232,7 +232,8 @@ typedef struct mp_colsum_parts {
 } mp_colsum_parts;
 
 /* mp_gemm_bwd_dw_grouped that also finishes nsums (0..4, host array) such column sums, beside the product tiles where those
- * leave compute units idle and behind them elsewhere: same results and bits as the finish launch that mp_layernorm_bwd ends with.  st covers them too. */
+ * leave compute units idle and behind them elsewhere: same results and bits as the finish launch that mp_layernorm_bwd ends
+ * with.  st covers them too. */
 int mp_gemm_bwd_dw_grouped_sums(const mp_gemm_group_item* items, int count, const mp_colsum_parts* sums /* host */, int nsums,
                                 mp_scale_state* st, mp_stream stream);
 

@@ -117,8 +117,9 @@ static bool matrix_path_ok(const GemmArgs& g, bool a_kc, bool b_kc) {
 }
 
 // What the direct-to-LDS kernels take: operand rows that are whole 16-byte pieces (the output's too unless both operands are
-// contraction-contiguous), a contraction of whole pieces (any where both are
-// output-contiguous: what lies beyond it reads as zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out of the matrix.
+// contraction-contiguous), a contraction of whole pieces (any where both are output-contiguous: what lies beyond it reads as
+// zero) and long enough for the load stream's lead, offsets inside a tile within the buffer size.  Output tiles may stick out
+// of the matrix.
 static bool dtl_ok(const GemmArgs& g, bool a_kc, bool b_kc, long long batches) {
     const bool operands = aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0;
     return g_tuning.dtl != 0 && (g.aligned || (operands && a_kc && b_kc)) && batches == 1 && g.K >= DTL_MIN_K && (a_kc ? g.K % 8 == 0 : !b_kc) &&

@@ -1,7 +1,7 @@
 // Contraction kernel whose operand tiles go from global memory straight into LDS (`buffer_load ... lds`: no staging
 // registers, no LDS store instructions), for products whose rows are 16-byte aligned and whose contraction is a multiple of 8
-// (any, where both operands are output-contiguous).  Same arithmetic as gemm_kernels.hpp (paper Section 3.1: fp16 operands, fp32 sums, one rounding); what differs
-// is how the operands reach the matrix cores and how the results leave them.
+// (any, where both operands are output-contiguous).  Same arithmetic as gemm_kernels.hpp (paper Section 3.1: fp16 operands,
+// fp32 sums, one rounding); what differs is how the operands reach the matrix cores and how the results leave them.
 //
 // What bounds it.  Under a full-chip load the matrix cores' clock follows the power that the operands draw, so both the
 // issue slots and the energy per flop count:
