@@ -73,14 +73,18 @@ inline bool dtl_takes(int tile, int K, int splits, int kps) {
     return tile < kNumTiles && kTiles[tile].dtl.per_kt > 0.f && (splits == 1 ? K : std::min(kps, K - (splits - 1) * kps)) >= DTL_MIN_K;
 }
 
-// Factor on the estimate of a direct-to-LDS shape whose operands arrive more slowly than in the fitted range.  Chosen on 16000
-// forced launches of input and weight gradients (500 to 8192 tokens, vocabularies of 3000 to 32768, 128 to 1024 wide, every shape
-// and split count): geometric mean 1.5 % faster than without it, and not slower than the register-staged kernel's best by more than a few
-// percent but for input gradients of rows 64 KB apart (8192 x 320 over 32768: 269 us, register-staged 234).  What it moves, us,
-// without / with it:
+// Factor on the estimate of a direct-to-LDS shape whose operands arrive more slowly than in the fitted range.  Chosen on 20000
+// forced launches of input and weight gradients (500 to 16384 tokens, vocabularies of 3000 to 65536, 128 to 1024 wide, every
+// shape and split count).  What it moves, us, without / with it:
 //   input gradients over more than 4096, where each row of the first operand lies in pages of its own: 7949 x 768 over 16440
-//     300 / 210, 8075 x 320 over 14864 141 / 117, 6130 x 192 over 23552 108 / 90, 8192 x 128 over 16384 70 / 62; operands of more
-//     than 500 MB come at the rate of the HBM, 8192 x 512 over 32768 278 / 253; without a workspace 7260 x 128 over 27448 234 / 199;
+//     300 / 210, 8075 x 320 over 14864 141 / 117, 6130 x 192 over 23552 108 / 90, 8192 x 128 over 16384 70 / 62; without a
+//     workspace 7260 x 128 over 27448 234 / 199;
+//   of more than 400 MB, where the fewest bytes count: 256 x 256 tiles however few (T tokens x d over V, 75 sizes with V no multiple
+//     of 16384: 1.0 % from the best of all launches on average, 2.6 % behind the register-staged kernel's best at most; without
+//     the factor 3.0 and 20 %);
+//   of more than 500 MB with rows a multiple of 32 KB apart, where the memory channels are met unevenly: the register-staged kernel
+//     up to 512 columns, whose loads are further apart (8192 over 32768, straight into LDS / staged: 320 wide 246-266 / 230, 384
+//     249 / 235, 192 184 / 180, 512 251 / 254, 256 182 / 192; 640 and wider 365 / 385);
 //   weight gradients on operands of more than 200 MB (the memory-side cache holds 256): 32768 x 128 over 8192 118 / 112, 20000 x 192
 //     over 8192 132 / 117, 31864 x 192 over 4677 102 / 87.
 inline double arrival(const int t, const int M, const int N, const int K, const bool a_kc, const bool allow_split) {
@@ -88,8 +92,9 @@ inline double arrival(const int t, const int M, const int N, const int K, const 
     if (a_kc) {
         if (K <= 4096) return 1.;
         if (!allow_split && t == 5 && mb > 400. && N <= 192) return 1.2;
-        if (mb > 500.) return t == 0 && N <= 512 ? 1.15 : 1.;
-        return t == 1 ? 1.1 : t == 4 ? 1.2 : 1.;
+        if (mb > 500. && K % 16384 == 0 && N <= 512) return 1.3;
+        if (t == 4) return 1.2;
+        return t == 1 || (t != 0 && mb > 400.) ? 1.1 : 1.;
     }
     if (mb < 200.) return 1.;
     if (mb < 256. || N > 192) return t == 3 ? 1.15 : 1.;

@@ -103,6 +103,13 @@ FAR = [  # input gradients M x N over K (with a workspace or without), weight gr
     ("dx", True, 7949, 768, 16440, 232.9, {(0, 2): 210.1, (2, 1): 222.6, (2, 4): 226.9}),
     ("dx", True, 4096, 128, 32768, 67.6, {(3, 8): 63.8, (5, 4): 66.4}),
     ("dx", True, 8192, 512, 32768, 263.4, {(1, 2): 252.9}),
+    ("dx", True, 8192, 384, 32000, 224.6, {(0, 4): 207.6}),
+    ("dx", True, 8192, 192, 32760, 157.3, {(0, 8): 148.3, (2, 4): 148.2}),
+    ("dx", True, 7900, 512, 32128, 245.3, {(0, 4): 220.9, (2, 2): 239.6, (0, 8): 241.0}),
+    ("dx", True, 8192, 320, 30016, 205.9, {(0, 4): 194.2}),
+    ("dx", True, 7000, 256, 32768, 159.4, {(0, 8): 154.7, (1, 4): 160.2}),
+    ("dx", True, 8192, 320, 32768, 229.9, {}),
+    ("dx", True, 8192, 384, 32768, 235.3, {}),
     ("dx", False, 7260, 128, 27448, 199.2, {}),
     ("dx", False, 8192, 128, 32768, 236.2, {(4, 1): 222.4}),
     ("dw", True, 32768, 128, 8192, 112.2, {}),
