@@ -548,7 +548,8 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
 // The same for tiles of 128 x 64 and 64 x 128, which have a quarter of the matrix-core work per k-tile: a k-tile's loads need
 // several k-tiles of lead, so the stages form a ring (six, all of a compute unit's LDS) and each is worked on as a whole; a
 // stage is free once its fragments are in registers, one k-tile ahead of its use.  One barrier per k-tile.  What bounds a
-// k-tile is the LDS (48 KB read and 24 KB written against 16 matrix-core instructions per wave) and the barrier: 0.27 us, the
+// k-tile is that chain and no unit's rate (counters over a layer of d_model 512, 4096 tokens, in the compute units' busy cycles: LDS
+// instructions 19 %, with a transposed operand 31 % of which 12 are bank conflicts, matrix cores 23 %; waves wait 35 %): 0.27 us, the
 // register-staged kernel 0.38 (4096 x 512 over 2048: 16.4 -> 13.5 us; input gradient 1600 x 1024 over 4096: 29.5 -> 23.2).
 constexpr int    DEEP_STAGES = 6;
 constexpr size_t deep_lds(int bm, int bn) { return DEEP_STAGES * (size_t)dtl_stage(bm, bn) + 4 * dtl_out_bytes(bn / 2); }
