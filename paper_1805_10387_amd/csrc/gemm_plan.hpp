@@ -78,17 +78,23 @@ inline bool dtl_takes(int tile, int K, int splits, int kps) {
 // shape and split count).  What it moves, us, without / with it:
 //   input gradients over more than 4096, where each row of the first operand lies in pages of its own: 7949 x 768 over 16440
 //     300 / 210, 8075 x 320 over 14864 141 / 117, 6130 x 192 over 23552 108 / 90, 8192 x 128 over 16384 70 / 62; without a
-//     workspace 7260 x 128 over 27448 234 / 199;
-//   of more than 400 MB, where the fewest bytes count: 256 x 256 tiles however few (T tokens x d over V, 75 sizes with V no multiple
-//     of 16384: 1.0 % from the best of all launches on average, 2.6 % behind the register-staged kernel's best at most; without
-//     the factor 3.0 and 20 %);
+//     workspace 7260 x 128 over 27448 234 / 199.  344 sizes of 500 to 8192 rows, 128 to 1024 wide, up to 400 MB: 1.7 % from the best
+//     of all launches on average, without the factor 3.8;
+//   of more than 400 MB, where the fewest bytes count: 256 x 256 tiles however few (75 sizes of up to 16384 rows, rows no multiple of 32
+//     KB apart: 1.0 % from the best, 2.6 % behind the register-staged kernel's best at most; without the factor 3.0 and 20 %);
 //   of more than 500 MB with rows a multiple of 32 KB apart, where the memory channels are met unevenly: the register-staged kernel
 //     up to 512 columns, whose loads are further apart (8192 over 32768, straight into LDS / staged: 320 wide 246-266 / 230, 384
 //     249 / 235, 192 184 / 180, 512 251 / 254, 256 182 / 192; 640 and wider 365 / 385);
 //   weight gradients on operands of more than 200 MB (the memory-side cache holds 256): 32768 x 128 over 8192 118 / 112, 20000 x 192
-//     over 8192 132 / 117, 31864 x 192 over 4677 102 / 87.
-inline double arrival(const int t, const int M, const int N, const int K, const bool a_kc, const bool allow_split) {
+//     over 8192 132 / 117, 31864 x 192 over 4677 102 / 87;
+//   forward products in the six-stage shapes: where rows are no multiple of 128 bytes apart, 64 elements of a row lie in two cache
+//     lines, for which their short k-tile leaves no time (1564 x 320 over 3928 30.4 / 21.5, 680 x 1216 over 3760 28.1 / 21.2, 954 x 1152
+//     over 400 7.9 / 6.9); other rows 205 x 1216 over 3008 16.5 / 14.3.  311 forward products of 200 to 8192 rows, 192 to 4096 wide, over
+//     192 to 4096: 1.0 % from the best of all launches on average, 5 % behind the register-staged kernel's best at most; without
+//     the factor 2.0 and 42 %.  (Input and weight gradients, 589, need none there: 2 % behind at most.)
+inline double arrival(const int t, const int M, const int N, const int K, const bool a_kc, const bool b_kc, const bool allow_split) {
     const double mb = 2e-6 * ((double)M + N) * K;
+    if (b_kc) return t != 4 && t != 5 ? 1. : K % 64 == 0 ? 1.08 : 1.35;
     if (a_kc) {
         if (K <= 4096) return 1.;
         if (!allow_split && t == 5 && mb > 400. && N <= 192) return 1.2;
@@ -135,7 +141,7 @@ inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
                 const bool d = v == 0;
                 if (d ? !dtl || !dtl_takes(t, K, s, kps) : dtl_only) continue;
                 const TileTime& time = d ? kTiles[t].dtl : kTiles[t].reg;
-                const double    cost = parts + (d && batches == 1 && !kc_kc ? arrival(t, M, N, K, a_kc, allow_split) : 1.) *
+                const double    cost = parts + (d && batches == 1 ? arrival(t, M, N, K, a_kc, b_kc, allow_split) : 1.) *
                                                 rounds_us(time, (int)std::min(tiles * s, 1ll << 30), kps / (double)BK);
                 if (cost < best_cost) {
                     best_cost = cost;
