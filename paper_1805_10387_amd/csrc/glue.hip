@@ -473,8 +473,8 @@ __global__ __launch_bounds__(GL_THREADS) void lstm_cell_bwd_kernel(int B, int H,
     if (dh_a != nullptr) dh += h2f(dh_a[(long long)b * ld_a + j]);
     if (dh_b != nullptr) dh += h2f(dh_b[(long long)b * ld_b + j]);
     uint16_t d4[4];
-    dc_io[idx] = lstm_cell_backward(h2f(g[j]), h2f(g[H + j]), h2f(g[2 * H + j]), h2f(g[3 * H + j]), c_prev[idx], c[idx], dh,
-                                    dc_io[idx], d4);
+    dc_io[idx] = lstm_cell_backward(lstm_cell_act(h2f(g[j]), h2f(g[H + j]), h2f(g[2 * H + j]), h2f(g[3 * H + j]), c[idx]),
+                                    c_prev[idx], dh, dc_io[idx], d4);
     dg[j]         = d4[0];
     dg[H + j]     = d4[1];
     dg[2 * H + j] = d4[2];

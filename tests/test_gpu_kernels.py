@@ -1331,6 +1331,44 @@ def test_lstm_persistent_layer_step_rows(T, Bn, I, H, block):
     assert_close16(db, db_ref, 1e-3, what="db")
 
 
+@pytest.mark.parametrize("T,Bn,H", [(9, 64, 512), (9, 65, 512), (2, 8, 64), (1, 9, 64), (6, 24, 192), (5, 64, 384), (5, 72, 384), (7, 128, 256)])
+def test_lstm_persistent_layer_places(T, Bn, H):
+    """Groups of workgroups on one XCD each, several to an XCD, and one group more than that allows; a workspace that holds the
+    exchange rings but not the words in which workgroups tell where they run gives the same bits, and both the oracle's."""
+    r = RNG(T + Bn + H)
+    I, ld = 8, 8 + H
+    x_seq, dh_seq = S16(r.standard_normal((T, Bn, I))), S16(r.standard_normal((T, Bn, H)))
+    w, b = S16(r.uniform(-0.1, 0.1, (4 * H, ld))), S16(r.standard_normal(4 * H) * 0.1)
+    wd, bd, dh = h16(w), h16(b), h16(dh_seq)
+    d = mp.lstm_layer_desc(T, Bn, I, H, ld, ld, H, step_rows=Bn)
+    full = mp.mp_lstm_layer_desc_workspace_bytes(d) // 4
+    rings = (Bn + 7) // 8 * 4 * 4 * 1024 * (H // 64) // 4 + 4
+    assert full >= rings and (full > rings) == (H // 16 * ((Bn + 63) // 64) <= 32)
+    outs = []
+    for words in (full, rings):
+        xh = torch.zeros(T, Bn, ld, dtype=torch.float16, device="cuda")
+        xh[:, :, :I].copy_(h16(x_seq))
+        gx, up = empty32(T * Bn, 4 * H), empty16(T, Bn, H)
+        mp.mp_gemm_fwd(mp.gemm_desc(T * Bn, 4 * H, I, ldx=ld, ldw=ld), xh, wd, None, None, None, gx)
+        gates, c, dgates = empty16(T, Bn, 4 * H), torch.zeros(T + 1, Bn, H, dtype=torch.float32, device="cuda"), empty16(T, Bn, 4 * H)
+        status, ws = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(words, dtype=torch.int32, device="cuda")
+        mp.mp_lstm_layer_fwd(d, gx, wd, bd, gates, c, xh, up, status, ws)
+        mp.mp_lstm_layer_bwd(d, wd, gates, c, dh, dgates, status, ws)
+        assert int(status.item()) == 0
+        outs.append((gates, c, xh, up, dgates))
+    for a, b_ in zip(*outs):
+        assert torch.equal(a, b_)
+    gates, c, xh, up, dgates = outs[0]
+    h_ref, (_, gates_ref, c_ref, _) = L.lstm_layer_fwd(MIXED, x_seq, w, b)
+    assert_close16(gates, gates_ref, 1e-3, what="gates")
+    assert_close16(up, h_ref, 1e-3, what="h")
+    assert rel_fro(np32(c), np.stack(c_ref)) <= 1e-3
+    _, _, db_ref = L.lstm_layer_bwd(MIXED, dh_seq, (np32(xh), np32(gates), list(np32(c)), I), w)
+    db = empty16(4 * H)
+    mp.mp_colsum(T * Bn, 4 * H, dgates, 4 * H, db, None, ws_bytes(mp.mp_colsum_workspace_bytes(T * Bn, 4 * H)))
+    assert_close16(db, db_ref, 1e-3, what="db")
+
+
 def test_lstm_persistent_layer_workspace_at_any_word():
     """A workspace of the stated size at a 4-byte boundary that is no 16-byte boundary is enough."""
     T, Bn, I, H = 6, 32, 8, 1024
