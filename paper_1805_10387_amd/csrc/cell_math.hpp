@@ -6,12 +6,38 @@
 
 namespace mp {
 
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + __expf(-x)); }
+// A cell stands between the arrival of one slice and the departure of the next in the recurrent kernels, where nothing hides an
+// instruction, so both functions are branch-free and divide by a reciprocal: a forward cell is 84 instructions, and 137 with
+// the IEEE division and the library's tanh, whose two branches both run in a wave of mixed values (0.05 to 0.1 us of a step).
+// Relative error against 64 bits on N(0, 1) values, root mean square (largest), that way and this: sigma 4.3e-8 (2.8e-7) and the
+// same; tanh 2.8e-8 (1.5e-7) and 2.6e-8 (1.1e-7).
+// sigma(x): the hardware's reciprocal with one Newton step
+__device__ __forceinline__ float sigmoidf_(float x) {
+    const float d = 1.0f + __expf(-x);
+    const float r = __builtin_amdgcn_rcpf(d);
+    const float s = __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
+    return d == INFINITY ? 0.0f : s;  // (a NaN stays one)
+}
+// tanh(x): 1 - 2 / (exp(2|x|) + 1), and near zero, where that cancels, x + x^3 P(x^2) with P fitted to the smallest largest
+// relative error (7e-10)
+__device__ __forceinline__ float tanhf_(float x) {
+    const float a = __builtin_fabsf(x), u = a * a;
+    float       p = -0.0004824179923f;
+    p = __builtin_fmaf(p, u, 0.002651009941f);
+    p = __builtin_fmaf(p, u, -0.008331941441f);
+    p = __builtin_fmaf(p, u, 0.02169604227f);
+    p = __builtin_fmaf(p, u, -0.05393717065f);
+    p = __builtin_fmaf(p, u, 0.1333306581f);
+    p = __builtin_fmaf(p, u, -0.3333332539f);
+    const float near = __builtin_fmaf(a * u, p, a);
+    const float far  = __builtin_fmaf(-2.0f, __builtin_amdgcn_rcpf(__expf(2.0f * a) + 1.0f), 1.0f);
+    return __builtin_copysignf(a < 0.875f ? near : far, x);
+}
 
 // gi, gf, gg, go: the STORED (fp16) gate sums of one cell.  Returns c_t; *h16 = RNE16(sigma(o) tanh(c_t)).
 __device__ __forceinline__ float lstm_cell_forward(float gi, float gf, float gg, float go, float c_prev, uint16_t* h16) {
-    const float cn = sigmoidf_(gf) * c_prev + sigmoidf_(gi) * tanhf(gg);
-    *h16           = f2h(sigmoidf_(go) * tanhf(cn));
+    const float cn = sigmoidf_(gf) * c_prev + sigmoidf_(gi) * tanhf_(gg);
+    *h16           = f2h(sigmoidf_(go) * tanhf_(cn));
     return cn;
 }
 
@@ -21,7 +47,7 @@ struct LstmCellAct {
     float si, sf, tg, so, tc;
 };
 __device__ __forceinline__ LstmCellAct lstm_cell_act(float gi, float gf, float gg, float go, float c) {
-    return {sigmoidf_(gi), sigmoidf_(gf), tanhf(gg), sigmoidf_(go), tanhf(c)};
+    return {sigmoidf_(gi), sigmoidf_(gf), tanhf_(gg), sigmoidf_(go), tanhf_(c)};
 }
 
 // Backward of one cell for one time step.  dh: fp32 sum of the gradients reaching h_t; dc_in: cell-state gradient
