@@ -294,10 +294,16 @@ int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits, int ld, c
                            const mp_scale_state* st, float* loss, mp_half* dlogits, void* ws,
                            size_t ws_bytes, mp_stream stream);
 
+/* The same, with dlogits also in `copy` (device, may be NULL; vocab contiguous elements a row, overlapping no other argument). */
+int mp_softmax_xent_scaled_copy(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                const mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* copy, void* ws,
+                                size_t ws_bytes, mp_stream stream);
+
 /* mp_softmax_xent_scaled that also returns the bias gradient of the projection behind the logits (Section 3.2: the
  * gradients are fp16 tensors): db[vocab] = RNE16( fp32 column sums over the rows of the dlogits values as stored ).
  * For vocabularies of 16385 to 32768 classes the sums are taken in the pass that writes dlogits (rows of any alignment), so
- * the gradient matrix is not read again; others run the plain call followed by mp_colsum.
+ * the gradient matrix is not read again; others run the plain call followed by mp_colsum (mp_gemm_bwd_dw of the projection
+ * has the bias gradient for less: see its db).
  * st is read for S as above; its overflow flag is set if a stored db value is non-finite (dlogits itself is bounded
  * by S / rows and is covered by whoever consumes it).  Workspace: mp_softmax_xent_db_workspace_bytes(rows, vocab),
  * 16-byte aligned.  Same results contract as the two separate calls (fp32 summation order differs). */

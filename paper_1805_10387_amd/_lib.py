@@ -86,6 +86,7 @@ SIGNATURES = {
     "mp_mse_scaled": (_I, [_I, _I, _P, _P, _I, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_scaled": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_db_workspace_bytes": (_SZ, [_I, _I]),
+    "mp_softmax_xent_scaled_copy": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_scaled_db": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_scaled_db_copy": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_layernorm_fwd": (_I, [_I, _I, _P, _P, _P, _P, _F, _P, _P, _P, _P]),

@@ -194,6 +194,11 @@ def mp_softmax_xent_db_workspace_bytes(rows: int, vocab: int) -> int:
     return int(L.load().mp_softmax_xent_db_workspace_bytes(rows, vocab))
 
 
+def mp_softmax_xent_scaled_copy(rows, vocab, logits, ld, targets, st, loss, dlogits, copy, ws):
+    _check(L.load().mp_softmax_xent_scaled_copy(rows, vocab, _p(logits), ld, _p(targets), _p(st), _p(loss), _p(dlogits), _p(copy),
+                                                _p(ws), ws.numel() * ws.element_size(), _stream()))
+
+
 def mp_softmax_xent_scaled_db(rows, vocab, logits, ld, targets, st, loss, dlogits, db, ws):
     _check(L.load().mp_softmax_xent_scaled_db(rows, vocab, _p(logits), ld, _p(targets), _p(st), _p(loss), _p(dlogits),
                                               _p(db), _p(ws), ws.numel() * ws.element_size(), _stream()))

@@ -21,11 +21,22 @@ extern template int launch_dtl_grouped<256, 256>(const GroupArgs&, hipStream_t);
 extern template int launch_dtl_grouped<256, 128>(const GroupArgs&, hipStream_t);
 extern template int launch_dtl_grouped<128, 128>(const GroupArgs&, hipStream_t);
 
-// Sum split-K partials in split order, scale, round once, optional non-finite flag.
+// Sum split-K partials in split order, scale, round once, optional non-finite flag.  db (may be NULL): the same for the
+// sums of the first operand, db_part[splits][db_n], which have no scale.
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ part, int splits, long long mn,
                                                             int N, int ldc, float alpha, const uint16_t* __restrict__ bias,
-                                                            uint16_t* __restrict__ C, int* found_inf) {
+                                                            uint16_t* __restrict__ C, int* found_inf, const float* __restrict__ db_part,
+                                                            int db_n, uint16_t* __restrict__ db) {
     bool bad = false;
+    if (db) {
+        for (int m = blockIdx.x * 256 + threadIdx.x; m < db_n; m += gridDim.x * 256) {
+            float s = db_part[m];
+            for (int p = 1; p < splits; ++p) s += db_part[(long long)p * db_n + m];
+            const uint16_t h = f2h(s);
+            db[m]            = h;
+            bad |= half_nonfinite(h);
+        }
+    }
     for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v * 4 < mn; v += (long long)gridDim.x * 256) {
         const long long e = v * 4;  // N % 4 == 0 on this path
         float4          s = *reinterpret_cast<const float4*>(part + e);
@@ -135,9 +146,17 @@ static bool scalar_wins(const GemmArgs& g, long long batches) {
     return g_tuning.tile < 0 && !g.aligned && (batches == 1 ? g.K <= 12 && outs <= 65536 : g.K <= 16 && outs * g.K <= 1 << 21);
 }
 
-// ws: split-K partial buffer (may be NULL when !allow_split).
+// Column sums of dY as launches of their own: two, 2.5 + 2 us by themselves, 4.6 each behind a product in a captured chain.
+constexpr double SUMS_APART_US = 6.;
+
+// ws: split-K partial buffer (may be NULL when !allow_split).  sums_ws: room for the partial sums of g.db where the
+// contraction is split.  *sums_done: whether g.db was written; else it is the caller's to compute.
 static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool allow_split, float* ws, size_t ws_floats,
-                    hipStream_t hs) {
+                    hipStream_t hs, float* sums_ws = nullptr, size_t sums_floats = 0, bool* sums_done = nullptr) {
+    uint16_t* const db       = g.db;
+    const double    apart_us = db ? SUMS_APART_US : 0.;
+    g.db = nullptr;
+    if (sums_done) *sums_done = false;
     if (g.M == 0 || g.N == 0 || batches == 0) return MP_OK;
     g.aligned = fast_path_ok(g);
     if (!matrix_path_ok(g, a_kc, b_kc) || scalar_wins(g, batches) || batches > 65535) {
@@ -153,14 +172,14 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
         return MP_OK;
     }
     const bool dtl = dtl_ok(g, a_kc, b_kc, batches);
-    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc, b_kc, dtl, g_tuning);
+    Plan p = make_plan(g.M, g.N, g.K, batches, allow_split && ws != nullptr && (g.N & 3) == 0 && batches == 1, a_kc, b_kc, dtl, g_tuning, apart_us);
     // a workspace too small for that: the register-staged kernel's plan if it holds that one, else unsplit
     const auto too_small = [&] { return p.splits > 1 && (size_t)p.splits * g.M * g.N > ws_floats; };
     if (dtl && too_small()) {
-        p = make_plan(g.M, g.N, g.K, batches, true, a_kc, b_kc, false, g_tuning);
-        if (p.splits == 1) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
+        p = make_plan(g.M, g.N, g.K, batches, true, a_kc, b_kc, false, g_tuning, apart_us);
+        if (p.splits == 1) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning, apart_us);
     }
-    if (too_small()) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning);
+    if (too_small()) p = make_plan(g.M, g.N, g.K, batches, false, a_kc, b_kc, dtl, g_tuning, apart_us);
     // very long rows: 64 x 64 tiles, unless all loads are plain ones
     if (std::max(g.lda, g.ldb) >= LD_BUFFER_256 && !(g.aligned && g.M % 256 == 0 && g.N % 256 == 0 && g.K % BK == 0 && p.tile < kTileKcOnly))
         p = Plan{6, 1, (g.K + BK - 1) / BK * BK, false};
@@ -179,7 +198,13 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     const int  gx = (others == 1 && ntiles > resident) ? resident : ntiles;
     const dim3 grid((unsigned)gx, (unsigned)batches, (unsigned)p.splits);
 
-    GemmArgs k = g;
+    GemmArgs   k    = g;
+    const bool sums = db && !a_kc && !b_kc && sums_ride(p.tile, p.dtl, g.N) && (p.splits == 1 || (size_t)p.splits * g.M <= sums_floats);
+    if (sums) {
+        k.db       = db;
+        k.db_part  = sums_ws;
+        *sums_done = true;
+    }
     if (p.splits > 1) {  // partials to workspace, epilogue (scale, bias, rounding, flag) in the finish kernel
         k.C32       = ws;
         k.C         = nullptr;
@@ -190,6 +215,7 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
     if (small) rc = launch_small_tile(waves, a_kc, b_kc, k, p.splits, hs);
     else if (p.dtl && a_kc && b_kc) rc = launch_dtl_tile<true, true>(p.tile, k, grid, hs);
     else if (p.dtl && a_kc) rc = launch_dtl_tile<true, false>(p.tile, k, grid, hs);
+    else if (sums) rc = launch_dtl_sums_tile(p.tile, k, grid, hs);
     else if (p.dtl) rc = launch_dtl_tile<false, false>(p.tile, k, grid, hs);
     else if (a_kc && b_kc) rc = launch_tile<true, true>(p.tile, k, grid, hs);
     else if (a_kc && !b_kc) rc = launch_tile<true, false>(p.tile, k, grid, hs);
@@ -204,7 +230,7 @@ static int run_gemm(GemmArgs g, bool a_kc, bool b_kc, long long batches, bool al
         long long       nb = (mn / 4 + 255) / 256;
         if (nb > 4096) nb = 4096;
         hipLaunchKernelGGL(splitk_finish_kernel, dim3((unsigned)nb), dim3(256), 0, hs, ws, p.splits, mn, g.N, g.ldc, g.alpha,
-                           g.bias, g.C, g.found_inf);
+                           g.bias, g.C, g.found_inf, sums_ws, g.M, sums ? db : nullptr);
         MP_LAUNCH_CHECK("gemm (split-K finish)");
     }
     return MP_OK;
@@ -230,15 +256,15 @@ static void zero_args(GemmArgs& g) { g = GemmArgs{}; }
 using namespace mp;
 
 // fp32 partial-sum floats the product [M,N] with contraction K uses (0 when the plan does not split the contraction)
-static size_t splitk_floats(int M, int N, int K, bool a_kc, bool b_kc, bool dtl) {
+static size_t splitk_floats(int M, int N, int K, bool a_kc, bool b_kc, bool dtl, bool with_sums = false) {
     if (M <= 0 || N <= 0 || (N & 3) != 0) return 0;
-    const int splits = make_plan(M, N, K, 1, true, a_kc, b_kc, dtl, g_tuning).splits;
+    const int splits = make_plan(M, N, K, 1, true, a_kc, b_kc, dtl, g_tuning, with_sums ? SUMS_APART_US : 0.).splits;
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N : 0;
 }
 // ... where the pointers and leading dimensions, which decide between the kernels, are not known yet
-static size_t splitk_floats_any(int M, int N, int K, bool a_kc, bool b_kc) {
-    const size_t staged = splitk_floats(M, N, K, a_kc, b_kc, false);
-    return g_tuning.dtl != 0 && K >= DTL_MIN_K ? std::max(staged, splitk_floats(M, N, K, a_kc, b_kc, true)) : staged;
+static size_t splitk_floats_any(int M, int N, int K, bool a_kc, bool b_kc, bool with_sums = false) {
+    const size_t staged = splitk_floats(M, N, K, a_kc, b_kc, false, with_sums);
+    return g_tuning.dtl != 0 && K >= DTL_MIN_K ? std::max(staged, splitk_floats(M, N, K, a_kc, b_kc, true, with_sums)) : staged;
 }
 
 extern "C" int mp_gemm_tuning_override(int tile, int splits) {
@@ -259,7 +285,7 @@ extern "C" size_t mp_gemm_bwd_dw_workspace_bytes(const mp_gemm_desc* d, int with
     if (!d) return 0;
     const int rows = d->trans_w ? d->K : d->N, cols = d->trans_w ? d->N : d->K;
     size_t    b    = 0;
-    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats_any(rows, cols, d->M, false, false) * sizeof(float);
+    if (d->batch_outer * (long long)d->batch_inner == 1) b = splitk_floats_any(rows, cols, d->M, false, false, with_db && !d->trans_w) * sizeof(float);
     if (with_db) b += mp_colsum_workspace_bytes(d->M, d->N);
     return b + 256;
 }
@@ -356,23 +382,27 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
         g.B = dY; g.ldb = d->ldy; g.sb_o = d->sy_outer; g.sb_i = d->sy_inner; g.N = d->N;
     }
     // the partial sums of the plan that runs, or of the register-staged kernel's plan where the workspace holds only those (run_gemm)
+    const bool   sums     = db && !d->trans_w;   // (dY is the first operand)
     const size_t cs_bytes = db ? mp_colsum_workspace_bytes(d->M, d->N) : 0;
     const auto   need = [&](size_t floats) { return floats * sizeof(float) + cs_bytes + 256; };
     size_t       sk_floats = 0;
     if (batches == 1) {
         g.aligned = fast_path_ok(g);
-        sk_floats = splitk_floats(g.M, g.N, g.K, false, false, dtl_ok(g, false, false, 1));
-        if (ws_bytes < need(sk_floats)) sk_floats = std::min(sk_floats, splitk_floats(g.M, g.N, g.K, false, false, false));
+        sk_floats = splitk_floats(g.M, g.N, g.K, false, false, dtl_ok(g, false, false, 1), sums);
+        if (ws_bytes < need(sk_floats)) sk_floats = std::min(sk_floats, splitk_floats(g.M, g.N, g.K, false, false, false, sums));
     }
     if (!ws || ws_bytes < need(sk_floats) || !aligned16(ws)) {
         set_error("mp_gemm_bwd_dw: 16-byte aligned workspace of %zu bytes needed, %zu given", need(sk_floats), ws_bytes);
         return MP_E_WORKSPACE;
     }
-    rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? static_cast<float*>(ws) : nullptr, sk_floats, as_stream(stream));
+    char* const  cs_ws     = static_cast<char*>(ws) + ((sk_floats * sizeof(float) + 255) / 256) * 256;
+    const size_t cs_b      = ws_bytes - (size_t)(cs_ws - static_cast<char*>(ws));
+    bool         sums_done = false;
+    if (sums) g.db = db;
+    rc = run_gemm(g, false, false, batches, sk_floats > 0, sk_floats > 0 ? static_cast<float*>(ws) : nullptr, sk_floats, as_stream(stream),
+                  reinterpret_cast<float*>(cs_ws), cs_b / sizeof(float), &sums_done);
     if (rc) return rc;
-    if (db) {
-        char*  cs_ws = static_cast<char*>(ws) + ((sk_floats * sizeof(float) + 255) / 256) * 256;
-        size_t cs_b  = ws_bytes - (size_t)(cs_ws - static_cast<char*>(ws));
+    if (db && !sums_done) {
         return mp_colsum(d->M, d->N, dY, d->ldy, db, st, cs_ws, cs_b, stream);
     }
     return MP_OK;

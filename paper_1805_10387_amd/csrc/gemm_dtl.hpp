@@ -126,10 +126,20 @@ struct DtlOperand {
     // matrix-core fragment of slice KK (32 k): k = 8 (lane / 16) ... + 7 for row (lane % 16) of 16-row tile I of unit U
     template <int KK, int U, int I>
     __device__ __forceinline__ f16x8 frag(const char* stage) const {
+        if constexpr (KC) return *reinterpret_cast<const f16x8*>(stage + (foff[0] ^ (KK * 64)) + U * (UR * 128) + I * 2048);
+        else return frag_at<KK>(stage + frag_offset<U, I>());
+    }
+    // ... output-contiguous: in two steps
+    template <int U, int I>
+    __device__ __forceinline__ unsigned frag_offset() const {
+        return KC ? 0u : foff[KC ? 0 : I >> 1] + (I & 1) * 32 + U * (UR * 128);
+    }
+    template <int KK>
+    static __device__ __forceinline__ f16x8 frag_at(const char* p) {
         if constexpr (KC) {
-            return *reinterpret_cast<const f16x8*>(stage + (foff[0] ^ (KK * 64)) + U * (UR * 128) + I * 2048);
+            return f16x8{};
         } else {
-            const char* p  = stage + foff[I >> 1] + (I & 1) * 32 + U * (UR * 128) + KK * 32 * RB;
+            p += KK * 32 * RB;
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)MP_LDS_PTR(p));
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)MP_LDS_PTR(p + 4 * RB));
             typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -329,10 +339,68 @@ __device__ __forceinline__ u32x2g dtl_bias(const GemmArgs& g, const int n) {
     return u32x2g{b0, b1};
 }
 
+// Sums of the first operand over the contraction: the bias gradient that goes with a weight gradient, of which this kernel has
+// every element in LDS anyway.  A row tile of 16 is one matrix-core instruction per 32 k against a fragment of ones; the tiles
+// beside each other and the two wave columns of each share the row tiles out among them (`slot`), one to a wave, which reads its
+// fragments once more (picking them out of the registers by the wave's number costs branches or moves: 5 us of a 256 x 128
+// product of 25 k-tiles, 1 this way).  Against the column sums as launches of their own, us: see sums_ride in the plan.
+template <typename OPA, int TM, int UNIT, bool ON>   // UNIT: row tiles of a unit of OPA's rows
+struct DtlSums {
+    int      mine;      // row tile of this wave, or none
+    unsigned off;       // where its fragments lie in a stage
+    f16x8    f[2];
+    f32x4    sum[2];    // by slice
+    __device__ __forceinline__ void start(const GemmArgs& g, const OPA& oa, const int slot) {
+        if constexpr (ON) {
+            mine = __builtin_amdgcn_readfirstlane(slot < TM ? slot : -1);
+            off  = 0;
+            static_for<TM>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                if (mine == i) off = oa.template frag_offset<i / UNIT, i % UNIT>();
+            });
+            sum[0] = sum[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __device__ __forceinline__ bool upper() const { return ON && mine >= 0 && mine < UNIT; }
+    __device__ __forceinline__ bool lower() const { return ON && mine >= UNIT; }
+    __device__ __forceinline__ void read(const char* stage) {
+        if constexpr (ON) {
+            f[0] = OPA::template frag_at<0>(stage + off);
+            f[1] = OPA::template frag_at<1>(stage + off);
+        }
+    }
+    __device__ __forceinline__ void add() {
+        if constexpr (ON) {
+            if (mine >= 0) {
+                const f16   one  = (f16)1.f;
+                const f16x8 ones = {one, one, one, one, one, one, one, one};
+                sum[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, f[0], sum[0], 0, 0, 0);
+                sum[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, f[1], sum[1], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // mw: first row of the wave
+    __device__ __forceinline__ void store(const GemmArgs& g, const int mw, const bool split, bool& bad) const {
+        if constexpr (ON) {
+            const int lane = threadIdx.x & 63, m = mw + 16 * mine + lane;   // (the sum of row r is in lanes r, r + 16, ...)
+            if (mine < 0 || lane >= 16 || m >= g.M) return;
+            const float s = sum[0][0] + sum[1][0];
+            if (split) {
+                g.db_part[m] = s;
+            } else {
+                const uint16_t h = f2h(s);
+                g.db[m]          = h;
+                bad |= half_nonfinite(h);
+            }
+        }
+    }
+};
+
 // The output tiles vb0, vb0 + vb_step, ... (< tiles_m * tiles_n) of problem g, one after the other, with the load stream
 // running on from tile to tile.  remap: number the tiles so that each XCD gets a contiguous run (a launch of one problem);
 // otherwise vb is the tile number itself (the caller has placed the tiles).  split: g describes one part of a split contraction.
-template <int BM, int BN, bool A_KC, bool B_KC, int MODE>
+template <int BM, int BN, bool A_KC, bool B_KC, int MODE, bool SUMS>
 __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, const int vb_step, const bool remap, const bool split,
                                           char* smem, bool& bad) {
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16, TH = TM / 2;
@@ -470,6 +538,8 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
                 }
             });
         }
+        DtlSums<OpA, TM, TH, SUMS> sums;
+        sums.start(g, oa, 2 * (n0 / BN) + wn);
         // The previous tile's output stores are younger than the loads that the first three barriers of a tile need, which
         // therefore need not wait for them: `behind` counts those barriers (three, or none for the first tile).
         int behind = NS > 0 && vb != vb0 ? 3 : 0;
@@ -492,7 +562,14 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             // rows, and loads of the k-tile after next into the space of this k-tile's upper rows and second operand.
             static_for<MS>([&](auto mc) {
                 constexpr int m = decltype(mc)::value, j = m / (2 * TH), s = m / TH % 2, i = m % TH;
-                if constexpr (m == PB) barrier(std::integral_constant<int, FLY0>{});
+                // (rows to be summed are read once more: upper ones while they are there, lower ones once they are)
+                if constexpr (m == 0) {
+                    if (sums.upper()) sums.read(st);
+                }
+                if constexpr (m == PB) {
+                    barrier(std::integral_constant<int, FLY0>{});
+                    if (sums.lower()) sums.read(st);
+                }
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[s][j], alo[s][i], acc[i][j], 0, 0, 0);
                 if constexpr (m < 2) read_b(st, std::integral_constant<int, 2 * TN - 2 + m>{});
                 if constexpr (m >= PB) {
@@ -503,6 +580,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
+            sums.add();
             c_st = STAGE - c_st;
             st   = smem + c_st;
             // Phase 1: lower rows.  Behind the barrier: the next k-tile's upper rows, and its column c once this k-tile's
@@ -537,6 +615,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
             if (MODE != INTERIOR && left == 1) to_last();
         }
         if (fold_bias) load_bias(n1);
+        sums.store(g, m0 + wm * WM, split, bad);
         dtl_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM, n0 + wn * WN, split, fold_bias, smem + 2 * STAGE + wave * dtl_out_bytes(WN), bad);
         m0 = m1;
         n0 = n1;
@@ -553,7 +632,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
 // register-staged kernel 0.38 (4096 x 512 over 2048: 16.4 -> 13.5 us; input gradient 1600 x 1024 over 4096: 29.5 -> 23.2).
 constexpr int    DEEP_STAGES = 6;
 constexpr size_t deep_lds(int bm, int bn) { return DEEP_STAGES * (size_t)dtl_stage(bm, bn) + 4 * dtl_out_bytes(bn / 2); }
-template <int BM, int BN, bool A_KC, bool B_KC, int MODE>
+template <int BM, int BN, bool A_KC, bool B_KC, int MODE, bool SUMS>
 __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, const int vb_step, const bool split, char* smem, bool& bad) {
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
     typedef DtlOperand<BM, WM, A_KC, false, MODE != INTERIOR> OpA;
@@ -650,6 +729,10 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
     __syncthreads();
     unsigned c_st = 0;
     static_for<NR>([&](auto fc) { read(smem, std::integral_constant<int, 0>{}, fc); });
+    DtlSums<OpA, TM, TM, SUMS> sums;   // of the k-tile that is being read, one ahead of the matrix cores
+    sums.start(g, oa, 2 * (n0 / BN) + wn);
+    if (sums.upper()) sums.read(smem);
+    sums.add();
 
     for (int vb = vb0; vb < ntiles; vb += vb_step) {
         int m1 = m0, n1 = n0;
@@ -670,7 +753,8 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
                 }
             });
         }
-        auto ktile = [&](auto pc) {
+        DtlSums<OpA, TM, TM, SUMS> tile_sums;
+        auto ktile = [&](auto pc, const bool last) {
             constexpr int p = decltype(pc)::value;
             c_st = c_st + STAGE == DEEP_STAGES * STAGE ? 0 : c_st + STAGE;
             const char* st = smem + c_st;   // of the next k-tile
@@ -679,6 +763,11 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((DEEP_STAGES - 2) * NL) : "memory");
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
+            if (SUMS && last) {   // (the k-tile read here is the next tile's first)
+                tile_sums = sums;
+                sums.start(g, oa, 2 * (n1 / BN) + wn);
+            }
+            if (sums.upper()) sums.read(st);
             static_for<MS>([&](auto mc) {
                 constexpr int m = decltype(mc)::value, s = m / (TM * TN), i = m / TN % TM, j = m % TN;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bf[p][s][j], af[p][s][i], acc[i][j], 0, 0, 0);
@@ -688,17 +777,18 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
                 if constexpr (m / PI < NL && m % PI == 1) load(std::integral_constant<int, m / PI>{}, Load{});
                 __builtin_amdgcn_sched_barrier(0);
             });
+            sums.add();
             advance();
         };
         typedef std::integral_constant<int, 0> P0;
         typedef std::integral_constant<int, 1> P1;
         int kt = 0;
         for (; kt + 1 < nkt; kt += 2) {
-            ktile(P0{});
-            ktile(P1{});
+            ktile(P0{}, false);
+            ktile(P1{}, kt + 2 == nkt);
         }
         if (kt < nkt) {
-            ktile(P0{});
+            ktile(P0{}, true);
 #pragma unroll
             for (int s = 0; s < 2; ++s) {   // (a tile starts with its first fragments in set 0)
 #pragma unroll
@@ -708,6 +798,7 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
             }
         }
         if (fold_bias) load_bias(n1);
+        tile_sums.store(g, m0 + wm * WM, split, bad);
         dtl_epilogue<TM, TN, MODE>(g, acc, m0 + wm * WM, n0 + wn * WN, split, fold_bias, smem + DEEP_STAGES * STAGE + wave * dtl_out_bytes(WN), bad);
         m0 = m1;
         n0 = n1;
@@ -716,8 +807,9 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
     __syncthreads();
 }
 
-// grid: (workgroups, 1, splits of the contraction); g.k_per_split is a multiple of BK
-template <int BM, int BN, bool A_KC, bool B_KC, int MODE>
+// grid: (workgroups, 1, splits of the contraction); g.k_per_split is a multiple of BK.  SUMS: with g.db (see DtlSums; a kernel of
+// its own, since the branches cost a product without sums 3 to 10 %)
+template <int BM, int BN, bool A_KC, bool B_KC, int MODE, bool SUMS = false>
 __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_kernel(GemmArgs g) {
     extern __shared__ __align__(16) char smem[];
     bool       bad   = false;
@@ -727,10 +819,11 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_kernel(GemmArgs g) {
         g.A += A_KC ? k0 : k0 * g.lda;
         g.B += B_KC ? k0 : k0 * g.ldb;
         g.C32 += (long long)blockIdx.z * g.M * g.N;
+        if (SUMS) g.db_part += (long long)blockIdx.z * g.M;
         g.K = min(g.k_per_split, g.K - (int)k0);
     }
-    if constexpr (BM * BN < 128 * 128) deep_tiles<BM, BN, A_KC, B_KC, MODE>(g, blockIdx.x, gridDim.x, split, smem, bad);
-    else dtl_tiles<BM, BN, A_KC, B_KC, MODE>(g, blockIdx.x, gridDim.x, true, split, smem, bad);
+    if constexpr (BM * BN < 128 * 128) deep_tiles<BM, BN, A_KC, B_KC, MODE, SUMS>(g, blockIdx.x, gridDim.x, split, smem, bad);
+    else dtl_tiles<BM, BN, A_KC, B_KC, MODE, SUMS>(g, blockIdx.x, gridDim.x, true, split, smem, bad);
     if (g.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(g.found_inf, 1);
     }
@@ -747,7 +840,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void gemm_dtl_grouped_kernel(GroupArg
         int            first;
         const GemmArgs g = group_problem(ga, vb, first);
         bool           bad = false;
-        dtl_tiles<BM, BN, false, false, INTERIOR>(g, vb - first, 1 << 30, false, false, smem, bad);
+        dtl_tiles<BM, BN, false, false, INTERIOR, false>(g, vb - first, 1 << 30, false, false, smem, bad);
         bad_any |= bad;
     });
     if (flag && __any(bad_any)) {
@@ -771,17 +864,17 @@ int launch_dtl_grouped(const GroupArgs& ga, hipStream_t hs) {
 }
 
 // Launch (host): the caller has checked dtl_ok.
-template <int BM, int BN, bool AKC, bool BKC, int MODE>
+template <int BM, int BN, bool AKC, bool BKC, int MODE, bool SUMS = false>
 int launch_dtl_mode(const GemmArgs& g, dim3 grid, hipStream_t hs) {
     constexpr size_t  lds = BM * BN < 128 * 128 ? deep_lds(BM, BN) : dtl_lds(BM, BN);
     static std::once_flag once;
     static hipError_t     attr_err = hipSuccess;
     std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dtl_kernel<BM, BN, AKC, BKC, MODE>),
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dtl_kernel<BM, BN, AKC, BKC, MODE, SUMS>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return hip_fail(attr_err, "gemm: hipFuncSetAttribute(LDS size)");
-    hipLaunchKernelGGL((gemm_dtl_kernel<BM, BN, AKC, BKC, MODE>), grid, dim3(GEMM_THREADS), lds, hs, g);
+    hipLaunchKernelGGL((gemm_dtl_kernel<BM, BN, AKC, BKC, MODE, SUMS>), grid, dim3(GEMM_THREADS), lds, hs, g);
     MP_LAUNCH_CHECK("gemm launch (direct-to-LDS)");
     return MP_OK;
 }
@@ -794,6 +887,14 @@ int launch_dtl(const GemmArgs& g, dim3 grid, hipStream_t hs) {
     }
     return g.M % BM || g.N % BN || g.K % BK ? launch_dtl_mode<BM, BN, AKC, BKC, EDGE>(g, grid, hs) : launch_dtl_mode<BM, BN, AKC, BKC, INTERIOR>(g, grid, hs);
 }
+
+// weight gradients with sums (tile: as sums_ride has it)
+template <int BM, int BN>
+int launch_dtl_sums(const GemmArgs& g, dim3 grid, hipStream_t hs) {
+    return g.M % BM || g.N % BN || g.K % BK ? launch_dtl_mode<BM, BN, false, false, EDGE, true>(g, grid, hs)
+                                            : launch_dtl_mode<BM, BN, false, false, INTERIOR, true>(g, grid, hs);
+}
+int launch_dtl_sums_tile(int t, const GemmArgs& g, dim3 grid, hipStream_t hs);
 
 // tile index as in the planner's table; returns MP_E_UNSUPPORTED for shapes this kernel is not built for
 template <bool AKC, bool BKC>

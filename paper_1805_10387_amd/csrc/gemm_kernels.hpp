@@ -50,6 +50,8 @@ struct GemmArgs {
     int             k_per_split;  // multiple of BK; == K rounded up when not split
     int             tiles_m, tiles_n;
     int             aligned;      // pointers 16-byte aligned, leading dimensions and batch strides multiples of 8
+    uint16_t*       db;           // [M] or NULL: sums of A over the contraction (a weight gradient's bias gradient) ...
+    float*          db_part;      // ... or, where the contraction is split, [splits][M] partial sums of it
 };
 
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).

@@ -107,9 +107,20 @@ inline double arrival(const int t, const int M, const int N, const int K, const 
     return t == 3 ? 1.3 : t == 1 ? 1.1 : t == 4 ? 1.2 : 1.;
 }
 
+// The direct-to-LDS kernels of weight gradients also sum their first operand over the contraction (the bias gradient), 16 rows
+// to a wave, so the waves beside each other have to cover a tile's rows; 256 x 256 has no registers for it, and 128 x 256 is
+// hardly ever the best shape.  us of a weight gradient with its bias gradient, column sums apart / riding (rows x outputs x
+// inputs, in a captured chain): 1600 x 4096 x 2048 36.2 / 33.0, 1600 x 2048 x 1024 19.1 / 15.0, 1024 x 8000 x 512 19.9 / 15.6,
+// 1021 x 12008 x 512 29.9 / 22.8, 520 x 3000 x 256 10.8 / 8.1, 8000 x 640 x 640 26.8 / 19.8, 8192 x 3072 x 1024 76.0 / 74.7.
+inline bool sums_ride(int tile, bool dtl, int N) {
+    return dtl && (tile == 1 || (tile >= 3 && tile <= 5)) && 2 * ((N + kTiles[tile].bn - 1) / kTiles[tile].bn) >= kTiles[tile].bm / 32;
+}
+
 // Pick the tile shape (and split count when allowed) that minimises the estimate of run time.  a_kc, b_kc: contraction-contiguous
-// operands; dtl: the operands are fit for the direct-to-LDS kernels
-inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool a_kc, bool b_kc, bool dtl, const PlanTuning& tuning) {
+// operands; dtl: the operands are fit for the direct-to-LDS kernels; apart_us: what a kernel that does not sum its first operand
+// leaves to launches of their own
+inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, bool a_kc, bool b_kc, bool dtl, const PlanTuning& tuning,
+                      double apart_us = 0.) {
     const bool kc_kc = a_kc && b_kc;
     if (tuning.tile >= 0) {
         int t = tuning.tile < (kc_kc ? kNumTiles : kTileKcOnly) || tuning.tile >= kTileSmall4 ? tuning.tile : 0, sp = allow_split ? tuning.splits : 1;
@@ -124,7 +135,11 @@ inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
         return Plan{t, sp, kps > 0 ? kps : BK, dtl && dtl_takes(t, K, sp, kps)};
     }
     const bool dtl_only = dtl && tuning.dtl == 2;
-    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
+    // (with sums the small kernel and their launches against one of the others, us: 300 x 192 x 192 8.0 / 6.9, 3000 x 128 x 128 13.2 /
+    // 11.7, 800 x 1024 x 512 12.3 / 9.2; where few tiles make the others split the contraction, 1000 x 128 x 128 8.9 / 9.9, 1000 x 256 x
+    // 192 9.1 / 10.0, 2000 x 256 x 256 11.4 / 12.1)
+    const bool small_sums = !dtl || (small_tiles(M, N) <= 64 && K > 640 && K <= 2560);
+    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072) && (apart_us == 0. || small_sums))  // (longer ones: split over more workgroups)
         return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK, false};
     Plan   best{0, 1, 0, false};
     double best_cost = 1e300;
@@ -141,7 +156,7 @@ inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
                 const bool d = v == 0;
                 if (d ? !dtl || !dtl_takes(t, K, s, kps) : dtl_only) continue;
                 const TileTime& time = d ? kTiles[t].dtl : kTiles[t].reg;
-                const double    cost = parts + (d && batches == 1 ? arrival(t, M, N, K, a_kc, b_kc, allow_split) : 1.) *
+                const double    cost = parts + (sums_ride(t, d, N) ? 0. : apart_us) + (d && batches == 1 ? arrival(t, M, N, K, a_kc, b_kc, allow_split) : 1.) *
                                                 rounds_us(time, (int)std::min(tiles * s, 1ll << 30), kps / (double)BK);
                 if (cost < best_cost) {
                     best_cost = cost;

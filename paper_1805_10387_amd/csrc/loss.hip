@@ -395,6 +395,12 @@ extern "C" int mp_softmax_xent_scaled(int rows, int vocab, const mp_half* logits
     return xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, nullptr, ws, ws_bytes, stream);
 }
 
+extern "C" int mp_softmax_xent_scaled_copy(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                           const mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* copy, void* ws,
+                                           size_t ws_bytes, mp_stream stream) {
+    return xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, copy, ws, ws_bytes, stream);
+}
+
 // ---- cross-entropy that also leaves the bias gradient of the projection behind the logits
 static size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 // the fused path: rows cached in a 1024-lane workgroup, workgroups persistent over rows

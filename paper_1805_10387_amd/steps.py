@@ -368,7 +368,8 @@ class XentStep(_StepBase):
         self.logits = self.rows16 if V == self.ld_v else torch.empty(T, V, dtype=torch.float16, device="cuda")
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.desc = B.gemm_desc(T, V, d, ldy=self.ld_v, epilogue=ML.MP_EPI_BIAS)
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, False), B.mp_gemm_split_workspace_bytes(self.desc),
+        self.db_with_loss = 16384 < V <= 32768
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, not self.db_with_loss), B.mp_gemm_split_workspace_bytes(self.desc),
                            B.mp_softmax_xent_db_workspace_bytes(T, V)))
 
     def set_batch(self, batch):
@@ -379,10 +380,15 @@ class XentStep(_StepBase):
         wl, w, g = self.wl, self.P.w16, self.P.g16
         T, V = wl.tokens, wl.vocab
         B.mp_gemm_fwd(self.desc, self.h, w["w"], w["b"], None, self.rows16)
-        # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits
-        B.mp_softmax_xent_scaled_db_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16,
-                                         None if V == self.ld_v else self.logits, g["b"], self.ws)
-        B.mp_gemm_bwd_both(self.desc, self.rows16, w["w"], self.dh, self.desc, self.h, g["w"], None, self.st_grad, self.ws)
+        copy = None if V == self.ld_v else self.logits
+        # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits where that pass can, else out of
+        # the weight gradient
+        if self.db_with_loss:
+            B.mp_softmax_xent_scaled_db_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, g["b"], self.ws)
+        else:
+            B.mp_softmax_xent_scaled_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, self.ws)
+        B.mp_gemm_bwd_both(self.desc, self.rows16, w["w"], self.dh, self.desc, self.h, g["w"], None if self.db_with_loss else g["b"],
+                           self.st_grad, self.ws)
 
 
 # ====================================================================================== config 5

@@ -1655,3 +1655,35 @@ def test_scale_state_static_mode_and_validation():
         mp.mp_scale_state_init(st, 1, 2.0, 0)
     with pytest.raises(mp.MPError):
         mp.mp_scale_state_init(st, 7, 2.0, 1)
+
+
+@pytest.mark.parametrize("tile,splits", [(1, 1), (3, 1), (4, 1), (5, 1), (1, 3), (3, 2), (4, 3), (5, 4)])
+@pytest.mark.parametrize("T,N,K", [(192, 256, 512), (193, 520, 456), (1000, 264, 392), (640, 1024, 40)])
+def test_bias_gradient_from_the_weight_gradient(T, N, K, tile, splits):
+    """Both gradients from one launch in every tile shape that carries the sums, split or not, with rows, columns and a contraction
+    that stick out of the tiles, and (few inputs) where the waves beside each other do not cover a tile's rows and the sums
+    are launches of their own; a sum that overflows raises the flag."""
+    r = RNG(T + N + K)
+    dy, x, w = S16(r.standard_normal((T, N))), S16(r.standard_normal((T, K))), S16(r.standard_normal((N, K)))
+    d, st = mp.gemm_desc(T, N, K), mp.scale_state_alloc()
+    mp.mp_scale_state_init(st, ML.MP_SCALE_BACKOFF, 2.0, 100, 1.0, 2.0 ** 24)
+    ws = ws_bytes(8 << 20)
+    xd = h16(x)
+    _, dw_ref, db_ref = L.linear_bwd(MIXED, dy, x, w)
+    mp.mp_gemm_tuning_override(tile, splits)
+    try:
+        for bad in (False, True):
+            dyd, dw, db = h16(dy), empty16(N, K), empty16(N)
+            if bad:
+                dyd[:, N - 1] = 30000.0
+            mp.mp_gemm_bwd_dw(d, dyd, xd, dw, db, st, ws)
+            if not bad:
+                # (fp32 sums in another order: one ulp of the result, and of the summed magnitudes where they cancel)
+                assert_close16(dw, dw_ref, 1e-3, max_ulp=1, what="dw")
+                assert_close16(db, db_ref, 1e-3, max_ulp=1, what="db")
+                assert mp.scale_state_read(st).found_inf == 0
+            else:
+                assert torch.isinf(db[N - 1]) and torch.equal(db[:N - 1], good) and mp.scale_state_read(st).found_inf == 1
+            good = db[:N - 1]
+    finally:
+        mp.mp_gemm_tuning_override(-1, 1)
