@@ -110,6 +110,18 @@ int mp_scale_state_init(mp_scale_state* st, int mode, float init_scale, int grow
  * STATIC mode never changes S (an overflowing step is still skipped and counted). */
 int mp_loss_scale_update(mp_scale_state* st, mp_stream stream);
 
+/* Partial sums of a mean on the device: sum(part[0 .. n-1]) / denom.  Filled by the *_parts losses below. */
+typedef struct mp_mean_parts {
+    const float* part;
+    double       denom;
+    int32_t      n;
+    int32_t      reserved;
+} mp_mean_parts;
+
+/* mp_loss_scale_update that also stores the mean of `parts` (host struct; its partial sums on the device are as the call that
+ * filled it left them) in *loss (device): the iteration's loss without a launch of its own. */
+int mp_loss_scale_update_mean(mp_scale_state* st, const mp_mean_parts* parts, float* loss, mp_stream stream);
+
 /* ------------------------------------------------------------------------------------------
  * Dense contractions (Section 3.1: fp16 operands, fp32 accumulation, result stored in fp16).
  * One descriptor serves the three calls of a linear layer  Y[M,N] = X[M,K] W[N,K]^T :
@@ -286,6 +298,11 @@ int mp_mse_scaled(int rows, int cols, const mp_half* y, const mp_half* target, i
                   const mp_scale_state* st, float* loss, mp_half* dy, void* ws, size_t ws_bytes,
                   mp_stream stream);
 
+/* mp_mse_scaled without the last step: the loss stays in ws as partial sums (ws is the caller's to keep until they are used),
+ * described in *parts (host).  Same bits as mp_mse_scaled once mp_loss_scale_update_mean has taken them. */
+int mp_mse_scaled_parts(int rows, int cols, const mp_half* y, const mp_half* target, int ld, const mp_scale_state* st,
+                        mp_half* dy, void* ws, size_t ws_bytes, mp_mean_parts* parts, mp_stream stream);
+
 /* loss = mean over rows of (logsumexp(z) - z[target]), z = float(logits), max-subtracted, fp32;
  * dlogits = RNE16( float(S / rows) * (softmax(z) - onehot(target)) ).
  * A target outside [0, vocab) gives that row zero loss and zero gradient (the mean still divides
@@ -316,6 +333,11 @@ int mp_softmax_xent_scaled_db(int rows, int vocab, const mp_half* logits, int ld
 int mp_softmax_xent_scaled_db_copy(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
                                    mp_scale_state* st, float* loss, mp_half* dlogits, mp_half* copy, mp_half* db, void* ws,
                                    size_t ws_bytes, mp_stream stream);
+/* The calls above without the last step, as mp_mse_scaled_parts: copy and db may be NULL; ws (16-byte aligned) is of
+ * mp_softmax_xent_db_workspace_bytes(rows, vocab) bytes, without db of mp_loss_workspace_bytes(rows, vocab). */
+int mp_softmax_xent_scaled_parts(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                 mp_scale_state* st, mp_half* dlogits, mp_half* copy, mp_half* db, void* ws,
+                                 size_t ws_bytes, mp_mean_parts* parts, mp_stream stream);
 
 /* ------------------------------------------------------------------------------------------
  * Bandwidth-bound layer pieces (fp32 arithmetic between fp16 storage points, Section 3.2).

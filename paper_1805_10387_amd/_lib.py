@@ -41,6 +41,10 @@ class ColsumParts(C.Structure):
                 ("out", C.c_void_p * 3)]
 
 
+class MeanParts(C.Structure):
+    _fields_ = [("part", C.c_void_p), ("denom", C.c_double), ("n", C.c_int32), ("reserved", C.c_int32)]
+
+
 class LstmLayerDesc(C.Structure):
     _fields_ = [("T", C.c_int32), ("B", C.c_int32), ("I", C.c_int32), ("H", C.c_int32),
                 ("ldw", C.c_int32), ("ldxh", C.c_int32), ("ld_up", C.c_int32), ("wait_limit_us", C.c_int32),
@@ -87,6 +91,9 @@ SIGNATURES = {
     "mp_softmax_xent_scaled": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_db_workspace_bytes": (_SZ, [_I, _I]),
     "mp_softmax_xent_scaled_copy": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _SZ, _P]),
+    "mp_softmax_xent_scaled_parts": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _SZ, C.POINTER(MeanParts), _P]),
+    "mp_mse_scaled_parts": (_I, [_I, _I, _P, _P, _I, _P, _P, _P, _SZ, C.POINTER(MeanParts), _P]),
+    "mp_loss_scale_update_mean": (_I, [_P, C.POINTER(MeanParts), _P, _P]),
     "mp_softmax_xent_scaled_db": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_softmax_xent_scaled_db_copy": (_I, [_I, _I, _P, _I, _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_layernorm_fwd": (_I, [_I, _I, _P, _P, _P, _P, _F, _P, _P, _P, _P]),

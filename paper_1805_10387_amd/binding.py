@@ -185,6 +185,24 @@ def mp_mse_scaled(rows, cols, y, target, ld, st, loss, dy, ws):
                                   ws.numel() * ws.element_size(), _stream()))
 
 
+def mp_mse_scaled_parts(rows, cols, y, target, ld, st, dy, ws) -> L.MeanParts:
+    parts = L.MeanParts()
+    _check(L.load().mp_mse_scaled_parts(rows, cols, _p(y), _p(target), ld, _p(st), _p(dy), _p(ws), ws.numel() * ws.element_size(),
+                                        C.byref(parts), _stream()))
+    return parts
+
+
+def mp_softmax_xent_scaled_parts(rows, vocab, logits, ld, targets, st, dlogits, copy, db, ws) -> L.MeanParts:
+    parts = L.MeanParts()
+    _check(L.load().mp_softmax_xent_scaled_parts(rows, vocab, _p(logits), ld, _p(targets), _p(st), _p(dlogits), _p(copy), _p(db), _p(ws),
+                                                 ws.numel() * ws.element_size(), C.byref(parts), _stream()))
+    return parts
+
+
+def mp_loss_scale_update_mean(st, parts, loss):
+    _check(L.load().mp_loss_scale_update_mean(_p(st), C.byref(parts), _p(loss), _stream()))
+
+
 def mp_softmax_xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, ws):
     _check(L.load().mp_softmax_xent_scaled(rows, vocab, _p(logits), ld, _p(targets), _p(st), _p(loss), _p(dlogits),
                                            _p(ws), ws.numel() * ws.element_size(), _stream()))

@@ -1,36 +1,20 @@
 // Loss kernels: fp32 loss value and loss-scaled fp16 seed gradient (paper Section 3.1 item 1).
 // Both are streaming kernels bound by HBM: every fp16 input is read once and the fp16 seed
 // gradient written once; reductions are two-stage and deterministic (no float atomics).
-#include "common.hpp"
+#include "mean.hpp"
 
 namespace mp {
 
 constexpr int LOSS_THREADS = 256;
-constexpr int FM_LOADS     = 16;  // partials a thread of the finish kernel has on their way, where there are that many
 
-// Sum `n` fp32 partials with one workgroup (fixed order), divide by `denom`, store to *out.
-// Bound by memory latency: a thread has 16 loads on their way at a time and adds them in index order, so 8192 row losses
-// cost two round trips and not 32 (8192 x 32768 vocabulary iteration 1840 -> 1834 us; the kernel took 12.7 us before).
-// LOADS 1 is for up to one partial per thread, where 16 loads each cost 0.2 us more than one (losses of 1 to 100 rows).
 template <int LOADS>
-__global__ __launch_bounds__(LOSS_THREADS) void finish_mean_kernel(const float* __restrict__ part, int n, double denom,
-                                                                   float* __restrict__ out) {
-    __shared__ float red[LOSS_THREADS / 64];
-    float            acc = 0.f;
-    for (long long i = threadIdx.x; i < n; i += LOADS * LOSS_THREADS) {
-        float v[LOADS];
-#pragma unroll
-        for (int k = 0; k < LOADS; ++k) v[k] = part[min(i + k * LOSS_THREADS, (long long)n - 1)];
-#pragma unroll
-        for (int k = 0; k < LOADS; ++k) acc += i + k * LOSS_THREADS < n ? v[k] : 0.f;
-    }
-    const float tot = block_sum<LOSS_THREADS / 64>(acc, red);
-    if (threadIdx.x == 0) *out = tot / (float)denom;
+__global__ __launch_bounds__(MEAN_THREADS) void finish_mean_kernel(const float* __restrict__ part, int n, double denom, float* __restrict__ out) {
+    mean_of_parts<LOADS>(part, n, denom, out);
 }
 
-static void launch_finish_mean(const float* part, int n, double denom, float* out, hipStream_t hs) {
-    if (n <= LOSS_THREADS) hipLaunchKernelGGL(finish_mean_kernel<1>, dim3(1), dim3(LOSS_THREADS), 0, hs, part, n, denom, out);
-    else hipLaunchKernelGGL(finish_mean_kernel<FM_LOADS>, dim3(1), dim3(LOSS_THREADS), 0, hs, part, n, denom, out);
+static void launch_finish_mean(const mp_mean_parts& p, float* out, hipStream_t hs) {
+    if (p.n <= MEAN_THREADS) hipLaunchKernelGGL(finish_mean_kernel<1>, dim3(1), dim3(MEAN_THREADS), 0, hs, p.part, p.n, p.denom, out);
+    else hipLaunchKernelGGL(finish_mean_kernel<MEAN_LOADS>, dim3(1), dim3(MEAN_THREADS), 0, hs, p.part, p.n, p.denom, out);
 }
 
 // ------------------------------------------------------------------------------- MSE
@@ -308,11 +292,10 @@ extern "C" size_t mp_loss_workspace_bytes(int rows, int cols) {
     return a > b ? a : b;
 }
 
-extern "C" int mp_mse_scaled(int rows, int cols, const mp_half* y, const mp_half* target, int ld,
-                             const mp_scale_state* st, float* loss, mp_half* dy, void* ws, size_t ws_bytes,
-                             mp_stream stream) {
+extern "C" int mp_mse_scaled_parts(int rows, int cols, const mp_half* y, const mp_half* target, int ld, const mp_scale_state* st,
+                                   mp_half* dy, void* ws, size_t ws_bytes, mp_mean_parts* parts, mp_stream stream) {
     MP_REQUIRE(rows > 0 && cols > 0 && ld >= cols, "mp_mse_scaled: bad shape rows=%d cols=%d ld=%d", rows, cols, ld);
-    MP_REQUIRE(y && target && st && loss && dy, "mp_mse_scaled: NULL argument");
+    MP_REQUIRE(y && target && st && dy && parts, "mp_mse_scaled: NULL argument");
     if (!ws || ws_bytes < mp_loss_workspace_bytes(rows, cols)) {
         set_error("mp_mse_scaled: workspace of %zu bytes needed, %zu given", mp_loss_workspace_bytes(rows, cols), ws_bytes);
         return MP_E_WORKSPACE;
@@ -326,7 +309,18 @@ extern "C" int mp_mse_scaled(int rows, int cols, const mp_half* y, const mp_half
     else
         hipLaunchKernelGGL(mse_kernel<false>, dim3(nb), dim3(LOSS_THREADS), 0, hs, rows, cols, ld, y, target, st, dy, part);
     MP_LAUNCH_CHECK("mp_mse_scaled");
-    launch_finish_mean(part, nb, (double)rows * (double)cols, loss, hs);
+    *parts = mp_mean_parts{part, (double)rows * (double)cols, nb, 0};
+    return MP_OK;
+}
+
+extern "C" int mp_mse_scaled(int rows, int cols, const mp_half* y, const mp_half* target, int ld,
+                             const mp_scale_state* st, float* loss, mp_half* dy, void* ws, size_t ws_bytes,
+                             mp_stream stream) {
+    MP_REQUIRE(loss, "mp_mse_scaled: NULL argument");
+    mp_mean_parts parts;
+    const int     rc = mp_mse_scaled_parts(rows, cols, y, target, ld, st, dy, ws, ws_bytes, &parts, stream);
+    if (rc != MP_OK) return rc;
+    launch_finish_mean(parts, loss, as_stream(stream));
     MP_LAUNCH_CHECK("mp_mse_scaled(finish)");
     return MP_OK;
 }
@@ -360,19 +354,10 @@ static void launch_xent_cached(int rows, int vocab, int ld, const mp_half* logit
                            row_loss, colpart);
 }
 
-static int xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets, const mp_scale_state* st, float* loss,
-                       mp_half* dlogits, mp_half* copy, void* ws, size_t ws_bytes, mp_stream stream) {
-    MP_REQUIRE(rows > 0 && vocab > 0 && ld >= vocab, "mp_softmax_xent_scaled: bad shape rows=%d vocab=%d ld=%d", rows,
-               vocab, ld);
-    MP_REQUIRE(logits && targets && st && loss && dlogits, "mp_softmax_xent_scaled: NULL argument");
-    if (!ws || ws_bytes < mp_loss_workspace_bytes(rows, vocab)) {
-        set_error("mp_softmax_xent_scaled: workspace of %zu bytes needed, %zu given", mp_loss_workspace_bytes(rows, vocab),
-                  ws_bytes);
-        return MP_E_WORKSPACE;
-    }
-    float*      row_loss = static_cast<float*>(ws);
-    hipStream_t hs       = as_stream(stream);
-    const int   nvec     = (vocab + 7) / 8;
+// the row losses in row_loss
+static int xent_rows(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets, const mp_scale_state* st,
+                     mp_half* dlogits, mp_half* copy, float* row_loss, hipStream_t hs) {
+    const int nvec = (vocab + 7) / 8;
     if (vocab <= XENT_SHORT && !xent_pieces(vocab, ld, logits, dlogits))
         hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy, row_loss);
     else if (nvec <= XENT_VECS * 256)
@@ -384,7 +369,23 @@ static int xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const
     else
         hipLaunchKernelGGL(xent_kernel, dim3(rows), dim3(LOSS_THREADS), 0, hs, vocab, ld, logits, targets, st, rows, dlogits, copy, row_loss);
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled");
-    launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
+    return MP_OK;
+}
+
+static int xent_scaled(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets, const mp_scale_state* st, float* loss,
+                       mp_half* dlogits, mp_half* copy, void* ws, size_t ws_bytes, mp_stream stream) {
+    MP_REQUIRE(rows > 0 && vocab > 0 && ld >= vocab, "mp_softmax_xent_scaled: bad shape rows=%d vocab=%d ld=%d", rows,
+               vocab, ld);
+    MP_REQUIRE(logits && targets && st && loss && dlogits, "mp_softmax_xent_scaled: NULL argument");
+    if (!ws || ws_bytes < mp_loss_workspace_bytes(rows, vocab)) {
+        set_error("mp_softmax_xent_scaled: workspace of %zu bytes needed, %zu given", mp_loss_workspace_bytes(rows, vocab),
+                  ws_bytes);
+        return MP_E_WORKSPACE;
+    }
+    float* const row_loss = static_cast<float*>(ws);
+    const int    rc       = xent_rows(rows, vocab, logits, ld, targets, st, dlogits, copy, row_loss, as_stream(stream));
+    if (rc != MP_OK) return rc;
+    launch_finish_mean(mp_mean_parts{row_loss, (double)rows, rows, 0}, loss, as_stream(stream));
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled(finish)");
     return MP_OK;
 }
@@ -434,19 +435,43 @@ extern "C" int mp_softmax_xent_scaled_db_copy(int rows, int vocab, const mp_half
         return MP_E_WORKSPACE;
     }
     const size_t head = round256(mp_loss_workspace_bytes(rows, vocab));
-    float*       part = reinterpret_cast<float*>(static_cast<char*>(ws) + head);
-    hipStream_t  hs   = as_stream(stream);
     if (!xent_db_fused(vocab)) {
         // small (or very large) vocabularies: the plain loss call, then a column sum over the gradient it stored
         const int rc = xent_scaled(rows, vocab, logits, ld, targets, st, loss, dlogits, copy, ws, head, stream);
         if (rc != MP_OK) return rc;
-        return mp_colsum(rows, vocab, dlogits, ld, db, st, part, ws_bytes - head, stream);
+        return mp_colsum(rows, vocab, dlogits, ld, db, st, static_cast<char*>(ws) + head, ws_bytes - head, stream);
     }
-    float*    row_loss = static_cast<float*>(ws);
-    const int grid     = xent_grid(rows, 1024);
-    launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, part, hs);
-    MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db");
-    launch_finish_mean(row_loss, rows, (double)rows, loss, hs);
+    mp_mean_parts parts;
+    const int     rc = mp_softmax_xent_scaled_parts(rows, vocab, logits, ld, targets, st, dlogits, copy, db, ws, ws_bytes, &parts, stream);
+    if (rc != MP_OK) return rc;
+    launch_finish_mean(parts, loss, as_stream(stream));
     MP_LAUNCH_CHECK("mp_softmax_xent_scaled_db(finish)");
-    return finish_colsum_launch(part, grid, vocab, db, st, hs);
+    return MP_OK;
+}
+
+extern "C" int mp_softmax_xent_scaled_parts(int rows, int vocab, const mp_half* logits, int ld, const int32_t* targets,
+                                            mp_scale_state* st, mp_half* dlogits, mp_half* copy, mp_half* db, void* ws,
+                                            size_t ws_bytes, mp_mean_parts* parts, mp_stream stream) {
+    MP_REQUIRE(rows > 0 && vocab > 0 && ld >= vocab, "mp_softmax_xent_scaled_parts: bad shape rows=%d vocab=%d ld=%d", rows, vocab, ld);
+    MP_REQUIRE(logits && targets && st && dlogits && parts, "mp_softmax_xent_scaled_parts: NULL argument");
+    const size_t need = db ? mp_softmax_xent_db_workspace_bytes(rows, vocab) : mp_loss_workspace_bytes(rows, vocab);
+    if (!ws || ws_bytes < need || !aligned16(ws)) {
+        set_error("mp_softmax_xent_scaled_parts: 16-byte aligned workspace of %zu bytes needed, %zu given", need, ws_bytes);
+        return MP_E_WORKSPACE;
+    }
+    hipStream_t  hs       = as_stream(stream);
+    float* const row_loss = static_cast<float*>(ws);
+    const size_t head     = round256(mp_loss_workspace_bytes(rows, vocab));
+    int          rc;
+    if (db && xent_db_fused(vocab)) {
+        float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + head);
+        launch_xent_cached<1024, true>(rows, vocab, ld, logits, targets, st, dlogits, copy, row_loss, part, hs);
+        MP_LAUNCH_CHECK("mp_softmax_xent_scaled_parts");
+        rc = finish_colsum_launch(part, xent_grid(rows, 1024), vocab, db, st, hs);
+    } else {
+        rc = xent_rows(rows, vocab, logits, ld, targets, st, dlogits, copy, row_loss, hs);
+        if (rc == MP_OK && db) rc = mp_colsum(rows, vocab, dlogits, ld, db, st, static_cast<char*>(ws) + head, ws_bytes - head, stream);
+    }
+    if (rc == MP_OK) *parts = mp_mean_parts{row_loss, (double)rows, rows, 0};
+    return rc;
 }

@@ -5,7 +5,7 @@
 //   update  : Adam reads g16 + w32 + m + v (14 B) and writes w32 + m + v + w16 (14 B) = 28 B/param,
 //             SGD reads 6 B and writes 6 B = 12 B/param,
 // with 16-byte accesses per lane, consecutive lanes on consecutive addresses.
-#include "common.hpp"
+#include "mean.hpp"
 
 #include <mutex>
 #include <string.h>
@@ -50,8 +50,7 @@ __global__ void scale_state_init_kernel(mp_scale_state* st, int mode, float s, i
     }
 }
 
-__global__ void loss_scale_update_kernel(mp_scale_state* st) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+__device__ __forceinline__ void loss_scale_update(mp_scale_state* st) {
     const int   found = st->found_inf != 0;
     float       s     = st->scale;
     const int   slot  = st->total_steps % MP_HISTORY;
@@ -74,6 +73,17 @@ __global__ void loss_scale_update_kernel(mp_scale_state* st) {
     st->scale     = s;
     st->inv_scale = 1.0f / s;
     st->found_inf = 0;
+}
+__global__ void loss_scale_update_kernel(mp_scale_state* st) {
+    if (threadIdx.x == 0) loss_scale_update(st);
+}
+// The end of an iteration: the loss out of its partial sums as well, so that it needs no launch between loss and backward (1.6 us of
+// a captured chain of small kernels, up to 4.7 behind one that has written much).
+template <int LOADS>
+__global__ __launch_bounds__(MEAN_THREADS) void loss_scale_update_mean_kernel(mp_scale_state* st, const float* __restrict__ part, int n,
+                                                                              double denom, float* __restrict__ loss) {
+    if (threadIdx.x == MEAN_THREADS - 1) loss_scale_update(st);
+    mean_of_parts<LOADS>(part, n, denom, loss);
 }
 
 // ------------------------------------------------------------------ multi-tensor update
@@ -305,6 +315,18 @@ extern "C" int mp_loss_scale_update(mp_scale_state* st, mp_stream stream) {
     MP_REQUIRE(st != nullptr, "mp_loss_scale_update: st is NULL");
     hipLaunchKernelGGL(loss_scale_update_kernel, dim3(1), dim3(64), 0, as_stream(stream), st);
     MP_LAUNCH_CHECK("mp_loss_scale_update");
+    return MP_OK;
+}
+
+extern "C" int mp_loss_scale_update_mean(mp_scale_state* st, const mp_mean_parts* parts, float* loss, mp_stream stream) {
+    MP_REQUIRE(st && parts && loss, "mp_loss_scale_update_mean: NULL argument");
+    MP_REQUIRE(parts->part && parts->n > 0, "mp_loss_scale_update_mean: no partial sums");
+    hipStream_t hs = as_stream(stream);
+    if (parts->n <= MEAN_THREADS)
+        hipLaunchKernelGGL(loss_scale_update_mean_kernel<1>, dim3(1), dim3(MEAN_THREADS), 0, hs, st, parts->part, parts->n, parts->denom, loss);
+    else
+        hipLaunchKernelGGL(loss_scale_update_mean_kernel<MEAN_LOADS>, dim3(1), dim3(MEAN_THREADS), 0, hs, st, parts->part, parts->n, parts->denom, loss);
+    MP_LAUNCH_CHECK("mp_loss_scale_update_mean");
     return MP_OK;
 }
 

@@ -83,6 +83,9 @@ class _StepBase:
         # every gradient producer also reports non-finite outputs into the state itself, which is what
         # `prechecked` relies on to drop the separate inspection pass
         self.st_grad = self.st
+        # the loss as partial sums, from the loss call to the end of the iteration (step()); forward_backward() alone finishes it
+        self.loss_part: Optional[torch.Tensor] = None
+        self._later, self._parts = False, None
 
     def _alloc_ws(self, nbytes: int):
         self.ws = torch.empty(_round_up(max(nbytes, 1024), 256) // 4, dtype=torch.float32, device="cuda")
@@ -93,10 +96,30 @@ class _StepBase:
             B.mp_unscale_check_update(self.P.flat_list, 1, self.cfg, self.st, flags)
         else:
             B.mp_unscale_check_update(self.P.tensor_list, self.P.n_tensors, self.cfg, self.st, flags)
-        B.mp_loss_scale_update(self.st)
+        if self._parts is not None:
+            B.mp_loss_scale_update_mean(self.st, self._parts, self.loss)
+            self._parts = None
+        else:
+            B.mp_loss_scale_update(self.st)
+
+    def _alloc_loss(self, rows: int, cols: int, nbytes: int = 0):
+        n = max(B.mp_loss_workspace_bytes(rows, cols), nbytes)
+        self.loss_part = torch.empty(_round_up(n, 256) // 4, dtype=torch.float32, device="cuda")
+
+    def _mse(self, rows, cols, y, target, dy):
+        """Loss and seed gradient; within step() the loss itself is finished by the launch that ends the iteration."""
+        self._parts = None
+        if self._later:
+            self._parts = B.mp_mse_scaled_parts(rows, cols, y, target, cols, self.st, dy, self.loss_part)
+        else:
+            B.mp_mse_scaled(rows, cols, y, target, cols, self.st, self.loss, dy, self.loss_part)
 
     def step(self, inject: Optional[Callable] = None):
-        self.forward_backward()
+        self._later = True
+        try:
+            self.forward_backward()
+        finally:
+            self._later = False
         if inject is not None:
             inject(self.P.g16)
         self.optimizer()
@@ -130,8 +153,8 @@ class MLPStep(_StepBase):
         self.h, self.y, self.dy, self.dpre, self.dx = e16(R, dh), e16(R, do), e16(R, do), e16(R, dh), e16(R, di)
         self.d1 = B.gemm_desc(R, dh, di, epilogue=ML.MP_EPI_BIAS_RELU)
         self.d2 = B.gemm_desc(R, do, dh, epilogue=ML.MP_EPI_BIAS)
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.d1, True), B.mp_gemm_bwd_dw_workspace_bytes(self.d2, True),
-                           B.mp_loss_workspace_bytes(R, do)))
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.d1, True), B.mp_gemm_bwd_dw_workspace_bytes(self.d2, True)))
+        self._alloc_loss(R, do)
 
     def set_batch(self, batch):
         self.x.copy_(_h16(batch["x"]))
@@ -142,7 +165,7 @@ class MLPStep(_StepBase):
         R, do = self.wl.rows, self.wl.d_out
         B.mp_gemm_fwd(self.d1, self.x, w["w1"], w["b1"], None, self.h)
         B.mp_gemm_fwd(self.d2, self.h, w["w2"], w["b2"], None, self.y)
-        B.mp_mse_scaled(R, do, self.y, self.target, do, self.st, self.loss, self.dy, self.ws)
+        self._mse(R, do, self.y, self.target, self.dy)
         B.mp_gemm_bwd_both(self.d2, self.dy, w["w2"], self.dpre, self.d2, self.h, g["w2"], g["b2"], st, self.ws,
                            relu_src=self.h, ld_aux=self.wl.d_hidden)
         B.mp_gemm_bwd_both(self.d1, self.dpre, w["w1"], self.dx, self.d1, self.x, g["w1"], g["b1"], st, self.ws)
@@ -208,8 +231,9 @@ class TransformerStep(_StepBase):
         self.grouped_dw = self.grouped_dw and not self.joint_bwd
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)]
         need += [B.mp_gemm_bwd_dw_workspace_bytes(self.d_s, False), B.mp_gemm_bwd_dw_workspace_bytes(self.d_c, False),
-                 B.mp_layernorm_bwd_workspace_bytes(T, d), B.mp_loss_workspace_bytes(T, d)]
+                 B.mp_layernorm_bwd_workspace_bytes(T, d)]
         self._alloc_ws(max(need))
+        self._alloc_loss(T, d)
         self.ws_side = torch.empty_like(self.ws)
         # partial column sums of a layer's two LayerNorm backwards, finished by its grouped launch (which alternate by layer)
         self.ln_parts = []
@@ -345,7 +369,7 @@ class TransformerStep(_StepBase):
     def forward_backward(self):
         wl = self.wl
         y = self.forward()
-        B.mp_mse_scaled(wl.tokens, wl.d_model, y, self.target, wl.d_model, self.st, self.loss, self.gbuf[0], self.ws)
+        self._mse(wl.tokens, wl.d_model, y, self.target, self.gbuf[0])
         self.backward()
 
 
@@ -369,8 +393,8 @@ class XentStep(_StepBase):
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.desc = B.gemm_desc(T, V, d, ldy=self.ld_v, epilogue=ML.MP_EPI_BIAS)
         self.db_with_loss = 16384 < V <= 32768
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, not self.db_with_loss), B.mp_gemm_split_workspace_bytes(self.desc),
-                           B.mp_softmax_xent_db_workspace_bytes(T, V)))
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, not self.db_with_loss), B.mp_gemm_split_workspace_bytes(self.desc)))
+        self._alloc_loss(T, V, B.mp_softmax_xent_db_workspace_bytes(T, V) if self.db_with_loss else 0)
 
     def set_batch(self, batch):
         self.h.copy_(_h16(batch["h"]))
@@ -383,10 +407,14 @@ class XentStep(_StepBase):
         copy = None if V == self.ld_v else self.logits
         # the bias gradient (column sums of dlogits) comes out of the pass that writes dlogits where that pass can, else out of
         # the weight gradient
-        if self.db_with_loss:
-            B.mp_softmax_xent_scaled_db_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, g["b"], self.ws)
+        self._parts = None
+        if self._later:
+            self._parts = B.mp_softmax_xent_scaled_parts(T, V, self.rows16, self.ld_v, self.targets, self.st, self.rows16, copy,
+                                                         g["b"] if self.db_with_loss else None, self.loss_part)
+        elif self.db_with_loss:
+            B.mp_softmax_xent_scaled_db_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, g["b"], self.loss_part)
         else:
-            B.mp_softmax_xent_scaled_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, self.ws)
+            B.mp_softmax_xent_scaled_copy(T, V, self.rows16, self.ld_v, self.targets, self.st, self.loss, self.rows16, copy, self.loss_part)
         B.mp_gemm_bwd_both(self.desc, self.rows16, w["w"], self.dh, self.desc, self.h, g["w"], None if self.db_with_loss else g["b"],
                            self.st_grad, self.ws)
 
@@ -453,10 +481,11 @@ class LSTMStep(_StepBase):
         self.dc = z32(Bt, H)
         self.d_gate = [B.gemm_desc(Bt, 4 * H, self.in_dims[l] + H, epilogue=ML.MP_EPI_BIAS) for l in range(NL)]
         self.d_gate_all = [B.gemm_desc(T * Bt, 4 * H, self.in_dims[l] + H) for l in range(NL)]
-        need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in self.d_gate_all] + [B.mp_loss_workspace_bytes(T * Bt, H)]
+        need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in self.d_gate_all]
         # the recurrent products have only `batch` rows: with a workspace they split their contraction over the chip
         need += [B.mp_gemm_split_workspace_bytes(x) for x in self.d_gate]
         self._alloc_ws(max(need))
+        self._alloc_loss(T * Bt, H)
         if self.persistent:
             self.gx = z32(T * Bt, 4 * H)                                     # input half of the gate sums, all steps
             self.dx = [z16(T * Bt, max(self.in_dims)) for _ in range(2)]     # input gradient of a layer, all steps
@@ -506,7 +535,7 @@ class LSTMStep(_StepBase):
             for d, gx, gates, c, xh, up in self.rl_fwd[l]:
                 B.mp_lstm_layer_fwd_chain(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, ws, ready, ws_next)
                 ws, ws_next, ready = ws_next, ws, True
-        B.mp_mse_scaled(T * Bt, H, self.y, self.target, H, self.st, self.loss, self.dy, self.ws)
+        self._mse(T * Bt, H, self.y, self.target, self.dy)
         for l in range(NL - 1, -1, -1):
             for d, gates, c, above, dgates in self.rl_bwd[l]:
                 B.mp_lstm_layer_bwd_chain(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, ws, ready, ws_next)
@@ -532,7 +561,7 @@ class LSTMStep(_StepBase):
                     up, ldup = self.y[t], H
                 rec = self.xh[l][t + 1][:, I:] if t + 1 < T else None
                 B.mp_lstm_cell_fwd(Bt, H, self.gates[l][t], 4 * H, self.c[l][t], self.c[l][t + 1], up, ldup, rec, ldxh)
-        B.mp_mse_scaled(T * Bt, H, self.y, self.target, H, self.st, self.loss, self.dy, self.ws)
+        self._mse(T * Bt, H, self.y, self.target, self.dy)
         above, ld_above = self.dy, H
         for l in range(NL - 1, -1, -1):
             I = self.in_dims[l]

@@ -808,3 +808,21 @@ def test_workload_runner_command_line(capsys):
     assert [l["config"] for l in lines] == [1, 2] and lines[1]["launch"] == "HIP graph replay"
     assert all(l["ms_per_step"] > 0 and np.isfinite(l["loss"]) and l["skipped"] == 0 for l in lines)
     assert lines[0]["opt_steps"] == 4 and lines[1]["opt_steps"] == 4          # warm-up + capture/first replay + timed
+
+
+@pytest.mark.parametrize("make", [lambda: St.MLPStep(I.C1), lambda: St.TransformerStep(I.C2_SMALL), lambda: St.XentStep(I.C4_SMALL), lambda: St.LSTMStep(I.C5_SMALL)])
+def test_a_step_is_its_two_halves(make):
+    """step() finishes the loss with the scale update, forward_backward() by itself: same loss, weights and state, in turn too."""
+    a, b = make(), make()
+    batch = a.wl.batch()
+    a.set_batch(batch), b.set_batch(batch)
+    for k in range(3):
+        if k == 1:
+            a.forward_backward()
+            a.optimizer()
+        else:
+            a.step()
+        b.forward_backward()
+        lb = b.loss.clone()
+        b.optimizer()
+        assert torch.equal(a.loss, lb) and torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.st, b.st)

@@ -1687,3 +1687,37 @@ def test_bias_gradient_from_the_weight_gradient(T, N, K, tile, splits):
             good = db[:N - 1]
     finally:
         mp.mp_gemm_tuning_override(-1, 1)
+
+
+@pytest.mark.parametrize("kind,rows,cols,ld", [("mse", 3, 8, 8), ("mse", 300, 29, 31), ("mse", 4096, 512, 512), ("xent", 5, 40, 40),
+                                               ("xent", 257, 1001, 1008), ("xent", 600, 17000, 17000), ("xent", 9000, 264, 264)])
+def test_loss_finished_with_the_scale_update(kind, rows, cols, ld):
+    """A loss left as partial sums and finished by the launch that updates the scale: the bits of the plain call, the state that
+    mp_loss_scale_update leaves, for one and for many partial sums per thread, with and without the bias gradient."""
+    r = RNG(rows + cols)
+    y, t = h16(r.standard_normal((rows, ld))), h16(r.standard_normal((rows, ld)))
+    tgt, ws = i32(r.integers(0, cols, rows)), ws_bytes(mp.mp_softmax_xent_db_workspace_bytes(rows, cols))
+    for with_db in ((False, True) if kind == "xent" else (False,)):
+        out = []
+        for parts in (False, True):
+            st, loss, g, db = mp.scale_state_alloc(), empty32(1), empty16(rows, ld), empty16(cols)
+            mp.mp_scale_state_init(st, ML.MP_SCALE_BACKOFF, 2.0 ** 12, 1, 1.0, 2.0 ** 24)
+            g.zero_(), db.zero_()
+            if kind == "mse" and parts:
+                p = mp.mp_mse_scaled_parts(rows, cols, y, t, ld, st, g, ws)
+            elif kind == "mse":
+                mp.mp_mse_scaled(rows, cols, y, t, ld, st, loss, g, ws)
+            elif parts:
+                p = mp.mp_softmax_xent_scaled_parts(rows, cols, y, ld, tgt, st, g, None, db if with_db else None, ws)
+            elif with_db:
+                mp.mp_softmax_xent_scaled_db(rows, cols, y, ld, tgt, st, loss, g, db, ws)
+            else:
+                mp.mp_softmax_xent_scaled(rows, cols, y, ld, tgt, st, loss, g, ws)
+            if parts:
+                mp.mp_loss_scale_update_mean(st, p, loss)
+            else:
+                mp.mp_loss_scale_update(st)
+            out.append((loss, st, g, db))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
+        assert float(out[0][0]) > 0 and mp.scale_state_read(out[1][1]).scale == 2.0 ** 13
