@@ -340,16 +340,19 @@ __device__ __forceinline__ u32x2g dtl_bias(const GemmArgs& g, const int n) {
 }
 
 // Sums of the first operand over the contraction: the bias gradient that goes with a weight gradient, of which this kernel has
-// every element in LDS anyway.  A row tile of 16 is one matrix-core instruction per 32 k against a fragment of ones; the tiles
-// beside each other and the two wave columns of each share the row tiles out among them (`slot`), one to a wave, which reads its
-// fragments once more (picking them out of the registers by the wave's number costs branches or moves: 5 us of a 256 x 128
-// product of 25 k-tiles, 1 this way).  Against the column sums as launches of their own, us: see sums_ride in the plan.
-template <typename OPA, int TM, int UNIT, bool ON>   // UNIT: row tiles of a unit of OPA's rows
+// every element in LDS anyway.  The tiles beside each other and the two wave columns of each share the row tiles of 16 out among
+// them (`slot`), one to a wave, which reads that row tile's fragments once more.  (Picking them out of the registers by the
+// wave's number costs a chain of branches: 5 us of a product of 28.)  DOT: summed with 8 two-element dot products per k-tile,
+// for the kernels whose accumulators fill the matrix cores' half of the registers, where a conditional matrix instruction costs
+// 8 copies each way (8192 x 3072 x 1024 74.0 us that way, 67.6 this way, 63.4 without sums); else with 2 matrix instructions
+// against a fragment of ones (2048 x 1024 x 1024 14.9 / 14.3).
+template <typename OPA, int TM, int UNIT, bool ON, bool DOT>   // UNIT: row tiles of a unit of OPA's rows
 struct DtlSums {
     int      mine;      // row tile of this wave, or none
     unsigned off;       // where its fragments lie in a stage
-    f16x8    f[2];
-    f32x4    sum[2];    // by slice
+    f16x8    f[2];      // of slice 0 and 1
+    float    dot[2];
+    f32x4    mfma[2];
     __device__ __forceinline__ void start(const GemmArgs& g, const OPA& oa, const int slot) {
         if constexpr (ON) {
             mine = __builtin_amdgcn_readfirstlane(slot < TM ? slot : -1);
@@ -358,7 +361,8 @@ struct DtlSums {
                 constexpr int i = decltype(ic)::value;
                 if (mine == i) off = oa.template frag_offset<i / UNIT, i % UNIT>();
             });
-            sum[0] = sum[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            dot[0] = dot[1] = 0.f;
+            mfma[0] = mfma[1] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
     __device__ __forceinline__ bool upper() const { return ON && mine >= 0 && mine < UNIT; }
@@ -371,11 +375,20 @@ struct DtlSums {
     }
     __device__ __forceinline__ void add() {
         if constexpr (ON) {
+            const f16   one  = (f16)1.f;
+            const f16x2 ones = {one, one};
             if (mine >= 0) {
-                const f16   one  = (f16)1.f;
-                const f16x8 ones = {one, one, one, one, one, one, one, one};
-                sum[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, f[0], sum[0], 0, 0, 0);
-                sum[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, f[1], sum[1], 0, 0, 0);
+                if constexpr (DOT) {
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) dot[q] = __builtin_amdgcn_fdot2(f16x2{f[q][e], f[q][e + 1]}, ones, dot[q], false);
+                    }
+                } else {
+                    const f16x8 ones8 = {one, one, one, one, one, one, one, one};
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) mfma[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones8, f[q], mfma[q], 0, 0, 0);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -383,9 +396,14 @@ struct DtlSums {
     // mw: first row of the wave
     __device__ __forceinline__ void store(const GemmArgs& g, const int mw, const bool split, bool& bad) const {
         if constexpr (ON) {
-            const int lane = threadIdx.x & 63, m = mw + 16 * mine + lane;   // (the sum of row r is in lanes r, r + 16, ...)
-            if (mine < 0 || lane >= 16 || m >= g.M) return;
-            const float s = sum[0][0] + sum[1][0];
+            if (mine < 0) return;
+            const int lane = threadIdx.x & 63, m = mw + 16 * mine + lane;
+            float     s    = DOT ? dot[0] + dot[1] : mfma[0][0] + mfma[1][0];
+            if constexpr (DOT) {   // (lanes r, r + 16, r + 32 and r + 48 have row r over k of their own)
+                s += __shfl_xor(s, 16, 64);
+                s += __shfl_xor(s, 32, 64);
+            }
+            if (lane >= 16 || m >= g.M) return;
             if (split) {
                 g.db_part[m] = s;
             } else {
@@ -538,7 +556,7 @@ __device__ __forceinline__ void dtl_tiles(const GemmArgs& g, const int vb0, cons
                 }
             });
         }
-        DtlSums<OpA, TM, TH, SUMS> sums;
+        DtlSums<OpA, TM, TH, SUMS, true> sums;
         sums.start(g, oa, 2 * (n0 / BN) + wn);
         // The previous tile's output stores are younger than the loads that the first three barriers of a tile need, which
         // therefore need not wait for them: `behind` counts those barriers (three, or none for the first tile).
@@ -729,7 +747,7 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
     __syncthreads();
     unsigned c_st = 0;
     static_for<NR>([&](auto fc) { read(smem, std::integral_constant<int, 0>{}, fc); });
-    DtlSums<OpA, TM, TM, SUMS> sums;   // of the k-tile that is being read, one ahead of the matrix cores
+    DtlSums<OpA, TM, TM, SUMS, false> sums;   // of the k-tile that is being read, one ahead of the matrix cores
     sums.start(g, oa, 2 * (n0 / BN) + wn);
     if (sums.upper()) sums.read(smem);
     sums.add();
@@ -753,7 +771,7 @@ __device__ __forceinline__ void deep_tiles(const GemmArgs& g, const int vb0, con
                 }
             });
         }
-        DtlSums<OpA, TM, TM, SUMS> tile_sums;
+        DtlSums<OpA, TM, TM, SUMS, false> tile_sums;
         auto ktile = [&](auto pc, const bool last) {
             constexpr int p = decltype(pc)::value;
             c_st = c_st + STAGE == DEEP_STAGES * STAGE ? 0 : c_st + STAGE;
