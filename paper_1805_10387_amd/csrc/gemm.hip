@@ -421,7 +421,7 @@ static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     // (as matrix_path_ok, for both: stored rows of at least 8 elements, offsets inside a tile within the buffer size)
     if (dx->N < 8 || dx->K < 8 || dw->K < 8 || std::max(std::max(dx->ldy, dx->ldw), dw->ldx) >= LD_BUFFER_64) return false;
     return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M) &&
-           small_tiles(dx->M, dx->K) + small_tiles(dw->N, dw->K) + (dw->N + SM_STRIP - 1) / SM_STRIP <= 3 * kCUs;
+           small_tiles(dx->M, dx->K) + small_tiles(dw->N, dw->K) + (dw->N + 31) / 32 <= 3 * kCUs;
 }
 
 extern "C" int mp_gemm_bwd_both_joint(const mp_gemm_desc* d_dx, const mp_gemm_desc* d_dw) {
@@ -445,14 +445,13 @@ extern "C" int mp_gemm_bwd_both(const mp_gemm_desc* d_dx, const mp_half* dY, con
         x.M = d_dx->M; x.N = d_dx->K; x.K = d_dx->N;
         x.lda = d_dx->ldy; x.ldb = d_dx->ldw; x.ldc = d_dx->ldx; x.alpha = d_dx->alpha; x.batch_inner = 1;
         GemmArgs& w = b.dw;
-        w.A = dY; w.B = X; w.C = dW; w.found_inf = st ? &st->found_inf : nullptr;
+        w.A = dY; w.B = X; w.C = dW; w.db = db; w.found_inf = st ? &st->found_inf : nullptr;
         w.M = d_dw->N; w.N = d_dw->K; w.K = d_dw->M;
         w.lda = d_dw->ldy; w.ldb = d_dw->ldx; w.ldc = d_dw->ldw; w.alpha = d_dw->alpha; w.batch_inner = 1;
         for (GemmArgs* g : {&x, &w}) {
             g->tiles_m = (g->M + 31) / 32;
             g->tiles_n = (g->N + 31) / 32;
         }
-        b.dY = dY; b.db = db; b.rows = d_dw->M; b.cols = d_dw->N; b.ld = d_dw->ldy;
         return launch_small_both(small_waves((long long)x.tiles_m * x.tiles_n + (long long)w.tiles_m * w.tiles_n, std::max(x.K, w.K)), b,
                                  as_stream(stream));
     }

@@ -111,8 +111,11 @@ inline double arrival(const int t, const int M, const int N, const int K, const 
 // to a wave, so the waves beside each other have to cover a tile's rows; 256 x 256 has no registers for it, and 128 x 256 is
 // hardly ever the best shape.  us of a weight gradient with its bias gradient, column sums apart / riding (rows x outputs x
 // inputs, in a captured chain): 1600 x 4096 x 2048 36.2 / 33.0, 1600 x 2048 x 1024 19.1 / 15.0, 1024 x 8000 x 512 19.9 / 15.6,
-// 1021 x 12008 x 512 29.9 / 22.8, 520 x 3000 x 256 10.8 / 8.1, 8000 x 640 x 640 26.8 / 19.8, 8192 x 3072 x 1024 76.0 / 74.7.
+// 1021 x 12008 x 512 29.9 / 22.8, 520 x 3000 x 256 10.8 / 8.1, 8000 x 640 x 640 26.8 / 19.8, 8192 x 3072 x 1024 76.0 / 67.6; in
+// the small kernel (the first tile of a row of tiles sums) 1500 x 29 x 1024 12.0 / 8.5, 1200 x 512 x 320 11.0 / 6.4, 64 x 1024 x 256
+// 7.4 / 3.9.
 inline bool sums_ride(int tile, bool dtl, int N) {
+    if (tile >= kTileSmall4) return true;
     return dtl && (tile == 1 || (tile >= 3 && tile <= 5)) && 2 * ((N + kTiles[tile].bn - 1) / kTiles[tile].bn) >= kTiles[tile].bm / 32;
 }
 
@@ -135,11 +138,7 @@ inline Plan make_plan(int M, int N, int K, long long batches, bool allow_split, 
         return Plan{t, sp, kps > 0 ? kps : BK, dtl && dtl_takes(t, K, sp, kps)};
     }
     const bool dtl_only = dtl && tuning.dtl == 2;
-    // (with sums the small kernel and their launches against one of the others, us: 300 x 192 x 192 8.0 / 6.9, 3000 x 128 x 128 13.2 /
-    // 11.7, 800 x 1024 x 512 12.3 / 9.2; where few tiles make the others split the contraction, 1000 x 128 x 128 8.9 / 9.9, 1000 x 256 x
-    // 192 9.1 / 10.0, 2000 x 256 x 256 11.4 / 12.1)
-    const bool small_sums = !dtl || (small_tiles(M, N) <= 64 && K > 640 && K <= 2560);
-    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072) && (apart_us == 0. || small_sums))  // (longer ones: split over more workgroups)
+    if (!dtl_only && batches == 1 && small_wins(M, N, K) && (!allow_split || K <= 3072))  // (longer ones: split over more workgroups)
         return Plan{small_waves(small_tiles(M, N), K) == 8 ? kTileSmall8 : kTileSmall4, 1, (K + BK - 1) / BK * BK, false};
     Plan   best{0, 1, 0, false};
     double best_cost = 1e300;

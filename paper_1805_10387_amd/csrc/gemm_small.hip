@@ -20,7 +20,7 @@ static void launch_both(const BothArgs& b, bool tail, int n, hipStream_t hs) {
 int launch_small_both(int waves, const BothArgs& b, hipStream_t hs) {
     const auto odd  = [](int v) { return v % 8 != 0; };
     const bool tail = odd(b.dx.K) || odd(b.dx.N) || odd(b.dw.M) || odd(b.dw.N);
-    const int  n = b.dx.tiles_m * b.dx.tiles_n + b.dw.tiles_m * b.dw.tiles_n + (b.db ? (b.cols + SM_STRIP - 1) / SM_STRIP : 0);
+    const int  n = b.dx.tiles_m * b.dx.tiles_n + b.dw.tiles_m * b.dw.tiles_n;
     if (waves == 8) launch_both<8>(b, tail, n, hs);
     else launch_both<4>(b, tail, n, hs);
     MP_LAUNCH_CHECK("gemm launch (both gradients)");

@@ -72,7 +72,7 @@ struct WaveOperand {
 
 // Output tile (tm, tn) of problem g, k-tiles [kt0, kt1).  split: leave the raw sums in C32 (partials of a split
 // contraction, or the fp32 result with scale and addend when !split).
-template <int NW, bool A_KC, bool B_KC, int MODE>
+template <int NW, bool A_KC, bool B_KC, int MODE, bool SUMS>
 __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, const int tn, const int kt0, const int kt1, float* C32,
                                            const bool split, char* smem, bool& bad) {
     const int lane = threadIdx.x & 63;
@@ -99,6 +99,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
     int off[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) off[c] = r * 128 + ((((2 * c) | h) ^ swz(r)) << 4);
+    // SUMS: sums of the first operand over the contraction (a weight gradient's bias gradient) where g.db is given.  The first tile
+    // of a tile row has its rows' fragments anyway: 16 dot products of two per k-tile; a lane sums the k of its own slots of row r.
+    const bool sums = SUMS && g.db != nullptr && tn == 0;
+    float      rsum = 0.f;
     auto step = [&](auto& a, auto& b, const int kt) {
         a.store(own);
         b.store(own + E * 128);
@@ -108,6 +112,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
             const f16x8   af = *reinterpret_cast<const f16x8*>(own + off[kk]);
             const f16x8   bf = *reinterpret_cast<const f16x8*>(own + E * 128 + off[kk]);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, af, acc, 0, 0, 0);
+            if (sums) {
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) rsum = __builtin_amdgcn_fdot2(f16x2{af[e], af[e + 1]}, f16x2{(f16)1.f, (f16)1.f}, rsum, false);
+            }
         });
     };
     int kt = kt0 + wave;
@@ -126,7 +134,23 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
     for (int q = 0; q < 4; ++q)
         *reinterpret_cast<f32x4*>(own + r * (4 * E) + (((2 * q + h) ^ (r & SX)) << 4)) =
             f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    if (sums) {   // (behind the 4 KB of partial sums)
+        rsum += __shfl_xor(rsum, 32, 64);
+        *reinterpret_cast<float*>(own + 4 * E * E + 4 * r) = rsum;
+    }
     __syncthreads();
+    if (sums && wave == NW - 1 && lane < E && m0 + lane < g.M) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += *reinterpret_cast<const float*>(smem + w * SM_WAVE + 4 * E * E + 4 * lane);
+        if (split) {
+            g.db_part[m0 + lane] = s;
+        } else {
+            const uint16_t hv = f2h(s);
+            g.db[m0 + lane]   = hv;
+            bad |= half_nonfinite(hv);
+        }
+    }
     // wave w finishes rows E / NW w ..., a lane (of the first E E / 8 / NW) 8 consecutive columns of one
     const uint16_t* const aux = g.relu_src ? g.relu_src : g.add;
     constexpr int         CG = E / 8;  // column groups
@@ -201,89 +225,41 @@ __device__ __forceinline__ int2 small_tile_of(const int id, const int tiles_m, c
 }
 
 // grid: (tiles, 1, splits of the contraction); g.k_per_split is a multiple of BK
-template <int NW, bool A_KC, bool B_KC, int MODE>
+template <int NW, bool A_KC, bool B_KC, int MODE, bool SUMS = false>
 __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
     extern __shared__ __align__(16) char smem[];
     bool      bad = false;
+    if (SUMS && gridDim.z > 1) g.db_part += (long long)blockIdx.z * g.M;
     const int2 t = small_tile_of(blockIdx.x, g.tiles_m, g.tiles_n);
     const int  per = g.k_per_split / BK, nkt = (g.K + BK - 1) / BK;
     const bool split = gridDim.z > 1;
-    small_tile<NW, A_KC, B_KC, MODE>(g, t.x, t.y, blockIdx.z * per, min(nkt, (int)(blockIdx.z + 1) * per),
+    small_tile<NW, A_KC, B_KC, MODE, SUMS>(g, t.x, t.y, blockIdx.z * per, min(nkt, (int)(blockIdx.z + 1) * per),
                                  g.C32 ? g.C32 + (long long)blockIdx.z * g.M * g.N : nullptr, split, smem, bad);
     if (g.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(g.found_inf, 1);
     }
 }
 
-// Both gradients of a linear layer in one launch: tiles of dX, tiles of dW, and strips of column sums of dY (the bias
-// gradient), numbered one after the other.  They share dY and depend on nothing else, and each alone leaves most of a
-// small layer's time to launches.
+// Both gradients of a linear layer in one launch: tiles of dX, then tiles of dW, which have the bias gradient with them.  They
+// share dY and depend on nothing else, and each alone leaves most of a small layer's time to launches.  (With the column sums of
+// dY as workgroups of their own, 32 columns each, their rounds of rows were the longest chain: see both_joint.)
 struct BothArgs {
-    GemmArgs        dx, dw;
-    const uint16_t* dY;       // [rows, cols] of the bias gradient
-    uint16_t*       db;       // or NULL
-    int             rows, cols, ld;
+    GemmArgs dx, dw;
 };
-
-// db[SM_STRIP strip ...] = RNE16(fp32 column sums): pairs of columns, 16 rows in flight per thread (the chain of rounds is
-// what a strip costs: 1500 rows in 6 rounds, or 3 with 8 waves), rows added in a fixed order.
-constexpr int SM_STRIP = 32;
-typedef unsigned u32_u __attribute__((aligned(2)));
-template <int NW>
-__device__ __forceinline__ void small_colsum(const BothArgs& b, const int strip, char* smem, bool& bad) {
-    constexpr int LANES = 4 * NW, U = 16;
-    const int     cp = threadIdx.x & 15, rl = threadIdx.x >> 4, c = SM_STRIP * strip + 2 * cp;
-    const bool    two = c + 1 < b.cols, one = c < b.cols;
-    float         s0 = 0.f, s1 = 0.f;
-    for (int r0 = rl; r0 < b.rows; r0 += LANES * U) {
-        unsigned v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int       rr = r0 + LANES * u;
-            const uint16_t* p  = b.dY + (long long)rr * b.ld + c;
-            v[u] = 0u;
-            if (rr < b.rows) {
-                if (two) v[u] = *reinterpret_cast<const u32_u*>(p);
-                else if (one) v[u] = *p;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            s0 += h2f((uint16_t)(v[u] & 0xFFFFu));
-            s1 += h2f((uint16_t)(v[u] >> 16));
-        }
-    }
-    float* red = reinterpret_cast<float*>(smem);
-    red[rl * SM_STRIP + 2 * cp] = s0;
-    red[rl * SM_STRIP + 2 * cp + 1] = s1;
-    __syncthreads();
-    if (threadIdx.x < SM_STRIP && SM_STRIP * strip + (int)threadIdx.x < b.cols) {
-        float t = 0.f;
-#pragma unroll
-        for (int q = 0; q < LANES; ++q) t += red[q * SM_STRIP + threadIdx.x];
-        const uint16_t hv = f2h(t);
-        b.db[SM_STRIP * strip + threadIdx.x] = hv;
-        bad |= half_nonfinite(hv);
-    }
-}
 
 template <int NW, int MODE>
 __global__ __launch_bounds__(64 * NW) void gemm_small_both_kernel(BothArgs b) {
     extern __shared__ __align__(16) char smem[];
     bool      bad = false;
-    const int ndx = b.dx.tiles_m * b.dx.tiles_n, ndw = b.dw.tiles_m * b.dw.tiles_n;
+    const int ndx = b.dx.tiles_m * b.dx.tiles_n;
     const int id = blockIdx.x;
     if (id < ndx) {
         const int2 t = small_tile_of(id, b.dx.tiles_m, b.dx.tiles_n);
-        small_tile<NW, true, false, MODE>(b.dx, t.x, t.y, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
+        small_tile<NW, true, false, MODE, false>(b.dx, t.x, t.y, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
         return;  // (dX has no overflow flag)
     }
-    if (id < ndx + ndw) {
-        const int t = id - ndx;
-        small_tile<NW, false, false, MODE>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
-    } else {
-        small_colsum<NW>(b, id - ndx - ndw, smem, bad);
-    }
+    const int t = id - ndx;
+    small_tile<NW, false, false, MODE, true>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
     if (b.dw.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(b.dw.found_inf, 1);
     }
@@ -294,6 +270,14 @@ template <int NW, bool AKC, bool BKC>
 int launch_small(const GemmArgs& g, int splits, hipStream_t hs) {
     const bool tail = (AKC ? g.K : g.M) % 8 != 0 || (BKC ? g.K : g.N) % 8 != 0 || g.N % 8 != 0;
     const dim3 grid(g.tiles_m * g.tiles_n, 1, splits);
+    if constexpr (!AKC && !BKC) {   // (a kernel of its own: the branch costs a product without sums 0.1 to 0.3 us)
+        if (g.db) {
+            if (tail) hipLaunchKernelGGL((gemm_small_kernel<NW, false, false, TAIL, true>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
+            else hipLaunchKernelGGL((gemm_small_kernel<NW, false, false, EDGE, true>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
+            MP_LAUNCH_CHECK("gemm launch (small)");
+            return MP_OK;
+        }
+    }
     if (tail) hipLaunchKernelGGL((gemm_small_kernel<NW, AKC, BKC, TAIL>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
     else hipLaunchKernelGGL((gemm_small_kernel<NW, AKC, BKC, EDGE>), grid, dim3(64 * NW), sm_lds(NW), hs, g);
     MP_LAUNCH_CHECK("gemm launch (small)");

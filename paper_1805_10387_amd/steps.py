@@ -87,8 +87,11 @@ class _StepBase:
         self.loss_part: Optional[torch.Tensor] = None
         self._later, self._parts = False, None
 
-    def _alloc_ws(self, nbytes: int):
-        self.ws = torch.empty(_round_up(max(nbytes, 1024), 256) // 4, dtype=torch.float32, device="cuda")
+    def _alloc_ws(self, nbytes: int, loss_bytes: int):
+        """One buffer: the calls' workspace, and the loss's partial sums, which stay from the loss call to the end of step()."""
+        n = _round_up(max(nbytes, 1024), 256) // 4
+        buf = torch.empty(n + _round_up(loss_bytes, 256) // 4, dtype=torch.float32, device="cuda")
+        self.ws, self.loss_part = buf[:n], buf[n:]
 
     def optimizer(self):
         flags = ML.MP_UPDATE_PRECHECKED if self.prechecked else ML.MP_UPDATE_DEFAULT
@@ -101,10 +104,6 @@ class _StepBase:
             self._parts = None
         else:
             B.mp_loss_scale_update(self.st)
-
-    def _alloc_loss(self, rows: int, cols: int, nbytes: int = 0):
-        n = max(B.mp_loss_workspace_bytes(rows, cols), nbytes)
-        self.loss_part = torch.empty(_round_up(n, 256) // 4, dtype=torch.float32, device="cuda")
 
     def _mse(self, rows, cols, y, target, dy):
         """Loss and seed gradient; within step() the loss itself is finished by the launch that ends the iteration."""
@@ -153,8 +152,8 @@ class MLPStep(_StepBase):
         self.h, self.y, self.dy, self.dpre, self.dx = e16(R, dh), e16(R, do), e16(R, do), e16(R, dh), e16(R, di)
         self.d1 = B.gemm_desc(R, dh, di, epilogue=ML.MP_EPI_BIAS_RELU)
         self.d2 = B.gemm_desc(R, do, dh, epilogue=ML.MP_EPI_BIAS)
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.d1, True), B.mp_gemm_bwd_dw_workspace_bytes(self.d2, True)))
-        self._alloc_loss(R, do)
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.d1, True), B.mp_gemm_bwd_dw_workspace_bytes(self.d2, True)),
+                       B.mp_loss_workspace_bytes(R, do))
 
     def set_batch(self, batch):
         self.x.copy_(_h16(batch["x"]))
@@ -232,8 +231,7 @@ class TransformerStep(_StepBase):
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)]
         need += [B.mp_gemm_bwd_dw_workspace_bytes(self.d_s, False), B.mp_gemm_bwd_dw_workspace_bytes(self.d_c, False),
                  B.mp_layernorm_bwd_workspace_bytes(T, d)]
-        self._alloc_ws(max(need))
-        self._alloc_loss(T, d)
+        self._alloc_ws(max(need), B.mp_loss_workspace_bytes(T, d))
         self.ws_side = torch.empty_like(self.ws)
         # partial column sums of a layer's two LayerNorm backwards, finished by its grouped launch (which alternate by layer)
         self.ln_parts = []
@@ -393,8 +391,8 @@ class XentStep(_StepBase):
         self.dh = torch.empty(T, d, dtype=torch.float16, device="cuda")
         self.desc = B.gemm_desc(T, V, d, ldy=self.ld_v, epilogue=ML.MP_EPI_BIAS)
         self.db_with_loss = 16384 < V <= 32768
-        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, not self.db_with_loss), B.mp_gemm_split_workspace_bytes(self.desc)))
-        self._alloc_loss(T, V, B.mp_softmax_xent_db_workspace_bytes(T, V) if self.db_with_loss else 0)
+        self._alloc_ws(max(B.mp_gemm_bwd_dw_workspace_bytes(self.desc, not self.db_with_loss), B.mp_gemm_split_workspace_bytes(self.desc)),
+                       B.mp_softmax_xent_db_workspace_bytes(T, V) if self.db_with_loss else B.mp_loss_workspace_bytes(T, V))
 
     def set_batch(self, batch):
         self.h.copy_(_h16(batch["h"]))
@@ -484,8 +482,7 @@ class LSTMStep(_StepBase):
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in self.d_gate_all]
         # the recurrent products have only `batch` rows: with a workspace they split their contraction over the chip
         need += [B.mp_gemm_split_workspace_bytes(x) for x in self.d_gate]
-        self._alloc_ws(max(need))
-        self._alloc_loss(T * Bt, H)
+        self._alloc_ws(max(need), B.mp_loss_workspace_bytes(T * Bt, H))
         if self.persistent:
             self.gx = z32(T * Bt, 4 * H)                                     # input half of the gate sums, all steps
             self.dx = [z16(T * Bt, max(self.in_dims)) for _ in range(2)]     # input gradient of a layer, all steps

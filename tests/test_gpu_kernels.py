@@ -1657,11 +1657,11 @@ def test_scale_state_static_mode_and_validation():
         mp.mp_scale_state_init(st, 7, 2.0, 1)
 
 
-@pytest.mark.parametrize("tile,splits", [(1, 1), (3, 1), (4, 1), (5, 1), (1, 3), (3, 2), (4, 3), (5, 4)])
-@pytest.mark.parametrize("T,N,K", [(192, 256, 512), (193, 520, 456), (1000, 264, 392), (640, 1024, 40)])
+@pytest.mark.parametrize("tile,splits", [(1, 1), (3, 1), (4, 1), (5, 1), (1, 3), (3, 2), (4, 3), (5, 4), (9, 1), (10, 1), (9, 2)])
+@pytest.mark.parametrize("T,N,K", [(192, 256, 512), (193, 520, 456), (1000, 264, 392), (640, 1024, 40), (65, 36, 24), (700, 29, 36)])
 def test_bias_gradient_from_the_weight_gradient(T, N, K, tile, splits):
-    """Both gradients from one launch in every tile shape that carries the sums, split or not, with rows, columns and a contraction
-    that stick out of the tiles, and (few inputs) where the waves beside each other do not cover a tile's rows and the sums
+    """Both gradients from one launch in every tile shape that carries the sums (9 and 10: the small kernel), split or not, with rows,
+    columns and a contraction that stick out of the tiles and rows at any alignment, and (few inputs) where the waves beside each other do not cover a tile's rows and the sums
     are launches of their own; a sum that overflows raises the flag."""
     r = RNG(T + N + K)
     dy, x, w = S16(r.standard_normal((T, N))), S16(r.standard_normal((T, K))), S16(r.standard_normal((N, K)))
