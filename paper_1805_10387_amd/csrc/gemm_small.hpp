@@ -15,7 +15,11 @@
 namespace mp {
 
 constexpr int E        = 32;            // tile edge
-constexpr int SM_DEPTH = 4;             // k-tiles a wave has on their way
+// k-tiles a wave has on their way (32 registers each).  The joint launch of both gradients has two or three workgroups to a
+// compute unit, which its registers have to leave room for; a product alone has one and short chains (us, depth 4 / 3 / 2:
+// both gradients of 2000 x 256 x 256 11.2 / 11.2 / 9.3, of 1200 x 512 x 320 10.0 / 10.0 / 8.3, of 1500 x 1024 x 161 13.8 / 13.4 / 12.9;
+// forward 200 x 576 over 192 3.64 / 3.61 / 3.74; input gradient 520 x 256 over 3000 9.0 / 8.6 / 8.0, 64 x 1024 over 256 3.67 / 3.64 / 3.74).
+constexpr int SM_DEPTH = 3, SM_DEPTH_BOTH = 2;
 constexpr int SM_WAVE  = 2 * E * 128;   // LDS bytes of one wave: a k-tile of both operands, later its partial sums
 constexpr int sm_lds(int waves) { return waves * SM_WAVE; }
 
@@ -72,7 +76,7 @@ struct WaveOperand {
 
 // Output tile (tm, tn) of problem g, k-tiles [kt0, kt1).  split: leave the raw sums in C32 (partials of a split
 // contraction, or the fp32 result with scale and addend when !split).
-template <int NW, bool A_KC, bool B_KC, int MODE, bool SUMS>
+template <int NW, bool A_KC, bool B_KC, int MODE, bool SUMS, int DEPTH>
 __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, const int tn, const int kt0, const int kt1, float* C32,
                                            const bool split, char* smem, bool& bad) {
     const int lane = threadIdx.x & 63;
@@ -83,10 +87,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
 
     f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    WaveOperand<A_KC, MODE> a[SM_DEPTH];  // k-tiles on their way
-    WaveOperand<B_KC, MODE> b[SM_DEPTH];
+    WaveOperand<A_KC, MODE> a[DEPTH];  // k-tiles on their way
+    WaveOperand<B_KC, MODE> b[DEPTH];
 #pragma unroll
-    for (int d = 0; d < SM_DEPTH; ++d) {
+    for (int d = 0; d < DEPTH; ++d) {
         a[d].init(g.lda);
         b[d].init(g.ldb);
     }
@@ -106,7 +110,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
     auto step = [&](auto& a, auto& b, const int kt) {
         a.store(own);
         b.store(own + E * 128);
-        if (kt + NW * SM_DEPTH < kt1) load(a, b, kt + NW * SM_DEPTH);
+        if (kt + NW * DEPTH < kt1) load(a, b, kt + NW * DEPTH);
         static_for<4>([&](auto kc) {
             constexpr int kk = decltype(kc)::value;
             const f16x8   af = *reinterpret_cast<const f16x8*>(own + off[kk]);
@@ -120,11 +124,11 @@ __device__ __forceinline__ void small_tile(const GemmArgs& g, const int tm, cons
     };
     int kt = kt0 + wave;
 #pragma unroll
-    for (int d = 0; d < SM_DEPTH; ++d)
+    for (int d = 0; d < DEPTH; ++d)
         if (kt + NW * d < kt1) load(a[d], b[d], kt + NW * d);
-    for (; kt < kt1; kt += NW * SM_DEPTH) {
+    for (; kt < kt1; kt += NW * DEPTH) {
 #pragma unroll
-        for (int d = 0; d < SM_DEPTH; ++d)
+        for (int d = 0; d < DEPTH; ++d)
             if (kt + NW * d < kt1) step(a[d], b[d], kt + NW * d);
     }
 
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
     const int2 t = small_tile_of(blockIdx.x, g.tiles_m, g.tiles_n);
     const int  per = g.k_per_split / BK, nkt = (g.K + BK - 1) / BK;
     const bool split = gridDim.z > 1;
-    small_tile<NW, A_KC, B_KC, MODE, SUMS>(g, t.x, t.y, blockIdx.z * per, min(nkt, (int)(blockIdx.z + 1) * per),
+    small_tile<NW, A_KC, B_KC, MODE, SUMS, SM_DEPTH>(g, t.x, t.y, blockIdx.z * per, min(nkt, (int)(blockIdx.z + 1) * per),
                                  g.C32 ? g.C32 + (long long)blockIdx.z * g.M * g.N : nullptr, split, smem, bad);
     if (g.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(g.found_inf, 1);
@@ -255,11 +259,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_both_kernel(BothArgs b) {
     const int id = blockIdx.x;
     if (id < ndx) {
         const int2 t = small_tile_of(id, b.dx.tiles_m, b.dx.tiles_n);
-        small_tile<NW, true, false, MODE, false>(b.dx, t.x, t.y, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
+        small_tile<NW, true, false, MODE, false, SM_DEPTH_BOTH>(b.dx, t.x, t.y, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
         return;  // (dX has no overflow flag)
     }
     const int t = id - ndx;
-    small_tile<NW, false, false, MODE, true>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
+    small_tile<NW, false, false, MODE, true, SM_DEPTH_BOTH>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
     if (b.dw.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(b.dw.found_inf, 1);
     }
