@@ -545,6 +545,14 @@ int mp_unscale_check_update(const mp_tensor_desc* tensors /* host */, int ntenso
                             const mp_opt_cfg* cfg /* host */, mp_scale_state* st, int flags,
                             mp_stream stream);
 
+/* The end of an iteration in one call: mp_unscale_check_update, then mp_loss_scale_update_mean(st, parts, loss), or
+ * mp_loss_scale_update(st) where parts (host) is NULL.  Where the update is small its last workgroup does the rest, counted in
+ * `counters` (device, mp_update_counters_bytes() of them, zero before the first call and zero again after every one; calls that
+ * may overlap need their own). */
+size_t mp_update_counters_bytes(void);
+int mp_unscale_check_update_end(const mp_tensor_desc* tensors /* host array */, int ntensors, const mp_opt_cfg* cfg, mp_scale_state* st,
+                                int flags, const mp_mean_parts* parts, float* loss, int32_t* counters, mp_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

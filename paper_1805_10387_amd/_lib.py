@@ -119,6 +119,8 @@ SIGNATURES = {
     "mp_fill_u32": (_I, [_SZ, C.c_uint32, _P, _P]),
     "mp_mfma_sustained_rate": (_I, [_P, _SZ, _P, _SZ, _I, _I, C.POINTER(C.c_double), _P]),
     "mp_unscale_check_update": (_I, [C.POINTER(TensorDesc), _I, C.POINTER(OptCfg), _P, _I, _P]),
+    "mp_unscale_check_update_end": (_I, [C.POINTER(TensorDesc), _I, C.POINTER(OptCfg), _P, _I, C.POINTER(MeanParts), _P, _P, _P]),
+    "mp_update_counters_bytes": (_SZ, []),
 }
 
 _lib = None

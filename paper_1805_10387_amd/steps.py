@@ -74,6 +74,7 @@ class _StepBase:
         mode = ML.MP_SCALE_BACKOFF if scale_cfg.mode == "backoff" else ML.MP_SCALE_STATIC
         B.mp_scale_state_init(self.st, mode, scale_cfg.init_scale, scale_cfg.growth_interval, scale_cfg.min_scale,
                               scale_cfg.max_scale)
+        self.counters = B.update_counters_alloc()
         self.loss = torch.zeros(1, dtype=torch.float32, device="cuda")
         self.prechecked = prechecked
         self.flat_update = flat_update
@@ -95,15 +96,9 @@ class _StepBase:
 
     def optimizer(self):
         flags = ML.MP_UPDATE_PRECHECKED if self.prechecked else ML.MP_UPDATE_DEFAULT
-        if self.flat_update:
-            B.mp_unscale_check_update(self.P.flat_list, 1, self.cfg, self.st, flags)
-        else:
-            B.mp_unscale_check_update(self.P.tensor_list, self.P.n_tensors, self.cfg, self.st, flags)
-        if self._parts is not None:
-            B.mp_loss_scale_update_mean(self.st, self._parts, self.loss)
-            self._parts = None
-        else:
-            B.mp_loss_scale_update(self.st)
+        parts, self._parts = self._parts, None
+        tensors, n = (self.P.flat_list, 1) if self.flat_update else (self.P.tensor_list, self.P.n_tensors)
+        B.mp_unscale_check_update_end(tensors, n, self.cfg, self.st, self.counters, flags, parts, self.loss)
 
     def _mse(self, rows, cols, y, target, dy):
         """Loss and seed gradient; within step() the loss itself is finished by the launch that ends the iteration."""

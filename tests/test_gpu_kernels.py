@@ -1721,3 +1721,50 @@ def test_loss_finished_with_the_scale_update(kind, rows, cols, ld):
         for a, b in zip(*out):
             assert torch.equal(a, b)
         assert float(out[0][0]) > 0 and mp.scale_state_read(out[1][1]).scale == 2.0 ** 13
+
+
+@pytest.mark.parametrize("kind", ["adam", "sgd"])
+@pytest.mark.parametrize("sizes", [(5,), (1000, 40000), (31 * 1024 + 1,), (1024 * 1024,), (1024 * 1024 + 1,), (3000,) * 33])
+def test_iteration_ended_by_the_update(sizes, kind):
+    """mp_unscale_check_update_end against the calls it stands for: one workgroup, fewer and more than there are counters, the most
+    it counts and one more, more tensors than a launch takes; clean and overflowing iterations in turn, as calls and as a replayed
+    graph; the counters are clear afterwards."""
+    r = RNG(sum(sizes))
+    cfg = mp.opt_cfg(kind, 1e-3, 0.9, 0.999, 1e-8, 0.01)
+    part, part_n = torch.from_numpy(r.random(300).astype(np.float32)).cuda(), 300
+    parts = ML.MeanParts()
+    parts.part, parts.denom, parts.n = part.data_ptr(), 7.0, part_n
+    g0, w0 = [h16(r.standard_normal(n)) for n in sizes], [torch.from_numpy(r.standard_normal(n).astype(np.float32)).cuda() for n in sizes]
+    outs = []
+    for how in ("apart", "end", "graph"):
+        t = [dict(g16=g.clone(), w32=w.clone(), w16=w.half(), m=torch.zeros_like(w), v=torch.zeros_like(w)) for g, w in zip(g0, w0)]
+        tl, st, loss, counters = mp.tensor_list(t), mp.scale_state_alloc(), empty32(1), mp.update_counters_alloc()
+        mp.mp_scale_state_init(st, ML.MP_SCALE_BACKOFF, 2.0 ** 10, 2, 1.0, 2.0 ** 24)
+
+        def one(p):
+            if how == "apart":
+                mp.mp_unscale_check_update(tl, len(t), cfg, st)
+                mp.mp_loss_scale_update_mean(st, p, loss) if p is not None else mp.mp_loss_scale_update(st)
+            else:
+                mp.mp_unscale_check_update_end(tl, len(t), cfg, st, counters, ML.MP_UPDATE_DEFAULT, p, None if p is None else loss)
+        one(None)
+        run = lambda: one(parts)  # noqa: E731
+        if how == "graph":
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                one(parts)
+            run = graph.replay
+        seen = []
+        for k in range(5):
+            t[-1]["g16"][-1:].fill_(float("inf") if k == 2 else 0.5)
+            run()
+            torch.cuda.synchronize()
+            seen.append([loss.clone(), st.clone()] + [x[f].clone() for x in t for f in ("w32", "w16", "m", "v")])
+            assert int(counters.abs().max()) == 0
+        outs.append(seen)
+        s = mp.scale_state_read(st)
+        assert s.total_steps == 6 and s.skipped_steps == 1 and s.opt_step == 5 and s.found_inf == 0
+    for a, b, c in zip(*outs):
+        for x, y, z in zip(a, b, c):
+            assert torch.equal(x, y) and torch.equal(x, z)
