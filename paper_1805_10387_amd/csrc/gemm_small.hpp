@@ -246,7 +246,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
 
 // Both gradients of a linear layer in one launch: tiles of dX, then tiles of dW, which have the bias gradient with them.  They
 // share dY and depend on nothing else, and each alone leaves most of a small layer's time to launches.  (With the column sums of
-// dY as workgroups of their own, 32 columns each, their rounds of rows were the longest chain: see both_joint.)
+// dY as workgroups of their own, 32 columns each, their rounds of rows were the longest chain: 3000 x 512 x 96 14.4 us,
+// 12.0 with them in the tiles.)
 struct BothArgs {
     GemmArgs dx, dw;
 };
