@@ -408,11 +408,11 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
     return MP_OK;
 }
 
-// One launch for both gradients: each product for the small kernel by itself, and together no more than three workgroups
-// per compute unit.  us, separate calls / one launch, with the bias gradient: 64 x 256 over 1024 (328 workgroups) 10.0 / 3.7,
-// 704 x 504 over 512 (624) 14.3 / 8.4, 1500 x 300 over 300 (580) 18.1 / 13.6; without it the last, whose weight gradient is
-// a long chain, 12.9 / 13.7.  The line lies short of where the gain ends: 512 x 1024 over 512 (800) 14.9 / 10.3,
-// 704 x 704 over 704 (990) 17.1 / 11.2.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and
+// One launch for both gradients: each product for the small kernel by itself (so together at most four workgroups per compute
+// unit).  us, separate calls / one launch, with the bias gradient, M x N x K: 616 x 240 x 112 8.1 / 4.8, 824 x 440 x 592 (760
+// workgroups) 12.8 / 8.8, 1000 x 848 x 504 (944) 17.2 / 13.5, 1604 x 889 x 304 (792) 24.0 / 16.4, 1681 x 1690 x 255 (848) 30.2 / 27.8;
+// of 310 random sizes the geometric mean is 0.75, the worst 20.9 / 22.0 (3668 x 15 x 67, a long chain in few tiles).  Two encoder
+// layers 320 wide on 384 tokens 215 -> 183 us against the grouped launch.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and
 // the small tiles, of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained
 // then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
@@ -420,8 +420,7 @@ static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     if (g_tuning.tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;
     // (as matrix_path_ok, for both: stored rows of at least 8 elements, offsets inside a tile within the buffer size)
     if (dx->N < 8 || dx->K < 8 || dw->K < 8 || std::max(std::max(dx->ldy, dx->ldw), dw->ldx) >= LD_BUFFER_64) return false;
-    return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M) &&
-           small_tiles(dx->M, dx->K) + small_tiles(dw->N, dw->K) + (dw->N + 31) / 32 <= 3 * kCUs;
+    return small_wins(dx->M, dx->K, dx->N) && small_wins(dw->N, dw->K, dw->M);
 }
 
 extern "C" int mp_gemm_bwd_both_joint(const mp_gemm_desc* d_dx, const mp_gemm_desc* d_dw) {

@@ -248,6 +248,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
 // share dY and depend on nothing else, and each alone leaves most of a small layer's time to launches.  (With the column sums of
 // dY as workgroups of their own, 32 columns each, their rounds of rows were the longest chain: 3000 x 512 x 96 14.4 us,
 // 12.0 with them in the tiles.)
+// Either product's tiles go to the XCDs as those of a product alone do (small_tile_of; a run of ids that starts anywhere still has
+// every eighth on one XCD): M x N x K 3033 x 2525 x 78 31.4 -> 27.9 us, 1424 x 1584 x 232 16.5 -> 14.8, 2744 x 2352 x 8 11.6 -> 9.7,
+// small ones as before.  The tiles of dW come first where their chain is long: 3033 x 2525 x 78 27.9 -> 24.6, 1848 x 1272 x 248 19.2 ->
+// 16.9, 1604 x 889 x 304 19.8 -> 16.4, at worst 13.0 -> 13.3 (1544 x 944 x 264); below the line it loses where the tiles are many:
+// 1216 x 1144 x 384 14.3 -> 16.8, 544 x 472 x 920 9.6 -> 11.3.
+constexpr int SM_DW_FIRST = 1536;
 struct BothArgs {
     GemmArgs dx, dw;
 };
@@ -257,14 +263,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_both_kernel(BothArgs b) {
     extern __shared__ __align__(16) char smem[];
     bool      bad = false;
     const int ndx = b.dx.tiles_m * b.dx.tiles_n;
-    const int id = blockIdx.x;
-    if (id < ndx) {
+    const int id = b.dw.K > SM_DW_FIRST ? (int)blockIdx.x - b.dw.tiles_m * b.dw.tiles_n : (int)blockIdx.x;   // (dX: 0 ... ndx - 1)
+    if (id >= 0 && id < ndx) {
         const int2 t = small_tile_of(id, b.dx.tiles_m, b.dx.tiles_n);
         small_tile<NW, true, false, MODE, false, SM_DEPTH_BOTH>(b.dx, t.x, t.y, 0, (b.dx.K + BK - 1) / BK, nullptr, false, smem, bad);
         return;  // (dX has no overflow flag)
     }
-    const int t = id - ndx;
-    small_tile<NW, false, false, MODE, true, SM_DEPTH_BOTH>(b.dw, t / b.dw.tiles_n, t % b.dw.tiles_n, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
+    const int2 t = small_tile_of(id < 0 ? (int)blockIdx.x : id - ndx, b.dw.tiles_m, b.dw.tiles_n);
+    small_tile<NW, false, false, MODE, true, SM_DEPTH_BOTH>(b.dw, t.x, t.y, 0, (b.dw.K + BK - 1) / BK, nullptr, false, smem, bad);
     if (b.dw.found_inf && __any(bad)) {
         if ((threadIdx.x & 63) == 0) atomicOr(b.dw.found_inf, 1);
     }

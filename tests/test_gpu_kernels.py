@@ -635,6 +635,16 @@ def test_gemm_both_gradients_of_a_layer(joint, M, N, Kx, Kw, aligned):
     assert mp.scale_state_read(st).found_inf == 0
 
 
+@pytest.mark.parametrize("aligned", [False, True])
+@pytest.mark.parametrize("M,N,Kx,Kw", [
+    (1536, 24, 40, 72), (1537, 24, 40, 72), (1545, 41, 33, 29),     # the weight gradient's tiles last; first, 8 waves
+    (1601, 131, 300, 90), (4096, 41, 97, 33),                       # first, 4 waves
+    (700, 700, 700, 700), (333, 500, 1000, 900), (1001, 849, 500, 500),   # more than three workgroups per compute unit
+])
+def test_gemm_both_gradients_in_many_tiles(M, N, Kx, Kw, aligned):
+    test_gemm_both_gradients_of_a_layer(1, M, N, Kx, Kw, aligned)
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 64, 40), (130, 65, 41), (640, 131, 67)])
 def test_gemm_both_gradients_flag_what_the_separate_calls_flag(M, N, K):
     """A joint launch raises found_inf for the weight gradient alone and for the bias gradient alone, not for the input
