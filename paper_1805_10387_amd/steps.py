@@ -220,8 +220,12 @@ class TransformerStep(_StepBase):
         self.d_c = G(S, dk, S, ldx=S, ldw=3 * d, ldy=d, trans_w=1, batch_outer=NB, batch_inner=h,
                      sx=(h * S * S, S * S), sw=(S * 3 * d, dk), sy=(S * d, dk))
         # a layer small enough for it: both gradients of each linear layer in one launch (then there is no grouped launch
-        # and nothing for a second stream)
-        self.joint_bwd = grouped_dw and all(B.mp_gemm_bwd_both_joint(x, x) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2))
+        # and nothing for a second stream).  The grouped launch, where the widths allow it, takes two launches a layer less
+        # (it finishes the LayerNorm sums); above 384 tokens it is no slower on the device either (us a layer's iteration as a
+        # graph / call by call, grouped and joint: 1024 x 128 87 / 96 and 89 / 100, 400 x 256 90 / 95 and 91 / 98; 128 x 128
+        # 76.3 / 95.8 and 75.2 / 101).
+        self.joint_bwd = (grouped_dw and not (self.grouped_dw and T > 384) and
+                          all(B.mp_gemm_bwd_both_joint(x, x) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)))
         self.grouped_dw = self.grouped_dw and not self.joint_bwd
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)]
         need += [B.mp_gemm_bwd_dw_workspace_bytes(self.d_s, False), B.mp_gemm_bwd_dw_workspace_bytes(self.d_c, False),
