@@ -473,6 +473,7 @@ __global__ __launch_bounds__(RL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     lds_barrier();
     if (owner) activate();
+    lds_barrier();  // (`in` is written again in the first step, ahead of its first barrier; in later steps the barrier behind `red` is between)
 
     for (int t = T - 1; t >= 0; --t) {
         const int n = T - 1 - t;  // number of the slice
