@@ -485,6 +485,18 @@ int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d /* host */, const mp_hal
                             const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
                             int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream);
 
+/* The chain calls with the workgroups of each block of 8 batch rows on one XCD, chosen by ws, where at most 32 come to an XCD
+ * (H / 16 of them a block; wider layers run as above): slices of a step then go through that XCD's L2.  Same results.  An XCD has
+ * room for 64 workgroups, so that fitting the device together is not enough here: of what may run at the same time, count a
+ * launch of this kind, however small, as half of the device - no more than two, or one beside launches of the calls above
+ * that take no more than the other half. */
+int mp_lstm_layer_fwd_placed(const mp_lstm_layer_desc* d /* host */, const float* gx, const mp_half* w, const mp_half* bias,
+                             mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws, size_t ws_bytes,
+                             int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream);
+int mp_lstm_layer_bwd_placed(const mp_lstm_layer_desc* d /* host */, const mp_half* w, const mp_half* gates, const float* c,
+                             const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                             int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream);
+
 /* dst = RNE16(src), n elements (initial fp16 copies of masters and inputs). */
 int mp_cast_f32_to_f16(size_t n, const float* src, mp_half* dst, mp_stream stream);
 /* Fill n 32-bit words (a kernel, safe inside HIP graph capture). */

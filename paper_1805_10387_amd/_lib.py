@@ -113,7 +113,9 @@ SIGNATURES = {
     "mp_lstm_layer_desc_workspace_bytes": (_SZ, [C.POINTER(LstmLayerDesc)]),
     "mp_lstm_layer_fwd": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_lstm_layer_fwd_chain": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _I, _P, _SZ, _P]),
+    "mp_lstm_layer_fwd_placed": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _P, _P, _SZ, _I, _P, _SZ, _P]),
     "mp_lstm_layer_bwd_chain": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _SZ, _I, _P, _SZ, _P]),
+    "mp_lstm_layer_bwd_placed": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _SZ, _I, _P, _SZ, _P]),
     "mp_lstm_layer_bwd": (_I, [C.POINTER(LstmLayerDesc), _P, _P, _P, _P, _P, _P, _P, _SZ, _P]),
     "mp_cast_f32_to_f16": (_I, [_SZ, _P, _P, _P]),
     "mp_fill_u32": (_I, [_SZ, C.c_uint32, _P, _P]),

@@ -320,6 +320,16 @@ def mp_lstm_layer_bwd_chain(desc, w, gates, c, dh_above, dgates, status, ws, ws_
                                             _nbytes(ws), int(ws_is_empty), _p(next_ws), _nbytes(next_ws), _stream()))
 
 
+def mp_lstm_layer_fwd_placed(desc, gx, w, bias, gates, c, xh, h_up, status, ws, ws_is_empty=False, next_ws=None):
+    _check(L.load().mp_lstm_layer_fwd_placed(C.byref(desc), _p(gx), _p(w), _p(bias), _p(gates), _p(c), _p(xh), _p(h_up), _p(status),
+                                             _p(ws), _nbytes(ws), int(ws_is_empty), _p(next_ws), _nbytes(next_ws), _stream()))
+
+
+def mp_lstm_layer_bwd_placed(desc, w, gates, c, dh_above, dgates, status, ws, ws_is_empty=False, next_ws=None):
+    _check(L.load().mp_lstm_layer_bwd_placed(C.byref(desc), _p(w), _p(gates), _p(c), _p(dh_above), _p(dgates), _p(status), _p(ws),
+                                             _nbytes(ws), int(ws_is_empty), _p(next_ws), _nbytes(next_ws), _stream()))
+
+
 def mp_cast_f32_to_f16(n, src, dst):
     _check(L.load().mp_cast_f32_to_f16(n, _p(src), _p(dst), _stream()))
 

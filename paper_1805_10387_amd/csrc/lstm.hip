@@ -31,13 +31,14 @@
 //   columns of an operand hold 8 rows of two successive k-steps; each is multiplied with both k-steps' weights into
 //   separate sums, and the half of each result that pairs the right ones is kept.
 //   Distance: a slice takes 0.57 us between two XCDs and 0.45 inside one when it is stored to the whole device, 0.28 inside
-//   one when the store stays in the L2 that reader and writer share (both ways in turn between two workgroups).  So a group of
-//   up to 32 workgroups is placed on one XCD, and stores to its L2 once every member has told that it runs there (RlXcds);
-//   wider layers have groups that no XCD holds with one workgroup per compute unit, and keep the order of the ids.
+//   one when the store stays in the L2 that reader and writer share (both ways in turn between two workgroups).  So the
+//   placed calls put a group of up to 32 workgroups on one XCD, which stores to its L2 once every member has told that it runs
+//   there (RlXcds); wider layers have groups that no XCD holds with one workgroup per compute unit, and keep the order of the ids,
+//   as all others of the calls do: three one-group launches that fit the device may not fit one XCD.
 //   What else an owner of cells does between two slices counts in full, so it does nothing else: inputs and results go through
 //   waves 2 and 3 (RlCellIn), the backward activations are made while the slices are on their way, and the status word
 //   is looked at after 16 looks in vain, not after the first.
-// us per time step, forward / backward, 50 steps, one launch: units x batch 1024 x 32 2.04 / 2.51 before these four and 1.76 /
+// us per time step, forward / backward, 50 steps, one launch of the placed calls: units x batch 1024 x 32 2.04 / 2.51 before these four and 1.76 /
 // 2.29 with them, 768 x 40 1.86 / 2.31 -> 1.66 / 2.05, 512 x 64 1.68 / 2.06 -> 1.20 / 1.44, 256 x 32 1.53 / 1.79 -> 1.05 / 1.02, 128 x 8
 // 1.50 / 1.65 -> 0.96 / 0.92 (one flag per workgroup behind a device-scope release and acquire, 1024 x 32: 6.7 / 10.0).
 // All workgroups must be co-resident: the register use allows two per compute unit and the host refuses larger grids.
@@ -597,8 +598,9 @@ extern "C" size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d
 
 static uintptr_t align_up16(const void* p) { return (reinterpret_cast<uintptr_t>(p) + 15) & ~(uintptr_t)15; }
 
+// place: groups on one XCD each where one holds them (see the *_placed calls in mp.h for what that asks of the caller)
 static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, int ws_is_empty,
-                   void* next_ws, size_t next_ws_bytes, mp_stream stream, const char* who, RlSync* out) {
+                   void* next_ws, size_t next_ws_bytes, bool place, mp_stream stream, const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
     const size_t need = d->step_rows > 0 ? rl_rings(d->B, d->H) : mp_lstm_layer_workspace_bytes();
     if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 3u)) {
@@ -615,8 +617,8 @@ static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, 
     }
     char* const  ring = reinterpret_cast<char*>(align_up16(ws));
     const int    units = d->H / RL_UNITS, groups = rl_groups(d->B);
-    const size_t used = (size_t)groups * RL_RING * slot, xcds = rl_xcds_bytes(units, groups);
-    out->per_xcd   = rl_per_xcd(units, groups);
+    const size_t used = (size_t)groups * RL_RING * slot, xcds = place ? rl_xcds_bytes(units, groups) : 0;
+    out->per_xcd   = place ? rl_per_xcd(units, groups) : 0;
     out->first_xcd = (int)(((unsigned)(reinterpret_cast<uintptr_t>(ring) >> 8) * 0x9E3779B1u) >> 29);  // (several models of one group: not all on XCD 0)
     // (a workspace that holds the rings alone will do: the group's stores then go to the whole device)
     out->xcds = xcds > 0 && ws_bytes - (size_t)(ring - static_cast<char*>(ws)) >= used + xcds ? ring + used : nullptr;
@@ -631,16 +633,9 @@ static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, 
     return MP_OK;
 }
 
-extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
-                                 mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
-                                 size_t ws_bytes, mp_stream stream) {
-    return mp_lstm_layer_fwd_chain(d, gx, w, bias, gates, c, xh, h_up, status, ws, ws_bytes, 0, nullptr, 0, stream);
-}
-
-extern "C" int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
-                                       mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
-                                       size_t ws_bytes, int ws_is_empty, void* next_ws, size_t next_ws_bytes,
-                                       mp_stream stream) {
+static int rl_fwd(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias, mp_half* gates, float* c,
+                  mp_half* xh, mp_half* h_up, int32_t* status, void* ws, size_t ws_bytes, int ws_is_empty, void* next_ws,
+                  size_t next_ws_bytes, bool place, mp_stream stream) {
     int nwg = 0;
     int rc  = rl_check(d, "mp_lstm_layer_fwd", &nwg);
     if (rc) return rc;
@@ -649,7 +644,7 @@ extern "C" int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d, const float*
     MP_REQUIRE(aligned16(w) && aligned16(xh) && aligned16(gx) && aligned16(gates) && aligned16(c) && (h_up == nullptr || aligned16(h_up)),
                "mp_lstm_layer_fwd: pointers must be 16-byte aligned");
     LstmFwdArgs a{};
-    rc = rl_sync(d, rl_fwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, stream, "mp_lstm_layer_fwd", &a.sync);
+    rc = rl_sync(d, rl_fwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, place, stream, "mp_lstm_layer_fwd", &a.sync);
     if (rc) return rc;
     a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.gx = gx; a.w = w; a.ldw = d->ldw; a.bias = bias; a.gates = gates; a.c = c; a.xh = xh; a.ldxh = d->ldxh;
@@ -661,15 +656,9 @@ extern "C" int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d, const float*
     return MP_OK;
 }
 
-extern "C" int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
-                                 const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
-                                 mp_stream stream) {
-    return mp_lstm_layer_bwd_chain(d, w, gates, c, dh_above, dgates, status, ws, ws_bytes, 0, nullptr, 0, stream);
-}
-
-extern "C" int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
-                                       const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
-                                       int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream) {
+static int rl_bwd(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c, const mp_half* dh_above,
+                  mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes, int ws_is_empty, void* next_ws,
+                  size_t next_ws_bytes, bool place, mp_stream stream) {
     int nwg = 0;
     int rc  = rl_check(d, "mp_lstm_layer_bwd", &nwg);
     if (rc) return rc;
@@ -678,7 +667,7 @@ extern "C" int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d, const mp_hal
     MP_REQUIRE(aligned16(w) && aligned16(gates) && aligned16(c) && aligned16(dh_above) && aligned16(dgates),
                "mp_lstm_layer_bwd: pointers must be 16-byte aligned");
     LstmBwdArgs a{};
-    rc = rl_sync(d, rl_bwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, stream, "mp_lstm_layer_bwd", &a.sync);
+    rc = rl_sync(d, rl_bwd_slot(d->H), status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, place, stream, "mp_lstm_layer_bwd", &a.sync);
     if (rc) return rc;
     a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H; a.step_rows = d->step_rows > 0 ? d->step_rows : d->B;
     a.w = w; a.ldw = d->ldw; a.gates = gates; a.c = c; a.dh_above = dh_above; a.ld_above = d->ld_up; a.dgates = dgates;
@@ -687,4 +676,42 @@ extern "C" int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d, const mp_hal
     });
     MP_LAUNCH_CHECK("mp_lstm_layer_bwd");
     return MP_OK;
+}
+
+extern "C" int mp_lstm_layer_fwd(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
+                                 mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
+                                 size_t ws_bytes, mp_stream stream) {
+    return rl_fwd(d, gx, w, bias, gates, c, xh, h_up, status, ws, ws_bytes, 0, nullptr, 0, false, stream);
+}
+
+extern "C" int mp_lstm_layer_fwd_chain(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
+                                       mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
+                                       size_t ws_bytes, int ws_is_empty, void* next_ws, size_t next_ws_bytes,
+                                       mp_stream stream) {
+    return rl_fwd(d, gx, w, bias, gates, c, xh, h_up, status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, false, stream);
+}
+
+extern "C" int mp_lstm_layer_fwd_placed(const mp_lstm_layer_desc* d, const float* gx, const mp_half* w, const mp_half* bias,
+                                        mp_half* gates, float* c, mp_half* xh, mp_half* h_up, int32_t* status, void* ws,
+                                        size_t ws_bytes, int ws_is_empty, void* next_ws, size_t next_ws_bytes,
+                                        mp_stream stream) {
+    return rl_fwd(d, gx, w, bias, gates, c, xh, h_up, status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, true, stream);
+}
+
+extern "C" int mp_lstm_layer_bwd(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
+                                 const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                                 mp_stream stream) {
+    return rl_bwd(d, w, gates, c, dh_above, dgates, status, ws, ws_bytes, 0, nullptr, 0, false, stream);
+}
+
+extern "C" int mp_lstm_layer_bwd_chain(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
+                                       const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                                       int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream) {
+    return rl_bwd(d, w, gates, c, dh_above, dgates, status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, false, stream);
+}
+
+extern "C" int mp_lstm_layer_bwd_placed(const mp_lstm_layer_desc* d, const mp_half* w, const mp_half* gates, const float* c,
+                                        const mp_half* dh_above, mp_half* dgates, int32_t* status, void* ws, size_t ws_bytes,
+                                        int ws_is_empty, void* next_ws, size_t next_ws_bytes, mp_stream stream) {
+    return rl_bwd(d, w, gates, c, dh_above, dgates, status, ws, ws_bytes, ws_is_empty, next_ws, next_ws_bytes, true, stream);
 }

@@ -449,8 +449,9 @@ class LSTMStep(_StepBase):
     step by step: per time step one gate product with W[4H, I+H] (mp_gemm_fwd_ws) and one cell kernel; the cell
       kernel writes h_t both into xh[l][t+1] (recurrence) and into the next layer's xh[l+1][t] (or the output).
 
-    A persistent launch may take half of the GPU's workgroup slots until it is done, so at most two models whose iterations
-    may overlap (other streams, other processes on the GPU) run this plan safely; more of them need persistent=False.  Where
+    A persistent launch may take half of the GPU's workgroup slots, or half of one XCD's, until it is done, so at most two models
+    whose iterations may overlap (other streams, other processes on the GPU) run this plan safely; more of them, small ones too,
+    need persistent=False.  Where
     that is not kept, a wait ends after 2 s.  What had not arrived by then reads as NaN: the iteration's gradients are
     flagged and its update is skipped, as those of later iterations are until rl_status, which recurrent_kernels_ok()
     looks at, is cleared."""
@@ -529,12 +530,12 @@ class LSTMStep(_StepBase):
         for l in range(NL):
             B.mp_gemm_fwd(self.d_in_all[l], self.xh[l], w[f"l{l}.w"], None, None, None, self.gx)
             for d, gx, gates, c, xh, up in self.rl_fwd[l]:
-                B.mp_lstm_layer_fwd_chain(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, ws, ready, ws_next)
+                B.mp_lstm_layer_fwd_placed(d, gx, w[f"l{l}.w"], w[f"l{l}.b"], gates, c, xh, up, self.rl_status, ws, ready, ws_next)
                 ws, ws_next, ready = ws_next, ws, True
         self._mse(T * Bt, H, self.y, self.target, self.dy)
         for l in range(NL - 1, -1, -1):
             for d, gates, c, above, dgates in self.rl_bwd[l]:
-                B.mp_lstm_layer_bwd_chain(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, ws, ready, ws_next)
+                B.mp_lstm_layer_bwd_placed(d, w[f"l{l}.w"], gates, c, above, dgates, self.rl_status, ws, ready, ws_next)
                 ws, ws_next = ws_next, ws
             B.mp_gemm_bwd_both(self.d_dx_all[l], self.dgates, w[f"l{l}.w"], self.dx[l % 2], self.d_gate_all[l], self.xh[l],
                                g[f"l{l}.w"], g[f"l{l}.b"], self.st_grad, self.ws)

@@ -35,7 +35,8 @@ struct dim3 {
 };
 
 namespace host {
-extern int order[4];   // waves by precedence
+extern int              order[4];    // waves by precedence
+extern std::atomic<int> worked[8];   // workgroups by XCD (ids go round them) that did not return at once
 constexpr int LANES = 64, THREADS = 256, STACK = 256 << 10;
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float    f4 __attribute__((ext_vector_type(4)));
@@ -57,6 +58,7 @@ struct Group {
     ucontext_t            scheduler;
     std::function<void()> body;
     int                   now = 0, waiting = 0, in_wave[4] = {0, 0, 0, 0};
+    bool                  barriers = false;
 
     void yield() { swapcontext(&lanes[now].ctx, &scheduler); }
     static void enter();
@@ -87,7 +89,8 @@ struct Group {
     }
     void barrier() {
         if (++waiting == THREADS) {
-            waiting = 0;
+            waiting  = 0;
+            barriers = true;
             for (Lane& l : lanes)
                 if (l.state == BARRIER) l.state = READY;
             return;
@@ -128,6 +131,7 @@ void launch(dim3 grid, const F& body) {
             g->body  = body;
             group    = g.get();
             g->run();
+            worked[b & 7] += g->barriers;
         });
     for (std::thread& t : wgs) t.join();
 }
@@ -256,7 +260,7 @@ using std::min;
 #define __builtin_amdgcn_update_dpp(old, v, ctrl, rows, banks, bound) host::row_shift(v, ctrl)
 #define __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, x, y, z) host::mfma(a, b, c)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) host::read_tr((const void*)(p))
-#define __builtin_amdgcn_s_getreg(r) (host::group->block.x & 7u)   // (the XCD: ids go round them)
+#define __builtin_amdgcn_s_getreg(r) (host::group->block.x & 7u)   // (the XCD)
 #define __builtin_amdgcn_s_waitcnt(n) ((void)0)
 #define __builtin_amdgcn_sched_barrier(n) ((void)0)
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))

@@ -1379,6 +1379,37 @@ def test_lstm_persistent_layer_places(T, Bn, H):
     assert_close16(db, db_ref, 1e-3, what="db")
 
 
+@pytest.mark.parametrize("T,Bn,H", [(9, 64, 512), (9, 65, 512), (2, 8, 64), (1, 9, 64), (6, 24, 192), (5, 64, 384), (5, 72, 384), (7, 128, 256), (4, 32, 1024)])
+def test_lstm_persistent_layer_placed_calls(T, Bn, H):
+    """The calls that put each group of workgroups on one XCD, several groups to an XCD, and one group or width more than that
+    allows, with the words in which workgroups tell where they run and without: the bits of the plain calls."""
+    r = RNG(T + Bn + H)
+    I, ld = 8, 8 + H
+    x_seq, wd, bd = h16(r.standard_normal((T, Bn, I))), h16(r.uniform(-0.1, 0.1, (4 * H, ld))), h16(r.standard_normal(4 * H) * 0.1)
+    dh, gx = h16(r.standard_normal((T, Bn, H))), f32(r.standard_normal((T * Bn, 4 * H)))
+    d = mp.lstm_layer_desc(T, Bn, I, H, ld, ld, H, step_rows=Bn)
+    full = mp.mp_lstm_layer_desc_workspace_bytes(d) // 4
+    rings = (Bn + 7) // 8 * 4 * 4 * 1024 * (H // 64) // 4 + 4
+    outs = []
+    for placed, words in ((False, full), (True, full), (True, rings)):
+        xh = torch.zeros(T, Bn, ld, dtype=torch.float16, device="cuda")
+        xh[:, :, :I].copy_(x_seq)
+        gates, up, dgates = empty16(T, Bn, 4 * H), empty16(T, Bn, H), empty16(T, Bn, 4 * H)
+        c, status = torch.zeros(T + 1, Bn, H, dtype=torch.float32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        a, b = (torch.zeros(words, dtype=torch.int32, device="cuda") for _ in range(2))
+        if placed:
+            mp.mp_lstm_layer_fwd_placed(d, gx, wd, bd, gates, c, xh, up, status, a, False, b)
+            mp.mp_lstm_layer_bwd_placed(d, wd, gates, c, dh, dgates, status, b, True)
+        else:
+            mp.mp_lstm_layer_fwd(d, gx, wd, bd, gates, c, xh, up, status, a)
+            mp.mp_lstm_layer_bwd(d, wd, gates, c, dh, dgates, status, b)
+        assert int(status.item()) == 0
+        outs.append((gates, c, xh, up, dgates))
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert torch.equal(a, b)
+
+
 def test_lstm_persistent_layer_workspace_at_any_word():
     """A workspace of the stated size at a 4-byte boundary that is no 16-byte boundary is enough."""
     T, Bn, I, H = 6, 32, 8, 1024
