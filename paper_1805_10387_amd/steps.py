@@ -109,7 +109,9 @@ class _StepBase:
             B.mp_mse_scaled(rows, cols, y, target, cols, self.st, self.loss, dy, self.loss_part)
 
     def step(self, inject: Optional[Callable] = None):
-        self._later = True
+        """One iteration.  inject(gradients) runs between backward and update and sees this iteration's loss; without it the loss
+        is there when the update is (`optimizer`, which finishes it)."""
+        self._later = inject is None
         try:
             self.forward_backward()
         finally:

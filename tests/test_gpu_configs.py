@@ -826,3 +826,19 @@ def test_a_step_is_its_two_halves(make):
         lb = b.loss.clone()
         b.optimizer()
         assert torch.equal(a.loss, lb) and torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.st, b.st)
+
+
+@pytest.mark.parametrize("make", [lambda: St.MLPStep(I.C1), lambda: St.TransformerStep(I.C2_SMALL), lambda: St.XentStep(I.C4_SMALL), lambda: St.LSTMStep(I.C5_SMALL)])
+def test_what_runs_between_backward_and_update_sees_this_iterations_loss(make):
+    """step(inject): `loss` inside is what forward_backward() leaves for these weights and this batch, and the iteration is the
+    one without inject."""
+    a, b = make(), make()
+    for k in range(3):
+        for s in (a, b):
+            s.set_batch(s.wl.batch() if k < 2 else {n: v[::-1].copy() for n, v in s.wl.batch().items()})
+        b.forward_backward()
+        want, seen = float(b.loss), []
+        a.step(inject=lambda g: seen.append(float(a.loss)))
+        b.step()
+        assert seen == [want] and float(a.loss) == want == float(b.loss)
+        assert torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.st, b.st)
