@@ -28,13 +28,10 @@ def _p(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-
-
 def _stream():
     # torch's current stream of the current device as a raw hipStream_t, without a Stream object around it (which costs
     # as much as a launch: 2.8 us against 0.3 us a call)
-    return _raw_stream(_device())
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def mp_version() -> int:
@@ -380,5 +377,3 @@ def update_counters_alloc(device="cuda") -> torch.Tensor:
 def mp_unscale_check_update_end(tensors, ntensors: int, cfg: OptCfg, st, counters, flags: int = L.MP_UPDATE_DEFAULT, parts=None, loss=None):
     _check(L.load().mp_unscale_check_update_end(tensors, ntensors, C.byref(cfg), _p(st), flags, None if parts is None else C.byref(parts),
                                                 _p(loss), _p(counters), _stream()))
-
-

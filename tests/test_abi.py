@@ -36,6 +36,17 @@ def test_binding_has_the_same_names():
         assert hasattr(mp, n), f"binding lacks {n}"
 
 
+def test_the_package_imports_on_a_torch_without_gpu_entry_points():
+    """What needs no stream (versions, sizes, descriptions) works on such a torch; only a call that launches something asks for one."""
+    import subprocess
+    code = ("import torch\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
+            "import paper_1805_10387_amd as mp\n"
+            "assert mp.mp_version() >= 1 and mp.mp_loss_workspace_bytes(8, 8) > 0\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
 def test_struct_layouts_match_the_header():
     from paper_1805_10387_amd import _lib
     assert C.sizeof(_lib.ScaleState) == 12 * 4 + _lib.MP_HISTORY * 8
