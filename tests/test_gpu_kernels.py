@@ -1730,6 +1730,35 @@ def test_bias_gradient_from_the_weight_gradient(T, N, K, tile, splits):
         mp.mp_gemm_tuning_override(-1, 1)
 
 
+@pytest.mark.parametrize("tile,splits", [(1, 1), (3, 1), (4, 1), (5, 1), (1, 3), (3, 2), (4, 3), (5, 4), (9, 1), (10, 1), (9, 2), (0, 1), (-1, 1)])
+@pytest.mark.parametrize("T,N,K", [(640, 264, 392), (193, 520, 456), (700, 29, 36)])
+def test_bias_gradient_of_subnormal_gradients(T, N, K, tile, splits):
+    """Gradients below the least normal half (multiples of 2^-24, what loss scaling is about), and beside them one row of 2^-3: every
+    partial sum is a multiple of 2^-24 below 2^-2, exact in fp32 in any order, so the bias gradient is the sum's one rounding.  Every
+    tile shape that carries the sums, one that leaves them to launches of their own (0), and the joint launch (-1)."""
+    r = RNG(T + N + K)
+    k = r.integers(-1023, 1024, (T, N))
+    k[1, :] = 1                            # a lone least subnormal is not lost beside the large row either
+    big = k.copy()
+    big[0, ::2] = 1 << 21
+    d, x, w = mp.gemm_desc(T, N, K), h16(r.standard_normal((T, K))), h16(r.standard_normal((N, K)))
+    ws = ws_bytes(8 << 20)
+    mp.mp_gemm_tuning_override(tile, splits)
+    try:
+        for units in (k, big, np.where(np.arange(T)[:, None] == 1, k, 0)):
+            dy, dw, db = h16(units * 2.0 ** -24), empty16(N, K), empty16(N)
+            if tile < 0:
+                assert mp.mp_gemm_bwd_both_joint(d, d)
+                mp.mp_gemm_bwd_both(d, dy, w, empty16(T, K), d, x, dw, db, None, ws)
+            else:
+                mp.mp_gemm_bwd_dw(d, dy, x, dw, db, None, ws)
+            assert np.abs(units).sum(0).max() < 1 << 22
+            want = h16(units.sum(0).astype(np.float64) * 2.0 ** -24)
+            assert torch.equal(db, want) and torch.count_nonzero(db) > 0
+    finally:
+        mp.mp_gemm_tuning_override(-1, 1)
+
+
 @pytest.mark.parametrize("kind,rows,cols,ld", [("mse", 3, 8, 8), ("mse", 300, 29, 31), ("mse", 4096, 512, 512), ("xent", 5, 40, 40),
                                                ("xent", 257, 1001, 1008), ("xent", 600, 17000, 17000), ("xent", 9000, 264, 264)])
 def test_loss_finished_with_the_scale_update(kind, rows, cols, ld):
