@@ -223,10 +223,12 @@ class TransformerStep(_StepBase):
                      sx=(h * S * S, S * S), sw=(S * 3 * d, dk), sy=(S * d, dk))
         # a layer small enough for it: both gradients of each linear layer in one launch (then there is no grouped launch
         # and nothing for a second stream).  The grouped launch, where the widths allow it, takes two launches a layer less
-        # (it finishes the LayerNorm sums); above 384 tokens it is no slower on the device either (us a layer's iteration as a
-        # graph / call by call, grouped and joint: 1024 x 128 87 / 96 and 89 / 100, 400 x 256 90 / 95 and 91 / 98; 128 x 128
-        # 76.3 / 95.8 and 75.2 / 101).
-        self.joint_bwd = (grouped_dw and not (self.grouped_dw and T > 384) and
+        # (it finishes the LayerNorm sums), which call by call is worth 10 us a layer of 128 and 5 of 256 units, whatever the
+        # tokens.  On the device they cross between 256 and 320 tokens, and the line is halfway: us of two layers' iteration as a
+        # graph, grouped / joint, 128 wide on 128, 256, 320, 384, 512 and 1024 tokens 135.8 / 134.1, 137.9 / 134.9, 140.2 / 140.4,
+        # 140.8 / 141.8, 144.1 / 146.8, 166.2 / 170.8; 256 wide on 128, 256, 320, 384 and 512 156.9 / 154.7, 164.4 / 163.0,
+        # 164.9 / 168.9, 166.8 / 169.4, 168.6 / 171.3.
+        self.joint_bwd = (grouped_dw and not (self.grouped_dw and T > 288) and
                           all(B.mp_gemm_bwd_both_joint(x, x) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)))
         self.grouped_dw = self.grouped_dw and not self.joint_bwd
         need = [B.mp_gemm_bwd_dw_workspace_bytes(x, True) for x in (self.d_qkv, self.d_o, self.d_f1, self.d_f2)]

@@ -461,6 +461,7 @@ def test_config5_reduced_prechecked_configuration_matches_default():
 @pytest.mark.parametrize("kind,d_model,n_heads,d_ff,seq_len,n_seq", [
     ("joint", 256, 4, 512, 48, 6),          # one launch for both gradients of a layer: nothing is left for a second stream
     ("grouped", 256, 4, 512, 48, 32),       # the grouped launch of a layer on the second stream
+    ("grouped", 256, 4, 512, 40, 8),        # ... just beyond the tokens up to which it is one launch per layer
     ("separate", 192, 3, 768, 61, 66),      # every weight gradient by itself on the second stream
 ])
 def test_second_stream_for_weight_gradients_gives_the_same_bits(kind, d_model, n_heads, d_ff, seq_len, n_seq):
