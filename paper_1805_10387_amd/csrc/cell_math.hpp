@@ -18,8 +18,8 @@ __device__ __forceinline__ float sigmoidf_(float x) {
     const float s = __builtin_fmaf(r, __builtin_fmaf(-d, r, 1.0f), r);
     return d == INFINITY ? 0.0f : s;  // (a NaN stays one)
 }
-// tanh(x): 1 - 2 / (exp(2|x|) + 1), and near zero, where that cancels, x + x^3 P(x^2) with P fitted to the smallest largest
-// relative error (7e-10)
+// tanh(x): 1 - 2 / (exp(2|x|) + 1), and near zero, where that cancels, x + x^3 P(x^2) with P fitted for a small largest relative
+// error (5e-9, at 0.86)
 __device__ __forceinline__ float tanhf_(float x) {
     const float a = __builtin_fabsf(x), u = a * a;
     float       p = -0.0004824179923f;

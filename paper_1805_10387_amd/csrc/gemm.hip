@@ -412,9 +412,9 @@ extern "C" int mp_gemm_bwd_dw(const mp_gemm_desc* d, const mp_half* dY, const mp
 // unit).  us, separate calls / one launch, with the bias gradient, M x N x K: 616 x 240 x 112 8.1 / 4.8, 824 x 440 x 592 (760
 // workgroups) 12.8 / 8.8, 1000 x 848 x 504 (944) 17.2 / 13.5, 1604 x 889 x 304 (792) 24.0 / 16.4, 1681 x 1690 x 255 (848) 30.2 / 27.8;
 // of 310 random sizes the geometric mean is 0.75, the worst 20.9 / 22.0 (3668 x 15 x 67, a long chain in few tiles).  Two encoder
-// layers 320 wide on 384 tokens 215 -> 183 us against the grouped launch.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and
-// the small tiles, of a ragged 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained
-// then.)
+// layers 320 wide (a width that the grouped launch does not take) on 384 tokens: 218 us an iteration with a product each and
+// 187 so.  (An iteration of a 64 x 256 -> 1024 -> 256 network 84 -> 57 us with this launch and the small tiles, of a ragged
+// 192-wide encoder layer 191 -> 144 us, both with the host's part of the time that remained then.)
 static bool both_joint(const mp_gemm_desc* dx, const mp_gemm_desc* dw) {
     const auto plain = [](const mp_gemm_desc* d) { return d->batch_outer == 1 && d->batch_inner == 1 && d->trans_w == 0 && d->M > 0 && d->N > 0 && d->K > 0; };
     if (g_tuning.tile >= 0 || !plain(dx) || !plain(dw) || dx->M != dw->M || dx->N != dw->N || dx->ldy != dw->ldy) return false;

@@ -16,9 +16,11 @@ namespace mp {
 
 constexpr int E        = 32;            // tile edge
 // k-tiles a wave has on their way (32 registers each).  The joint launch of both gradients has two or three workgroups to a
-// compute unit, which its registers have to leave room for; a product alone has one and short chains (us, depth 4 / 3 / 2:
+// compute unit, which its registers have to leave room for; a product alone has one or two.  us, depth 4 / 3 / 2:
 // both gradients of 2000 x 256 x 256 11.2 / 11.2 / 9.3, of 1200 x 512 x 320 10.0 / 10.0 / 8.3, of 1500 x 1024 x 161 13.8 / 13.4 / 12.9;
-// forward 200 x 576 over 192 3.64 / 3.61 / 3.74; input gradient 520 x 256 over 3000 9.0 / 8.6 / 8.0, 64 x 1024 over 256 3.67 / 3.64 / 3.74).
+// alone, where the chain is short, forward 200 x 576 over 192 3.64 / 3.61 / 3.74, input gradient 64 x 1024 over 256 3.67 / 3.64 /
+// 3.74, and where it is long, input gradient 520 x 256 over 3000 9.0 / 8.6 / 8.0: a product alone has the depth of the short
+// ones whatever its contraction.
 constexpr int SM_DEPTH = 3, SM_DEPTH_BOTH = 2;
 constexpr int SM_WAVE  = 2 * E * 128;   // LDS bytes of one wave: a k-tile of both operands, later its partial sums
 constexpr int sm_lds(int waves) { return waves * SM_WAVE; }
