@@ -109,9 +109,9 @@ class _StepBase:
             B.mp_mse_scaled(rows, cols, y, target, cols, self.st, self.loss, dy, self.loss_part)
 
     def step(self, inject: Optional[Callable] = None):
-        """One iteration.  inject(gradients) runs between backward and update and sees this iteration's loss; without it the loss
-        is there when the update is (`optimizer`, which finishes it)."""
-        self._later = inject is None
+        """One iteration.  inject(gradients) runs between backward and update and sees this iteration's loss, and so does an
+        `optimizer` of a derived class; otherwise the loss is there when the update is, which finishes it."""
+        self._later = inject is None and getattr(self.optimizer, "__func__", None) is _StepBase.optimizer
         try:
             self.forward_backward()
         finally:

@@ -829,6 +829,29 @@ def test_a_step_is_its_two_halves(make):
         assert torch.equal(a.loss, lb) and torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.st, b.st)
 
 
+@pytest.mark.parametrize("cls,wl", [(St.MLPStep, I.C1), (St.TransformerStep, I.C2_SMALL), (St.XentStep, I.C4_SMALL), (St.LSTMStep, I.C5_SMALL)])
+@pytest.mark.parametrize("how", ["derived", "assigned"])
+def test_an_update_of_the_callers_own_finds_the_loss_finished(cls, wl, how):
+    """A derived class's optimizer(), or one put in its place, that makes the two calls itself: same loss and iteration."""
+    def own(self):
+        seen.append(float(self.loss))
+        mp.mp_unscale_check_update(self.P.tensor_list, self.P.n_tensors, self.cfg, self.st)
+        mp.mp_loss_scale_update(self.st)
+    a, b = (type("Own", (cls,), {"optimizer": own}) if how == "derived" else cls)(wl), cls(wl)
+    if how == "assigned":
+        a.optimizer = lambda: own(a)
+    seen, want = [], []
+    for s in (a, b):
+        s.set_batch(wl.batch())
+    for _ in range(3):
+        a.step()
+        b.step()
+        want.append(float(b.loss))
+        assert float(a.loss) == want[-1]
+        assert torch.equal(a.P.w32_arena, b.P.w32_arena) and torch.equal(a.st, b.st)
+    assert seen == want
+
+
 @pytest.mark.parametrize("make", [lambda: St.MLPStep(I.C1), lambda: St.TransformerStep(I.C2_SMALL), lambda: St.XentStep(I.C4_SMALL), lambda: St.LSTMStep(I.C5_SMALL)])
 def test_what_runs_between_backward_and_update_sees_this_iterations_loss(make):
     """step(inject): `loss` inside is what forward_backward() leaves for these weights and this batch, and the iteration is the
