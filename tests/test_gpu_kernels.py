@@ -1362,8 +1362,8 @@ def test_lstm_persistent_layer_places(T, Bn, H):
         mp.mp_gemm_fwd(mp.gemm_desc(T * Bn, 4 * H, I, ldx=ld, ldw=ld), xh, wd, None, None, None, gx)
         gates, c, dgates = empty16(T, Bn, 4 * H), torch.zeros(T + 1, Bn, H, dtype=torch.float32, device="cuda"), empty16(T, Bn, 4 * H)
         status, ws = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(words, dtype=torch.int32, device="cuda")
-        mp.mp_lstm_layer_fwd(d, gx, wd, bd, gates, c, xh, up, status, ws)
-        mp.mp_lstm_layer_bwd(d, wd, gates, c, dh, dgates, status, ws)
+        mp.mp_lstm_layer_fwd_placed(d, gx, wd, bd, gates, c, xh, up, status, ws)
+        mp.mp_lstm_layer_bwd_placed(d, wd, gates, c, dh, dgates, status, ws)
         assert int(status.item()) == 0
         outs.append((gates, c, xh, up, dgates))
     for a, b_ in zip(*outs):
