@@ -33,8 +33,10 @@
 //   Distance: a slice takes 0.57 us between two XCDs and 0.45 inside one when it is stored to the whole device, 0.28 inside
 //   one when the store stays in the L2 that reader and writer share (both ways in turn between two workgroups).  So the
 //   placed calls put a group of up to 32 workgroups on one XCD, which stores to its L2 once every member has told that it runs
-//   there (RlXcds); wider layers have groups that no XCD holds with one workgroup per compute unit, and keep the order of the ids,
-//   as all others of the calls do: three one-group launches that fit the device may not fit one XCD.
+//   there (RlXcds); wider layers have groups that no XCD holds with one workgroup per compute unit, and keep the order of the ids.
+//   So do the other calls unless the groups come out even over the XCDs: three one-group launches that fit the device may not fit
+//   one XCD.  (us per time step, forward / backward, spread and placed: 512 x 8 1.58 / 1.71 and 1.20 / 1.45, 256 x 32 1.49 / 1.53
+//   and 1.06 / 1.06, 128 x 8 1.45 / 1.41 and 0.98 / 0.94.)
 //   What else an owner of cells does between two slices counts in full, so it does nothing else: inputs and results go through
 //   waves 2 and 3 (RlCellIn), the backward activations are made while the slices are on their way, and the status word
 //   is looked at after 16 looks in vain, not after the first.
@@ -598,7 +600,8 @@ extern "C" size_t mp_lstm_layer_desc_workspace_bytes(const mp_lstm_layer_desc* d
 
 static uintptr_t align_up16(const void* p) { return (reinterpret_cast<uintptr_t>(p) + 15) & ~(uintptr_t)15; }
 
-// place: groups on one XCD each where one holds them (see the *_placed calls in mp.h for what that asks of the caller)
+// place: groups on one XCD each where one holds them (see the *_placed calls in mp.h for what that asks of the caller).  Where the
+// groups come out even over the 8 XCDs that asks for nothing: each has as many workgroups as if the ids went round them.
 static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, void* ws, size_t ws_bytes, int ws_is_empty,
                    void* next_ws, size_t next_ws_bytes, bool place, mp_stream stream, const char* who, RlSync* out) {
     MP_REQUIRE(status != nullptr, "%s: status is NULL", who);
@@ -617,6 +620,7 @@ static int rl_sync(const mp_lstm_layer_desc* d, unsigned slot, int32_t* status, 
     }
     char* const  ring = reinterpret_cast<char*>(align_up16(ws));
     const int    units = d->H / RL_UNITS, groups = rl_groups(d->B);
+    if (groups % 8 == 0) place = true;
     const size_t used = (size_t)groups * RL_RING * slot, xcds = place ? rl_xcds_bytes(units, groups) : 0;
     out->per_xcd   = place ? rl_per_xcd(units, groups) : 0;
     out->first_xcd = (int)(((unsigned)(reinterpret_cast<uintptr_t>(ring) >> 8) * 0x9E3779B1u) >> 29);  // (several models of one group: not all on XCD 0)

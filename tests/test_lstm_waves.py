@@ -107,10 +107,11 @@ def test_any_order_of_waves_gives_the_layer(lib, T, Bn, I, H):
             assert np.array_equal(a, b_, equal_nan=True)
 
 
-@pytest.mark.parametrize("Bn,H", [(1, 192), (11, 128)])
+@pytest.mark.parametrize("Bn,H", [(1, 192), (11, 128), (61, 64), (65, 64)])
 def test_only_the_placed_calls_put_a_block_of_rows_on_one_xcd(lib, Bn, H):
     """Launches that together fit the device may run at the same time: the plain calls take the XCDs evenly, so that what fits the device
-    fits every XCD.  The placed calls, which ask more of their caller, have all H / 16 workgroups of 8 rows on one."""
+    fits every XCD, blocks of rows on one XCD or not.  The placed calls, which ask more of their caller, have all H / 16 workgroups of
+    8 rows on one."""
     inputs, n = _inputs(1, Bn, 8, H), (C.c_int * 8)()
     units, groups = H // 16, -(-Bn // 8)
     for placed in (False, True):
@@ -119,4 +120,7 @@ def test_only_the_placed_calls_put_a_block_of_rows_on_one_xcd(lib, Bn, H):
         lib.take_worked(n)
         per = [k // 2 for k in n]                  # forward and backward
         assert sum(per) == units * groups
-        assert sorted(per, reverse=True)[:groups] == [units] * groups if placed else max(per) == -(-units * groups // 8)
+        if placed:
+            assert all(k % units == 0 for k in per) and max(per) == -(-groups // 8) * units
+        else:
+            assert max(per) == -(-units * groups // 8)
