@@ -28,10 +28,16 @@ def _p(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# (looked up once: per call that is 2 us of a 67 us iteration of small launches.  A torch without them says so when a call asks for
+# a device.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+
+
 def _stream():
     # torch's current stream of the current device as a raw hipStream_t, without a Stream object around it (which costs
     # as much as a launch: 2.8 us against 0.3 us a call)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
 
 
 def mp_version() -> int:

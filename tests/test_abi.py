@@ -43,7 +43,13 @@ def test_the_package_imports_on_a_torch_without_gpu_entry_points():
             "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
             "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
             "import paper_1805_10387_amd as mp\n"
-            "assert mp.mp_version() >= 1 and mp.mp_loss_workspace_bytes(8, 8) > 0\n")
+            "assert mp.mp_version() >= 1 and mp.mp_loss_workspace_bytes(8, 8) > 0\n"
+            "try:\n"
+            "    mp.binding._stream()\n"
+            "except (RuntimeError, AssertionError, AttributeError, TypeError) as e:\n"
+            "    assert 'GPU' in str(e) or 'CUDA' in str(e) or torch.cuda.is_available(), e\n"
+            "else:\n"
+            "    assert False\n")
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
 
 
