@@ -353,7 +353,8 @@ int mp_layernorm_fwd(int rows, int d, const mp_half* x, const mp_half* a, const 
  * dgamma[d] = RNE16( sum_rows dy xhat ), dbeta[d] = RNE16( sum_rows dy ).  dz is the gradient of both
  * x and a.  If dz_colsum != NULL it also receives RNE16( column sums over rows of the stored dz ): the bias
  * gradient of the linear layer whose output entered this LayerNorm, at no extra pass over memory.
- * Optional overflow flag on dgamma / dbeta / dz_colsum.  Workspace: mp_layernorm_bwd_workspace_bytes, at any 4-byte boundary. */
+ * Optional overflow flag on dgamma / dbeta / dz_colsum.  Workspace: mp_layernorm_bwd_workspace_bytes (of these rows, or of
+ * more), at any 4-byte boundary. */
 size_t mp_layernorm_bwd_workspace_bytes(int rows, int d);
 int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,

@@ -649,21 +649,29 @@ extern "C" int mp_layernorm_fwd(int rows, int d, const mp_half* x, const mp_half
 // us, 4 rows / as many as this: 200 x 192 7.6 / 5.7, 200 x 1024 9.8 / 6.6, 500 x 320 8.5 / 6.4, 800 x 512 9.4 / 7.1).
 constexpr int LN_BWD_FEW = 128;
 static int ln_bwd_waves(int rows, int d) { return rows >= 256 * 8 * 4 && d <= 64 * 8 * 2 ? 8 : GL_WAVES; }
-static int ln_bwd_blocks(int rows, int d) {
-    const int nw = ln_bwd_waves(rows, d), each = std::min(4, std::max(1, (rows + nw * LN_BWD_FEW - 1) / (nw * LN_BWD_FEW)));
+static int ln_bwd_blocks_of(int rows, int d, int each) {
+    const int nw = ln_bwd_waves(rows, d);
     return std::max(1, std::min((rows + nw * each - 1) / (nw * each), 2048 / nw));
 }
+static int ln_bwd_blocks(int rows, int d) {
+    const int nw = ln_bwd_waves(rows, d);
+    return ln_bwd_blocks_of(rows, d, std::min(4, std::max(1, (rows + nw * LN_BWD_FEW - 1) / (nw * LN_BWD_FEW))));
+}
+static size_t ln_bwd_bytes(int blocks, int d) { return (size_t)blocks * 3 * d * sizeof(float); }
 
+// Also enough for any smaller number of rows (a batch that is not full): the workgroups are most where waves have one row each, and
+// ahead of where workgroups have 8 waves.
 extern "C" size_t mp_layernorm_bwd_workspace_bytes(int rows, int d) {
     if (rows <= 0 || d <= 0) return 0;
-    return (size_t)ln_bwd_blocks(rows, d) * 3 * d * sizeof(float);
+    const int one = std::min(rows, GL_WAVES * LN_BWD_FEW), four_waves = std::min(rows, 256 * 8 * 4 - 1);
+    return ln_bwd_bytes(std::max({ln_bwd_blocks(rows, d), ln_bwd_blocks(one, d), ln_bwd_blocks(four_waves, d)}), d);
 }
 
 extern "C" int mp_layernorm_bwd_nparts(int rows, int d) { return rows > 0 && d > 0 ? ln_bwd_blocks(rows, d) : 0; }
 
-extern "C" int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
-                                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,
-                                      int with_dz_colsum, void* ws, size_t ws_bytes, mp_stream stream) {
+// nb: workgroups, and rows of partial sums in ws
+static int ln_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a, const mp_half* gamma, const float* mean,
+                        const float* rstd, mp_half* dz, int with_dz_colsum, void* ws, size_t ws_bytes, int nb, mp_stream stream) {
     MP_REQUIRE(rows > 0 && d > 0, "mp_layernorm_bwd: bad shape rows=%d d=%d", rows, d);
     MP_REQUIRE(dy && x && gamma && mean && rstd && dz, "mp_layernorm_bwd: NULL argument");
     if (!ln_shape_ok(d)) {
@@ -672,12 +680,10 @@ extern "C" int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const 
     }
     MP_REQUIRE(aligned16(dy) && aligned16(x) && (a == nullptr || aligned16(a)) && aligned16(gamma) && aligned16(dz),
                "mp_layernorm_bwd: pointers must be 16-byte aligned");
-    if (!ws || ws_bytes < mp_layernorm_bwd_workspace_bytes(rows, d)) {
-        set_error("mp_layernorm_bwd: workspace of %zu bytes needed, %zu given", mp_layernorm_bwd_workspace_bytes(rows, d),
-                  ws_bytes);
+    if (!ws || ws_bytes < ln_bwd_bytes(nb, d)) {
+        set_error("mp_layernorm_bwd: workspace of %zu bytes needed, %zu given", ln_bwd_bytes(nb, d), ws_bytes);
         return MP_E_WORKSPACE;
     }
-    const int   nb   = ln_bwd_blocks(rows, d);
     const int   ns   = with_dz_colsum ? 3 : 2;
     float*      part = static_cast<float*>(ws);
     hipStream_t hs   = as_stream(stream);
@@ -704,17 +710,26 @@ extern "C" int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const 
     return MP_OK;
 }
 
+extern "C" int mp_layernorm_bwd_parts(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
+                                      const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz,
+                                      int with_dz_colsum, void* ws, size_t ws_bytes, mp_stream stream) {
+    return ln_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, dz, with_dz_colsum, ws, ws_bytes, mp_layernorm_bwd_nparts(rows, d), stream);
+}
+
 extern "C" int mp_layernorm_bwd(int rows, int d, const mp_half* dy, const mp_half* x, const mp_half* a,
                                 const mp_half* gamma, const float* mean, const float* rstd, mp_half* dz, mp_half* dgamma,
                                 mp_half* dbeta, mp_half* dz_colsum, mp_scale_state* st, void* ws, size_t ws_bytes,
                                 mp_stream stream) {
     MP_REQUIRE(dgamma && dbeta, "mp_layernorm_bwd: NULL argument");
-    const int rc = mp_layernorm_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, dz, dz_colsum != nullptr, ws, ws_bytes, stream);
+    // (a workspace for 4 rows to a wave will do)
+    int nb = mp_layernorm_bwd_nparts(rows, d);
+    if (nb > 0 && ws_bytes < ln_bwd_bytes(nb, d)) nb = ln_bwd_blocks_of(rows, d, 4);
+    const int rc = ln_bwd_parts(rows, d, dy, x, a, gamma, mean, rstd, dz, dz_colsum != nullptr, ws, ws_bytes, nb, stream);
     if (rc != MP_OK) return rc;
     const int  ns = dz_colsum ? 3 : 2;
     FinishOuts outs{{dgamma, dbeta, dz_colsum}};
     hipLaunchKernelGGL(finish_colsum_kernel, dim3((ns * d + 31) / 32), dim3(GL_THREADS), 0, as_stream(stream), static_cast<const float*>(ws),
-                       ln_bwd_blocks(rows, d), (long long)ns * d, d, ns, outs, st);
+                       nb, (long long)ns * d, d, ns, outs, st);
     MP_LAUNCH_CHECK("mp_layernorm_bwd(finish)");
     return MP_OK;
 }

@@ -142,6 +142,17 @@ def test_workspace_queries_are_consistent():
     assert lib.mp_layernorm_bwd_workspace_bytes(8192, 1024) % (2 * 1024 * 4) == 0
 
 
+@pytest.mark.parametrize("d", [8, 192, 1024, 2048])
+def test_a_layernorm_workspace_for_more_rows_is_enough_for_fewer(d):
+    """What a call needs, mp_layernorm_bwd_nparts rows of partial sums, is in a workspace that was sized for a full batch."""
+    from paper_1805_10387_amd import _lib
+    lib = _lib.load()
+    most = 0
+    for rows in range(1, 9000):
+        most = max(most, lib.mp_layernorm_bwd_nparts(rows, d) * 3 * d * 4)
+        assert lib.mp_layernorm_bwd_workspace_bytes(rows, d) >= most
+
+
 def test_joint_gradients_query_says_what_the_call_does():
     """mp_gemm_bwd_both_joint is 1 only where mp_gemm_bwd_both is one launch: a pair it names needs no workspace, and any
     other pair is refused without one before anything is launched."""

@@ -1166,6 +1166,31 @@ def test_layernorm_bwd_workspace_at_any_word(rows, d):
         assert all(torch.equal(a, b) for a, b in zip(out, outs[0]))
 
 
+@pytest.mark.parametrize("rows,d", [(512, 192), (513, 1024), (200, 2048), (1100, 64)])
+def test_layernorm_bwd_takes_any_workspace_that_holds_four_rows_to_a_wave(rows, d):
+    """The sums are the same within fp32 order whether the workspace holds a row of partial sums per workgroup of the rule or only one
+    per 16 rows (the least), nothing behind it is written, and less is refused."""
+    r = RNG(rows + d)
+    dy, x, gam = (h16(S16(r.standard_normal(s))) for s in ((rows, d), (rows, d), d))
+    mean, rstd = torch.randn(rows, device="cuda") * 0.1, torch.rand(rows, device="cuda") + 0.5
+    least, outs = (rows + 15) // 16 * 3 * d, []
+    for words in (mp.mp_layernorm_bwd_workspace_bytes(rows, d) // 4, mp.mp_layernorm_bwd_nparts(rows, d) * 3 * d, least, least - 1):
+        ws = torch.full((words + 64,), 7.0, dtype=torch.float32, device="cuda")
+        out = [empty16(rows, d)] + [empty16(d) for _ in range(3)]
+        call = lambda: mp.mp_layernorm_bwd(rows, d, dy, x, None, gam, mean, rstd, out[0], out[1], out[2], None, ws[:words], dz_colsum=out[3])  # noqa: B023,E731
+        if words < least:
+            with pytest.raises(RuntimeError):
+                call()
+        else:
+            call()
+            outs.append(out)
+        assert torch.all(ws[words:] == 7.0)
+    for out in outs[1:]:
+        assert torch.equal(out[0], outs[0][0])
+        for a, b in zip(out[1:], outs[0][1:]):
+            assert_close16(a, np32(b), 1e-3, max_ulp=1)
+
+
 @pytest.mark.parametrize("rows,cols", [(64, 64), (1000, 128), (77, 40), (50, 256), (9, 512), (13, 301), (6, 1000)])
 def test_softmax_fwd_bwd(rows, cols):
     r = RNG(rows + cols)
